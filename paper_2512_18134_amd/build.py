@@ -38,10 +38,10 @@ def generate_sources(verbose=False, out_dir=None):
     gen = os.path.join(HERE, "csrc", "gen_attn_loop.py")
     out_dir = out_dir or os.path.join(HERE, "csrc", "generated")
     os.makedirs(out_dir, exist_ok=True)
-    for name, dtype in (("d64", "bf16"), ("d64", "f16"), ("d64_w4", "bf16"), ("d128", "bf16"), ("d128", "f16"),
-                        ("d128a", "bf16"), ("d128a", "f16"), ("d256a", "bf16"), ("d256a", "f16")):
-        out = os.path.join(out_dir, "attn_loop_%s%s.inc" % (name, "" if dtype == "bf16" else "_" + dtype))
-        _run_generator([sys.executable, gen, name, out, dtype], verbose)
+    for name in ("d64", "d64_w4", "d64_w2", "d128", "d128a", "d128_w2", "d256a"):
+        for dtype in ("bf16", "f16"):
+            out = os.path.join(out_dir, "attn_loop_%s%s.inc" % (name, "" if dtype == "bf16" else "_" + dtype))
+            _run_generator([sys.executable, gen, name, out, dtype], verbose)
     gen3 = os.path.join(HERE, "csrc", "gen_attn_bwd_loop.py")
     for kind, d, dtype in (("kv", 128, "bf16"), ("q", 128, "bf16"), ("kv", 128, "f16"), ("q", 128, "f16"),
                            ("kv", 64, "bf16"), ("q", 64, "bf16"), ("kv", 64, "f16"), ("q", 64, "f16")):

@@ -18,8 +18,6 @@ namespace {
 
 using attn::Params;
 
-constexpr int kW4MaxKeys = 4096;  // D = 64, causal: up to this many keys the 4-wave workgroups win (measured)
-
 using attn::allow_lds;
 
 // persistent: as many workgroups as the chip holds at once, each walking the tile queue of its XCD
@@ -56,40 +54,93 @@ int launch_simple(const Params &p, int BH, int causal, hipStream_t stream)
 
 // one hand-scheduled tiling: QB 32-row query blocks per wave, SB 32-key blocks per K/V tile, NW waves; persistent
 // workgroups where the tiling has them
-template <int D, int QB, int SB, int NW, bool F16 = false>
+template <int D, int QB, int SB, int NW, bool F16 = false, int G = 1>
 int launch_asm(const Params &p, int BH, int causal, hipStream_t stream)
 {
-    typedef attn::FwdTiling<D, QB, SB, NW, false> T;
+    typedef attn::FwdTiling<D, QB, SB, NW, false, G> T;
     if (causal)
-        return launch(attn::attn_fwd_asm_kernel<D, QB, SB, NW, true, F16>, p, BH, T::BM, NW * 64, T::LDS_BYTES, stream,
-                      T::PERSIST);
-    return launch(attn::attn_fwd_asm_kernel<D, QB, SB, NW, false, F16>, p, BH, T::BM, NW * 64, T::LDS_BYTES, stream,
-                  T::PERSIST);
+        return launch(attn::attn_fwd_asm_kernel<D, QB, SB, NW, true, F16, false, G>, p, BH, T::BM, T::THREADS, T::LDS_BYTES,
+                      stream, T::PERSIST);
+    return launch(attn::attn_fwd_asm_kernel<D, QB, SB, NW, false, F16, false, G>, p, BH, T::BM, T::THREADS, T::LDS_BYTES,
+                  stream, T::PERSIST);
+}
+
+// Below this many queries a launch may use the tilings whose keys are shared out between two groups of waves.  They
+// cut the serial walk over the keys in half (D = 128, one query: 8 heads of 1024 keys 22.1 -> 10.6 us, 64 heads of
+// 4096 keys 70.5 -> 27.7 us) but add up in another order.  O moves by 5e-4 of its norm with that, well inside the
+// rounding of its 16 bits; the dQ that attn_bwd computes from such an O moves by 2e-2 when the softmax is nearly
+// one-hot (dO . O cancels there).  So calls as long as a wave's rows, training calls among them, keep one order.
+constexpr int kKeyGroupMaxQueries = 64;
+
+// D = 64: what a launch of one tiling costs, in us, fitted to launches of one kernel on 1 to 2000 heads of 1 to 16384
+// rows (within 10 % where two tilings are close).  `start` for every round of query tiles that a compute unit works
+// through (`wgs` workgroups that share a unit overlap theirs), and `per_tile` for every 64-key tile of the query tile
+// with the most of them.  Not causal: a last round that leaves most units idle runs at a higher clock.  Causal: heavy
+// and light tiles are handed out in pairs, so that r rounds cost 0.6 r times the heaviest tile.
+struct Tiling {
+    int rows, wgs;
+    float start, per_tile, per_tile_causal;
+};
+
+float tiling_cost(const Tiling &t, int BH, const Params &p, int causal, int cus)
+{
+    const long long tiles = (long long)BH * ((p.S_q + t.rows - 1) / t.rows);
+    const int keys = causal && p.S_q < p.S_kv ? p.S_q : p.S_kv;
+    const float n = (float)((keys + 63) / 64);
+    const float whole = (float)(tiles / cus), rest = (float)(tiles % cus) / (float)cus;
+    const float up = whole + (rest > 0.f ? 1.f : 0.f);   // rounds, the last one counted in full
+    if (!causal)
+        return t.start * fmaxf(1.f, up / t.wgs) + t.per_tile * n * (whole + (rest > 0.f ? 0.65f + 0.35f * rest : 0.f));
+    const float r = fmaxf(1.f, 0.5f * (whole + rest + up));
+    return t.start * fmaxf(1.f, r / t.wgs) + t.per_tile_causal * n * fmaxf(0.7f + 0.17f * r, 0.6f * r);
 }
 
 // D = 64.  tiling: -1 = choose, 0 = 8 waves x 32 rows (two waves per SIMD), 1 = 4 waves x 32 rows (two workgroups
-// per CU).
-// Measured: two 4-wave workgroups per CU instead of one 8-wave one change little when every workgroup
-// streams the same number of tiles (-3 % at long S, +-2 % at short S); with a causal mask and few tiles
-// the finer query tiles balance better (+13 % at S = 1024, +4 % at S = 4096).
+// per CU; the same results), 2 = 2 x 2 waves x 32 rows (64 rows, two key groups).
+// Measured, us for tiling 0 / 1: 16 heads of 512 rows 10.6 / 7.8, of 2048 rows 28.6 / 20.8; 32 heads of 2048 rows
+// 35.9 / 37.4, causal 31.3 / 25.9; 64 heads of 4096 rows 256 / 267; 2000 heads of 100 rows 40.3 / 24.4.
 template <bool F16>
 int launch_d64(const Params &p, int BH, int causal, hipStream_t stream, int tiling = -1)
 {
-    if (tiling < 0)
-        tiling = (!F16 && causal && p.S_kv <= kW4MaxKeys) ? 1 : 0;
-    if (tiling == 1 && !F16)
-        return launch_asm<64, 1, 2, 4>(p, BH, causal, stream);
+    if (tiling < 0) {
+        int cus = attn::cu_count(1);
+        if (cus < 1)
+            cus = 256;
+        // (two 128-row workgroups on a unit stream twice the keys per product of a 256-row one: with a causal mask
+        // that shows from long sequences on)
+        const Tiling t[3] = {{256, 1, 5.0f, 0.90f, 0.95f},
+                             {128, 2, 4.0f, 0.52f, p.S_kv > 4096 ? 0.60f : 0.54f},
+                             {64, 1, 4.5f, 0.31f, 0.31f}};
+        float best = tiling_cost(t[0], BH, p, causal, cus);
+        tiling = 0;
+        // (more than two rounds of 256-row tiles: they win, unless most of their rows do not exist)
+        const bool wide = p.S_q > 128 && (long long)BH * ((p.S_q + 255) / 256) > 2ll * cus;
+        for (int i = 1; i < (wide ? 1 : (p.S_q < kKeyGroupMaxQueries ? 3 : 2)); ++i) {
+            const float c = tiling_cost(t[i], BH, p, causal, cus);
+            if (c < best) {
+                best = c;
+                tiling = i;
+            }
+        }
+    }
+    if (tiling == 2)
+        return launch_asm<64, 1, 2, 2, F16, 2>(p, BH, causal, stream);
+    if (tiling == 1)
+        return launch_asm<64, 1, 2, 4, F16>(p, BH, causal, stream);
     return launch_asm<64, 1, 2, 8, F16>(p, BH, causal, stream);
 }
 
-// D = 128.  wide: -1 = choose, 0 = 8 waves x 32 rows (two waves per SIMD), 1 = 4 waves x 64 rows (one wave
-// per SIMD, half the LDS operand reads per MFMA).
+// D = 128.  tiling: -1 = choose, 0 = 8 waves x 32 rows (two waves per SIMD), 1 = 4 waves x 64 rows (one wave
+// per SIMD, half the LDS operand reads per MFMA), 2 = 2 x 2 waves x 32 rows (64 rows, two key groups).
 template <bool F16>
-int launch_d128(const Params &p, int BH, int causal, hipStream_t stream, int wide = -1)
+int launch_d128(const Params &p, int BH, int causal, hipStream_t stream, int tiling = -1)
 {
-    const bool use_wide = wide >= 0 ? wide != 0 : true;
-    return use_wide ? launch_asm<128, 2, 1, 4, F16>(p, BH, causal, stream)
-                    : launch_asm<128, 1, 2, 8, F16>(p, BH, causal, stream);
+    if (tiling < 0)
+        tiling = p.S_q < kKeyGroupMaxQueries ? 2 : 1;
+    if (tiling == 2)
+        return launch_asm<128, 1, 1, 2, F16, 2>(p, BH, causal, stream);
+    return tiling == 1 ? launch_asm<128, 2, 1, 4, F16>(p, BH, causal, stream)
+                       : launch_asm<128, 1, 2, 8, F16>(p, BH, causal, stream);
 }
 
 // the generic kernel: any scale, heads of any size, program order
@@ -292,7 +343,8 @@ extern "C" int attn_fwd(const void *q, const void *k, const void *v, void *o, fl
 // Test-only entry point of the debug build of the library (libmi355attn_debug.so): attn_fwd with the
 // kernel chosen by the caller.  variant 0: as attn_fwd; 1: the generic program-order kernel;
 // 2 / 5: D = 128 on the one-wave-per-SIMD tiling (4 waves x 64 query rows) / on the two-waves-per-SIMD
-// tiling (8 waves x 32 rows); 3 / 4: D = 64 with 8-wave / 4-wave workgroups.  A variant that does not
+// tiling (8 waves x 32 rows); 3 / 4: D = 64 with 8-wave / 4-wave workgroups; 6: D = 64 or 128 in 64-row
+// workgroups with two key groups.  A variant that does not
 // apply to the arguments returns ATTN_ERR_UNSUPPORTED.
 extern "C" int attn_fwd_variant(const void *q, const void *k, const void *v, void *o, float *lse, int B, int H,
                                 int S_q, int S_kv, int D, int causal, float scale, void *stream, int variant)
@@ -312,6 +364,10 @@ extern "C" int attn_fwd_variant(const void *q, const void *k, const void *v, voi
         return D == 128 && asm_ok ? launch_d128<false>(p, B * H, causal, st, 1) : ATTN_ERR_UNSUPPORTED;
     case 5:
         return D == 128 && asm_ok ? launch_d128<false>(p, B * H, causal, st, 0) : ATTN_ERR_UNSUPPORTED;
+    case 6:
+        return !asm_ok ? ATTN_ERR_UNSUPPORTED
+               : D == 128 ? launch_d128<false>(p, B * H, causal, st, 2)
+               : D == 64 ? launch_d64<false>(p, B * H, causal, st, 2) : ATTN_ERR_UNSUPPORTED;
     case 3:
     case 4:
         return D == 64 && asm_ok ? launch_d64<false>(p, B * H, causal, st, variant - 3) : ATTN_ERR_UNSUPPORTED;

@@ -12,9 +12,14 @@
 //
 // Tilings (template parameters; gen_attn_loop.py CONFIGS holds the matching loops):
 //   QB  32-row query blocks per wave     SB  32-key blocks per K/V tile (BN = 32 SB)
-//   NW  waves per workgroup (BM = 32 QB NW query rows)
+//   NW  waves per key group (BM = 32 QB NW query rows)    G  key groups per workgroup
 //   <D=64|128, QB=1, SB=2, NW=8>  two waves per SIMD, everything in 256 VGPRs
 //   <D=64,     QB=1, SB=2, NW=4>  the same with BM = 128 (two workgroups per CU)
+//   <D=128, QB=1, SB=1, NW=2, G=2>, <D=64, QB=1, SB=2, NW=2, G=2>
+//                                  launches with few queries: BM = 64, and the keys of a tile cut in two halves that
+//                                  two groups of NW waves (each with rings of its own) work on side by side; their
+//                                  results meet in LDS (finish_groups).  One wave per SIMD walks half the keys: what
+//                                  bounds it is the walk (0.4 us per 32 keys, issue and load latency), not the products
 //   <D=128,    QB=2, SB=1, NW=4>  one wave per SIMD, O and Q in AGPRs; a K / V^T fragment
 //                                  read from LDS feeds two MFMAs (half the LDS reads)
 //   <D=256,    QB=1, SB=1, NW=4>  one wave per SIMD, O and Q in AGPRs
@@ -75,24 +80,28 @@ struct ElemF16 {
 };
 
 // Workgroup shape and LDS budget of a tiling, shared by the kernel and the host code that launches it.
-template <int D, int QB, int SB, int NW, bool SPLIT>
+template <int D, int QB, int SB, int NW, bool SPLIT, int G = 1>
 struct FwdTiling {
     static constexpr int BN = 32 * SB, BM = NW * 32 * QB;
-    static constexpr int RING_BYTES = 8 * BN * D * 2;     // K ring [4] + V ring [4]
+    static constexpr int THREADS = NW * G * 64;
+    static constexpr int RING_BYTES = 8 * BN * D * 2;     // K ring [4] + V ring [4] of one key group
     static constexpr int STAGE_BYTES = BM * D * 2;        // O of one tile, 16-bit
     // A staging area [BM][D] next to the rings when it fits (160 KB of LDS per CU, one workgroup per CU): a tile's
     // Q rows arrive there by direct loads (whole rows, coalesced), the next tile's while the finished one is
     // written out.  Without it Q is loaded straight into registers (32-byte pieces).  O is staged in the rings
     // once the loop has left them.
-    static constexpr bool HAS_STAGE = !SPLIT && !(D == 64 && NW == 4) && RING_BYTES + STAGE_BYTES <= 160 * 1024;
-    static constexpr int LDS_BYTES = RING_BYTES + (HAS_STAGE ? STAGE_BYTES : 0);
+    static constexpr bool HAS_STAGE = !SPLIT && G == 1 && NW * QB == 8 && RING_BYTES + STAGE_BYTES <= 160 * 1024;
+    static constexpr int LDS_BYTES = G * RING_BYTES + (HAS_STAGE ? STAGE_BYTES : 0);
     // Persistent workgroups (see attn_fwd_asm_kernel) wherever the loop leaves the compiler registers to carry
     // a tile's state across it: the 8-wave D = 128 loop assigns all 256 VGPRs itself, and a split-KV launch
     // has a workgroup per (tile, key range)
-    static constexpr bool PERSIST = !SPLIT && !(D == 128 && QB == 1);
+    static constexpr bool PERSIST = !SPLIT && !(D == 128 && QB == 1 && SB == 2);
     // the 4-wave D = 64 workgroups are meant to run two to a CU: their waves must fit half a SIMD's registers
     static constexpr int MIN_WAVES_PER_SIMD = (D == 64 && NW == 4) ? 2 : 1;
     static_assert(SPLIT || STAGE_BYTES <= RING_BYTES, "O staging must fit the rings");
+    // the two key groups exchange half of their fp32 accumulators, their row maxima and sums, then stage half rows
+    static constexpr int XCH_O = 0, XCH_ML = 2 * NW * 32 * D * 2, XCH_STAGE = XCH_ML + 2 * NW * 64 * 8;
+    static_assert(G == 1 || (G == 2 && QB == 1 && XCH_STAGE + 2 * NW * 32 * D <= LDS_BYTES), "the exchange must fit the rings");
 };
 
 // SPLIT: the workgroup handles one key range of a split-KV launch (see Params) and writes its
@@ -101,18 +110,21 @@ struct FwdTiling {
 // Workgroups are persistent (FwdTiling::PERSIST): the launch has at most one workgroup per CU slot (gridDim.x a
 // multiple of the XCD count unless every tile has a workgroup of its own), and workgroup `blockIdx.x` walks the
 // tile queue of its XCD (persistent_entry), so that no dispatch gap separates two tiles of a CU.
-template <int D, int QB, int SB, int NW, bool CAUSAL, bool F16 = false, bool SPLIT = false>
-__global__ __launch_bounds__(NW * 64, (D == 64 && NW == 4) ? 2 : 1)  // = FwdTiling::MIN_WAVES_PER_SIMD
+template <int D, int QB, int SB, int NW, bool CAUSAL, bool F16 = false, bool SPLIT = false, int G = 1>
+__global__ __launch_bounds__(NW * G * 64, (D == 64 && NW == 4) ? 2 : 1)  // = FwdTiling::MIN_WAVES_PER_SIMD
     void attn_fwd_asm_kernel(const Params p)
 {
-    static_assert((QB == 1 && SB == 2 && (D == 64 || D == 128) && (NW == 8 || (NW == 4 && D == 64 && !F16 && !SPLIT))) ||
-                      (QB == 2 && SB == 1 && D == 128 && NW == 4) || (QB == 1 && SB == 1 && D == 256 && NW == 4 && !SPLIT),
+    static_assert((QB == 1 && SB == 2 && (D == 64 || D == 128) && NW == 8 && G == 1) ||
+                      (QB == 1 && SB == 2 && D == 64 && ((NW == 4 && G == 1) || (NW == 2 && G == 2))) ||
+                      (QB == 1 && SB == 1 && D == 128 && NW == 2 && G == 2) ||
+                      (QB == 2 && SB == 1 && D == 128 && NW == 4 && G == 1) ||
+                      (QB == 1 && SB == 1 && D == 256 && NW == 4 && G == 1 && !SPLIT),
                   "no generated loop for this tiling");
     static_assert(!(SPLIT && CAUSAL), "split-KV launches are not causal");
     typedef typename std::conditional<F16, ElemF16, ElemBF16>::type E;
     typedef typename E::t elem_t;
     typedef typename E::x8 ex8;
-    typedef FwdTiling<D, QB, SB, NW, SPLIT> T;
+    typedef FwdTiling<D, QB, SB, NW, SPLIT, G> T;
     constexpr int BN = T::BN, BM = T::BM, NST = 4;
     constexpr int CPR = D / 8;   // 16-byte chunks per row
     constexpr int KS = D / 16;   // k-steps of K Q^T
@@ -130,11 +142,13 @@ __global__ __launch_bounds__(NW * 64, (D == 64 && NW == 4) ? 2 : 1)  // = FwdTil
     constexpr uint32_t KRING = 0, VRING = NST * TB;
     constexpr uint32_t STAGE = HAS_STAGE ? T::RING_BYTES : 0;   // Q staging area
     unsigned char *const o_stage = smem;                          // O is staged in the rings, after the loop
-    const uint32_t lds0 = (uint32_t)(uintptr_t)(ATTN_LDS_PTR(unsigned char))smem;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave_wg = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int grp = G == 1 ? 0 : wave_wg / NW;    // key group of this wave
+    const int wave = G == 1 ? wave_wg : wave_wg % NW;   // ... and its place in the group
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(ATTN_LDS_PTR(unsigned char))smem + grp * T::RING_BYTES;
     const int lq = lane & 31;
     const int g = lane >> 5;
 
@@ -146,7 +160,7 @@ __global__ __launch_bounds__(NW * 64, (D == 64 && NW == 4) ? 2 : 1)  // = FwdTil
 
     // ---- one tile of the launch: which head and query rows, which keys
     struct Tile {
-        int vb, bh, split, q0, kv0, S_kv, n_tiles, j_mask, t_full, skv_m1;
+        int vb, bh, split, q0, kv0, S_kv, n_tiles, own_tiles, j_mask, t_full, skv_m1;
         const elem_t *qg, *k_head, *v_head;
     };
     auto locate = [&](int vb) -> Tile {
@@ -167,15 +181,27 @@ __global__ __launch_bounds__(NW * 64, (D == 64 && NW == 4) ? 2 : 1)  // = FwdTil
         t.kv0 = SPLIT ? t.split * p.split_len : 0;                        // first key of this tile's range
         t.S_kv = SPLIT ? min(p.split_len, p.S_kv - t.kv0) : p.S_kv;       // keys of this tile's range
         t.q0 = qt * BM;
-        t.qg = reinterpret_cast<const elem_t *>(p.q) + (size_t)t.bh * p.S_q * D;
-        t.k_head = reinterpret_cast<const elem_t *>(p.k) + ((size_t)t.bh * p.S_kv + t.kv0) * D;
-        t.v_head = reinterpret_cast<const elem_t *>(p.v) + ((size_t)t.bh * p.S_kv + t.kv0) * D;
         int kv_end = t.S_kv;
         if (CAUSAL)
             kv_end = min(kv_end, min(t.q0 + BM, p.S_q));
         t.n_tiles = (kv_end + BN - 1) / BN;
         const int j_tail = (t.n_tiles * BN > t.S_kv) ? t.n_tiles - 1 : t.n_tiles;
         t.j_mask = CAUSAL ? min(t.q0 / BN, j_tail) : j_tail;  // first K/V tile whose scores need a mask
+        t.own_tiles = t.n_tiles;
+        if constexpr (G == 2) {
+            // the first key group takes the larger half of the tiles; a single tile is computed by both groups and
+            // left out of the second one's result (run_tile: idle)
+            const int n0 = (t.n_tiles + 1) / 2;
+            const int j0 = grp && t.n_tiles > 1 ? n0 : 0;
+            t.own_tiles = grp ? max(t.n_tiles - n0, 1) : n0;
+            t.n_tiles = n0;
+            t.j_mask = max(t.j_mask - j0, 0);
+            t.kv0 += j0 * BN;
+            t.S_kv -= j0 * BN;
+        }
+        t.qg = reinterpret_cast<const elem_t *>(p.q) + (size_t)t.bh * p.S_q * D;
+        t.k_head = reinterpret_cast<const elem_t *>(p.k) + ((size_t)t.bh * p.S_kv + t.kv0) * D;
+        t.v_head = reinterpret_cast<const elem_t *>(p.v) + ((size_t)t.bh * p.S_kv + t.kv0) * D;
         t.t_full = t.S_kv / BN;                               // K/V tiles below this lie inside [0, S_kv)
         t.skv_m1 = t.S_kv - 1;
         return t;
@@ -288,8 +314,95 @@ __global__ __launch_bounds__(NW * 64, (D == 64 && NW == 4) ? 2 : 1)  // = FwdTil
     // ---- end of a tile: normalise, write O (16-bit) and the log-sum-exp (fp32)
     typename F32Vec<QB>::type m_ref_v, l_run_v;
     f32x16 o_acc[QB * DB];
+    bool idle = false;   // second key group only: this wave's result does not count
+    // Two key groups: wave w of either group holds the same 32 query rows, lane for lane.  Each wave hands the other
+    // one half of the head dimension (fp32, with its row maxima and sums), combines the half it keeps -- the
+    // accumulator rescale of the online softmax, once more -- and writes that half of the rows out.
+    auto finish_groups = [&](const Tile &t) {
+        constexpr int HB = DB / 2, HCPR = CPR / 2, HROWB = ROWB / 2;
+        const float l_lane = F32Vec<QB>::get(l_run_v, 0);
+        const float l_own = idle ? 0.f : l_lane + xor32(l_lane);
+        const float m_own = idle ? -INFINITY : F32Vec<QB>::get(m_ref_v, 0);
+        float *const xo = reinterpret_cast<float *>(smem + T::XCH_O);
+        f32x2 *const xml = reinterpret_cast<f32x2 *>(smem + T::XCH_ML);
+        // element r of the half this wave keeps (mine) or hands over
+        auto half = [&](bool mine, int r) -> float {
+            const float lo = o_acc[r / 16][r % 16], hi = o_acc[HB + r / 16][r % 16];
+            return (grp == 0) == mine ? lo : hi;
+        };
+#pragma unroll
+        for (int i = 0; i < 4 * HB; ++i) {
+            const f32x4 w = {half(false, 4 * i), half(false, 4 * i + 1), half(false, 4 * i + 2), half(false, 4 * i + 3)};
+            *reinterpret_cast<f32x4 *>(xo + ((wave_wg * 4 * HB + i) * 64 + lane) * 4) = w;
+        }
+        const f32x2 ml = {m_own, l_own};
+        xml[wave_wg * 64 + lane] = ml;
+        __syncthreads();
+        const int other = wave + (1 - grp) * NW;
+        const f32x2 ml_o = xml[other * 64 + lane];
+        const float m = fmaxf(m_own, ml_o[0]);
+        const float w_own = __builtin_amdgcn_exp2f((m_own - m) * p.c), w_oth = __builtin_amdgcn_exp2f((ml_o[0] - m) * p.c);
+        const float l_tot = w_own * l_own + w_oth * ml_o[1];
+        const float inv = 1.f / l_tot;
+        const float a_own = w_own * inv, a_oth = w_oth * inv;
+        const float lse_row = m * p.scale + __builtin_amdgcn_logf(l_tot) * 0.69314718055994530942f;
+        f32x16 o_half[HB];
+#pragma unroll
+        for (int i = 0; i < 4 * HB; ++i) {
+            const f32x4 x = *reinterpret_cast<const f32x4 *>(xo + ((other * 4 * HB + i) * 64 + lane) * 4);
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                o_half[i / 4][4 * (i % 4) + r] = half(true, 4 * i + r) * a_own + x[r] * a_oth;
+        }
+        const int row0 = t.q0 + wave * 32, qrow = row0 + lq;
+        if constexpr (SPLIT) {
+            const size_t n_rows = (size_t)(p.total_wg / (p.n_qt * p.n_split)) * p.S_q;
+            if (qrow < p.S_q) {
+                const size_t row = (size_t)t.split * n_rows + (size_t)t.bh * p.S_q + qrow;
+                float *orow = p.o_part + row * D + grp * (D / 2);
+#pragma unroll
+                for (int i = 0; i < 4 * HB; ++i) {
+                    const f32x16 &x = o_half[i / 4];
+                    const int r = 4 * (i % 4);
+                    const f32x4 w = {x[r], x[r + 1], x[r + 2], x[r + 3]};
+                    *reinterpret_cast<f32x4 *>(orow + 8 * i + 4 * g) = w;
+                }
+                if (grp == 0 && g == 0)
+                    p.lse_part[row] = lse_row;
+            }
+        } else {
+            unsigned char *stage = smem + T::XCH_STAGE + wave_wg * 32 * HROWB;   // as in finish: whole rows out
+#pragma unroll
+            for (int i = 0; i < 4 * HB; ++i) {
+                const f32x16 &x = o_half[i / 4];
+                const int r = 4 * (i % 4);
+                const f32x2 lo = {x[r], x[r + 1]}, hi = {x[r + 2], x[r + 3]};
+                const typename E::x2 blo = __builtin_convertvector(lo, typename E::x2);  // round to nearest even
+                const typename E::x2 bhi = __builtin_convertvector(hi, typename E::x2);
+                const typename E::x4 out = {blo[0], blo[1], bhi[0], bhi[1]};
+                *reinterpret_cast<typename E::x4 *>(stage + lq * HROWB + ((i ^ (lq & (HCPR - 1))) * 16) + g * 8) = out;
+            }
+            elem_t *o_blk = reinterpret_cast<elem_t *>(p.o) + ((size_t)t.bh * p.S_q + row0) * D + grp * (D / 2);
+            const int rows_left = p.S_q - row0;
+#pragma unroll
+            for (int i = 0; i < 32 * HCPR / 64; ++i) {
+                const int idx = i * 64 + lane;
+                const int r = idx / HCPR, c = idx % HCPR;
+                const u32x4 w = *reinterpret_cast<const u32x4 *>(stage + r * HROWB + ((c ^ (r & (HCPR - 1))) * 16));
+                if (r < rows_left)
+                    *reinterpret_cast<u32x4 *>(o_blk + (size_t)r * D + c * 8) = w;
+            }
+            if (qrow < p.S_q && grp == 0 && g == 0)
+                p.lse[(size_t)t.bh * p.S_q + qrow] = lse_row;
+        }
+        ATTN_TRACE(p, t.vb, 5);
+    };
     // between(k), k = 0 .. 2 QB - 1: called after each block's conversion and after each block's stores
     auto finish = [&](const Tile &t, auto between) {
+        if constexpr (G == 2) {
+            finish_groups(t);
+            return;
+        }
         float inv[QB], lse_row[QB];
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) {
@@ -428,30 +541,47 @@ __global__ __launch_bounds__(NW * 64, (D == 64 && NW == 4) ? 2 : 1)  // = FwdTil
                 f.a[k4] = bq[(4 * i + k4) / KS][(4 * i + k4) % KS];
             q_pack[i] = __builtin_bit_cast(u32x16, f);
         }
+        // Second key group: a wave none of whose rows sees a key of the group (causal; its rows and the group's keys
+        // both start at multiples of 32), or a tile too short for two groups: it runs one unmasked tile, so that
+        // everything stays finite, and its result does not count
+        const int last_row = min(t.q0 + (wave + 1) * 32 * QB, p.S_q) - 1;
+        if constexpr (G == 2)
+            idle = grp && (t.kv0 == (SPLIT ? t.split * p.split_len : 0) ||
+                           (CAUSAL && min(t.q0 + wave * 32, last_row) < t.kv0));
         // key index limit of this lane's queries, minus the lane-group part of the accumulator row
         typename U32Vec<QB>::type thr_base_v;
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb)
-            U32Vec<QB>::set(thr_base_v, qb, (uint32_t)((CAUSAL ? min(qcol(t, qb), t.skv_m1) : t.skv_m1) - 4 * g));
+            U32Vec<QB>::set(thr_base_v, qb,
+                            (uint32_t)((CAUSAL && !idle ? min(qcol(t, qb) - t.kv0, t.skv_m1) : t.skv_m1) - 4 * g));
         const float c_log2e = p.c;
         const elem_t *k_head = t.k_head, *v_head = t.v_head;
         const int n_tiles = t.n_tiles, j_mask = t.j_mask, t_full = t.t_full, skv_m1 = t.skv_m1;
         // causal: the keys behind this wave's last row are masked for all of its rows; the loop leaves the
         // tiles that hold nothing else to the waves below (it keeps their barriers and issues its loads)
-        const int last_row = min(t.q0 + (wave + 1) * 32 * QB, p.S_q) - 1;
-        const int n_tiles_wave = CAUSAL ? min(n_tiles, last_row / BN + 1) : n_tiles;
+        const int n_tiles_wave = idle ? 1 : (CAUSAL ? min(t.own_tiles, (last_row - t.kv0) / BN + 1) : t.own_tiles);
         ATTN_TRACE(p, t.vb, 2);
 
-        if constexpr (D == 128 && QB == 1 && !F16) {
+        if constexpr (D == 128 && SB == 2 && !F16) {
 #include "generated/attn_loop_d128.inc"
-        } else if constexpr (D == 128 && QB == 1 && F16) {
+        } else if constexpr (D == 128 && SB == 2 && F16) {
 #include "generated/attn_loop_d128_f16.inc"
         } else if constexpr (D == 128 && QB == 2 && !F16) {
 #include "generated/attn_loop_d128a.inc"
         } else if constexpr (D == 128 && QB == 2 && F16) {
 #include "generated/attn_loop_d128a_f16.inc"
-        } else if constexpr (D == 64 && NW == 4) {
+        } else if constexpr (D == 128 && !F16) {
+#include "generated/attn_loop_d128_w2.inc"
+        } else if constexpr (D == 128) {
+#include "generated/attn_loop_d128_w2_f16.inc"
+        } else if constexpr (D == 64 && NW == 4 && !F16) {
 #include "generated/attn_loop_d64_w4.inc"
+        } else if constexpr (D == 64 && NW == 4) {
+#include "generated/attn_loop_d64_w4_f16.inc"
+        } else if constexpr (D == 64 && NW == 2 && !F16) {
+#include "generated/attn_loop_d64_w2.inc"
+        } else if constexpr (D == 64 && NW == 2) {
+#include "generated/attn_loop_d64_w2_f16.inc"
         } else if constexpr (D == 64 && !F16) {
 #include "generated/attn_loop_d64.inc"
         } else if constexpr (D == 64 && F16) {

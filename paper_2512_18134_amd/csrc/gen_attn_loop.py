@@ -87,8 +87,10 @@ CONFIGS = {
     # NF: fragment buffers; PFD: groups between a fragment's LDS read and its MFMA; W: groups per s_waitcnt
     "d64":    dict(D=64,  QB=1, SB=2, NW=8, AG=False, NACC=1, NF=8, PFD=6, W=2),
     "d64_w4": dict(D=64,  QB=1, SB=2, NW=4, AG=False, NACC=1, NF=8, PFD=6, W=2),
+    "d64_w2": dict(D=64,  QB=1, SB=2, NW=2, AG=False, NACC=1, NF=8, PFD=7, W=4, LS=2),
     "d128":   dict(D=128, QB=1, SB=2, NW=8, AG=False, NACC=1, NF=4, PFD=3, W=1),
     "d128a":  dict(D=128, QB=2, SB=1, NW=4, AG=True,  NACC=1, NF=8, PFD=7, W=4),
+    "d128_w2": dict(D=128, QB=1, SB=1, NW=2, AG=False, NACC=1, NF=8, PFD=7, W=4, LS=1),
     "d256a":  dict(D=256, QB=1, SB=1, NW=4, AG=True,  NACC=2, NF=8, PFD=7, W=4, LS=2),
 }
 
@@ -480,13 +482,14 @@ class Gen(Emitter):
                 # them.  The out-of-line clamped loads (all of K and V at once, from the first load slot) come
                 # back with SCC still set, which sends the other slots past their loads.
                 one = self.dma_fast("k", b) + self.dma_fast("v", (b + 2) % 4)
-                ls = min(self.LS, (n_soft - 2) // (len(one) - 1))      # the first iteration has fewer slots
+                ls = min(self.LS, (n_soft - 1) // (len(one) - 1))      # the first iteration has fewer slots
                 assert ls >= 1
                 for n, ld in enumerate(one):
                     lab = L(("KRET%s_" if n == 0 else "LD%d_%%s_" % n) % tag)
                     to = L("KSLOW%s_" % tag) if n == 0 else lab
                     extra[n * ls] = ["s_cbranch_scc1 %s" % to] + ld + ["%s:" % lab]
-                extra[(len(one) - 1) * ls + 1] = bumps
+                after = min((len(one) - 1) * ls + 1, n_soft - 1)
+                extra[after] = extra.get(after, []) + bumps
             if "nodma" in self.exp:
                 assert self.LS == 0
                 extra[0], extra[1] = ["%s:" % L("KRET%s_" % tag)], ["%s:" % L("VRET%s_" % tag)]

@@ -1,0 +1,50 @@
+"""The forward tilings whose keys are shared out between two groups of waves (64 query rows, D = 64 and
+128), each forced through the debug build on the sizes where it can go wrong: fewer keys than the two groups have
+tiles, an odd number of tiles, ragged ends, causal blocks of which the second group's keys are all masked.  Against the
+fp64 oracle, bars as in test_parity_gpu.py; and the same shapes through the dispatcher in both element types."""
+import numpy as np
+import pytest
+import torch
+
+import debug_lib
+from oracle.attn_oracle import attn_ref
+from paper_2512_18134_amd import binding, synth
+
+pytestmark = pytest.mark.gpu
+
+SIZES = [(1, 1), (1, 33), (1, 2000), (31, 32), (33, 64), (64, 65), (65, 64), (96, 97), (100, 31), (128, 160), (129, 128),
+         (192, 191), (257, 289), (300, 1000), (515, 70)]
+TILINGS = [(128, debug_lib.FWD_KEY_GROUPS), (64, debug_lib.FWD_KEY_GROUPS), (64, debug_lib.FWD_D64_4_WAVES)]
+
+
+def on_gpu(bits, dt):
+    return torch.from_numpy(bits.view(np.int16)).cuda().view(dt)
+
+
+def f64(t):
+    return t.float().cpu().numpy().astype(np.float64)
+
+
+def check(o, lse, want, o_tol):
+    assert np.max(np.abs(f64(o) - want[0])) <= o_tol
+    assert np.max(np.abs(f64(lse) - want[1])) <= 1e-3
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("S_q,S_kv", SIZES)
+def test_key_groups_against_the_oracle(S_q, S_kv, causal):
+    for D in (64, 128):
+        scale = synth.default_scale(D)
+        for dtype, dt, o_tol in (("bf16", torch.bfloat16, 2e-2), ("f16", torch.float16, 4e-3)):
+            q, k, v = synth.make_qkv(1, 3, S_q, S_kv, D, seed=77, sharp=(dtype == "bf16"), dtype=dtype)
+            want = attn_ref(q, k, v, causal, scale, dtype=dtype)
+            qd, kd, vd = (on_gpu(x, dt) for x in (q, k, v))
+            if dtype == "f16":
+                o, lse = binding.attn_fwd_f16(qd, kd, vd, causal=causal, scale=scale)
+                check(o, lse, want, o_tol)
+                continue
+            for d, variant in TILINGS:
+                if d == D:
+                    print("S_q", S_q, "S_kv", S_kv, "D", D, "causal", causal, "variant", variant, flush=True)
+                    o, lse = debug_lib.attn_fwd_variant(qd, kd, vd, causal, scale, variant)
+                    check(o, lse, want, o_tol)
