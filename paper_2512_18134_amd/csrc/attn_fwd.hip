@@ -231,29 +231,60 @@ extern "C" long long attn_fwd_splitkv_workspace_bytes(int B, int H, int S_q, int
     return (long long)n_split * B * H * S_q * (D + 1) * 4;
 }
 
+// the forward kernel over (query tile, key range) pairs, one workgroup each
+template <int D, int QB, int SB, int NW, bool F16, int G>
+static int launch_ranges(Params &p, int BH, int n_eff, hipStream_t st)
+{
+    typedef attn::FwdTiling<D, QB, SB, NW, true, G> T;
+    p.n_qt = (p.S_q + T::BM - 1) / T::BM;
+    const long long total = (long long)BH * p.n_qt * n_eff;
+    if (total > 0x7fffffffLL)
+        return ATTN_ERR_SHAPE;
+    p.total_wg = (int)total;
+    auto kern = attn::attn_fwd_asm_kernel<D, QB, SB, NW, false, F16, true, G>;
+    if (!allow_lds(reinterpret_cast<const void *>(kern), T::LDS_BYTES))
+        return ATTN_ERR_LAUNCH;
+    hipLaunchKernelGGL(kern, dim3((unsigned)p.total_wg), dim3(T::THREADS), T::LDS_BYTES, st, p);
+    return hipGetLastError() == hipSuccess ? ATTN_OK : ATTN_ERR_LAUNCH;
+}
+
+// Tiling of the ranges.  Up to 64 queries (decode) a 256-row tile is mostly rows that do not exist: 64-row tiles with
+// two key groups stream the keys at the rate of a large copy (D = 128, one query, 64 heads of 8191 keys in 8 ranges:
+// 77.4 -> 51.9 us; 16 heads of 131072 keys in 64 ranges: 260 -> 187 us), at D = 64 for long ranges or few of them, the
+// 128-row workgroups (two to a CU) otherwise (512 ranges of 1024 keys: 42.6 us with 256-row tiles, 28.3 with 128, 29.8
+// with 64; 1024 ranges of 2048 keys: 151 / 113 / 96).  With more queries the small tiles win while they find idle
+// compute units (256 queries, 8 heads of 8192 keys in 8 ranges: D = 128 28.9 -> 17.5 us, D = 64 19.6 -> 11.2 us), the
+// wide ones after that (32 ranges of 4096 keys: 137 against 197 us).
 template <int D, bool F16>
 static int launch_splitkv(Params &p, int BH, int n_eff, void *o, float *lse, hipStream_t st)
 {
     typedef typename std::conditional<F16, _Float16, attn::bf16_t>::type out_t;
     const long long n_rows = (long long)BH * p.S_q;
-    constexpr int BM = 256;
-    p.n_qt = (p.S_q + BM - 1) / BM;
-    const long long total = (long long)BH * p.n_qt * n_eff;
-    if (total > 0x7fffffffLL)
-        return ATTN_ERR_SHAPE;
-    p.total_wg = (int)total;
-    const int lds = attn::FwdTiling<D, 1, 2, 8, true>::LDS_BYTES;
-    auto kern = attn::attn_fwd_asm_kernel<D, 1, 2, 8, false, F16, true>;   // one workgroup per (tile, key range)
-    if (!allow_lds(reinterpret_cast<const void *>(kern), lds))
-        return ATTN_ERR_LAUNCH;
-    hipLaunchKernelGGL(kern, dim3((unsigned)p.total_wg), dim3(512), lds, st, p);
-    if (hipGetLastError() != hipSuccess)
-        return ATTN_ERR_LAUNCH;
-    const int rpb = 256 / (D / 4);
+    const int cus = attn::cu_count(1) > 0 ? attn::cu_count(1) : 256;
+    const long long ranges = (long long)BH * n_eff;
+    const long long wg64 = ranges * ((p.S_q + 63) / 64), wg128 = ranges * ((p.S_q + 127) / 128);
+    int rc;
+    if constexpr (D == 128) {
+        rc = p.S_q <= 64 || wg64 <= cus ? launch_ranges<128, 1, 1, 2, F16, 2>(p, BH, n_eff, st)
+                                        : launch_ranges<128, 1, 2, 8, F16, 1>(p, BH, n_eff, st);
+    } else {
+        const bool groups = p.S_q <= 64 ? p.split_len >= 2048 || (2 * wg64 <= cus && p.split_len >= 512)
+                                        : wg64 <= cus && p.split_len >= 512;
+        if (groups)
+            rc = launch_ranges<64, 1, 2, 2, F16, 2>(p, BH, n_eff, st);
+        else if (p.S_q <= 128 || wg128 <= cus)
+            rc = launch_ranges<64, 1, 2, 4, F16, 1>(p, BH, n_eff, st);
+        else
+            rc = launch_ranges<64, 1, 2, 8, F16, 1>(p, BH, n_eff, st);
+    }
+    if (rc != ATTN_OK)
+        return rc;
+    const int lanes_log2 = attn::merge_lanes_log2(D, n_eff);
+    const int rpb = (attn::kMergeThreads / (D / 4)) >> lanes_log2;
     const long long blocks = (n_rows + rpb - 1) / rpb;
-    const unsigned grid = (unsigned)(blocks < 8192 ? blocks : 8192);
-    hipLaunchKernelGGL((attn::attn_splitkv_merge_kernel<D, out_t>), dim3(grid), dim3(256), 0, st, p.o_part, p.lse_part,
-                       static_cast<out_t *>(o), lse, n_rows, n_eff);
+    const unsigned grid = (unsigned)(blocks < 16384 ? blocks : 16384);
+    hipLaunchKernelGGL((attn::attn_splitkv_merge_kernel<D, out_t>), dim3(grid), dim3(attn::kMergeThreads), 0, st, p.o_part,
+                       p.lse_part, static_cast<out_t *>(o), lse, n_rows, n_eff, lanes_log2);
     return hipGetLastError() == hipSuccess ? ATTN_OK : ATTN_ERR_LAUNCH;
 }
 

@@ -48,3 +48,25 @@ def test_key_groups_against_the_oracle(S_q, S_kv, causal):
                     print("S_q", S_q, "S_kv", S_kv, "D", D, "causal", causal, "variant", variant, flush=True)
                     o, lse = debug_lib.attn_fwd_variant(qd, kd, vd, causal, scale, variant)
                     check(o, lse, want, o_tol)
+
+
+# heads, S_q, S_kv, ranges: one tile per range, ranges of unequal length, every count of lanes of the merge, many rows
+SPLITS = [(2, 1, 130, 2), (3, 1, 5000, 3), (2, 64, 5000, 2), (2, 65, 3000, 5), (1, 130, 9000, 17), (2, 257, 4097, 8),
+          (40, 129, 2000, 16), (300, 2, 300, 4), (2, 7, 12800, 200), (70, 200, 4200, 2)]
+
+
+@pytest.mark.parametrize("heads,S_q,S_kv,n_split", SPLITS)
+def test_ranges_against_the_oracle(heads, S_q, S_kv, n_split):
+    for D in (64, 128):
+        scale = synth.default_scale(D)
+        for dtype, dt, o_tol, call in (("bf16", torch.bfloat16, 2e-2, binding.attn_fwd_splitkv),
+                                       ("f16", torch.float16, 4e-3, binding.attn_fwd_splitkv_f16)):
+            q, k, v = synth.make_qkv(1, heads, S_q, S_kv, D, seed=78, sharp=(heads == 3), dtype=dtype)
+            qd, kd, vd = (on_gpu(x, dt) for x in (q, k, v))
+            print("heads", heads, "S_q", S_q, "S_kv", S_kv, "D", D, dtype, "ranges", n_split, flush=True)
+            need = binding.attn_fwd_splitkv_workspace_bytes(1, heads, S_q, D, n_split)
+            ws = torch.full((need // 4,), float("nan"), dtype=torch.float32, device="cuda")
+            o, lse = call(qd, kd, vd, n_split, workspace=ws, scale=scale)
+            keep = sorted({0, heads - 1})                     # two heads are enough for the oracle
+            sel = lambda x: np.ascontiguousarray(x[:, keep])
+            check(o[:, keep], lse[:, keep], attn_ref(sel(q), sel(k), sel(v), False, scale, dtype=dtype), o_tol)
