@@ -13,7 +13,8 @@
 // Requires scale > 0 (masked scores are set to -inf before the multiply by scale*log2e).
 //
 // Workgroups are persistent, like the forward kernels': a launch has as many workgroups as the chip holds at
-// once and each walks the queue of owner tiles of its XCD (persistent_entry in attn_common.h).
+// once and each walks the queue of owner tiles of its XCD (persistent_entry in attn_common.h).  One launch holds both
+// sweeps: the queue is all key-owner tiles, then all query-owner tiles (BwdSweeps).
 #pragma once
 #include "attn_bwd_kernels.h"  // BwdParams
 #include "attn_common.h"
@@ -22,10 +23,22 @@
 
 namespace attn {
 
+// The queue of a launch: entries [0, n_kv) are key-owner tiles (heavier: four products per streamed tile against three,
+// so they go first), entries [q_first, q_first + n_q) query-owner tiles; q_first is n_kv rounded up to a multiple of the
+// XCD count, so that entry e belongs to XCD e % 8 in both halves.  Entries in between stand for nothing.
+struct BwdQueue {
+    int n_kv, q_first, n_entries;
+    __host__ __device__ BwdQueue(int kv, int q)
+        : n_kv(kv), q_first((kv + kNumXcd - 1) / kNumXcd * kNumXcd), n_entries(q ? q_first + q : kv)
+    {
+    }
+};
+
+// One sweep's part of the workgroup's walk: takes up entries from pass `pass` on for as long as they are this sweep's.
 // F16: q, k, v, d_o and the gradients are IEEE fp16 instead of bf16 (the element type of the paper's
 // Section 6.3 figures); the pointers in BwdParams are then reinterpreted.
-template <int D, bool CAUSAL, bool KEY_OWNER, bool F16 = false>
-__global__ __launch_bounds__(256) void attn_bwd_asm_kernel(const BwdParams p)
+template <int D, bool CAUSAL, bool KEY_OWNER, bool F16>
+__device__ __forceinline__ void bwd_sweep(const BwdParams &p, const BwdQueue &queue, int &pass)
 {
     static_assert(D == 128 || D == 64, "hand-scheduled backward sweeps: D = 64 or 128");
     typedef typename std::conditional<F16, ElemF16, ElemBF16>::type E;
@@ -45,7 +58,8 @@ __global__ __launch_bounds__(256) void attn_bwd_asm_kernel(const BwdParams p)
     constexpr uint32_t RING1 = 0, RING2 = NST * TB, AUX = 2 * NST * TB;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(ATTN_LDS_PTR(unsigned char))smem;
 
-    const int tid = threadIdx.x;
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));   // no address of one sweep is kept in registers across the other one's loop
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lq = lane & 31;
@@ -111,21 +125,21 @@ __global__ __launch_bounds__(256) void attn_bwd_asm_kernel(const BwdParams p)
     }
     const uint32_t aux_off = lds_aux + 16 * g;
 
-    const int n_slots = (int)gridDim.x;
-    const int n_pass =   // the longest queue of an XCD, in passes of n_slots / 8 entries
-        n_slots >= p.total_wg ? 1 : ((p.total_wg + kNumXcd - 1) / kNumXcd + n_slots / kNumXcd - 1) / (n_slots / kNumXcd);
+    const int n_t = KEY_OWNER ? p.n_t : p.n_tq, total = KEY_OWNER ? p.total_wg : p.total_q;
 #pragma clang loop unroll(disable)
-    for (int pass = 0; pass < n_pass; ++pass) {
-        const int vb = persistent_entry(blockIdx.x, n_slots, p.total_wg, pass);
-        if (vb < 0)
-            break;  // only the last pass can be short
+    for (;; ++pass) {
+        const int entry = persistent_entry(blockIdx.x, (int)gridDim.x, queue.n_entries, pass);
+        if (entry < 0 || (KEY_OWNER && entry >= queue.n_kv))
+            break;   // (entries rise from pass to pass; only the last pass can be short)
+        if (!KEY_OWNER && entry < queue.q_first)
+            continue;
         if (pass > 0)
             __syncthreads();  // every wave has read the previous tile's staged gradients back: the rings are free
         int bh, ot;
         // a head's sweeps stream Q, dO, K and V between them
-        wg_to_tile_n<CAUSAL>(vb, p.total_wg, p.n_t, 4ll * (p.S_q + p.S_kv) * D, bh, ot);
+        wg_to_tile_n<CAUSAL>(KEY_OWNER ? entry : entry - queue.q_first, total, n_t, 4ll * (p.S_q + p.S_kv) * D, bh, ot);
         if (CAUSAL && KEY_OWNER)
-            ot = p.n_t - 1 - ot;  // early key tiles stream the most queries: heaviest first
+            ot = n_t - 1 - ot;  // early key tiles stream the most queries: heaviest first
         const int S_own = KEY_OWNER ? p.S_kv : p.S_q;
         const int S_str = KEY_OWNER ? p.S_q : p.S_kv;
         const int o0 = ot * BO;
@@ -293,6 +307,18 @@ __global__ __launch_bounds__(256) void attn_bwd_asm_kernel(const BwdParams p)
         if constexpr (KEY_OWNER)
             write_out(acc + DB, 1.f, reinterpret_cast<elem_t *>(p.dv) + k_head, RING2);
     }
+}
+
+// SWEEPS: 1 = key owners, 2 = query owners, 3 = both (at D = 64 either one alone as well: attn_bwd.hip, launch_hand)
+template <int D, bool CAUSAL, bool F16, int SWEEPS>
+__global__ __launch_bounds__(256) void attn_bwd_asm_kernel(const BwdParams p)
+{
+    const BwdQueue queue(SWEEPS & 1 ? p.total_wg : 0, SWEEPS & 2 ? p.total_q : 0);
+    int pass = 0;
+    if constexpr (SWEEPS & 1)
+        bwd_sweep<D, CAUSAL, true, F16>(p, queue, pass);
+    if constexpr (SWEEPS & 2)
+        bwd_sweep<D, CAUSAL, false, F16>(p, queue, pass);
 }
 
 }  // namespace attn

@@ -37,8 +37,9 @@ struct BwdParams {
     float *delta;  // workspace, [B][H][S_q], directly behind lse2: Delta
     bf16_t *dq, *dk, *dv;
     int S_q, S_kv;
-    int n_t;       // owner tiles per (b,h) of the launched sweep
+    int n_t;       // owner tiles per (b,h) of the launched sweep (a launch of both: of the key-owner sweep)
     int total_wg;  // B*H*n_t
+    int n_tq, total_q;  // the same for the query-owner sweep (hand-scheduled sweeps)
     long long n_rows;  // B*H*S_q (delta kernel)
     float c;       // scale * log2(e)
     float scale;
