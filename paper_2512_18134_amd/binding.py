@@ -1,8 +1,12 @@
-"""ctypes binding of libmi355attn.so: argument marshalling only.
+"""Binding of libmi355attn.so: argument marshalling only.
 
 Same names as include/attn_fwd.h.  There is no fallback: importing this module
 raises if the library has not been built (python -m paper_2512_18134_amd.build).
 PyTorch appears only as the owner of device memory and of the stream.
+
+A call on plain contiguous tensors goes through the extension module _marshal
+(csrc/marshal.cpp); it hands every other call back, and the code here checks its
+arguments, raises what is to be raised and calls the library through ctypes.
 """
 import ctypes
 import os
@@ -91,6 +95,32 @@ def attn_workgroup_tile(causal, workgroup, n_heads, n_tiles, head_bytes=0):
     return head.value, tile.value
 
 
+_marshal_module = None
+
+
+def _native():
+    """The extension module, loaded on first use (it needs torch's libraries in the process)."""
+    global _marshal_module
+    if _marshal_module is None:
+        import torch
+        from . import _marshal as module
+        address = lambda f: ctypes.cast(f, ctypes.c_void_p).value
+        module.set_entries(address(_lib.attn_fwd), address(_lib.attn_fwd_f16), address(_lib.attn_fwd_splitkv),
+                           address(_lib.attn_fwd_splitkv_f16), address(_lib.attn_bwd), address(_lib.attn_bwd_f16),
+                           address(_lib.attn_fwd_splitkv_workspace_bytes),
+                           getattr(torch._C, "_cuda_getCurrentRawStream",
+                                   lambda index: torch.cuda.current_stream(index).cuda_stream))
+        _marshal_module = module
+    return _marshal_module
+
+
+def _finish(result):
+    """What a native call returned: its outputs, or a status to raise."""
+    if type(result) is tuple:
+        return result
+    raise AttnError(result)
+
+
 def attn_fwd_raw(q_ptr, k_ptr, v_ptr, o_ptr, lse_ptr, B, H, S_q, S_kv, D, causal, scale, stream_ptr):
     """The C entry point with raw integer addresses; returns the attn_status."""
     return int(_lib.attn_fwd(q_ptr, k_ptr, v_ptr, o_ptr, lse_ptr, B, H, S_q, S_kv, D,
@@ -111,12 +141,18 @@ def attn_fwd(q, k, v, o=None, lse=None, causal=False, scale=None, stream=None):
     `stream` (default: torch's current stream) and is asynchronous.
     Returns (o, lse).
     """
+    r = (_marshal_module or _native()).fwd(0, q, k, v, o, lse, causal, scale, stream)
+    if r is not None:
+        return _finish(r)
     import torch
     return _marshal(attn_fwd_raw, torch.bfloat16, q, k, v, o, lse, causal, scale, stream)
 
 
 def attn_fwd_f16(q, k, v, o=None, lse=None, causal=False, scale=None, stream=None):
     """attn_fwd_f16 on torch device tensors: as attn_fwd, with fp16 q, k, v, o (D = 64 or 128)."""
+    r = (_marshal_module or _native()).fwd(1, q, k, v, o, lse, causal, scale, stream)
+    if r is not None:
+        return _finish(r)
     import torch
     return _marshal(attn_fwd_f16_raw, torch.float16, q, k, v, o, lse, causal, scale, stream)
 
@@ -183,6 +219,9 @@ def attn_bwd_noalloc(q, k, v, o, d_o, lse, dq, dk, dv, causal=False, scale=None,
 def attn_bwd_f16(q, k, v, o, d_o, lse, dq=None, dk=None, dv=None, delta_ws=None, causal=False, scale=None,
                  stream=None):
     """attn_bwd_f16 on torch device tensors: as attn_bwd, with fp16 tensors."""
+    r = (_marshal_module or _native()).bwd(1, q, k, v, o, d_o, lse, dq, dk, dv, delta_ws, causal, scale, stream)
+    if r is not None:
+        return _finish(r)
     import torch
     return _marshal_bwd(attn_bwd_f16_raw, torch.float16, q, k, v, o, d_o, lse, dq, dk, dv, delta_ws, causal, scale,
                         stream)
@@ -195,6 +234,9 @@ def attn_bwd(q, k, v, o, d_o, lse, dq=None, dk=None, dv=None, delta_ws=None, cau
     written by attn_fwd.  dq, dk, dv (bf16) and the fp32 workspace delta_ws (2*B*H*S_q floats) are
     allocated when not given.  Asynchronous on `stream`.  Returns (dq, dk, dv).
     """
+    r = (_marshal_module or _native()).bwd(0, q, k, v, o, d_o, lse, dq, dk, dv, delta_ws, causal, scale, stream)
+    if r is not None:
+        return _finish(r)
     import torch
     return _marshal_bwd(attn_bwd_raw, torch.bfloat16, q, k, v, o, d_o, lse, dq, dk, dv, delta_ws, causal, scale, stream)
 
@@ -261,6 +303,9 @@ def attn_fwd_splitkv_f16_raw(q_ptr, k_ptr, v_ptr, o_ptr, lse_ptr, ws_ptr, ws_byt
 def attn_fwd_splitkv(q, k, v, n_split, o=None, lse=None, workspace=None, causal=False, scale=None, stream=None):
     """attn_fwd_splitkv on torch device tensors (bf16).  `workspace`: a contiguous GPU tensor of at least
     attn_fwd_splitkv_workspace_bytes(...) bytes (allocated when not given).  Returns (o, lse)."""
+    r = (_marshal_module or _native()).splitkv(0, q, k, v, n_split, o, lse, workspace, causal, scale, stream)
+    if r is not None:
+        return _finish(r)
     import torch
     return _marshal_splitkv(attn_fwd_splitkv_raw, torch.bfloat16, q, k, v, n_split, o, lse, workspace, causal, scale,
                             stream)
@@ -268,6 +313,9 @@ def attn_fwd_splitkv(q, k, v, n_split, o=None, lse=None, workspace=None, causal=
 
 def attn_fwd_splitkv_f16(q, k, v, n_split, o=None, lse=None, workspace=None, causal=False, scale=None, stream=None):
     """attn_fwd_splitkv_f16 on torch device tensors: as attn_fwd_splitkv, with fp16 tensors."""
+    r = (_marshal_module or _native()).splitkv(1, q, k, v, n_split, o, lse, workspace, causal, scale, stream)
+    if r is not None:
+        return _finish(r)
     import torch
     return _marshal_splitkv(attn_fwd_splitkv_f16_raw, torch.float16, q, k, v, n_split, o, lse, workspace, causal, scale,
                             stream)

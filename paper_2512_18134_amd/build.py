@@ -2,19 +2,24 @@
 
     python -m paper_2512_18134_amd.build
 
-Two libraries come out of the same sources: libmi355attn.so (the product) and
+Three files come out.  Two libraries of the same sources: libmi355attn.so (the product) and
 libmi355attn_debug.so (-DATTN_DEBUG_ENTRY_POINTS: the same code plus test-only entry
 points that let a test pick the kernel, e.g. the program-order reference of the
 schedule-equivalence tests).  Nothing in the package loads the debug library.
+And _marshal.so, the host-only extension module that takes torch tensors to the entry
+points (csrc/marshal.cpp).
 """
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 SOURCES = [os.path.join(HERE, "csrc", "attn_fwd.hip"), os.path.join(HERE, "csrc", "attn_bwd.hip")]
 LIB_PATH = os.path.join(HERE, "libmi355attn.so")
+MARSHAL_SOURCE = os.path.join(HERE, "csrc", "marshal.cpp")
+MARSHAL_PATH = os.path.join(HERE, "_marshal.so")
 DEBUG_LIB_PATH = os.path.join(HERE, "libmi355attn_debug.so")
 
 HIPCC_FLAGS = [
@@ -51,8 +56,23 @@ def generate_sources(verbose=False, out_dir=None):
 
 def _compile(lib_path, extra, verbose):
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    return _run_compiler([hipcc] + HIPCC_FLAGS + extra, SOURCES, [], lib_path, verbose)
+
+
+def _compile_marshal(verbose):
+    """The extension module: host code against torch's headers and libraries (which the importing process has loaded)."""
+    import torch
+    from torch.utils import cpp_extension
+    inc = cpp_extension.include_paths() + [sysconfig.get_paths()["include"]]
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI)] + ["-I" + i for i in inc]
+    libs = ["-L" + os.path.join(os.path.dirname(torch.__file__), "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    return _run_compiler(cmd, [MARSHAL_SOURCE], libs, MARSHAL_PATH, verbose)
+
+
+def _run_compiler(cmd, sources, libs, lib_path, verbose):
     tmp = lib_path + ".tmp.%d" % os.getpid()
-    cmd = [hipcc] + HIPCC_FLAGS + extra + ["-o", tmp] + SOURCES
+    cmd = cmd + ["-o", tmp] + sources + libs
     if verbose:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
@@ -60,7 +80,7 @@ def _compile(lib_path, extra, verbose):
     if res.returncode != 0:
         if os.path.exists(tmp):
             os.remove(tmp)
-        raise RuntimeError("hipcc failed:\n" + out)
+        raise RuntimeError("%s failed:\n%s" % (cmd[0], out))
     if verbose and out.strip():
         print(out)
     os.replace(tmp, lib_path)
@@ -69,9 +89,10 @@ def _compile(lib_path, extra, verbose):
 
 def build_library(verbose=False, debug=True):
     """Generate the scheduled loops, then compile every HIP source into LIB_PATH (and, with the test-only
-    entry points, into DEBUG_LIB_PATH).  Raises on failure."""
+    entry points, into DEBUG_LIB_PATH), and the extension module.  Raises on failure."""
     generate_sources(verbose)
     _compile(LIB_PATH, [], verbose)
+    _compile_marshal(verbose)
     if debug:
         _compile(DEBUG_LIB_PATH, ["-DATTN_DEBUG_ENTRY_POINTS"], verbose)
     return LIB_PATH

@@ -1,0 +1,79 @@
+"""The binding's two ways to the library (csrc/marshal.cpp for plain tensors, Python for the rest) take the same calls
+and give the same bits: a `causal` that is no bool sends a call the Python way.  What one way refuses the other refuses."""
+import pytest
+import torch
+
+from paper_2512_18134_amd import binding
+
+pytestmark = pytest.mark.gpu
+
+
+def tensors(dt, B=2, H=3, S_q=70, S_kv=130, D=64):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    mk = lambda S: torch.empty((B, H, S, D), device="cuda").normal_(generator=g).to(dt)
+    return mk(S_q), mk(S_kv), mk(S_kv), mk(S_q)
+
+
+def same(a, b):
+    return len(a) == len(b) and all(x.dtype == y.dtype and torch.equal(x, y) for x, y in zip(a, b))
+
+
+@pytest.mark.parametrize("dt", [torch.bfloat16, torch.float16])
+def test_both_ways_give_the_same(dt):
+    fwd, split, bwd = ((binding.attn_fwd, binding.attn_fwd_splitkv, binding.attn_bwd) if dt == torch.bfloat16 else
+                       (binding.attn_fwd_f16, binding.attn_fwd_splitkv_f16, binding.attn_bwd_f16))
+    q, k, v, d_o = tensors(dt)
+    for causal in (False, True):
+        o, lse = fwd(q, k, v, causal=causal)
+        assert same(fwd(q, k, v, causal=int(causal)), (o, lse))
+        assert o.is_contiguous() and lse.shape == q.shape[:3] and lse.dtype == torch.float32
+        o2, lse2 = torch.full_like(o, 7), torch.full_like(lse, 7)
+        out = fwd(q, k, v, o2, lse2, causal=causal, scale=0.25)
+        assert out[0].data_ptr() == o2.data_ptr() and same(fwd(q, k, v, causal=int(causal), scale=0.25), (o2, lse2))
+        grads = bwd(q, k, v, o, d_o, lse, causal=causal)
+        assert same(bwd(q, k, v, o, d_o, lse, causal=int(causal)), grads)
+        ws = torch.empty(2 * lse.numel(), dtype=torch.float32, device="cuda")
+        given = [torch.full_like(t, 7) for t in (q, k, v)]
+        assert same(bwd(q, k, v, o, d_o, lse, *given, ws, causal=causal), grads) and same(given, grads)
+    part = split(q, k, v, 2)
+    assert same(split(q, k, v, 2, causal=0), part)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        on_current = fwd(q, k, v)
+    named = fwd(q, k, v, stream=side)
+    torch.cuda.synchronize()
+    assert same(on_current, fwd(q, k, v)) and same(named, on_current)
+    p = torch.nn.Parameter(q)                      # gradients are not tracked, as before
+    assert not fwd(p, k, v)[0].requires_grad
+
+
+def test_refusals_are_the_same():
+    q, k, v, d_o = tensors(torch.bfloat16)
+    o, lse = binding.attn_fwd(q, k, v)
+    bad_calls = [
+        (TypeError, lambda c: binding.attn_fwd(q.float(), k, v, causal=c)),
+        (TypeError, lambda c: binding.attn_fwd(q.transpose(1, 2), k, v, causal=c)),
+        (TypeError, lambda c: binding.attn_fwd(q[0], k[0], v[0], causal=c)),
+        (TypeError, lambda c: binding.attn_fwd(q.cpu(), k, v, causal=c)),
+        (ValueError, lambda c: binding.attn_fwd(q, k[:, :2].contiguous(), v, causal=c)),
+        (TypeError, lambda c: binding.attn_fwd(q, k, v, o=o.half(), causal=c)),
+        (TypeError, lambda c: binding.attn_fwd(q, k, v, lse=lse[:, :, :1].contiguous(), causal=c)),
+        (binding.AttnError, lambda c: binding.attn_fwd(q, k, v, scale=-1.0, causal=c)),
+        (binding.AttnError, lambda c: binding.attn_fwd(q, k, v, scale=float("nan"), causal=c)),
+        (binding.AttnError, lambda c: binding.attn_fwd(*(t[..., :32].contiguous() for t in (q, k, v)), causal=c)),
+        (ValueError, lambda c: binding.attn_bwd(q, k, v, o[:, :, :5].contiguous(), d_o, lse, causal=c)),
+        (TypeError, lambda c: binding.attn_bwd(q, k, v, o, d_o, lse.double(), causal=c)),
+        (TypeError, lambda c: binding.attn_bwd(q, k, v, o, d_o, lse, delta_ws=lse, causal=c)),
+        (binding.AttnError, lambda c: binding.attn_fwd_splitkv(q, k, v, 0, causal=c)),
+        (binding.AttnError, lambda c: binding.attn_fwd_splitkv(q, k, v, 300, causal=c)),
+        (binding.AttnError, lambda c: binding.attn_fwd_splitkv(q, k, v, 2, workspace=torch.empty(8, device="cuda"), causal=c)),
+        (AttributeError, lambda c: binding.attn_fwd(q, k, v, stream="none", causal=c)),
+    ]
+    for error, call in bad_calls:
+        for causal in (False, 0):
+            with pytest.raises(error):
+                call(causal)
+    with pytest.raises(binding.AttnError):
+        binding.attn_fwd_splitkv(q, k, v, 2, causal=True)
