@@ -193,6 +193,10 @@ __device__ __forceinline__ void bwd_sweep(const BwdParams &p, const BwdQueue &qu
                 b2[ks] = *reinterpret_cast<const ex8 *>(s2 + 16 * ks);
             }
         }
+        // the second operand is negated and dP starts from Delta: the MFMAs deliver t = Delta - dP (gen_attn_bwd_loop.py)
+    #pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+            b2[ks] = __builtin_bit_cast(ex8, __builtin_bit_cast(u32x4, b2[ks]) ^ 0x80008000u);
         f32x16 acc[NSET * DB];
     #pragma unroll
         for (int i = 0; i < NSET * DB; ++i)
@@ -203,23 +207,9 @@ __device__ __forceinline__ void bwd_sweep(const BwdParams &p, const BwdQueue &qu
         wait_vmcnt<0>();
         __syncthreads();
 
-        // S(0) and dP(0)
-        f32x16 s_init, dp_init;
-    #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            s_init[r] = 0.f;
-            dp_init[r] = 0.f;
-        }
-    #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            const ex8 a1 = *(ATTN_LDS_PTR(const ex8))(uintptr_t)(roff[ks]);
-            const ex8 a2 = *(ATTN_LDS_PTR(const ex8))(uintptr_t)(roff[ks] + (RING2 - RING1));
-            s_init = E::mfma(a1, b1[ks], s_init);
-            dp_init = E::mfma(a2, b2[ks], dp_init);
-        }
         // LSE' and Delta of tile 0 (key-owner: 16 rows per lane; query-owner: this lane's query)
-        typedef typename std::conditional<KEY_OWNER, f32x16, float>::type aux_t;
-        aux_t aux_l, aux_d;
+        typename std::conditional<KEY_OWNER, f32x16, float>::type aux_l;
+        f32x16 aux_d;
         if constexpr (KEY_OWNER) {
     #pragma unroll
             for (int a = 0; a < 4; ++a) {
@@ -233,7 +223,23 @@ __device__ __forceinline__ void bwd_sweep(const BwdParams &p, const BwdQueue &qu
             }
         } else {
             aux_l = aux_head[own_c];
-            aux_d = aux_head[p.n_rows + own_c];
+            const float delta = aux_head[p.n_rows + own_c];
+    #pragma unroll
+            for (int r = 0; r < 16; ++r)
+                aux_d[r] = delta;
+        }
+
+        // S(0) and t(0)
+        f32x16 s_init, dp_init = aux_d;
+    #pragma unroll
+        for (int r = 0; r < 16; ++r)
+            s_init[r] = 0.f;
+    #pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            const ex8 a1 = *(ATTN_LDS_PTR(const ex8))(uintptr_t)(roff[ks]);
+            const ex8 a2 = *(ATTN_LDS_PTR(const ex8))(uintptr_t)(roff[ks] + (RING2 - RING1));
+            s_init = E::mfma(a1, b1[ks], s_init);
+            dp_init = E::mfma(a2, b2[ks], dp_init);
         }
 
         typedef uint32_t u32x16 __attribute__((ext_vector_type(16)));
@@ -271,7 +277,7 @@ __device__ __forceinline__ void bwd_sweep(const BwdParams &p, const BwdQueue &qu
     #include "generated/attn_bwd_loop_q_d128_f16.inc"
         }
 
-        // ---- epilogue: dK = scale * acc[0..], dV = acc[DB..] (or dQ = scale * acc), 16-bit, row = owner.
+        // ---- epilogue: dK = -scale * acc[0..], dV = acc[DB..] (or dQ = -scale * acc), 16-bit, row = owner.
         // A lane holds 4-element pieces of ONE owner row: stored directly, a wave-wide store touches 32 rows
         // with 16 bytes each.  So the gradients go through LDS and leave in whole rows: every wave has its own
         // 32 x ROWB bytes of a ring (dK / dQ in the first, dV in the second) and reads back only what it wrote;
@@ -303,7 +309,7 @@ __device__ __forceinline__ void bwd_sweep(const BwdParams &p, const BwdQueue &qu
                     *reinterpret_cast<u32x4 *>(blk + (size_t)r * D + c * 8) = w;
             }
         };
-        write_out(acc, p.scale, reinterpret_cast<elem_t *>(KEY_OWNER ? p.dk : p.dq) + (KEY_OWNER ? k_head : q_head), RING1);
+        write_out(acc, -p.scale, reinterpret_cast<elem_t *>(KEY_OWNER ? p.dk : p.dq) + (KEY_OWNER ? k_head : q_head), RING1);
         if constexpr (KEY_OWNER)
             write_out(acc + DB, 1.f, reinterpret_cast<elem_t *>(p.dv) + k_head, RING2);
     }
