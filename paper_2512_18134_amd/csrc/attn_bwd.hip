@@ -37,17 +37,16 @@ int launch_sweep(K kern, BwdParams p, int BH, int S_own, int NW, int lds_bytes, 
     return hipGetLastError() == hipSuccess ? ATTN_OK : ATTN_ERR_LAUNCH;
 }
 
-// hand-scheduled sweeps (SWEEPS as in the kernel): as many workgroups as the chip holds at once, each walking the
-// queue of owner tiles of its XCD
-template <int D, bool F16, int SWEEPS>
+// both hand-scheduled sweeps: as many workgroups as the chip holds at once, each walking the queue of owner tiles of its
+// XCD
+template <int D, bool F16>
 int launch_asm(const BwdParams &p, int causal, hipStream_t stream)
 {
-    constexpr int LDS = 2 * 6 * 32 * D * 2 + (SWEEPS & 1 ? 6 * 256 : 0);
-    const long long entries = attn::BwdQueue(SWEEPS & 1 ? p.total_wg : 0, SWEEPS & 2 ? p.total_q : 0).n_entries;
-    auto kern = causal ? attn::attn_bwd_asm_kernel<D, true, F16, SWEEPS> : attn::attn_bwd_asm_kernel<D, false, F16, SWEEPS>;
+    constexpr int LDS = 2 * 6 * 32 * D * 2 + 6 * 256;
+    auto kern = causal ? attn::attn_bwd_asm_kernel<D, true, F16> : attn::attn_bwd_asm_kernel<D, false, F16>;
     if (!attn::allow_lds(reinterpret_cast<const void *>(kern), LDS))
         return ATTN_ERR_LAUNCH;
-    int grid = (int)entries;
+    int grid = attn::BwdQueue(p.total_wg, p.total_q).n_entries;
     // (a runtime that cannot tell the occupancy gets one workgroup per entry: the kernel takes either)
     const int slots = attn::persistent_slots(reinterpret_cast<const void *>(kern), 256, LDS, attn::kNumXcd);
     if (slots >= attn::kNumXcd && slots < grid)
@@ -67,11 +66,8 @@ int launch_delta(const BwdParams &p, hipStream_t stream)
 
 // Delta, then both hand-scheduled sweeps (scale > 0), in one launch: few owner tiles then fill the chip together, and
 // no launch gap or half-empty last round separates the sweeps.  The same bits.  Measured (whole call, one launch per
-// sweep -> one for both): D = 128, 16 heads of 128 rows 20.2 -> 13.2 us, of 1024 rows 54.4 -> 38.2, causal 53.5 -> 34.4;
-// of 4096 rows 408.8 -> 404.7; 128 heads of 2048 rows 860 -> 850.  D = 64, 16 heads of 1024 rows 38.4 -> 24.8, causal
-// 39.1 -> 24.0; but its query-owner sweep alone runs two workgroups to a CU (240 registers against 328), which is worth
-// more from about three rounds of tiles on (32 heads of 2048 rows 128.8 -> 131.9, 16 of 16384 rows 3625 -> 3759), six
-// with a causal mask (48 heads of 2048 rows 121.9 -> 118.1; 128 of 1024 rows 97.8 -> 100.8).
+// sweep -> one for both), D = 128: 16 heads of 128 rows 20.2 -> 13.2 us, of 1024 rows 54.4 -> 38.2, causal 53.5 -> 34.4;
+// of 4096 rows 408.8 -> 404.7; 128 heads of 2048 rows 860 -> 850.
 template <int D, bool F16>
 int launch_hand(BwdParams p, int BH, int causal, hipStream_t stream)
 {
@@ -82,17 +78,12 @@ int launch_hand(BwdParams p, int BH, int causal, hipStream_t stream)
         return ATTN_ERR_SHAPE;
     p.total_wg = (int)total_kv;
     p.total_q = (int)total_q;
+    const int cus = attn::cu_count(attn::kNumXcd);
+    p.cus_per_xcd = cus > 0 ? cus / attn::kNumXcd : 32;
     const int rc = launch_delta<D, typename std::conditional<F16, _Float16, attn::bf16_t>::type>(p, stream);
     if (rc != ATTN_OK)
         return rc;
-    if constexpr (D == 64) {
-        const int cus = attn::cu_count(1) > 0 ? attn::cu_count(1) : 256;
-        if (total_kv + total_q > (causal ? 6ll : 3ll) * cus) {
-            const int rk = launch_asm<D, F16, 1>(p, causal, stream);
-            return rk != ATTN_OK ? rk : launch_asm<D, F16, 2>(p, causal, stream);
-        }
-    }
-    return launch_asm<D, F16, 3>(p, causal, stream);
+    return launch_asm<D, F16>(p, causal, stream);
 }
 
 // plain: run the compiler-scheduled sweeps (always when scale == 0, which the hand-scheduled loops exclude)
@@ -155,6 +146,7 @@ static int validate_bwd(const void *q, const void *k, const void *v, const void 
     p.S_kv = S_kv;
     p.n_t = 0;
     p.total_wg = 0;
+    p.cus_per_xcd = 0;
     p.n_tq = 0;
     p.total_q = 0;
     p.n_rows = BH * S_q;
@@ -222,6 +214,15 @@ extern "C" int attn_bwd_noalloc(const void *q, const void *k, const void *v, con
 }
 
 #ifdef ATTN_DEBUG_ENTRY_POINTS
+// Test-only, host only: the queue entry that workgroup `wg` of a backward launch of n_slots workgroups takes up in pass
+// k, for n_kv key-owner and n_q query-owner tiles (BwdQueue); *first_q = entry number of the first query-owner tile.
+extern "C" int attn_bwd_queue_entry(int n_kv, int n_q, int wg, int n_slots, int cus, int k, int *first_q)
+{
+    const attn::BwdQueue queue(n_kv, n_q);
+    *first_q = queue.q_first;
+    return queue.entry(wg, n_slots < queue.n_entries ? n_slots : queue.n_entries, cus, k);
+}
+
 // Test-only entry point of the debug build of the library: attn_bwd on the compiler-scheduled sweeps
 // (the reference of the schedule-equivalence test).
 extern "C" int attn_bwd_plain(const void *q, const void *k, const void *v, const void *o, const void *d_o,

@@ -13,8 +13,8 @@
 // Requires scale > 0 (masked scores are set to -inf before the multiply by scale*log2e).
 //
 // Workgroups are persistent, like the forward kernels': a launch has as many workgroups as the chip holds at
-// once and each walks the queue of owner tiles of its XCD (persistent_entry in attn_common.h).  One launch holds both
-// sweeps: the queue is all key-owner tiles, then all query-owner tiles (BwdSweeps).
+// once and each walks the queue of owner tiles of its XCD.  One launch holds both sweeps: the queue is all key-owner
+// tiles, then all query-owner tiles (BwdQueue).
 #pragma once
 #include "attn_bwd_kernels.h"  // BwdParams
 #include "attn_common.h"
@@ -32,13 +32,32 @@ struct BwdQueue {
         : n_kv(kv), q_first((kv + kNumXcd - 1) / kNumXcd * kNumXcd), n_entries(q ? q_first + q : kv)
     {
     }
+    // The entry that workgroup `wg` of a launch of n_slots (a multiple of the XCD count, or >= n_entries) takes up in
+    // pass k, or -1.  A pass goes through one entry per workgroup of the XCD, odd passes in reverse, so that a
+    // workgroup pairs heavy with light tiles.  Workgroup m of an XCD runs on its compute unit m % cus, also where a unit
+    // holds two (measured): the first `cus` of them take their part of a pass in reverse, so that the two on a unit
+    // pair heavy with light as well, and the units with the lightest tiles are the ones that a second workgroup joins
+    // where there are not enough entries for all.  Entries rise from pass to pass.
+    __host__ __device__ int entry(int wg, int n_slots, int cus, int k) const
+    {
+        const int xcd = wg % kNumXcd, m = wg / kNumXcd;
+        const int n_x = (n_entries - xcd + kNumXcd - 1) / kNumXcd;   // queue length of this XCD
+        const bool single = n_slots >= n_entries;                    // one entry per workgroup, one pass
+        const int per_pass = single ? n_x : n_slots / kNumXcd;
+        if (single && (k > 0 || m >= n_x))
+            return -1;
+        const int first = per_pass < cus ? per_pass : cus;
+        const int at = m < first ? first - 1 - m : m;
+        const int idx = k * per_pass + (k & 1 ? per_pass - 1 - at : at);
+        return idx < n_x ? idx * kNumXcd + xcd : -1;
+    }
 };
 
 // One sweep's part of the workgroup's walk: takes up entries from pass `pass` on for as long as they are this sweep's.
 // F16: q, k, v, d_o and the gradients are IEEE fp16 instead of bf16 (the element type of the paper's
 // Section 6.3 figures); the pointers in BwdParams are then reinterpreted.
 template <int D, bool CAUSAL, bool KEY_OWNER, bool F16>
-__device__ __forceinline__ void bwd_sweep(const BwdParams &p, const BwdQueue &queue, int &pass)
+__device__ __forceinline__ void bwd_sweep(const BwdParams &p, const BwdQueue &queue, const int wave, int &pass)
 {
     static_assert(D == 128 || D == 64, "hand-scheduled backward sweeps: D = 64 or 128");
     typedef typename std::conditional<F16, ElemF16, ElemBF16>::type E;
@@ -58,24 +77,27 @@ __device__ __forceinline__ void bwd_sweep(const BwdParams &p, const BwdQueue &qu
     constexpr uint32_t RING1 = 0, RING2 = NST * TB, AUX = 2 * NST * TB;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(ATTN_LDS_PTR(unsigned char))smem;
 
-    int tid = threadIdx.x;
-    asm volatile("" : "+v"(tid));   // no address of one sweep is kept in registers across the other one's loop
-    const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // (the lane number is asked from the hardware again in either sweep, at D = 64 in the epilogue too: no address made
+    // from it is kept in registers across a loop)
+    auto lane_id = []() -> int {
+        int ones = -1;
+        asm volatile("" : "+s"(ones));
+        return __builtin_amdgcn_mbcnt_hi(ones, __builtin_amdgcn_mbcnt_lo(ones, 0));
+    };
+    const int lane = lane_id();
     const int lq = lane & 31;
     const int g = lane >> 5;
 
     // ---- direct-load addressing
-    typename U32Vec<NLD>::type dma_row_v, dma_choff_v, dma_voff_v;
-    uint32_t dma_row[NLD], dma_choff[NLD];
+    typename U32Vec<NLD>::type dma_row_v, dma_voff_v;
+    uint32_t dma_row[NLD], dma_voff[NLD];
 #pragma unroll
     for (int i = 0; i < NLD; ++i) {
         const int gi = i * NW + wave;
         dma_row[i] = (1024 / ROWB) * gi + lane / CPR;
-        dma_choff[i] = (uint32_t)(((lane % CPR) ^ swz<D>(dma_row[i])) * 16);
+        dma_voff[i] = dma_row[i] * ROWB + (uint32_t)(((lane % CPR) ^ swz<D>(dma_row[i])) * 16);
         U32Vec<NLD>::set(dma_row_v, i, dma_row[i]);
-        U32Vec<NLD>::set(dma_choff_v, i, dma_choff[i]);
-        U32Vec<NLD>::set(dma_voff_v, i, dma_row[i] * ROWB + dma_choff[i]);
+        U32Vec<NLD>::set(dma_voff_v, i, dma_voff[i]);
     }
     const uint32_t lds_1_wave = lds0 + RING1 + wave * 1024;
     const uint32_t lds_2_wave = lds0 + RING2 + wave * 1024;
@@ -87,7 +109,7 @@ __device__ __forceinline__ void bwd_sweep(const BwdParams &p, const BwdQueue &qu
 #pragma unroll
         for (int i = 0; i < NLD; ++i) {
             const int r = min(t * BN + (int)dma_row[i], S_str - 1);
-            const uint32_t voff = (uint32_t)r * ROWB + dma_choff[i];
+            const uint32_t voff = dma_voff[i] + (uint32_t)(r - (int)dma_row[i]) * ROWB;
             dma16(lds_1_wave + stage * TB + i * NW * 1024, t1_head, voff);
             dma16(lds_2_wave + stage * TB + i * NW * 1024, t2_head, voff);
         }
@@ -128,7 +150,7 @@ __device__ __forceinline__ void bwd_sweep(const BwdParams &p, const BwdQueue &qu
     const int n_t = KEY_OWNER ? p.n_t : p.n_tq, total = KEY_OWNER ? p.total_wg : p.total_q;
 #pragma clang loop unroll(disable)
     for (;; ++pass) {
-        const int entry = persistent_entry(blockIdx.x, (int)gridDim.x, queue.n_entries, pass);
+        const int entry = queue.entry(blockIdx.x, (int)gridDim.x, p.cus_per_xcd, pass);
         if (entry < 0 || (KEY_OWNER && entry >= queue.n_kv))
             break;   // (entries rise from pass to pass; only the last pass can be short)
         if (!KEY_OWNER && entry < queue.q_first)
@@ -283,6 +305,8 @@ __device__ __forceinline__ void bwd_sweep(const BwdParams &p, const BwdQueue &qu
         // 32 x ROWB bytes of a ring (dK / dQ in the first, dV in the second) and reads back only what it wrote;
         // rows are XOR-swizzled by 16-byte chunk.
         __syncthreads();  // every wave has left the loop (its loads have landed): the rings are free
+        const int e_lane = D == 64 ? lane_id() : lane;
+        const int e_lq = e_lane & 31, e_g = e_lane >> 5;
         auto write_out = [&](const f32x16 *a, float mul, elem_t *out_head, uint32_t ring) {
             typedef typename E::x2 ex2;
             typedef typename E::x4 ex4;
@@ -295,14 +319,14 @@ __device__ __forceinline__ void bwd_sweep(const BwdParams &p, const BwdQueue &qu
                     const f32x2 hi = {a[db][4 * rb + 2] * mul, a[db][4 * rb + 3] * mul};
                     const ex2 blo = __builtin_convertvector(lo, ex2), bhi = __builtin_convertvector(hi, ex2);  // nearest even
                     const ex4 w = {blo[0], blo[1], bhi[0], bhi[1]};
-                    const int chunk = (4 * db + rb) ^ (lq & (CPR - 1));
-                    *reinterpret_cast<ex4 *>(stage + lq * ROWB + chunk * 16 + g * 8) = w;
+                    const int chunk = (4 * db + rb) ^ (e_lq & (CPR - 1));
+                    *reinterpret_cast<ex4 *>(stage + e_lq * ROWB + chunk * 16 + e_g * 8) = w;
                 }
             elem_t *blk = out_head + (size_t)o0w * D;
             const int rows_left = S_own - o0w;  // rows of this wave's block that exist
     #pragma unroll
             for (int i = 0; i < 32 * CPR / 64; ++i) {
-                const int idx = i * 64 + lane;
+                const int idx = i * 64 + e_lane;
                 const int r = idx / CPR, c = idx % CPR;
                 const u32x4 w = *reinterpret_cast<const u32x4 *>(stage + r * ROWB + ((c ^ (r & (CPR - 1))) * 16));
                 if (r < rows_left)
@@ -315,16 +339,19 @@ __device__ __forceinline__ void bwd_sweep(const BwdParams &p, const BwdQueue &qu
     }
 }
 
-// SWEEPS: 1 = key owners, 2 = query owners, 3 = both (at D = 64 either one alone as well: attn_bwd.hip, launch_hand)
-template <int D, bool CAUSAL, bool F16, int SWEEPS>
+// At D = 64 two workgroups share a CU: 256 registers a wave (VGPRs and AGPRs together) must hold either sweep, which a
+// test of the compiled kernel checks.  A lone wave per SIMD is bound by the instructions it can issue (matrix pipe 43 %
+// busy); two of them fill each other's gaps.  Whole call against one workgroup per CU: 16 heads of 4096 rows 236 -> 223
+// us, causal 139 -> 125; 128 heads of 512 rows 46.6 -> 39.9; 512 heads of 300 rows, causal 84 -> 71.  Where one
+// workgroup per CU is all there is, the half as many operand buffers cost 2-4 % (16 heads of 1024 rows 22.6 -> 23.1).
+template <int D, bool CAUSAL, bool F16>
 __global__ __launch_bounds__(256) void attn_bwd_asm_kernel(const BwdParams p)
 {
-    const BwdQueue queue(SWEEPS & 1 ? p.total_wg : 0, SWEEPS & 2 ? p.total_q : 0);
+    const BwdQueue queue(p.total_wg, p.total_q);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int pass = 0;
-    if constexpr (SWEEPS & 1)
-        bwd_sweep<D, CAUSAL, true, F16>(p, queue, pass);
-    if constexpr (SWEEPS & 2)
-        bwd_sweep<D, CAUSAL, false, F16>(p, queue, pass);
+    bwd_sweep<D, CAUSAL, true, F16>(p, queue, wave, pass);
+    bwd_sweep<D, CAUSAL, false, F16>(p, queue, wave, pass);
 }
 
 }  // namespace attn

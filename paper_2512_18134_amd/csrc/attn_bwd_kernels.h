@@ -40,6 +40,7 @@ struct BwdParams {
     int n_t;       // owner tiles per (b,h) of the launched sweep (a launch of both: of the key-owner sweep)
     int total_wg;  // B*H*n_t
     int n_tq, total_q;  // the same for the query-owner sweep (hand-scheduled sweeps)
+    int cus_per_xcd;    // compute units of an XCD (hand-scheduled sweeps)
     long long n_rows;  // B*H*S_q (delta kernel)
     float c;       // scale * log2(e)
     float scale;

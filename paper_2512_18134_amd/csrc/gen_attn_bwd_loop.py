@@ -53,7 +53,7 @@ from asm_emit import Emitter, spread  # noqa: E402
 DEFAULTS = {
     (True, 128):  dict(NF=8, PFD=6, W=2),
     (False, 128): dict(NF=8, PFD=4, W=2),
-    (True, 64):   dict(NF=8, PFD=4, W=2),
+    (True, 64):   dict(NF=4, PFD=3, W=1),      # (what 256 registers a wave leave room for)
     (False, 64):  dict(NF=4, PFD=2, W=1),
 }
 
@@ -126,16 +126,17 @@ class Gen(Emitter):
         self.TOFF2 = self.TOFF1 if self.IMM2 else take(2 * self.DB)
         self.DVOFF = take(self.NLD)
         self.DROW = take(self.NLD)
-        self.DCH = take(self.NLD)
         self.DT = take(self.NLD)
-        self.AOFF = take(1)
-        self.AUXROW = take(1)
-        self.AUXSEL = take(1)
-        self.AT = take(1)
+        if key_owner:
+            self.AOFF = take(1)
+            self.AUXROW = take(1)
+            self.AUXSEL = take(1)
         self.THRLOB = take(1)
         self.THRHIB = take(1)
-        self.THR = take(1)
-        self.NEGINF = take(1)
+        # temporaries of the clamped loads, of the mask pre-passes and of the LSE' / Delta load: never live together.
+        # D = 64: the mask limits go through a scalar register, one instruction more per element, for want of a register
+        self.AT = self.NEGINF = self.DT
+        self.THR = None if D == 64 else take(1)
         self.NV = r
         assert r <= 256, r
         # ---- SGPR map (inputs pinned by the asm constraints, the rest clobbered)
@@ -254,10 +255,11 @@ class Gen(Emitter):
         for i in range(self.NLD):
             t = self.DT + i
             off = stage * self.TB + i * self.NW * 1024
+            # offset of the clamped row: the row's own offset (DVOFF) plus what clamping moves it by
             self.e("v_add_u32 v%d, s%d, v%d" % (t, self.s_t2, self.DROW + i))
             self.e("v_min_i32 v%d, s%d, v%d" % (t, self.s_strm1, t))
-            self.e("v_lshlrev_b32 v%d, %d, v%d" % (t, sh, t))
-            self.e("v_add_u32 v%d, v%d, v%d" % (t, t, self.DCH + i))
+            self.e("v_sub_u32 v%d, v%d, v%d" % (t, t, self.DROW + i))
+            self.e("v_lshl_add_u32 v%d, v%d, %d, v%d" % (t, t, sh, self.DVOFF + i))
             self.e("s_add_u32 m0, s%d, %d" % (self.s_lds1, off))
             self.e("s_nop 0")
             self.e("global_load_lds_dwordx4 v%d, %s" % (t, self.sr(self.s_t1base, 2)))
@@ -376,11 +378,16 @@ class Gen(Emitter):
         for kind, base, cmp in (("LO", self.THRLOB, "v_cmp_lt_i32"), ("HI", self.THRHIB, "v_cmp_gt_i32")):
             self.e("%s:" % L("MASK%s%d_" % (kind, b)))
             self.e("s_lshl_b32 s%d, s%d, 5" % (self.s_t2, self.s_j))
-            self.e("v_subrev_u32 v%d, s%d, v%d" % (self.THR, self.s_t2, base))
             self.e("v_mov_b32 v%d, 0xff800000" % self.NEGINF)
+            if self.THR is not None:
+                self.e("v_subrev_u32 v%d, s%d, v%d" % (self.THR, self.s_t2, base))
             for r in range(16):
                 const = 8 * (r >> 2) + (r & 3)
-                self.e("%s vcc, %d, v%d" % (cmp, const, self.THR))
+                if self.THR is None:
+                    self.e("s_add_i32 s%d, s%d, %d" % (self.s_t3, self.s_t2, const))
+                    self.e("%s vcc, s%d, v%d" % (cmp, self.s_t3, base))
+                else:
+                    self.e("%s vcc, %d, v%d" % (cmp, const, self.THR))
                 self.e("v_cndmask_b32 v%d, v%d, v%d, vcc" % (S_cur + r, S_cur + r, self.NEGINF))
             self.e("s_branch %s" % L("MASK%sRET%d_" % (kind, b)))
         self.dma_slow((b + 4) % self.NST, L("SLOW%d_" % b), L("SLOWRET%d_" % b))
@@ -464,10 +471,10 @@ class Gen(Emitter):
             ins.append('"{%s}"(toff2_v)' % self.vr(self.TOFF2, 2 * DB))
         ins.append('"{%s}"(dma_voff_v)' % self.vr(self.DVOFF, self.NLD))
         ins.append('"{%s}"(dma_row_v)' % self.vr(self.DROW, self.NLD))
-        ins.append('"{%s}"(dma_choff_v)' % self.vr(self.DCH, self.NLD))
-        ins.append('"{v%d}"(aux_off)' % self.AOFF)
-        ins.append('"{v%d}"(aux_row)' % self.AUXROW)
-        ins.append('"{v%d}"(aux_sel)' % self.AUXSEL)
+        if self.KO:
+            ins.append('"{v%d}"(aux_off)' % self.AOFF)
+            ins.append('"{v%d}"(aux_row)' % self.AUXROW)
+            ins.append('"{v%d}"(aux_sel)' % self.AUXSEL)
         ins.append('"{v%d}"(thr_lo_base)' % self.THRLOB)
         ins.append('"{v%d}"(thr_hi_base)' % self.THRHIB)
         ins.append('"{%s}"(t1_head)' % self.sr(self.s_t1base, 2))
@@ -486,8 +493,8 @@ class Gen(Emitter):
         pinned = set()
         for base, n in ((self.SA, 16), (self.DPA, 16), (self.AUXL, self.NAUX),
                         (self.ROFF1, KS), (self.ROFF2, KS), (self.TOFF1, 2 * DB), (self.TOFF2, 2 * DB),
-                        (self.DVOFF, self.NLD), (self.DROW, self.NLD), (self.DCH, self.NLD), (self.AOFF, 1),
-                        (self.AUXROW, 1), (self.AUXSEL, 1), (self.THRLOB, 1), (self.THRHIB, 1)):
+                        (self.DVOFF, self.NLD), (self.DROW, self.NLD), (self.THRLOB, 1), (self.THRHIB, 1)) + (
+                        ((self.AOFF, 1), (self.AUXROW, 1), (self.AUXSEL, 1)) if self.KO else ()):
             pinned.update(range(base, base + n))
         if not self.KO:
             pinned.update(range(self.AUXD, self.AUXD + 16))
