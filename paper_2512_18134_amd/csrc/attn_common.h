@@ -95,6 +95,7 @@ struct Params {
     int total_wg;  // B*H*n_qt
     float c;       // scale * log2(e): the softmax runs in the base-2 domain
     float scale;
+    int cus_per_xcd;  // compute units of an XCD (causal launches with two workgroups to a CU)
     // split-KV launches only: the keys are cut into n_split ranges of split_len keys (a multiple of
     // the K/V tile), every range is a workgroup of its own and writes a normalised partial result
     int n_split, split_len;

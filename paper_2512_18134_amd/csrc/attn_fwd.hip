@@ -33,6 +33,8 @@ int launch(K kern, Params p, int BH, int BM, int threads, int lds_bytes, hipStre
     if (!allow_lds(reinterpret_cast<const void *>(kern), lds_bytes))
         return ATTN_ERR_LAUNCH;
     int grid = p.total_wg;
+    const int cus = attn::cu_count(attn::kNumXcd);
+    p.cus_per_xcd = cus > 0 ? cus / attn::kNumXcd : 32;
     if (persistent) {
         // (a runtime that cannot tell the occupancy gets one workgroup per tile: the kernel takes either)
         const int slots = attn::persistent_slots(reinterpret_cast<const void *>(kern), threads, lds_bytes, attn::kNumXcd);
@@ -205,6 +207,7 @@ static int validate(const void *q, const void *k, const void *v, void *o, float 
     p.total_wg = 0;
     p.c = scale * 1.44269504088896340736f;
     p.scale = scale;
+    p.cus_per_xcd = 0;
     p.n_split = 1;
 #ifdef ATTN_DEBUG_ENTRY_POINTS
     p.trace = nullptr;
