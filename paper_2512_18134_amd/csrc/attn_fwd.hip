@@ -132,17 +132,50 @@ int launch_d64(const Params &p, int BH, int causal, hipStream_t stream, int tili
     return launch_asm<64, 1, 2, 8, F16>(p, BH, causal, stream);
 }
 
+// D = 128: the same estimate for the 256-row tiling (one workgroup per CU) and the 128-row one (two).  A CU with a single
+// 128-row workgroup walks a tile's keys at 0.6 us per 32 of them.  Causal: the sum of the tiles' keys, ragged last
+// tiles included, or the walk of the tile with the most of them in an otherwise idle chip, whichever is longer.
+float d128_cost(int rows, int BH, const Params &p, int causal, int cus)
+{
+    const bool two = rows == 128;
+    const long long nt = (p.S_q + rows - 1) / rows, tiles = (long long)BH * nt, slots = (two ? 2ll : 1ll) * cus;
+    const long long n = ((causal && p.S_q < p.S_kv ? p.S_q : p.S_kv) + 31) / 32;
+    const float whole = (float)(tiles / slots), rest = (float)(tiles % slots) / (float)slots;
+    if (!causal) {
+        const float start = two ? 8.5f : 6.0f, per_tile = two ? 0.86f : 0.80f;
+        const float last = two ? (rest > 0.5f ? 0.83f : 0.60f) : per_tile * (0.65f + 0.35f * rest);
+        return whole * (start + per_tile * n) + (rest > 0.f ? start + last * n : 0.f);
+    }
+    const long long step = rows / 32, k = nt < n / step ? nt : n / step;   // tiles below the last keys
+    const float sum = (float)(step * k * (k + 1) / 2 + (nt - k) * n);
+    const float start = two ? 7.0f : 6.0f, r = fmaxf(1.f, whole + 0.5f * (rest + (rest > 0.f ? 1.f : 0.f)));
+    return fmaxf(start + 0.60f * n, start * r + (two ? 0.83f : 0.72f) * sum * BH / (float)slots);
+}
+
 // D = 128.  tiling: -1 = choose, 0 = 8 waves x 32 rows (two waves per SIMD), 1 = 4 waves x 64 rows (one wave
-// per SIMD, half the LDS operand reads per MFMA), 2 = 2 x 2 waves x 32 rows (64 rows, two key groups).
+// per SIMD, half the LDS operand reads per MFMA), 2 = 2 x 2 waves x 32 rows (64 rows, two key groups), 3 = 2 waves x 64
+// rows (two workgroups per CU; the same results as 1).
+// Measured, us for tiling 1 / 3: 300 heads of 100 queries and 2048 keys 112 / 61; 100 heads of 600 rows 39.0 / 26.2; 512
+// heads of 300 rows 59.1 / 50.8; causal: 128 heads of 520 rows 32.2 / 25.0, 100 of 777 rows 37.8 / 31.6, 128 of 1100
+// rows 68.4 / 59.3.  Full rounds of full tiles stay with tiling 1: 32 heads of 4096 rows 207 / 221, causal 116 / 120.
 template <bool F16>
 int launch_d128(const Params &p, int BH, int causal, hipStream_t stream, int tiling = -1)
 {
-    if (tiling < 0)
-        tiling = p.S_q < kKeyGroupMaxQueries ? 2 : 1;
-    if (tiling == 2)
+    if (tiling < 0) {
+        const int cus = attn::cu_count(1) > 0 ? attn::cu_count(1) : 256;
+        tiling = p.S_q < kKeyGroupMaxQueries ? 2
+                 : d128_cost(128, BH, p, causal, cus) < d128_cost(256, BH, p, causal, cus) ? 3 : 1;
+    }
+    switch (tiling) {
+    case 0:
+        return launch_asm<128, 1, 2, 8, F16>(p, BH, causal, stream);
+    case 2:
         return launch_asm<128, 1, 1, 2, F16, 2>(p, BH, causal, stream);
-    return tiling == 1 ? launch_asm<128, 2, 1, 4, F16>(p, BH, causal, stream)
-                       : launch_asm<128, 1, 2, 8, F16>(p, BH, causal, stream);
+    case 3:
+        return launch_asm<128, 2, 1, 2, F16>(p, BH, causal, stream);
+    default:
+        return launch_asm<128, 2, 1, 4, F16>(p, BH, causal, stream);
+    }
 }
 
 // the generic kernel: any scale, heads of any size, program order
@@ -378,7 +411,7 @@ extern "C" int attn_fwd(const void *q, const void *k, const void *v, void *o, fl
 // kernel chosen by the caller.  variant 0: as attn_fwd; 1: the generic program-order kernel;
 // 2 / 5: D = 128 on the one-wave-per-SIMD tiling (4 waves x 64 query rows) / on the two-waves-per-SIMD
 // tiling (8 waves x 32 rows); 3 / 4: D = 64 with 8-wave / 4-wave workgroups; 6: D = 64 or 128 in 64-row
-// workgroups with two key groups.  A variant that does not
+// workgroups with two key groups; 7: D = 128 in 128-row workgroups (2 waves x 64 rows).  A variant that does not
 // apply to the arguments returns ATTN_ERR_UNSUPPORTED.
 extern "C" int attn_fwd_variant(const void *q, const void *k, const void *v, void *o, float *lse, int B, int H,
                                 int S_q, int S_kv, int D, int causal, float scale, void *stream, int variant)
@@ -402,6 +435,8 @@ extern "C" int attn_fwd_variant(const void *q, const void *k, const void *v, voi
         return !asm_ok ? ATTN_ERR_UNSUPPORTED
                : D == 128 ? launch_d128<false>(p, B * H, causal, st, 2)
                : D == 64 ? launch_d64<false>(p, B * H, causal, st, 2) : ATTN_ERR_UNSUPPORTED;
+    case 7:
+        return D == 128 && asm_ok ? launch_d128<false>(p, B * H, causal, st, 3) : ATTN_ERR_UNSUPPORTED;
     case 3:
     case 4:
         return D == 64 && asm_ok ? launch_d64<false>(p, B * H, causal, st, variant - 3) : ATTN_ERR_UNSUPPORTED;

@@ -22,6 +22,7 @@
 //                                  bounds it is the walk (0.4 us per 32 keys, issue and load latency), not the products
 //   <D=128,    QB=2, SB=1, NW=4>  one wave per SIMD, O and Q in AGPRs; a K / V^T fragment
 //                                  read from LDS feeds two MFMAs (half the LDS reads)
+//   <D=128,    QB=2, SB=1, NW=2>  the same with BM = 128 (two workgroups per CU; the same results)
 //   <D=256,    QB=1, SB=1, NW=4>  one wave per SIMD, O and Q in AGPRs
 // K/V tiles in two 4-stage LDS rings (8 * BN * D * 2 bytes).  The kernel starts S(0) as soon as K(0)
 // and Q have landed; the other five tiles of the ring fill behind it.
@@ -98,6 +99,8 @@ struct FwdTiling {
     static constexpr bool PERSIST = !SPLIT && !(D == 128 && QB == 1 && SB == 2);
     // the 4-wave D = 64 workgroups are meant to run two to a CU: their waves must fit half a SIMD's registers
     static constexpr int MIN_WAVES_PER_SIMD = (D == 64 && NW == 4) ? 2 : 1;
+    // ... and the 2-wave D = 128 ones, by their 64 KB of LDS
+    static constexpr bool TWO_PER_CU = (D == 64 && NW == 4) || (D == 128 && QB == 2 && NW == 2);
     static_assert(SPLIT || STAGE_BYTES <= RING_BYTES, "O staging must fit the rings");
     // the two key groups exchange half of their fp32 accumulators, their row maxima and sums, then stage half rows
     static constexpr int XCH_O = 0, XCH_ML = 2 * NW * 32 * D * 2, XCH_STAGE = XCH_ML + 2 * NW * 64 * 8;
@@ -117,7 +120,7 @@ __global__ __launch_bounds__(NW * G * 64, (D == 64 && NW == 4) ? 2 : 1)  // = Fw
     static_assert((QB == 1 && SB == 2 && (D == 64 || D == 128) && NW == 8 && G == 1) ||
                       (QB == 1 && SB == 2 && D == 64 && ((NW == 4 && G == 1) || (NW == 2 && G == 2))) ||
                       (QB == 1 && SB == 1 && D == 128 && NW == 2 && G == 2) ||
-                      (QB == 2 && SB == 1 && D == 128 && NW == 4 && G == 1) ||
+                      (QB == 2 && SB == 1 && D == 128 && (NW == 4 || (NW == 2 && !SPLIT)) && G == 1) ||
                       (QB == 1 && SB == 1 && D == 256 && NW == 4 && G == 1 && !SPLIT),
                   "no generated loop for this tiling");
     static_assert(!(SPLIT && CAUSAL), "split-KV launches are not causal");
@@ -159,7 +162,7 @@ __global__ __launch_bounds__(NW * G * 64, (D == 64 && NW == 4) ? 2 : 1)  // = Fw
     // persistent_entry does it between passes).  D = 64, causal: 32 heads of 2048 rows 26.1 -> 23.6 us, 17 of 4096 rows
     // 48.4 -> 43.5, 4 of 16384 rows 163 -> 151; launches with one tile per CU or many passes do not change
     int place = blockIdx.x;
-    if constexpr (CAUSAL && T::MIN_WAVES_PER_SIMD == 2) {
+    if constexpr (CAUSAL && T::TWO_PER_CU) {
         const int xcd = place % kNumXcd, m = place / kNumXcd;
         const int n = n_slots >= p.total_wg ? (p.total_wg - xcd + kNumXcd - 1) / kNumXcd : n_slots / kNumXcd;
         const int first = min(n, p.cus_per_xcd);
@@ -577,6 +580,10 @@ __global__ __launch_bounds__(NW * G * 64, (D == 64 && NW == 4) ? 2 : 1)  // = Fw
 #include "generated/attn_loop_d128.inc"
         } else if constexpr (D == 128 && SB == 2 && F16) {
 #include "generated/attn_loop_d128_f16.inc"
+        } else if constexpr (D == 128 && QB == 2 && NW == 2 && !F16) {
+#include "generated/attn_loop_d128a_w2.inc"
+        } else if constexpr (D == 128 && QB == 2 && NW == 2) {
+#include "generated/attn_loop_d128a_w2_f16.inc"
         } else if constexpr (D == 128 && QB == 2 && !F16) {
 #include "generated/attn_loop_d128a.inc"
         } else if constexpr (D == 128 && QB == 2 && F16) {

@@ -90,6 +90,7 @@ CONFIGS = {
     "d64_w2": dict(D=64,  QB=1, SB=2, NW=2, AG=False, NACC=1, NF=8, PFD=7, W=4, LS=2),
     "d128":   dict(D=128, QB=1, SB=2, NW=8, AG=False, NACC=1, NF=4, PFD=3, W=1),
     "d128a":  dict(D=128, QB=2, SB=1, NW=4, AG=True,  NACC=1, NF=8, PFD=7, W=4),
+    "d128a_w2": dict(D=128, QB=2, SB=1, NW=2, AG=True, NACC=1, NF=8, PFD=7, W=4),
     "d128_w2": dict(D=128, QB=1, SB=1, NW=2, AG=False, NACC=1, NF=8, PFD=7, W=4, LS=1),
     "d256a":  dict(D=256, QB=1, SB=1, NW=4, AG=True,  NACC=2, NF=8, PFD=7, W=4, LS=2),
 }

@@ -14,7 +14,8 @@ pytestmark = pytest.mark.gpu
 
 SIZES = [(1, 1), (1, 33), (1, 2000), (31, 32), (33, 64), (64, 65), (65, 64), (96, 97), (100, 31), (128, 160), (129, 128),
          (192, 191), (257, 289), (300, 1000), (515, 70)]
-TILINGS = [(128, debug_lib.FWD_KEY_GROUPS), (64, debug_lib.FWD_KEY_GROUPS), (64, debug_lib.FWD_D64_4_WAVES)]
+TILINGS = [(128, debug_lib.FWD_KEY_GROUPS), (64, debug_lib.FWD_KEY_GROUPS), (64, debug_lib.FWD_D64_4_WAVES),
+           (128, debug_lib.FWD_D128_2_WAVES)]
 
 
 def on_gpu(bits, dt):
@@ -70,3 +71,23 @@ def test_ranges_against_the_oracle(heads, S_q, S_kv, n_split):
             keep = sorted({0, heads - 1})                     # two heads are enough for the oracle
             sel = lambda x: np.ascontiguousarray(x[:, keep])
             check(o[:, keep], lse[:, keep], attn_ref(sel(q), sel(k), sel(v), False, scale, dtype=dtype), o_tol)
+
+
+# heads, S_q, S_kv: one tile, one round and several, workgroups that share a CU or not, both sides of the dispatch rules
+BOTH_TILINGS = [(1, 64, 64), (3, 300, 200), (70, 515, 515), (130, 520, 520), (300, 100, 700), (520, 129, 131), (600, 70, 90)]
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("heads,S_q,S_kv", BOTH_TILINGS)
+def test_the_128_row_tilings_give_the_bits_of_the_256_row_ones(heads, S_q, S_kv, causal):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(heads)
+    for D, wide, narrow in ((64, debug_lib.FWD_D64_8_WAVES, debug_lib.FWD_D64_4_WAVES),
+                            (128, debug_lib.FWD_D128_ONE_WAVE_PER_SIMD, debug_lib.FWD_D128_2_WAVES)):
+        q, k, v = (torch.empty((1, heads, S, D), device="cuda").normal_(0, 2, generator=g).bfloat16()
+                   for S in (S_q, S_kv, S_kv))
+        print("heads", heads, "S_q", S_q, "S_kv", S_kv, "D", D, "causal", causal, flush=True)
+        want = debug_lib.attn_fwd_variant(q, k, v, causal, synth.default_scale(D), wide)
+        for variant in (narrow, debug_lib.FWD_AS_DISPATCHED):
+            got = debug_lib.attn_fwd_variant(q, k, v, causal, synth.default_scale(D), variant)
+            assert all(torch.equal(x, y) for x, y in zip(got, want)), variant
