@@ -149,7 +149,8 @@ float d128_cost(int rows, int BH, const Params &p, int causal, int cus)
     const long long step = rows / 32, k = nt < n / step ? nt : n / step;   // tiles below the last keys
     const float sum = (float)(step * k * (k + 1) / 2 + (nt - k) * n);
     const float start = two ? 7.0f : 6.0f, r = fmaxf(1.f, whole + 0.5f * (rest + (rest > 0.f ? 1.f : 0.f)));
-    return fmaxf(start + 0.60f * n, start * r + (two ? 0.83f : 0.72f) * sum * BH / (float)slots);
+    const float alone = two && tiles <= cus ? 5.9f : start;   // (no second workgroup to share the CU's start with)
+    return fmaxf(alone + 0.60f * n, start * r + (two ? 0.83f : 0.72f) * sum * BH / (float)slots);
 }
 
 // D = 128.  tiling: -1 = choose, 0 = 8 waves x 32 rows (two waves per SIMD), 1 = 4 waves x 64 rows (one wave
@@ -157,7 +158,7 @@ float d128_cost(int rows, int BH, const Params &p, int causal, int cus)
 // rows (two workgroups per CU; the same results as 1).
 // Measured, us for tiling 1 / 3: 300 heads of 100 queries and 2048 keys 112 / 61; 100 heads of 600 rows 39.0 / 26.2; 512
 // heads of 300 rows 59.1 / 50.8; causal: 128 heads of 520 rows 32.2 / 25.0, 100 of 777 rows 37.8 / 31.6, 128 of 1100
-// rows 68.4 / 59.3.  Full rounds of full tiles stay with tiling 1: 32 heads of 4096 rows 207 / 221, causal 116 / 120.
+// rows 68.4 / 59.3, 16 of 777 rows 21.1 / 20.6.  Full rounds of full tiles stay with tiling 1: 32 heads of 4096 rows 207 / 221, causal 116 / 120.
 template <bool F16>
 int launch_d128(const Params &p, int BH, int causal, hipStream_t stream, int tiling = -1)
 {
