@@ -144,6 +144,8 @@ int attn_workgroup_tile(int causal, int workgroup, int n_heads, int n_tiles, lon
  * when n_entries tiles are queued, or -1 when that pass has none for it.  An XCD's workgroups share the XCD's
  * entries (id % 8); odd passes run through them in reverse, so that a slot pairs heavy with light tiles of a
  * causal launch.  n_workgroups >= n_entries: one entry each, in pass 0.
+ * `workgroup` is a place in the queue; causal launches with two workgroups to a CU hand the places out so that a CU
+ * pairs heavy with light tiles, every other launch by the hardware's workgroup id.
  * Returns ATTN_OK, or ATTN_ERR_NULL / ATTN_ERR_SHAPE (counts < 1, pass < 0, workgroup outside
  * [0, n_workgroups), n_workgroups < n_entries and not a multiple of 8).
  */

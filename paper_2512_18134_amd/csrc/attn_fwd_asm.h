@@ -573,7 +573,12 @@ __global__ __launch_bounds__(NW * G * 64, (D == 64 && NW == 4) ? 2 : 1)  // = Fw
         const int n_tiles = t.n_tiles, j_mask = t.j_mask, t_full = t.t_full, skv_m1 = t.skv_m1;
         // causal: the keys behind this wave's last row are masked for all of its rows; the loop leaves the
         // tiles that hold nothing else to the waves below (it keeps their barriers and issues its loads)
-        const int n_tiles_wave = idle ? 1 : (CAUSAL ? min(t.own_tiles, (last_row - t.kv0) / BN + 1) : t.own_tiles);
+        // a wave without a row below S_q writes nothing: after one tile it only keeps step (barriers, its share of the
+        // loads) and leaves the LDS port and the power to the others (128 heads of 520 rows, D = 128 35.0 -> 33.5 us, 512
+        // of 300 rows, D = 64 36.0 -> 32.1, D = 256 119 -> 113; launches without such waves do not change)
+        const bool no_rows = G == 1 && t.q0 + wave * 32 * QB >= p.S_q;
+        const int n_tiles_wave =
+            idle || no_rows ? 1 : (CAUSAL ? min(t.own_tiles, (last_row - t.kv0) / BN + 1) : t.own_tiles);
         ATTN_TRACE(p, t.vb, 2);
 
         if constexpr (D == 128 && SB == 2 && !F16) {
