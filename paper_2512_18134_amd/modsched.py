@@ -554,9 +554,10 @@ def gfx950_backward_key_owner(U=24):
 
 
 # S and dP (16 + 16), P and dS packed (8 + 8), dK^T and dV^T accumulators (64 + 64); resident: the owner's
-# K and V rows as B operands (64), LSE'/Delta of the tile (32), fragment ring (16), addresses and state (~56)
+# K and V rows as B operands (64), LSE' of the tile (16; its Delta is what dP's accumulator starts from), fragment ring
+# of eight operands (32), addresses of the LDS reads (32) and of the direct loads, mask limits and temporaries (12)
 GFX950_BWD_REGS = {"SDP": 32, "EW": 16, "CON": 128}
-GFX950_BWD_RESIDENT = 64 + 32 + 16 + 56
+GFX950_BWD_RESIDENT = 64 + 16 + 32 + 32 + 12
 
 
 if __name__ == "__main__":
