@@ -337,6 +337,13 @@ __global__ __launch_bounds__(NW * G * 64, (D == 64 && NW == 4) ? 2 : 1)  // = Fw
         const float l_lane = F32Vec<QB>::get(l_run_v, 0);
         const float l_own = idle ? 0.f : l_lane + xor32(l_lane);
         const float m_own = idle ? -INFINITY : F32Vec<QB>::get(m_ref_v, 0);
+        if (idle) {   // (a weight of zero would not do: keys that no row of this wave sees may hold NaN or infinities)
+#pragma unroll
+            for (int i = 0; i < DB; ++i)
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    o_acc[i][r] = 0.f;
+        }
         float *const xo = reinterpret_cast<float *>(smem + T::XCH_O);
         f32x2 *const xml = reinterpret_cast<f32x2 *>(smem + T::XCH_ML);
         // element r of the half this wave keeps (mine) or hands over
@@ -556,8 +563,8 @@ __global__ __launch_bounds__(NW * G * 64, (D == 64 && NW == 4) ? 2 : 1)  // = Fw
             q_pack[i] = __builtin_bit_cast(u32x16, f);
         }
         // Second key group: a wave none of whose rows sees a key of the group (causal; its rows and the group's keys
-        // both start at multiples of 32), or a tile too short for two groups: it runs one unmasked tile, so that
-        // everything stays finite, and its result does not count
+        // both start at multiples of 32), or a tile too short for two groups: it runs one tile, and its result does not
+        // count
         const int last_row = min(t.q0 + (wave + 1) * 32 * QB, p.S_q) - 1;
         if constexpr (G == 2)
             idle = grp && (t.kv0 == (SPLIT ? t.split * p.split_len : 0) ||
@@ -567,7 +574,7 @@ __global__ __launch_bounds__(NW * G * 64, (D == 64 && NW == 4) ? 2 : 1)  // = Fw
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb)
             U32Vec<QB>::set(thr_base_v, qb,
-                            (uint32_t)((CAUSAL && !idle ? min(qcol(t, qb) - t.kv0, t.skv_m1) : t.skv_m1) - 4 * g));
+                            (uint32_t)((CAUSAL ? min(qcol(t, qb) - t.kv0, t.skv_m1) : t.skv_m1) - 4 * g));
         const float c_log2e = p.c;
         const elem_t *k_head = t.k_head, *v_head = t.v_head;
         const int n_tiles = t.n_tiles, j_mask = t.j_mask, t_full = t.t_full, skv_m1 = t.skv_m1;

@@ -91,3 +91,23 @@ def test_the_128_row_tilings_give_the_bits_of_the_256_row_ones(heads, S_q, S_kv,
         for variant in (narrow, debug_lib.FWD_AS_DISPATCHED):
             got = debug_lib.attn_fwd_variant(q, k, v, causal, synth.default_scale(D), variant)
             assert all(torch.equal(x, y) for x, y in zip(got, want)), variant
+
+
+# queries, keys (with S_q >= 64 one key group works on all keys)
+HIDDEN = [(1, 200), (31, 96), (33, 64), (40, 4096), (63, 130), (64, 100)]
+
+
+@pytest.mark.parametrize("S_q,S_kv", HIDDEN)
+def test_keys_that_no_query_sees_leave_no_trace(S_q, S_kv):
+    """Causal: the keys from S_q on are masked for every row, so what K holds there reaches no output bit, NaN included."""
+    for D in (64, 128):
+        for dt, call in ((torch.bfloat16, binding.attn_fwd), (torch.float16, binding.attn_fwd_f16)):
+            g = torch.Generator(device="cuda")
+            g.manual_seed(S_q)
+            q, k, v = (torch.empty((1, 2, S, D), device="cuda").normal_(generator=g).to(dt) for S in (S_q, S_kv, S_kv))
+            print("S_q", S_q, "S_kv", S_kv, "D", D, dt, flush=True)
+            want = call(q, k, v, causal=True)
+            assert all(torch.isfinite(x).all() for x in want)
+            for value in (float("nan"), float("inf"), float("-inf")):
+                k[:, :, S_q:] = value
+                assert all(torch.equal(x, y) for x, y in zip(call(q, k, v, causal=True), want)), value
