@@ -87,11 +87,12 @@ CONFIGS = {
     # NF: fragment buffers; PFD: groups between a fragment's LDS read and its MFMA; W: groups per s_waitcnt
     "d64":    dict(D=64,  QB=1, SB=2, NW=8, AG=False, NACC=1, NF=8, PFD=6, W=2),
     "d64_w4": dict(D=64,  QB=1, SB=2, NW=4, AG=False, NACC=1, NF=8, PFD=6, W=2),
-    "d64_w2": dict(D=64,  QB=1, SB=2, NW=2, AG=False, NACC=1, NF=8, PFD=7, W=4, LS=2),
+    # LOW: the running reference starts at the lowest finite number instead of at -inf
+    "d64_w2": dict(D=64,  QB=1, SB=2, NW=2, AG=False, NACC=1, NF=8, PFD=7, W=4, LS=2, LOW=True),
     "d128":   dict(D=128, QB=1, SB=2, NW=8, AG=False, NACC=1, NF=4, PFD=3, W=1),
     "d128a":  dict(D=128, QB=2, SB=1, NW=4, AG=True,  NACC=1, NF=8, PFD=7, W=4),
     "d128a_w2": dict(D=128, QB=2, SB=1, NW=2, AG=True, NACC=1, NF=8, PFD=7, W=4),
-    "d128_w2": dict(D=128, QB=1, SB=1, NW=2, AG=False, NACC=1, NF=8, PFD=7, W=4, LS=1),
+    "d128_w2": dict(D=128, QB=1, SB=1, NW=2, AG=False, NACC=1, NF=8, PFD=7, W=4, LS=1, LOW=True),
     "d256a":  dict(D=256, QB=1, SB=1, NW=4, AG=True,  NACC=2, NF=8, PFD=7, W=4, LS=2),
 }
 
@@ -107,6 +108,11 @@ class Gen(Emitter):
         self.W = cfg["W"] if W is None else W
         assert dtype in ("bf16", "f16")
         self.name, self.dtype = name, dtype
+        # A key group starts in the middle of the keys, where all of a row's scores may be -inf (finite inputs whose
+        # products overflow): against a reference of -inf they would give NaN, and the whole row with them.  Against the
+        # lowest finite number they give exactly 0 and pass the row-sum test; a finite score fails it, as in a first tile.
+        # Sums and accumulators are the same bits as with -inf otherwise (0 until the first move of the reference)
+        self.ref0 = 0xff7fffff if cfg.get("LOW") else 0xff800000
         # the two element types differ only in the MFMA and in the pack instruction (both round to nearest even)
         self.mfma = "v_mfma_f32_32x32x16_" + dtype
         self.cvt = "v_cvt_pk_%s_f32" % dtype
@@ -587,6 +593,8 @@ class Gen(Emitter):
             self.e("v_exp_f32 v%d, v%d" % (self.ALPHA + qb, self.DD + qb))
             self.e("v_mov_b32 v%d, v%d" % (self.MREF + qb, self.T + qb))
             self.e("v_mul_f32 v%d, s%d, v%d" % (self.MRC + qb, self.s_c, self.T + qb))
+            if self.ref0 != 0xff800000:      # (c > 1: the product of a reference that has not moved yet stays finite)
+                self.e("v_max_f32 v%d, 0x%08x, v%d" % (self.MRC + qb, self.ref0, self.MRC + qb))
         self.e("s_nop 1")
         for qb in range(QB):
             self.e("v_mul_f32 v%d, v%d, v%d" % (self.L + qb, self.L + qb, self.ALPHA + qb))
@@ -698,8 +706,8 @@ class Gen(Emitter):
             e("s_add_u32 s%d, s%d, %d" % (self.s_lk + st, self.s_ldsk, st * self.TB))
             e("s_add_u32 s%d, s%d, %d" % (self.s_lv + st, self.s_ldsv, st * self.TB))
         for qb in range(QB):
-            e("v_mov_b32 v%d, 0xff800000" % (self.MREF + qb))        # no reference yet: the first tile's test fails
-            e("v_mov_b32 v%d, 0xff800000" % (self.MRC + qb))
+            e("v_mov_b32 v%d, 0x%08x" % (self.MREF + qb, self.ref0))  # no reference yet: the first tile's test fails
+            e("v_mov_b32 v%d, 0x%08x" % (self.MRC + qb, self.ref0))
             e("v_mov_b32 v%d, 0" % (self.L + qb))
         if "nolds" in self.exp:      # timing experiment: the fragments are never read; keep them finite
             for r in range(4 * self.NF):

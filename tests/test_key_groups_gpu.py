@@ -111,3 +111,34 @@ def test_keys_that_no_query_sees_leave_no_trace(S_q, S_kv):
             for value in (float("nan"), float("inf"), float("-inf")):
                 k[:, :, S_q:] = value
                 assert all(torch.equal(x, y) for x, y in zip(call(q, k, v, causal=True), want)), value
+
+
+# queries, keys, keys whose score is -inf, key ranges (0: attn_fwd)
+NO_WEIGHT = [(1, 256, (96, 256), 0), (5, 500, (100, 500), 0), (40, 2000, (1000, 1500), 0), (63, 192, (64, 192), 0),
+             (1, 1024, (96, 256), 4), (33, 5000, (1280, 1500), 2), (64, 4096, (256, 384), 8)]
+
+
+@pytest.mark.parametrize("S_q,S_kv,span,n_split", NO_WEIGHT)
+def test_keys_with_a_score_of_minus_infinity_weigh_nothing(S_q, S_kv, span, n_split):
+    """Finite inputs whose products overflow (a padding key marked by one feature of the lowest value): the first keys of a
+    group may then all weigh nothing.  The same as without those keys, in another order of the sums: bars as above."""
+    for D in (64, 128):
+        scale = synth.default_scale(D)
+        g = torch.Generator(device="cuda")
+        g.manual_seed(S_q)
+        q, k, v = (torch.empty((1, 3, S, D), device="cuda").normal_(generator=g).bfloat16() for S in (S_q, S_kv, S_kv))
+        q[..., 0], k[..., 0] = 4.0, 0.0
+        k[:, :, span[0]:span[1], 0] = torch.finfo(torch.bfloat16).min
+        keep = torch.cat([torch.arange(span[0]), torch.arange(span[1], S_kv)])
+        print("S_q", S_q, "S_kv", S_kv, "D", D, "ranges", n_split, flush=True)
+        got = ([binding.attn_fwd_splitkv(q, k, v, n_split, scale=scale)] if n_split else
+               [binding.attn_fwd(q, k, v, scale=scale),
+                debug_lib.attn_fwd_variant(q, k, v, False, scale, debug_lib.FWD_KEY_GROUPS)])
+        s = torch.matmul(f64_t(q), f64_t(k)[:, :, keep].transpose(-1, -2)) * scale
+        want = (torch.matmul(torch.softmax(s, -1), f64_t(v)[:, :, keep]).numpy(), torch.logsumexp(s, -1).numpy())
+        for o, lse in got:
+            check(o, lse, want, 2e-2)
+
+
+def f64_t(t):
+    return t.double().cpu()
