@@ -138,7 +138,10 @@ def attn_fwd(q, k, v, o=None, lse=None, causal=False, scale=None, stream=None):
 
     q [B,H,S_q,D], k/v [B,H,S_kv,D]: contiguous bf16 on the GPU.  o (bf16) and
     lse (fp32 [B,H,S_q]) are allocated when not given.  The launch goes to
-    `stream` (default: torch's current stream) and is asynchronous.
+    `stream` (default: torch's current stream) and is asynchronous.  What a call
+    with another stream allocates belongs to that stream; tensors that the caller
+    passes have to outlive the call's kernels (Tensor.record_stream), as with
+    any operation on a stream that is not the tensor's own.
     Returns (o, lse).
     """
     r = (_marshal_module or _native()).fwd(0, q, k, v, o, lse, causal, scale, stream)
@@ -157,6 +160,25 @@ def attn_fwd_f16(q, k, v, o=None, lse=None, causal=False, scale=None, stream=Non
     return _marshal(attn_fwd_f16_raw, torch.float16, q, k, v, o, lse, causal, scale, stream)
 
 
+def _allocate(make, device, stream, returned=True):
+    """A call's own allocation, made on the stream that its kernels run on: the caching allocator then gives the memory
+    to nobody else before they are done, and gives them none that kernels of another stream still use.  What is
+    returned to the caller may be used on the caller's current stream as well until it is freed."""
+    import torch
+
+    current = torch.cuda.current_stream(device)
+    if stream is None or stream.cuda_stream == current.cuda_stream:
+        return make()
+    if not isinstance(stream, torch.cuda.Stream):
+        stream = (torch.cuda.ExternalStream(stream.cuda_stream, device=device) if stream.cuda_stream else
+                  torch.cuda.default_stream(device))
+    with torch.cuda.stream(stream):
+        t = make()
+    if returned:
+        t.record_stream(current)
+    return t
+
+
 def _marshal(entry, dt, q, k, v, o, lse, causal, scale, stream):
     import torch
 
@@ -168,9 +190,9 @@ def _marshal(entry, dt, q, k, v, o, lse, causal, scale, stream):
         raise ValueError("q, k, v shapes do not agree")
     S_kv = k.shape[2]
     if o is None:
-        o = torch.empty_like(q)
+        o = _allocate(lambda: torch.empty_like(q), q.device, stream)
     if lse is None:
-        lse = torch.empty((B, H, S_q), dtype=torch.float32, device=q.device)
+        lse = _allocate(lambda: torch.empty((B, H, S_q), dtype=torch.float32, device=q.device), q.device, stream)
     if o.dtype != dt or o.shape != q.shape or not o.is_contiguous() or not o.is_cuda:
         raise TypeError("o must be a contiguous GPU tensor shaped and typed like q")
     if lse.dtype != torch.float32 or tuple(lse.shape) != (B, H, S_q) or not lse.is_contiguous() or not lse.is_cuda:
@@ -258,11 +280,12 @@ def _marshal_bwd(entry, dt, q, k, v, o, d_o, lse, dq, dk, dv, delta_ws, causal, 
     no_ws = delta_ws is False          # attn_bwd_noalloc: the library's own workspace, outputs from the caller
     if no_ws and (dq is None or dk is None or dv is None):
         raise TypeError("attn_bwd_noalloc: the caller passes dq, dk, dv")
-    dq = torch.empty_like(q) if dq is None else dq
-    dk = torch.empty_like(k) if dk is None else dk
-    dv = torch.empty_like(v) if dv is None else dv
+    dq = _allocate(lambda: torch.empty_like(q), q.device, stream) if dq is None else dq
+    dk = _allocate(lambda: torch.empty_like(k), q.device, stream) if dk is None else dk
+    dv = _allocate(lambda: torch.empty_like(v), q.device, stream) if dv is None else dv
     if delta_ws is None:
-        delta_ws = torch.empty((2, B, H, S_q), dtype=torch.float32, device=q.device)
+        delta_ws = _allocate(lambda: torch.empty((2, B, H, S_q), dtype=torch.float32, device=q.device), q.device, stream,
+                             returned=False)
     for t, like in ((dq, q), (dk, k), (dv, v)):
         if t.dtype != dt or t.shape != like.shape or not t.is_contiguous() or not t.is_cuda:
             raise TypeError("dq, dk, dv must be contiguous GPU tensors shaped and typed like q, k, v")
@@ -331,15 +354,17 @@ def _marshal_splitkv(entry, dt, q, k, v, n_split, o, lse, workspace, causal, sca
     if k.shape != v.shape or k.shape[0] != B or k.shape[1] != H or k.shape[3] != D:
         raise ValueError("q, k, v shapes do not agree")
     S_kv = k.shape[2]
-    o = torch.empty_like(q) if o is None else o
-    lse = torch.empty((B, H, S_q), dtype=torch.float32, device=q.device) if lse is None else lse
+    o = _allocate(lambda: torch.empty_like(q), q.device, stream) if o is None else o
+    if lse is None:
+        lse = _allocate(lambda: torch.empty((B, H, S_q), dtype=torch.float32, device=q.device), q.device, stream)
     if o.dtype != dt or o.shape != q.shape or not o.is_contiguous() or not o.is_cuda:
         raise TypeError("o must be a contiguous GPU tensor shaped and typed like q")
     if lse.dtype != torch.float32 or tuple(lse.shape) != (B, H, S_q) or not lse.is_contiguous() or not lse.is_cuda:
         raise TypeError("lse must be a contiguous fp32 GPU tensor [B,H,S_q]")
     need = attn_fwd_splitkv_workspace_bytes(B, H, S_q, D, n_split)
     if workspace is None:
-        workspace = torch.empty((max(need, 16),), dtype=torch.uint8, device=q.device)
+        workspace = _allocate(lambda: torch.empty((max(need, 16),), dtype=torch.uint8, device=q.device), q.device, stream,
+                              returned=False)
     if not workspace.is_cuda or not workspace.is_contiguous():
         raise TypeError("workspace must be a contiguous GPU tensor")
     if scale is None:

@@ -82,25 +82,43 @@ bool scale_of(PyObject *o, int D, float &scale)
     return true;
 }
 
-bool stream_of(PyObject *o, const c10::Device &dev, void *&stream)
+// the address in a Python int (the reference is taken over)
+bool address_of(PyObject *h, void *&address)
 {
-    PyObject *h;
-    if (o == Py_None) {
-        PyObject *index = PyLong_FromLong(dev.index());
-        h = index && g_current_stream ? PyObject_CallOneArg(g_current_stream, index) : nullptr;
-        Py_XDECREF(index);
-    } else {
-        h = PyObject_GetAttrString(o, "cuda_stream");
-    }
-    if (!h) {
-        PyErr_Clear();
-        return false;
-    }
-    stream = PyLong_CheckExact(h) ? PyLong_AsVoidPtr(h) : nullptr;
-    const bool ok = PyLong_CheckExact(h) && !PyErr_Occurred();
-    Py_DECREF(h);
+    address = h && PyLong_CheckExact(h) ? PyLong_AsVoidPtr(h) : nullptr;
+    const bool ok = h && PyLong_CheckExact(h) && !PyErr_Occurred();
+    Py_XDECREF(h);
     PyErr_Clear();
     return ok;
+}
+
+// The stream to launch on: the device's current one, or the one the caller names.  `allocates`: the call has something to
+// allocate, and what is allocated here belongs to the current stream; a call that needs memory of another stream goes the
+// other way.
+bool stream_of(PyObject *o, const c10::Device &dev, bool allocates, void *&stream)
+{
+    void *current = nullptr;
+    if (o == Py_None || allocates) {
+        PyObject *index = PyLong_FromLong(dev.index());
+        const bool ok = address_of(index && g_current_stream ? PyObject_CallOneArg(g_current_stream, index) : nullptr, current);
+        Py_XDECREF(index);
+        if (!ok)
+            return false;
+        if (o == Py_None) {
+            stream = current;
+            return true;
+        }
+    }
+    return address_of(PyObject_GetAttrString(o, "cuda_stream"), stream) && (!allocates || stream == current);
+}
+
+// one of these arguments is left for the call to allocate
+bool any_none(PyObject *const *a, int n)
+{
+    for (int i = 0; i < n; ++i)
+        if (a[i] == Py_None)
+            return true;
+    return false;
 }
 
 // the launch, with the tensors' device current and the interpreter lock released
@@ -174,7 +192,7 @@ PyObject *py_fwd(PyObject *, PyObject *const *a, Py_ssize_t n)
     at::Tensor o, lse;
     const int type = n == 9 ? type_of(a[0]) : 0, causal = n == 9 ? truth(a[6]) : -1;
     if (n != 9 || causal < 0 || !g_fwd[type] || !qkv(a + 1, kElem[type], t, s) || !scale_of(a[7], s.D, scale) ||
-        !stream_of(a[8], t[0]->device(), stream) || !output(a[4], *t[0], o) || !lse_output(a[5], s, *t[0], lse))
+        !stream_of(a[8], t[0]->device(), any_none(a + 4, 2), stream) || !output(a[4], *t[0], o) || !lse_output(a[5], s, *t[0], lse))
         Py_RETURN_NONE;
     const int rc = launch(t[0]->device(), [&] {
         return g_fwd[type](t[0]->data_ptr(), t[1]->data_ptr(), t[2]->data_ptr(), o.data_ptr(), (float *)lse.data_ptr(), s.B,
@@ -195,7 +213,7 @@ PyObject *py_splitkv(PyObject *, PyObject *const *a, Py_ssize_t n)
     at::Tensor o, lse, ws;
     const int type = n == 11 ? type_of(a[0]) : 0, causal = n == 11 ? truth(a[8]) : -1;
     if (n != 11 || causal < 0 || !g_split[type] || !g_ws || !PyLong_CheckExact(a[4]) || !qkv(a + 1, kElem[type], t, s) ||
-        !scale_of(a[9], s.D, scale) || !stream_of(a[10], t[0]->device(), stream))
+        !scale_of(a[9], s.D, scale) || !stream_of(a[10], t[0]->device(), any_none(a + 5, 3), stream))
         Py_RETURN_NONE;
     const long n_split = PyLong_AsLong(a[4]);
     if (PyErr_Occurred()) {
@@ -236,7 +254,7 @@ PyObject *py_bwd(PyObject *, PyObject *const *a, Py_ssize_t n)
     at::Tensor g[3], ws;
     const int type = n == 14 ? type_of(a[0]) : 0, causal = n == 14 ? truth(a[11]) : -1;
     if (n != 14 || causal < 0 || !g_bwd[type] || !qkv(a + 1, kElem[type], t, s) || !scale_of(a[12], s.D, scale) ||
-        !stream_of(a[13], t[0]->device(), stream))
+        !stream_of(a[13], t[0]->device(), any_none(a + 7, 4), stream))
         Py_RETURN_NONE;
     const at::Tensor *o = plain(a[4], kElem[type], 4), *d_o = plain(a[5], kElem[type], 4), *lse = plain(a[6], at::kFloat, 3);
     if (!o || !d_o || !lse || !same_shape(*o, *t[0]) || !same_shape(*d_o, *t[0]) || !is_lse(*lse, s, *t[0]))

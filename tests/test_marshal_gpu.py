@@ -77,3 +77,44 @@ def test_refusals_are_the_same():
                 call(causal)
     with pytest.raises(binding.AttnError):
         binding.attn_fwd_splitkv(q, k, v, 2, causal=True)
+
+
+def busy(stream, x):
+    """Some 20 ms of work on the stream."""
+    with torch.cuda.stream(stream):
+        y = torch.empty_like(x)
+        for _ in range(20):
+            torch.mm(x, x, out=y)
+    return y
+
+
+@pytest.mark.parametrize("dt", [torch.bfloat16, torch.float16])
+def test_a_call_on_a_named_stream_shares_no_memory_with_the_current_one(dt):
+    """What a call allocates for kernels of another stream is not given to the current stream before they have run (the
+    workspaces), and is no memory that the current stream has still to write (the results)."""
+    fwd, split, bwd = ((binding.attn_fwd, binding.attn_fwd_splitkv, binding.attn_bwd) if dt == torch.bfloat16 else
+                       (binding.attn_fwd_f16, binding.attn_fwd_splitkv_f16, binding.attn_bwd_f16))
+    q, k, v, d_o = tensors(dt, B=4, H=16, S_q=1000, S_kv=1000)
+    o, lse = fwd(q, k, v)
+    x = torch.ones((8192, 8192), dtype=torch.bfloat16, device="cuda")
+    calls = {"fwd": lambda s: fwd(q, k, v, stream=s), "splitkv": lambda s: split(q, k, v, 3, stream=s),
+             "bwd": lambda s: bwd(q, k, v, o, d_o, lse, stream=s), "fwd, not plain": lambda s: fwd(q, k, v, causal=0, stream=s)}
+    sizes = [o.nbytes, lse.nbytes, 2 * lse.nbytes, binding.attn_fwd_splitkv_workspace_bytes(4, 16, 1000, 64, 3)]
+    current = torch.cuda.current_stream()
+    for name, call in calls.items():
+        want = call(None)
+        for side in (torch.cuda.Stream(), torch.cuda.ExternalStream(torch.cuda.Stream().cuda_stream)):
+            print(name, dt, type(side).__name__, flush=True)
+            torch.cuda.synchronize()
+            keep = [busy(side, x)]
+            got = call(side)                                  # waits behind the products
+            keep += [torch.full((n // 4,), float("nan"), device="cuda") for n in sizes for _ in range(3)]
+            torch.cuda.synchronize()
+            assert same(got, want)
+            del got
+            keep.append(busy(current, x))
+            freed = [torch.full((n // 4,), float("nan"), device="cuda") for n in sizes for _ in range(3)]
+            del freed                                         # written behind the products, then free for this stream
+            got = call(side)
+            torch.cuda.synchronize()
+            assert same(got, want)
