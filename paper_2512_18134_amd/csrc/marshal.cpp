@@ -8,6 +8,7 @@
 #include <ATen/ATen.h>
 #include <Python.h>
 #include <c10/core/DeviceGuard.h>
+#include <pybind11/gil.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
@@ -148,11 +149,20 @@ PyObject *pack(std::initializer_list<const at::Tensor *> ts)
     return r;
 }
 
+// An allocation, with the interpreter lock released as torch's own functions do it: it may wait for the device, and other
+// threads of the program (host callbacks of queued work among them) must be able to run meanwhile.
+template <typename F>
+at::Tensor allocate(F make)
+{
+    const pybind11::gil_scoped_release no_gil;
+    return make();
+}
+
 // an output the caller may have given: taken as it is, or allocated like `like`; false if it needs the other way
 bool output(PyObject *given, const at::Tensor &like, at::Tensor &out)
 {
     if (given == Py_None) {
-        out = at::empty_like(like);
+        out = allocate([&] { return at::empty_like(like); });
         return true;
     }
     const at::Tensor *t = plain(given, like.scalar_type(), 0);
@@ -165,7 +175,7 @@ bool output(PyObject *given, const at::Tensor &like, at::Tensor &out)
 bool lse_output(PyObject *given, const Shape &s, const at::Tensor &q, at::Tensor &out)
 {
     if (given == Py_None) {
-        out = at::empty({s.B, s.H, s.S_q}, q.options().dtype(at::kFloat));
+        out = allocate([&] { return at::empty({s.B, s.H, s.S_q}, q.options().dtype(at::kFloat)); });
         return true;
     }
     const at::Tensor *t = plain(given, at::kFloat, 3);
@@ -233,7 +243,7 @@ PyObject *py_splitkv(PyObject *, PyObject *const *a, Py_ssize_t n)
     if (!output(a[5], *t[0], o) || !lse_output(a[6], s, *t[0], lse))
         Py_RETURN_NONE;
     if (!ws.defined())
-        ws = at::empty({need < 16 ? 16 : need}, t[0]->options().dtype(at::kByte));
+        ws = allocate([&] { return at::empty({need < 16 ? 16 : need}, t[0]->options().dtype(at::kByte)); });
     const int rc = launch(t[0]->device(), [&] {
         return g_split[type](t[0]->data_ptr(), t[1]->data_ptr(), t[2]->data_ptr(), o.data_ptr(), (float *)lse.data_ptr(),
                              ws.data_ptr(), (long long)ws.nbytes(), (int)n_split, s.B, s.H, s.S_q, s.S_kv, s.D, causal, scale,
@@ -270,7 +280,7 @@ PyObject *py_bwd(PyObject *, PyObject *const *a, Py_ssize_t n)
         if (!output(a[7 + i], *t[i], g[i]))
             Py_RETURN_NONE;
     if (!ws.defined())
-        ws = at::empty({rows2}, t[0]->options().dtype(at::kFloat));
+        ws = allocate([&] { return at::empty({rows2}, t[0]->options().dtype(at::kFloat)); });
     const int rc = launch(t[0]->device(), [&] {
         return g_bwd[type](t[0]->data_ptr(), t[1]->data_ptr(), t[2]->data_ptr(), o->data_ptr(), d_o->data_ptr(),
                            (const float *)lse->data_ptr(), g[0].data_ptr(), g[1].data_ptr(), g[2].data_ptr(),

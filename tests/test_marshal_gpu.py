@@ -1,5 +1,8 @@
 """The binding's two ways to the library (csrc/marshal.cpp for plain tensors, Python for the rest) take the same calls
 and give the same bits: a `causal` that is no bool sends a call the Python way.  What one way refuses the other refuses."""
+import ctypes
+import subprocess
+
 import pytest
 import torch
 
@@ -118,3 +121,49 @@ def test_a_call_on_a_named_stream_shares_no_memory_with_the_current_one(dt):
             got = call(side)
             torch.cuda.synchronize()
             assert same(got, want)
+
+
+ALLOCATOR = """
+#include <sys/types.h>
+int PyGILState_Check(void);
+static char *slab;
+static ssize_t used, size;
+static int calls, locked;
+void use_slab(void *p, ssize_t n) { slab = p; size = n; used = calls = locked = 0; }
+void counts(int *c, int *l) { *c = calls; *l = locked; }
+void *slab_alloc(ssize_t n, int device, void *stream)
+{
+    ++calls;
+    locked += PyGILState_Check();
+    n = (n + 511) / 512 * 512;
+    if (used + n > size)
+        return 0;
+    used += n;
+    return slab + used - n;
+}
+void slab_free(void *p, ssize_t n, int device, void *stream) {}
+"""
+
+
+def test_allocations_release_the_interpreter_lock(tmp_path):
+    """An allocation may wait for the device: no thread is kept from running meanwhile.  Seen from a memory pool whose
+    allocator asks whether the calling thread holds the lock."""
+    (tmp_path / "slab.c").write_text(ALLOCATOR)
+    so = str(tmp_path / "slab.so")
+    subprocess.run(["gcc", "-shared", "-fPIC", "-o", so, str(tmp_path / "slab.c")], check=True)
+    lib = ctypes.CDLL(so)
+    memory = torch.empty(1 << 28, dtype=torch.uint8, device="cuda")
+    skip = 1 << 20       # torch's allocator keys its blocks by address: none of the pool's starts where `memory` does
+    lib.use_slab(ctypes.c_void_p(memory.data_ptr() + skip), ctypes.c_ssize_t(memory.nbytes - skip))
+    q, k, v, d_o = tensors(torch.bfloat16, B=4, H=8, S_q=512, S_kv=512, D=128)          # every allocation more than 1 MB
+    o, lse = binding.attn_fwd(q, k, v)
+    allocator = torch.cuda.memory.CUDAPluggableAllocator(so, "slab_alloc", "slab_free")
+    pool = torch.cuda.MemPool(allocator.allocator())
+    with torch.cuda.use_mem_pool(pool):
+        keep = [binding.attn_fwd(q, k, v), binding.attn_fwd_splitkv(q, k, v, 2), binding.attn_bwd(q, k, v, o, d_o, lse)]
+    torch.cuda.synchronize()
+    calls, locked = ctypes.c_int(), ctypes.c_int()
+    lib.counts(ctypes.byref(calls), ctypes.byref(locked))
+    same_o = torch.equal(keep[0][0], o)
+    del keep, pool            # the pool goes before its allocator and its memory, also where an assertion fails
+    assert calls.value > 0 and locked.value == 0 and same_o
