@@ -315,8 +315,9 @@ __device__ __forceinline__ void bwd_sweep(const BwdParams &p, const BwdQueue &qu
             for (int db = 0; db < DB; ++db)
     #pragma unroll
                 for (int rb = 0; rb < 4; ++rb) {
-                    const f32x2 lo = {a[db][4 * rb + 0] * mul, a[db][4 * rb + 1] * mul};
-                    const f32x2 hi = {a[db][4 * rb + 2] * mul, a[db][4 * rb + 3] * mul};
+                    // (+ 0: a zero times -scale is a plain zero, as the keys that no query sees get it)
+                    const f32x2 lo = {fmaf(a[db][4 * rb + 0], mul, 0.f), fmaf(a[db][4 * rb + 1], mul, 0.f)};
+                    const f32x2 hi = {fmaf(a[db][4 * rb + 2], mul, 0.f), fmaf(a[db][4 * rb + 3], mul, 0.f)};
                     const ex2 blo = __builtin_convertvector(lo, ex2), bhi = __builtin_convertvector(hi, ex2);  // nearest even
                     const ex4 w = {blo[0], blo[1], bhi[0], bhi[1]};
                     const int chunk = (4 * db + rb) ^ (e_lq & (CPR - 1));

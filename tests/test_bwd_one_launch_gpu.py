@@ -1,6 +1,6 @@
 """The backward launch that holds both sweeps, on sizes where its tile queue can go wrong: fewer tiles than XCDs, tile
 counts that are no multiple of 8 in either sweep (entries between the sweeps that stand for nothing), one more tile than
-workgroups, workgroups that pass from one sweep to the other, and at D = 64 both sides of the line to separate launches.
+workgroups, workgroups that pass from one sweep to the other.
 Against the compiler-scheduled sweeps of the debug build (one launch each; the bar of the schedule-equivalence test), and
 every element of the outputs written."""
 import pytest
@@ -40,3 +40,15 @@ def test_both_sweeps_in_one_launch(heads, S_q, S_kv, causal):
             assert rel(x, y) <= 1e-2 or float(y.float().abs().max()) <= 2e-2
         if causal and S_kv > S_q:
             assert not got[1][:, :, S_q:].any() and not got[2][:, :, S_q:].any()
+
+
+@pytest.mark.parametrize("dt", [torch.bfloat16, torch.float16])
+def test_keys_that_no_query_sees_get_plain_zeros(dt):
+    fwd, bwd = ((binding.attn_fwd, binding.attn_bwd) if dt == torch.bfloat16 else
+                (binding.attn_fwd_f16, binding.attn_bwd_f16))
+    for D in (64, 128):
+        q, k, v, d_o = (torch.randn((1, 2, S, D), device="cuda").to(dt) for S in (100, 700, 700, 100))
+        o, lse = fwd(q, k, v, causal=True)
+        _, dk, dv = bwd(q, k, v, o, d_o, lse, causal=True)
+        for t in (dk, dv):      # all bits zero: no negative zeros
+            assert not t[:, :, 100:].contiguous().view(torch.int16).any()
