@@ -5,8 +5,10 @@ raises if the library has not been built (python -m paper_2512_18134_amd.build).
 PyTorch appears only as the owner of device memory and of the stream.
 
 A call on plain contiguous tensors goes through the extension module _marshal
-(csrc/marshal.cpp); it hands every other call back, and the code here checks its
-arguments, raises what is to be raised and calls the library through ctypes.
+(csrc/marshal.cpp), which is loaded on the first call; it hands every other call
+back, and the code here checks its arguments, raises what is to be raised and calls
+the library through ctypes.  Where the module was not built (no torch at build time)
+every call goes that way: the same kernels, some 10 us more of host work.
 """
 import ctypes
 import os
@@ -95,12 +97,20 @@ def attn_workgroup_tile(causal, workgroup, n_heads, n_tiles, head_bytes=0):
     return head.value, tile.value
 
 
+MARSHAL_PATH = os.path.join(_HERE, "_marshal.so")
 _marshal_module = None
+
+
+class _NotBuilt:
+    """In place of the extension module: every call is handed back."""
+    fwd = splitkv = bwd = staticmethod(lambda *args: None)
 
 
 def _native():
     """The extension module, loaded on first use (it needs torch's libraries in the process)."""
     global _marshal_module
+    if _marshal_module is None and not os.path.exists(MARSHAL_PATH):
+        _marshal_module = _NotBuilt
     if _marshal_module is None:
         import torch
         from . import _marshal as module

@@ -7,7 +7,8 @@ libmi355attn_debug.so (-DATTN_DEBUG_ENTRY_POINTS: the same code plus test-only e
 points that let a test pick the kernel, e.g. the program-order reference of the
 schedule-equivalence tests).  Nothing in the package loads the debug library.
 And _marshal.so, the host-only extension module that takes torch tensors to the entry
-points (csrc/marshal.cpp).
+points (csrc/marshal.cpp); it is left out where torch or the headers of Python are not
+installed (the C ABI needs neither).
 """
 import os
 import subprocess
@@ -54,18 +55,32 @@ def generate_sources(verbose=False, out_dir=None):
         _run_generator([sys.executable, gen3, kind, str(d), out, dtype], verbose)
 
 
+def _hipcc():
+    return os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+
+
 def _compile(lib_path, extra, verbose):
-    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    return _run_compiler([hipcc] + HIPCC_FLAGS + extra, SOURCES, [], lib_path, verbose)
+    return _run_compiler([_hipcc()] + HIPCC_FLAGS + extra, SOURCES, [], lib_path, verbose)
 
 
 def _compile_marshal(verbose):
-    """The extension module: host code against torch's headers and libraries (which the importing process has loaded)."""
-    import torch
-    from torch.utils import cpp_extension
-    inc = cpp_extension.include_paths() + [sysconfig.get_paths()["include"]]
-    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared",
-           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI)] + ["-I" + i for i in inc]
+    """The extension module: host code against torch's headers and libraries (which the importing process has loaded).
+    Without torch or Python's headers there is nothing to compile it against: no module, not an older one either, and
+    the binding does all of the marshalling in Python."""
+    if os.path.exists(MARSHAL_PATH):
+        os.remove(MARSHAL_PATH)
+    include = sysconfig.get_paths()["include"]
+    try:
+        import torch
+        from torch.utils import cpp_extension
+    except ImportError:
+        torch = None
+    if torch is None or not os.path.exists(os.path.join(include, "Python.h")):
+        print("_marshal.so: left out (torch or Python.h is not installed)", flush=True)
+        return None
+    cmd = [_hipcc(), "-no-hip-rt", "-x", "c++", "-O2", "-std=c++17", "-fPIC", "-shared",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI)]
+    cmd += ["-I" + i for i in cpp_extension.include_paths() + [include]]
     libs = ["-L" + os.path.join(os.path.dirname(torch.__file__), "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
     return _run_compiler(cmd, [MARSHAL_SOURCE], libs, MARSHAL_PATH, verbose)
 
@@ -92,9 +107,9 @@ def build_library(verbose=False, debug=True):
     entry points, into DEBUG_LIB_PATH), and the extension module.  Raises on failure."""
     generate_sources(verbose)
     _compile(LIB_PATH, [], verbose)
-    _compile_marshal(verbose)
     if debug:
         _compile(DEBUG_LIB_PATH, ["-DATTN_DEBUG_ENTRY_POINTS"], verbose)
+    _compile_marshal(verbose)
     return LIB_PATH
 
 

@@ -27,6 +27,7 @@ def test_both_ways_give_the_same(dt):
     fwd, split, bwd = ((binding.attn_fwd, binding.attn_fwd_splitkv, binding.attn_bwd) if dt == torch.bfloat16 else
                        (binding.attn_fwd_f16, binding.attn_fwd_splitkv_f16, binding.attn_bwd_f16))
     q, k, v, d_o = tensors(dt)
+    assert binding._native().fwd(dt == torch.float16, q, k, v, None, None, False, None, None) is not None
     for causal in (False, True):
         o, lse = fwd(q, k, v, causal=causal)
         assert same(fwd(q, k, v, causal=int(causal)), (o, lse))
