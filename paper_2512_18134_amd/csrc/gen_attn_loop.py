@@ -90,7 +90,11 @@ CONFIGS = {
     # LOW: the running reference starts at the lowest finite number instead of at -inf
     "d64_w2": dict(D=64,  QB=1, SB=2, NW=2, AG=False, NACC=1, NF=8, PFD=7, W=4, LS=2, LOW=True),
     "d128":   dict(D=128, QB=1, SB=2, NW=8, AG=False, NACC=1, NF=4, PFD=3, W=1),
-    "d128a":  dict(D=128, QB=2, SB=1, NW=4, AG=True,  NACC=1, NF=8, PFD=7, W=4),
+    # AT: the loop's first body starts that many bytes behind a multiple of 32, the window that instructions are fetched in;
+    # left to the code around the loop it moves with every change there.  One wave per SIMD notices: 32 heads of 4096 rows,
+    # causal, 117.9 us at 12, 118.1 at 16, 118.3 to 118.6 at the other multiples of 4; not causal 210.6 / 210.5 / 211.0 to
+    # 211.6; 16 heads of 16384 rows 1623 / 1621 / 1627 to 1631.  The other tilings change by less than 0.3 %.
+    "d128a":  dict(D=128, QB=2, SB=1, NW=4, AG=True,  NACC=1, NF=8, PFD=7, W=4, AT=12),
     "d128a_w2": dict(D=128, QB=2, SB=1, NW=2, AG=True, NACC=1, NF=8, PFD=7, W=4),
     "d128_w2": dict(D=128, QB=1, SB=1, NW=2, AG=False, NACC=1, NF=8, PFD=7, W=4, LS=1, LOW=True),
     "d256a":  dict(D=256, QB=1, SB=1, NW=4, AG=True,  NACC=2, NF=8, PFD=7, W=4, LS=2),
@@ -108,6 +112,7 @@ class Gen(Emitter):
         self.W = cfg["W"] if W is None else W
         assert dtype in ("bf16", "f16")
         self.name, self.dtype = name, dtype
+        self.at = cfg.get("AT")
         # A key group starts in the middle of the keys, where all of a row's scores may be -inf (finite inputs whose
         # products overflow): against a reference of -inf they would give NaN, and the whole row with them.  Against the
         # lowest finite number they give exactly 0 and pass the row-sum test; a finite score fails it, as in a first tile.
@@ -744,6 +749,8 @@ class Gen(Emitter):
         out.append("// VGPRs used: %d, AGPRs used: %d.  MFMA slots per iteration: %d." % (self.NV, self.NA, self.NM))
         out.append("asm volatile(")
         for ln in self.lines:
+            if ln == "%s:" % self.lab("BODY0_") and self.at is not None:     # (only branches lead here)
+                out += ['    "%s\\n\\t"' % pad for pad in [".p2align 5"] + self.at // 4 * ["s_nop 0"]]
             out.append('    "%s\\n\\t"' % ln)
         outs, ins = [], []
         for i in range(QB * DB):

@@ -8,7 +8,10 @@ may touch a destination register before a vector-memory wait that covers the loa
 
 2. The code around the hand-scheduled loop must not spill vector registers to scratch memory: a reload is followed
 by a wait for every load in flight, the K/V tiles of the stream included, which costs the short launches a quarter
-of their time.  (The 8-wave D = 128 loop assigns all 256 VGPRs itself; the few spills around it are known.)"""
+of their time.  (The 8-wave D = 128 loop assigns all 256 VGPRs itself; the few spills around it are known.)
+
+3. The D = 128 loop of 4 waves x 64 rows starts where it was measured to run best within the 32 bytes of an instruction
+fetch, whatever the compiler puts in front of it."""
 import os
 import re
 import subprocess
@@ -145,3 +148,13 @@ def test_no_use_of_q_registers_before_the_wait(compiled):
         assert not bad, (name, bad[:5])
         with_asm_loads += n_loads > 0
     assert with_asm_loads >= 8                     # the tilings without an LDS staging area for Q
+
+
+def test_where_the_wide_loop_starts(compiled):
+    starts = re.findall(r"^_ZN4attn19attn_fwd_asm_kernelILi128ELi2ELi1ELi4E\S+:(.*?)^\s*BODY0_\d+:", compiled, re.M | re.S)
+    assert len(starts) == 4                        # causal or not, both element types
+    for before in starts:
+        lines = [l.strip() for l in before.split("\n") if l.strip()]
+        assert lines[-5].startswith("s_branch BODY1_") and lines[-4:] == [".p2align 5"] + 3 * ["s_nop 0"], lines[-5:]
+    # ... which is an address: the kernels themselves start at multiples of 256
+    assert re.search(r"\.p2align\s+8.*\n(.*\n){0,3}_ZN4attn19attn_fwd_asm_kernelILi128ELi2ELi1ELi4E", compiled)
