@@ -120,6 +120,37 @@ def test_sharp_softmax(B, d):
         compare(run_gpu(B, q, k, v, d_o, causal, scale), attn_bwd_ref(q, k, v, d_o, causal, scale), "sharp D%d" % d)
 
 
+def shift_through_delta(q, k, v, d_o, causal, scale):
+    """What the 16-bit rounding in the forward pass can move dq and dk by.  P and o are rounded (2^-9 each), so Delta_i is
+    off by up to t_i = 2^-9 sum_d |d_o| (|o| + sum_j p_ij |v_j|), ds_ij by p_ij t_i, dq_i by scale t_i |sum_j p_ij k_j|
+    and dk_j by scale sum_i p_ij t_i |q_i|.  Where the softmax is nearly one-hot, dq itself is far smaller than this (dP and
+    Delta cancel), and with one query no other row sets the size of the tensor: the bar relative to it then says nothing."""
+    q, k, v, d_o = (torch.from_numpy(synth.bf16_bits_to_f32(x).astype(np.float64)) for x in (q, k, v, d_o))
+    s = torch.matmul(q, k.transpose(-1, -2)) * scale
+    if causal:
+        s = s.masked_fill(torch.arange(k.shape[2])[None, :] > torch.arange(q.shape[2])[:, None], float("-inf"))
+    p = torch.softmax(s, -1)
+    t = 2.0 ** -9 * (d_o.abs() * (torch.matmul(p, v).abs() + torch.matmul(p, v.abs()))).sum(-1, keepdim=True)
+    return (float((t * torch.matmul(p, k).abs()).max()) * scale,
+            float(torch.matmul(p.transpose(-1, -2), t * q.abs()).max()) * scale)
+
+
+@pytest.mark.parametrize("sharp", [False, True], ids=["plain", "sharp"])
+@pytest.mark.parametrize("s_q,s_kv", [(1, 500), (7, 63), (31, 2000), (33, 96), (63, 63), (63, 1100)])
+def test_few_queries(B, s_q, s_kv, sharp):
+    # forward and backward of calls with fewer than 64 queries: the forward pass then shares the keys out between two
+    # groups of waves (another order of the sums), and the gradients are built on what it wrote
+    for d in (64, 128):
+        q, k, v = synth.make_qkv(2, 3, s_q, s_kv, d, seed=600 + s_q, sharp=sharp)
+        d_o = synth.make_do(2, 3, s_q, d, seed=600 + s_q)
+        scale = synth.default_scale(d)
+        for causal in (False, True):
+            print("bwd few queries", (s_q, s_kv, d, causal, sharp), flush=True)
+            got, want = run_gpu(B, q, k, v, d_o, causal, scale), attn_bwd_ref(q, k, v, d_o, causal, scale)
+            for g, w, more in zip(got, want, shift_through_delta(q, k, v, d_o, causal, scale) + (0.0,)):
+                assert np.max(np.abs(g - w)) <= TOL * np.max(np.abs(w)) + ABS_FLOOR + more
+
+
 def test_invariants_and_invisible_keys(B):
     # causal with S_kv > S_q: keys no query sees get exact zeros; dK rows sum to ~0, dV rows to sum of dO
     b, h, sq, skv, d = 1, 2, 200, 333, 128
