@@ -135,6 +135,12 @@ int launch_d64(const Params &p, int BH, int causal, hipStream_t stream, int tili
 // D = 128: the same estimate for the 256-row tiling (one workgroup per CU) and the 128-row one (two).  A CU with a single
 // 128-row workgroup walks a tile's keys at 0.6 us per 32 of them.  Causal: the sum of the tiles' keys, ragged last
 // tiles included, or the walk of the tile with the most of them in an otherwise idle chip, whichever is longer.
+// With at most one 128-row tile per CU there is only that walk: the 128-row tiling starts 0.7 us sooner (not on a head of
+// at most 128 rows, where only two waves share its loads) and is 1 % slower at it, so that the line lies at some 3700
+// keys.  Measured, 1 to 64 heads, us for 256 / 128 rows: 16 heads of 128 rows 10.2 / 10.4, of 200 12.5 / 11.6, of 512
+// 17.4 / 16.7, of 777 21.5 / 20.8, of 1100 26.3 / 26.2, of 2048 41.6 / 41.1; 8 of 3000 55.7 / 54.9, of 4096 72.8 / 72.9;
+// 4 of 6000 101.3 / 102.6, of 8192 135.9 / 136.7; 1 of 16384 259.9 / 262.2.  Not causal, the estimates are good to 3 %:
+// 16 heads of 2048 rows 40.6 / 41.6, 8 of 4096 79.9 / 81.1, 600 of 384 65.2 / 66.8.
 float d128_cost(int rows, int BH, const Params &p, int causal, int cus)
 {
     const bool two = rows == 128;
@@ -143,14 +149,21 @@ float d128_cost(int rows, int BH, const Params &p, int causal, int cus)
     const float whole = (float)(tiles / slots), rest = (float)(tiles % slots) / (float)slots;
     if (!causal) {
         const float start = two ? 8.5f : 6.0f, per_tile = two ? 0.86f : 0.80f;
-        const float last = two ? (rest > 0.5f ? 0.83f : 0.60f) : per_tile * (0.65f + 0.35f * rest);
+        const float last = two ? (rest > 0.5f ? 0.83f : 0.62f) : per_tile * (0.65f + 0.35f * rest);
         return whole * (start + per_tile * n) + (rest > 0.f ? start + last * n : 0.f);
     }
     const long long step = rows / 32, k = nt < n / step ? nt : n / step;   // tiles below the last keys
     const float sum = (float)(step * k * (k + 1) / 2 + (nt - k) * n);
     const float start = two ? 7.0f : 6.0f, r = fmaxf(1.f, whole + 0.5f * (rest + (rest > 0.f ? 1.f : 0.f)));
-    const float alone = two && tiles <= cus ? 5.9f : start;   // (no second workgroup to share the CU's start with)
-    return fmaxf(alone + 0.60f * n, start * r + (two ? 0.83f : 0.72f) * sum * BH / (float)slots);
+    const float walk = two && tiles <= cus && nt > 1 ? 5.3f + 0.606f * n : start + 0.60f * n;
+    return fmaxf(walk, start * r + (two ? 0.83f : 0.72f) * sum * BH / (float)slots);
+}
+
+// 64 queries and more
+int choose_d128(int BH, const Params &p, int causal)
+{
+    const int cus = attn::cu_count(1) > 0 ? attn::cu_count(1) : 256;
+    return d128_cost(128, BH, p, causal, cus) < (causal ? 1.f : 0.97f) * d128_cost(256, BH, p, causal, cus) ? 3 : 1;
 }
 
 // D = 128.  tiling: -1 = choose, 0 = 8 waves x 32 rows (two waves per SIMD), 1 = 4 waves x 64 rows (one wave
@@ -158,15 +171,12 @@ float d128_cost(int rows, int BH, const Params &p, int causal, int cus)
 // rows (two workgroups per CU; the same results as 1).
 // Measured, us for tiling 1 / 3: 300 heads of 100 queries and 2048 keys 112 / 61; 100 heads of 600 rows 39.0 / 26.2; 512
 // heads of 300 rows 59.1 / 50.8; causal: 128 heads of 520 rows 32.2 / 25.0, 100 of 777 rows 37.8 / 31.6, 128 of 1100
-// rows 68.4 / 59.3, 16 of 777 rows 21.1 / 20.6.  Full rounds of full tiles stay with tiling 1: 32 heads of 4096 rows 207 / 221, causal 116 / 120.
+// rows 68.4 / 59.3.  Full rounds of full tiles stay with tiling 1: 32 heads of 4096 rows 207 / 221, causal 116 / 120.
 template <bool F16>
 int launch_d128(const Params &p, int BH, int causal, hipStream_t stream, int tiling = -1)
 {
-    if (tiling < 0) {
-        const int cus = attn::cu_count(1) > 0 ? attn::cu_count(1) : 256;
-        tiling = p.S_q < kKeyGroupMaxQueries ? 2
-                 : d128_cost(128, BH, p, causal, cus) < d128_cost(256, BH, p, causal, cus) ? 3 : 1;
-    }
+    if (tiling < 0)
+        tiling = p.S_q < kKeyGroupMaxQueries ? 2 : choose_d128(BH, p, causal);
     switch (tiling) {
     case 0:
         return launch_asm<128, 1, 2, 8, F16>(p, BH, causal, stream);
@@ -447,6 +457,15 @@ extern "C" int attn_fwd_variant(const void *q, const void *k, const void *v, voi
 #endif
 
 #ifdef ATTN_DEBUG_ENTRY_POINTS
+// Test-only, host only: rows of the query tiles that the dispatcher takes for D = 128 and at least 64 queries.
+extern "C" int attn_fwd_d128_tile_rows(int heads, int S_q, int S_kv, int causal)
+{
+    Params p;
+    p.S_q = S_q;
+    p.S_kv = S_kv;
+    return choose_d128(heads, p, causal) == 3 ? 128 : 256;
+}
+
 // Measurement entry point of the debug build: attn_fwd (hand-scheduled kernels) that also records, per
 // tile w of the launch's queue, trace[8 w + 0..5] = the 100 MHz constant clock when the tile is taken up, after
 // K(0) and Q have landed, before the main loop, after it, after O is staged in LDS, and when O is stored;
