@@ -95,6 +95,7 @@ struct Params {
     int total_wg;  // B*H*n_qt
     float c;       // scale * log2(e): the softmax runs in the base-2 domain
     float scale;
+    int idle_row;  // launches without a mask: a wave whose rows start here or later stops early (S_q, or more than any row)
     int cus_per_xcd;  // compute units of an XCD (causal launches with two workgroups to a CU)
     // split-KV launches only: the keys are cut into n_split ranges of split_len keys (a multiple of
     // the K/V tile), every range is a workgroup of its own and writes a normalised partial result

@@ -20,6 +20,23 @@ using attn::Params;
 
 using attn::allow_lds;
 
+// Params::idle_row of a launch.  A wave without a row below S_q that stops after its first K/V tile leaves the LDS port and
+// the power to the others (128 heads of 520 rows, D = 128 35.0 -> 33.5 us, 512 of 300 rows, D = 64 36.0 -> 32.1, D = 256
+// 119 -> 113), but it leaves the loop by code that the others do not run: 0.1 to 0.3 us of instruction fetches, which a
+// short walk does not win back.  Measured without / with, us: 200 heads of 70 rows, D = 128, 64 keys 7.7 / 7.9, 256 keys
+// 11.2 / 11.2, 700 keys 20.4 / 19.0; 4 such heads, 64 keys 7.1 / 7.3, 256 keys 10.5 / 10.7, 1000 keys 22.3 / 22.5; D = 256,
+// where all waves but one have no row, 64 heads of 5 rows, 64 keys 7.6 / 7.7, 135 keys 10.1 / 9.9, 700 keys 18.7 / 18.1;
+// 500 heads of 270 rows, D = 128, 100 keys 32.6 / 30.9; D = 256, 128 keys 60.5 / 60.9, 135 keys 63.3 / 62.1.  D = 64: never
+// slower.  Causal launches always do it: the last query tile of a head, which has these waves, walks the most
+// keys (128 heads of 520 rows, D = 128 25.6 / 25.2, 96 of 2100 rows 124.4 / 121.5; 4 of 70 rows 8.57 / 8.63), and one more
+// argument costs their crowded scalar registers as much as it brings.
+int idle_row(const Params &p, int D, long long tiles)
+{
+    const bool soon = D == 64 || (D == 128 && tiles > 512) || (D == 256 && p.S_q <= 64);
+    const int pays_from = soon ? 65 : tiles >= 128 ? 129 : 512;   // keys
+    return p.S_kv >= pays_from ? p.S_q : 0x7fffffff;
+}
+
 // persistent: as many workgroups as the chip holds at once, each walking the tile queue of its XCD
 // (attn_fwd_asm_kernel); otherwise one workgroup per tile
 template <typename K>
@@ -57,9 +74,10 @@ int launch_simple(const Params &p, int BH, int causal, hipStream_t stream)
 // one hand-scheduled tiling: QB 32-row query blocks per wave, SB 32-key blocks per K/V tile, NW waves; persistent
 // workgroups where the tiling has them
 template <int D, int QB, int SB, int NW, bool F16 = false, int G = 1>
-int launch_asm(const Params &p, int BH, int causal, hipStream_t stream)
+int launch_asm(Params p, int BH, int causal, hipStream_t stream)
 {
     typedef attn::FwdTiling<D, QB, SB, NW, false, G> T;
+    p.idle_row = idle_row(p, D, (long long)BH * ((p.S_q + T::BM - 1) / T::BM));
     if (causal)
         return launch(attn::attn_fwd_asm_kernel<D, QB, SB, NW, true, F16, false, G>, p, BH, T::BM, T::THREADS, T::LDS_BYTES,
                       stream, T::PERSIST);
@@ -251,6 +269,7 @@ static int validate(const void *q, const void *k, const void *v, void *o, float 
     p.total_wg = 0;
     p.c = scale * 1.44269504088896340736f;
     p.scale = scale;
+    p.idle_row = 0;
     p.cus_per_xcd = 0;
     p.n_split = 1;
 #ifdef ATTN_DEBUG_ENTRY_POINTS
@@ -288,6 +307,7 @@ static int launch_ranges(Params &p, int BH, int n_eff, hipStream_t st)
     if (total > 0x7fffffffLL)
         return ATTN_ERR_SHAPE;
     p.total_wg = (int)total;
+    p.idle_row = idle_row(p, D, total);
     auto kern = attn::attn_fwd_asm_kernel<D, QB, SB, NW, false, F16, true, G>;
     if (!allow_lds(reinterpret_cast<const void *>(kern), T::LDS_BYTES))
         return ATTN_ERR_LAUNCH;

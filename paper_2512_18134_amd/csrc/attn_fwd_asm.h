@@ -581,9 +581,8 @@ __global__ __launch_bounds__(NW * G * 64, (D == 64 && NW == 4) ? 2 : 1)  // = Fw
         // causal: the keys behind this wave's last row are masked for all of its rows; the loop leaves the
         // tiles that hold nothing else to the waves below (it keeps their barriers and issues its loads)
         // a wave without a row below S_q writes nothing: after one tile it only keeps step (barriers, its share of the
-        // loads) and leaves the LDS port and the power to the others (128 heads of 520 rows, D = 128 35.0 -> 33.5 us, 512
-        // of 300 rows, D = 64 36.0 -> 32.1, D = 256 119 -> 113; launches without such waves do not change)
-        const bool no_rows = G == 1 && t.q0 + wave * 32 * QB >= p.S_q;
+        // loads) and leaves the LDS port and the power to the others; not causal: in launches where that pays
+        const bool no_rows = G == 1 && t.q0 + wave * 32 * QB >= (CAUSAL ? p.S_q : p.idle_row);
         const int n_tiles_wave =
             idle || no_rows ? 1 : (CAUSAL ? min(t.own_tiles, (last_row - t.kv0) / BN + 1) : t.own_tiles);
         ATTN_TRACE(p, t.vb, 2);
