@@ -10,8 +10,8 @@ may touch a destination register before a vector-memory wait that covers the loa
 by a wait for every load in flight, the K/V tiles of the stream included, which costs the short launches a quarter
 of their time.  (The 8-wave D = 128 loop assigns all 256 VGPRs itself; the few spills around it are known.)
 
-3. The D = 128 loop of 4 waves x 64 rows starts where it was measured to run best within the 32 bytes of an instruction
-fetch, whatever the compiler puts in front of it."""
+3. The loops start where they were measured to run best within the 32 bytes of an instruction fetch, whatever the
+compiler puts in front of them."""
 import os
 import re
 import subprocess
@@ -150,11 +150,21 @@ def test_no_use_of_q_registers_before_the_wait(compiled):
     assert with_asm_loads >= 8                     # the tilings without an LDS staging area for Q
 
 
-def test_where_the_wide_loop_starts(compiled):
-    starts = re.findall(r"^_ZN4attn19attn_fwd_asm_kernelILi128ELi2ELi1ELi4E\S+:(.*?)^\s*BODY0_\d+:", compiled, re.M | re.S)
-    assert len(starts) == 4                        # causal or not, both element types
-    for before in starts:
-        lines = [l.strip() for l in before.split("\n") if l.strip()]
-        assert lines[-5].startswith("s_branch BODY1_") and lines[-4:] == [".p2align 5"] + 3 * ["s_nop 0"], lines[-5:]
+def test_where_the_loops_start(compiled):
+    from test_generated_loops import gen_attn_loop
+    # tiling as in the kernel's name: bytes behind a multiple of 32
+    at = {(c["D"], c["QB"], c["SB"], c["NW"]): c["AT"] for c in gen_attn_loop.CONFIGS.values() if "AT" in c}
+    assert len(at) == 5
+    seen = 0
+    for m in re.finditer(r"^_ZN4attn19attn_fwd_asm_kernelILi(\d+)ELi(\d)ELi(\d)ELi(\d)E\S+:(.*?)^\s*BODY0_\d+:",
+                         compiled, re.M | re.S):
+        want = at.get(tuple(int(x) for x in m.groups()[:4]))
+        if want is None:
+            continue
+        lines = [l.strip() for l in m.group(5).split("\n") if l.strip()]
+        n = want // 4
+        assert lines[-n - 2].startswith("s_branch BODY1_") and lines[-n - 1:] == [".p2align 5"] + n * ["s_nop 0"], lines[-n - 2:]
+        seen += 1
+    assert seen >= 20                              # causal or not, both element types
     # ... which is an address: the kernels themselves start at multiples of 256
     assert re.search(r"\.p2align\s+8.*\n(.*\n){0,3}_ZN4attn19attn_fwd_asm_kernelILi128ELi2ELi1ELi4E", compiled)
