@@ -157,8 +157,9 @@ int launch_d64(const Params &p, int BH, int causal, hipStream_t stream, int tili
 // at most 128 rows, where only two waves share its loads) and is 1 % slower at it, so that the line lies at some 3700
 // keys.  Measured, 1 to 64 heads, us for 256 / 128 rows: 16 heads of 128 rows 10.2 / 10.4, of 200 12.5 / 11.6, of 512
 // 17.4 / 16.7, of 777 21.5 / 20.8, of 1100 26.3 / 26.2, of 2048 41.6 / 41.1; 8 of 3000 55.7 / 54.9, of 4096 72.8 / 72.9;
-// 4 of 6000 101.3 / 102.6, of 8192 135.9 / 136.7; 1 of 16384 259.9 / 262.2.  Not causal, the estimates are good to 3 %:
-// 16 heads of 2048 rows 40.6 / 41.6, 8 of 4096 79.9 / 81.1, 600 of 384 65.2 / 66.8.
+// 4 of 6000 101.3 / 102.6, of 8192 135.9 / 136.7; 1 of 16384 259.9 / 262.2.  Not causal, such tiles walk at 0.64 us: 16
+// heads of 2048 rows 40.6 / 41.6, 8 of 4096 79.9 / 81.1; 500 of 270 rows and 100 keys 32.4 / 30.9.  (Over 848 launches the
+// choice costs more than 1 % against the better tiling at 384 rows only: 600 heads 65.2 / 66.8, 1024 heads 115 / 120.)
 float d128_cost(int rows, int BH, const Params &p, int causal, int cus)
 {
     const bool two = rows == 128;
@@ -167,7 +168,7 @@ float d128_cost(int rows, int BH, const Params &p, int causal, int cus)
     const float whole = (float)(tiles / slots), rest = (float)(tiles % slots) / (float)slots;
     if (!causal) {
         const float start = two ? 8.5f : 6.0f, per_tile = two ? 0.86f : 0.80f;
-        const float last = two ? (rest > 0.5f ? 0.83f : 0.62f) : per_tile * (0.65f + 0.35f * rest);
+        const float last = two ? (rest > 0.5f ? 0.83f : 0.64f) : per_tile * (0.65f + 0.35f * rest);
         return whole * (start + per_tile * n) + (rest > 0.f ? start + last * n : 0.f);
     }
     const long long step = rows / 32, k = nt < n / step ? nt : n / step;   // tiles below the last keys
@@ -181,7 +182,7 @@ float d128_cost(int rows, int BH, const Params &p, int causal, int cus)
 int choose_d128(int BH, const Params &p, int causal)
 {
     const int cus = attn::cu_count(1) > 0 ? attn::cu_count(1) : 256;
-    return d128_cost(128, BH, p, causal, cus) < (causal ? 1.f : 0.97f) * d128_cost(256, BH, p, causal, cus) ? 3 : 1;
+    return d128_cost(128, BH, p, causal, cus) < (causal ? 1.f : 0.99f) * d128_cost(256, BH, p, causal, cus) ? 3 : 1;
 }
 
 // D = 128.  tiling: -1 = choose, 0 = 8 waves x 32 rows (two waves per SIMD), 1 = 4 waves x 64 rows (one wave
