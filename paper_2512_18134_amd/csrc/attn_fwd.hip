@@ -94,12 +94,13 @@ constexpr int kKeyGroupMaxQueries = 64;
 
 // D = 64: what a launch of one tiling costs, in us, fitted to launches of one kernel on 1 to 2000 heads of 1 to 16384
 // rows (within 10 % where two tilings are close).  `start` for every round of query tiles that a compute unit works
-// through (`wgs` workgroups that share a unit overlap theirs), and `per_tile` for every 64-key tile of the query tile
-// with the most of them.  Not causal: a last round that leaves most units idle runs at a higher clock.  Causal: heavy
-// and light tiles are handed out in pairs, so that r rounds cost 0.6 r times the heaviest tile.
+// through (`wgs` workgroups that share a unit overlap theirs; `start_shared` where they do), and `per_tile` for every
+// 64-key tile of the query tile with the most of them.  Not causal: a last round that leaves most units idle runs at a
+// higher clock.  Causal: heavy and light tiles are handed out in pairs, so that r rounds cost 0.6 r times the heaviest
+// tile.
 struct Tiling {
     int rows, wgs;
-    float start, per_tile, per_tile_causal;
+    float start, start_shared, per_tile, per_tile_causal;
 };
 
 float tiling_cost(const Tiling &t, int BH, const Params &p, int causal, int cus)
@@ -110,9 +111,38 @@ float tiling_cost(const Tiling &t, int BH, const Params &p, int causal, int cus)
     const float whole = (float)(tiles / cus), rest = (float)(tiles % cus) / (float)cus;
     const float up = whole + (rest > 0.f ? 1.f : 0.f);   // rounds, the last one counted in full
     if (!causal)
-        return t.start * fmaxf(1.f, up / t.wgs) + t.per_tile * n * (whole + (rest > 0.f ? 0.65f + 0.35f * rest : 0.f));
+        return (up > 1.f ? t.start_shared * fmaxf(1.f, up / t.wgs) : t.start) + t.per_tile * n * (whole + (rest > 0.f ? 0.65f + 0.35f * rest : 0.f));
     const float r = fmaxf(1.f, 0.5f * (whole + rest + up));
     return t.start * fmaxf(1.f, r / t.wgs) + t.per_tile_causal * n * fmaxf(0.7f + 0.17f * r, 0.6f * r);
+}
+
+// Causal launches of 64 queries and more take the 128-row tiling up to 4096 keys, whatever the estimates say: over 876
+// launches of 1 to 1024 heads it is 20 % faster than the 256-row one on average, by up to 23 % where that one's last
+// round is nearly empty (256 heads of 567 rows 33.8 / 28.7, 96 of 1579 57.3 / 48.8, 128 of 1100 42.4 / 35.4), and slower
+// by more than 2 % in six of them, 5.6 % at worst (128 heads of 5504 rows and 576 keys 136.7 / 144.4).  Without a mask
+// the 256-row tiling wins wherever it needs as many rounds (96 heads of 320 rows 9.3 / 9.6, 64 of 520 12.3 / 13.0, 64 of
+// 777 16.3 / 16.7), and beyond two rounds of its tiles, unless most of their rows do not exist.
+int choose_d64(int BH, const Params &p, int causal)
+{
+    if (causal && p.S_q >= kKeyGroupMaxQueries && p.S_kv <= 4096)
+        return 1;
+    const int cus = attn::cu_count(1) > 0 ? attn::cu_count(1) : 256;
+    // (two 128-row workgroups on a unit stream twice the keys per product of a 256-row one: with a causal mask
+    // that shows from long sequences on)
+    const Tiling t[3] = {{256, 1, 5.0f, 5.0f, 0.90f, 0.95f},
+                         {128, 2, 4.0f, 5.2f, 0.52f, p.S_kv > 4096 ? 0.60f : 0.54f},
+                         {64, 1, 4.5f, 4.5f, 0.31f, 0.31f}};
+    float best = tiling_cost(t[0], BH, p, causal, cus);
+    int tiling = 0;
+    const bool wide = p.S_q > 128 && (long long)BH * ((p.S_q + 255) / 256) > 2ll * cus;
+    for (int i = 1; i < (wide ? 1 : (p.S_q < kKeyGroupMaxQueries ? 3 : 2)); ++i) {
+        const float c = tiling_cost(t[i], BH, p, causal, cus);
+        if (c < best) {
+            best = c;
+            tiling = i;
+        }
+    }
+    return tiling;
 }
 
 // D = 64.  tiling: -1 = choose, 0 = 8 waves x 32 rows (two waves per SIMD), 1 = 4 waves x 32 rows (two workgroups
@@ -122,27 +152,8 @@ float tiling_cost(const Tiling &t, int BH, const Params &p, int causal, int cus)
 template <bool F16>
 int launch_d64(const Params &p, int BH, int causal, hipStream_t stream, int tiling = -1)
 {
-    if (tiling < 0) {
-        int cus = attn::cu_count(1);
-        if (cus < 1)
-            cus = 256;
-        // (two 128-row workgroups on a unit stream twice the keys per product of a 256-row one: with a causal mask
-        // that shows from long sequences on)
-        const Tiling t[3] = {{256, 1, 5.0f, 0.90f, 0.95f},
-                             {128, 2, 4.0f, 0.52f, p.S_kv > 4096 ? 0.60f : 0.54f},
-                             {64, 1, 4.5f, 0.31f, 0.31f}};
-        float best = tiling_cost(t[0], BH, p, causal, cus);
-        tiling = 0;
-        // (more than two rounds of 256-row tiles: they win, unless most of their rows do not exist)
-        const bool wide = p.S_q > 128 && (long long)BH * ((p.S_q + 255) / 256) > 2ll * cus;
-        for (int i = 1; i < (wide ? 1 : (p.S_q < kKeyGroupMaxQueries ? 3 : 2)); ++i) {
-            const float c = tiling_cost(t[i], BH, p, causal, cus);
-            if (c < best) {
-                best = c;
-                tiling = i;
-            }
-        }
-    }
+    if (tiling < 0)
+        tiling = choose_d64(BH, p, causal);
     if (tiling == 2)
         return launch_asm<64, 1, 2, 2, F16, 2>(p, BH, causal, stream);
     if (tiling == 1)
@@ -478,13 +489,13 @@ extern "C" int attn_fwd_variant(const void *q, const void *k, const void *v, voi
 #endif
 
 #ifdef ATTN_DEBUG_ENTRY_POINTS
-// Test-only, host only: rows of the query tiles that the dispatcher takes for D = 128 and at least 64 queries.
-extern "C" int attn_fwd_d128_tile_rows(int heads, int S_q, int S_kv, int causal)
+// Test-only, host only: rows of the query tiles that the dispatcher takes for D = 64 or 128 and at least 64 queries.
+extern "C" int attn_fwd_tile_rows(int D, int heads, int S_q, int S_kv, int causal)
 {
     Params p;
     p.S_q = S_q;
     p.S_kv = S_kv;
-    return choose_d128(heads, p, causal) == 3 ? 128 : 256;
+    return (D == 128 ? choose_d128(heads, p, causal) == 3 : choose_d64(heads, p, causal) == 1) ? 128 : 256;
 }
 
 // Measurement entry point of the debug build: attn_fwd (hand-scheduled kernels) that also records, per
