@@ -26,10 +26,12 @@ using attn::allow_lds;
 // short walk does not win back.  Measured without / with, us: 200 heads of 70 rows, D = 128, 64 keys 7.7 / 7.9, 256 keys
 // 11.2 / 11.2, 700 keys 20.4 / 19.0; 4 such heads, 64 keys 7.1 / 7.3, 256 keys 10.5 / 10.7, 1000 keys 22.3 / 22.5; D = 256,
 // where all waves but one have no row, 64 heads of 5 rows, 64 keys 7.6 / 7.7, 135 keys 10.1 / 9.9, 700 keys 18.7 / 18.1;
-// 500 heads of 270 rows, D = 128, 100 keys 32.6 / 30.9; D = 256, 128 keys 60.5 / 60.9, 135 keys 63.3 / 62.1.  D = 64: never
-// slower.  Causal launches always do it: the last query tile of a head, which has these waves, walks the most
-// keys (128 heads of 520 rows, D = 128 25.6 / 25.2, 96 of 2100 rows 124.4 / 121.5; 4 of 70 rows 8.57 / 8.63), and one more
-// argument costs their crowded scalar registers as much as it brings.
+// 600 heads of 300 rows, D = 128, 128 keys 39.1 / 38.9; D = 256, 128 keys 75.4 / 76.0, 256 keys 116 / 111; D = 64, where it is
+// never slower, 96 keys 27.9 / 26.2.  Causal: the last query tile of a head, which has these waves, walks the most keys (128
+// heads of 520 rows, D = 128 25.6 / 25.2, 96 of 2100 rows 124.4 / 121.5; 4 of 70 rows 8.57 / 8.63), so that these launches
+// always do it (one more argument costs their crowded scalar registers as much as it brings), but for the 4-wave D = 64
+// ones, which never do: 1 head of 192 rows 5.6 / 5.8, 32 of 600 rows 9.9 / 10.1, 100 of 256 rows 7.3 / 7.4, 400 of 777 rows
+// 76.7 / 75.5.
 int idle_row(const Params &p, int D, long long tiles)
 {
     const bool soon = D == 64 || (D == 128 && tiles > 512) || (D == 256 && p.S_q <= 64);

@@ -159,8 +159,9 @@ __global__ __launch_bounds__(NW * G * 64, (D == 64 && NW == 4) ? 2 : 1)  // = Fw
     const int n_slots = T::PERSIST ? (int)gridDim.x : p.total_wg;
     // Where two workgroups share a CU, workgroups m and m + cus_per_xcd of an XCD do (measured): the first ones take their
     // places in the queue in reverse, so that a CU pairs heavy with light tiles of a causal launch (within a pass;
-    // persistent_entry does it between passes).  D = 64, causal: 32 heads of 2048 rows 26.1 -> 23.6 us, 17 of 4096 rows
-    // 48.4 -> 43.5, 4 of 16384 rows 163 -> 151; launches with one tile per CU or many passes do not change
+    // persistent_entry does it between passes).  D = 64, causal: 32 heads of 2048 rows 26.1 -> 23.6 us, of 2100 29.6 -> 26.8,
+    // 17 of 4096 rows 48.4 -> 43.5, 4 of 16384 rows 163 -> 151; launches with one tile per CU do not change; with many
+    // passes either order is a few percent ahead now and then (100 heads of 1352 rows 38.7 -> 36.9, 213 77.7 -> 81.8)
     int place = blockIdx.x;
     if constexpr (CAUSAL && T::TWO_PER_CU) {
         const int xcd = place % kNumXcd, m = place / kNumXcd;
@@ -581,8 +582,9 @@ __global__ __launch_bounds__(NW * G * 64, (D == 64 && NW == 4) ? 2 : 1)  // = Fw
         // causal: the keys behind this wave's last row are masked for all of its rows; the loop leaves the
         // tiles that hold nothing else to the waves below (it keeps their barriers and issues its loads)
         // a wave without a row below S_q writes nothing: after one tile it only keeps step (barriers, its share of the
-        // loads) and leaves the LDS port and the power to the others; not causal: in launches where that pays
-        const bool no_rows = G == 1 && t.q0 + wave * 32 * QB >= (CAUSAL ? p.S_q : p.idle_row);
+        // loads) and leaves the LDS port and the power to the others, in launches where that pays (idle_row in attn_fwd.hip)
+        const bool no_rows = G == 1 && !(CAUSAL && D == 64 && NW == 4) &&
+                             t.q0 + wave * 32 * QB >= (CAUSAL ? p.S_q : p.idle_row);
         const int n_tiles_wave =
             idle || no_rows ? 1 : (CAUSAL ? min(t.own_tiles, (last_row - t.kv0) / BN + 1) : t.own_tiles);
         ATTN_TRACE(p, t.vb, 2);
