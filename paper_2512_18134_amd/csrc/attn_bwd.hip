@@ -37,6 +37,24 @@ int launch_sweep(K kern, BwdParams p, int BH, int S_own, int NW, int lds_bytes, 
     return hipGetLastError() == hipSuccess ? ATTN_OK : ATTN_ERR_LAUNCH;
 }
 
+// Few queries against many keys: the query-owner tiles at the end of the queue are the long ones then, and where they
+// begin within a pass over the workgroups and end in the next one, some workgroups walk two of them while others walk
+// none.  Such launches run one sweep after the other: 123 heads of 72 queries and 5938 keys, D = 128, 372 -> 315 us, of 1500
+// keys 102 -> 90 (D = 64 60 -> 50); 16 heads of 1000 queries and 8000 keys 332 -> 258, causal 80 -> 72 (D = 64 208 -> 155,
+// 52 -> 45).  Where the tiles end in the pass they began in, are short, or enough for the workgroups (causal: for half of
+// them, as half of the tiles are short), one launch is ahead or level (48 heads of 72 x 1500 49 / 61, 123 of 64 x 512,
+// causal, 29 / 33; 48 of 1000 x 8000, causal, D = 64 83 / 92; 400 of 72 x 5938 983 / 1004).
+bool sweeps_apart(const BwdParams &p, int causal, int slots)
+{
+    const attn::BwdQueue queue(p.total_wg, p.total_q);
+    const int walk = causal && p.S_q < p.S_kv ? p.S_q : p.S_kv;          // keys of the longest query-owner tile
+    if (queue.n_entries <= slots || p.total_q > (causal ? slots / 2 : slots) || p.S_kv / 4 < p.S_q || walk < 1000)
+        return false;
+    const int per_pass = slots / attn::kNumXcd;                          // entries of an XCD in one pass
+    const int first = queue.q_first / attn::kNumXcd, last = (queue.n_entries - 1) / attn::kNumXcd;
+    return first % per_pass != 0 && first / per_pass != last / per_pass;
+}
+
 // both hand-scheduled sweeps: as many workgroups as the chip holds at once, each walking the queue of owner tiles of its
 // XCD
 template <int D, bool F16>
@@ -46,13 +64,22 @@ int launch_asm(const BwdParams &p, int causal, hipStream_t stream)
     auto kern = causal ? attn::attn_bwd_asm_kernel<D, true, F16> : attn::attn_bwd_asm_kernel<D, false, F16>;
     if (!attn::allow_lds(reinterpret_cast<const void *>(kern), LDS))
         return ATTN_ERR_LAUNCH;
-    int grid = attn::BwdQueue(p.total_wg, p.total_q).n_entries;
     // (a runtime that cannot tell the occupancy gets one workgroup per entry: the kernel takes either)
-    const int slots = attn::persistent_slots(reinterpret_cast<const void *>(kern), 256, LDS, attn::kNumXcd);
-    if (slots >= attn::kNumXcd && slots < grid)
-        grid = slots;
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(256), LDS, stream, p);
-    return hipGetLastError() == hipSuccess ? ATTN_OK : ATTN_ERR_LAUNCH;
+    int slots = attn::persistent_slots(reinterpret_cast<const void *>(kern), 256, LDS, attn::kNumXcd);
+    if (slots < attn::kNumXcd)
+        slots = 0x7fffffff;
+    const auto run = [&](int n_kv, int n_q) {
+        BwdParams r = p;
+        r.total_wg = n_kv;
+        r.total_q = n_q;
+        const int entries = attn::BwdQueue(n_kv, n_q).n_entries;
+        hipLaunchKernelGGL(kern, dim3((unsigned)(slots < entries ? slots : entries)), dim3(256), LDS, stream, r);
+        return hipGetLastError() == hipSuccess ? ATTN_OK : ATTN_ERR_LAUNCH;
+    };
+    if (!sweeps_apart(p, causal, slots))
+        return run(p.total_wg, p.total_q);
+    const int rc = run(p.total_wg, 0);
+    return rc == ATTN_OK ? run(0, p.total_q) : rc;
 }
 
 template <int D, typename ELEM>
@@ -221,6 +248,17 @@ extern "C" int attn_bwd_queue_entry(int n_kv, int n_q, int wg, int n_slots, int 
     const attn::BwdQueue queue(n_kv, n_q);
     *first_q = queue.q_first;
     return queue.entry(wg, n_slots < queue.n_entries ? n_slots : queue.n_entries, cus, k);
+}
+
+// Test-only, host only: whether a backward launch of `slots` workgroups runs one sweep after the other (sweeps_apart).
+extern "C" int attn_bwd_sweeps_apart(int heads, int S_q, int S_kv, int causal, int slots)
+{
+    BwdParams p;
+    p.S_q = S_q;
+    p.S_kv = S_kv;
+    p.total_wg = heads * ((S_kv + 127) / 128);
+    p.total_q = heads * ((S_q + 127) / 128);
+    return sweeps_apart(p, causal, slots);
 }
 
 // Test-only entry point of the debug build of the library: attn_bwd on the compiler-scheduled sweeps
