@@ -307,7 +307,7 @@ __device__ __forceinline__ void bwd_sweep(const BwdParams &p, const BwdQueue &qu
         __syncthreads();  // every wave has left the loop (its loads have landed): the rings are free
         const int e_lane = D == 64 ? lane_id() : lane;
         const int e_lq = e_lane & 31, e_g = e_lane >> 5;
-        auto write_out = [&](const f32x16 *a, float mul, elem_t *out_head, uint32_t ring) {
+        auto write_out = [&](const f32x16 *a, auto value, elem_t *out_head, uint32_t ring) {
             typedef typename E::x2 ex2;
             typedef typename E::x4 ex4;
             unsigned char *stage = smem + ring + wave * 32 * ROWB;
@@ -315,9 +315,8 @@ __device__ __forceinline__ void bwd_sweep(const BwdParams &p, const BwdQueue &qu
             for (int db = 0; db < DB; ++db)
     #pragma unroll
                 for (int rb = 0; rb < 4; ++rb) {
-                    // (+ 0: a zero times -scale is a plain zero, as the keys that no query sees get it)
-                    const f32x2 lo = {fmaf(a[db][4 * rb + 0], mul, 0.f), fmaf(a[db][4 * rb + 1], mul, 0.f)};
-                    const f32x2 hi = {fmaf(a[db][4 * rb + 2], mul, 0.f), fmaf(a[db][4 * rb + 3], mul, 0.f)};
+                    const f32x2 lo = {value(a[db][4 * rb + 0]), value(a[db][4 * rb + 1])};
+                    const f32x2 hi = {value(a[db][4 * rb + 2]), value(a[db][4 * rb + 3])};
                     const ex2 blo = __builtin_convertvector(lo, ex2), bhi = __builtin_convertvector(hi, ex2);  // nearest even
                     const ex4 w = {blo[0], blo[1], bhi[0], bhi[1]};
                     const int chunk = (4 * db + rb) ^ (e_lq & (CPR - 1));
@@ -334,9 +333,11 @@ __device__ __forceinline__ void bwd_sweep(const BwdParams &p, const BwdQueue &qu
                     *reinterpret_cast<u32x4 *>(blk + (size_t)r * D + c * 8) = w;
             }
         };
-        write_out(acc, -p.scale, reinterpret_cast<elem_t *>(KEY_OWNER ? p.dk : p.dq) + (KEY_OWNER ? k_head : q_head), RING1);
+        // (+ 0: a zero times -scale is a plain zero, which the keys that no query sees get)
+        write_out(acc, [&](float x) { return fmaf(x, -p.scale, 0.f); },
+                  reinterpret_cast<elem_t *>(KEY_OWNER ? p.dk : p.dq) + (KEY_OWNER ? k_head : q_head), RING1);
         if constexpr (KEY_OWNER)
-            write_out(acc + DB, 1.f, reinterpret_cast<elem_t *>(p.dv) + k_head, RING2);
+            write_out(acc + DB, [](float x) { return x; }, reinterpret_cast<elem_t *>(p.dv) + k_head, RING2);
     }
 }
 
