@@ -90,12 +90,13 @@ CONFIGS = {
     # d128a, 32 heads of 4096 rows, causal, 117.9 us (at 12) to 118.6, not causal 210.5 (16; 210.6 at 12) to 211.6, 16 heads
     # of 16384 rows 1621 (16; 1623 at 12) to 1631; d64_w4, 32 heads of 2048 rows, causal, 24.0 (4) to 24.3, 16 heads 20.2 (4)
     # to 20.4; d64, 64 heads of 4096 rows 262.8 (16) to 264.3; d256a, 16 heads of 2048 rows 61.8 (24) to 62.2, 8 of 8192,
-    # causal, 228.1 (28; 228.3 at 24) to 229.3; d128a_w2, 100 heads of 600 rows 24.1 (12) to 24.4
+    # causal, 228.1 (28; 228.3 at 24) to 229.3; d128a_w2, 100 heads of 600 rows 24.1 (12) to 24.4; d128 (at every multiple
+    # of 8), 32 heads of 200 x 30000 in 8 ranges 124.5 (16) to 127.1
     "d64":    dict(D=64,  QB=1, SB=2, NW=8, AG=False, NACC=1, NF=8, PFD=6, W=2, AT=16),
     "d64_w4": dict(D=64,  QB=1, SB=2, NW=4, AG=False, NACC=1, NF=8, PFD=6, W=2, AT=4),
     # LOW: the running reference starts at the lowest finite number instead of at -inf
     "d64_w2": dict(D=64,  QB=1, SB=2, NW=2, AG=False, NACC=1, NF=8, PFD=7, W=4, LS=2, LOW=True),
-    "d128":   dict(D=128, QB=1, SB=2, NW=8, AG=False, NACC=1, NF=4, PFD=3, W=1),
+    "d128":   dict(D=128, QB=1, SB=2, NW=8, AG=False, NACC=1, NF=4, PFD=3, W=1, AT=16),
     "d128a":  dict(D=128, QB=2, SB=1, NW=4, AG=True,  NACC=1, NF=8, PFD=7, W=4, AT=12),
     "d128a_w2": dict(D=128, QB=2, SB=1, NW=2, AG=True, NACC=1, NF=8, PFD=7, W=4, AT=12),
     "d128_w2": dict(D=128, QB=1, SB=1, NW=2, AG=False, NACC=1, NF=8, PFD=7, W=4, LS=1, LOW=True),

@@ -154,7 +154,7 @@ def test_where_the_loops_start(compiled):
     from test_generated_loops import gen_attn_loop
     # tiling as in the kernel's name: bytes behind a multiple of 32
     at = {(c["D"], c["QB"], c["SB"], c["NW"]): c["AT"] for c in gen_attn_loop.CONFIGS.values() if "AT" in c}
-    assert len(at) == 5
+    assert len(at) == 6
     seen = 0
     for m in re.finditer(r"^_ZN4attn19attn_fwd_asm_kernelILi(\d+)ELi(\d)ELi(\d)ELi(\d)E\S+:(.*?)^\s*BODY0_\d+:",
                          compiled, re.M | re.S):
