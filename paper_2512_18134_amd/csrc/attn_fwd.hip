@@ -458,6 +458,28 @@ extern "C" int attn_fwd(const void *q, const void *k, const void *v, void *o, fl
 // tiling (8 waves x 32 rows); 3 / 4: D = 64 with 8-wave / 4-wave workgroups; 6: D = 64 or 128 in 64-row
 // workgroups with two key groups; 7: D = 128 in 128-row workgroups (2 waves x 64 rows).  A variant that does not
 // apply to the arguments returns ATTN_ERR_UNSUPPORTED.
+template <bool F16>
+static int fwd_tiling(const Params &p, int BH, int D, int causal, hipStream_t st, int variant)
+{
+    if (!(p.scale > 0.f && (long long)p.S_kv * D * 2 < (1LL << 31)))
+        return ATTN_ERR_UNSUPPORTED;
+    switch (variant) {
+    case 2:
+        return D == 128 ? launch_d128<F16>(p, BH, causal, st, 1) : ATTN_ERR_UNSUPPORTED;
+    case 5:
+        return D == 128 ? launch_d128<F16>(p, BH, causal, st, 0) : ATTN_ERR_UNSUPPORTED;
+    case 6:
+        return D == 128 ? launch_d128<F16>(p, BH, causal, st, 2)
+               : D == 64 ? launch_d64<F16>(p, BH, causal, st, 2) : ATTN_ERR_UNSUPPORTED;
+    case 7:
+        return D == 128 ? launch_d128<F16>(p, BH, causal, st, 3) : ATTN_ERR_UNSUPPORTED;
+    case 3:
+    case 4:
+        return D == 64 ? launch_d64<F16>(p, BH, causal, st, variant - 3) : ATTN_ERR_UNSUPPORTED;
+    }
+    return ATTN_ERR_UNSUPPORTED;
+}
+
 extern "C" int attn_fwd_variant(const void *q, const void *k, const void *v, void *o, float *lse, int B, int H,
                                 int S_q, int S_kv, int D, int causal, float scale, void *stream, int variant)
 {
@@ -466,27 +488,25 @@ extern "C" int attn_fwd_variant(const void *q, const void *k, const void *v, voi
     if (rc != ATTN_OK)
         return rc;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const bool asm_ok = p.scale > 0.f && (long long)p.S_kv * D * 2 < (1LL << 31);
     switch (variant) {
     case 0:
         return dispatch_fwd(p, B * H, D, causal, st);
     case 1:
         return launch_generic(p, B * H, D, causal, st);
-    case 2:
-        return D == 128 && asm_ok ? launch_d128<false>(p, B * H, causal, st, 1) : ATTN_ERR_UNSUPPORTED;
-    case 5:
-        return D == 128 && asm_ok ? launch_d128<false>(p, B * H, causal, st, 0) : ATTN_ERR_UNSUPPORTED;
-    case 6:
-        return !asm_ok ? ATTN_ERR_UNSUPPORTED
-               : D == 128 ? launch_d128<false>(p, B * H, causal, st, 2)
-               : D == 64 ? launch_d64<false>(p, B * H, causal, st, 2) : ATTN_ERR_UNSUPPORTED;
-    case 7:
-        return D == 128 && asm_ok ? launch_d128<false>(p, B * H, causal, st, 3) : ATTN_ERR_UNSUPPORTED;
-    case 3:
-    case 4:
-        return D == 64 && asm_ok ? launch_d64<false>(p, B * H, causal, st, variant - 3) : ATTN_ERR_UNSUPPORTED;
+    default:
+        return fwd_tiling<false>(p, B * H, D, causal, st, variant);
     }
-    return ATTN_ERR_UNSUPPORTED;
+}
+
+// The same for attn_fwd_f16 (which has no program-order kernel: variant 1 is refused).
+extern "C" int attn_fwd_f16_variant(const void *q, const void *k, const void *v, void *o, float *lse, int B, int H,
+                                    int S_q, int S_kv, int D, int causal, float scale, void *stream, int variant)
+{
+    if (variant == 0)
+        return attn_fwd_f16(q, k, v, o, lse, B, H, S_q, S_kv, D, causal, scale, stream);
+    Params p;
+    const int rc = validate(q, k, v, o, lse, B, H, S_q, S_kv, D, scale, p);
+    return rc != ATTN_OK ? rc : fwd_tiling<true>(p, B * H, D, causal, static_cast<hipStream_t>(stream), variant);
 }
 #endif
 

@@ -24,21 +24,24 @@ def lib():
         _lib.attn_fwd_variant.restype = ctypes.c_int
         _lib.attn_fwd_variant.argtypes = ([ctypes.c_void_p] * 5 + [ctypes.c_int] * 6
                                           + [ctypes.c_float, ctypes.c_void_p, ctypes.c_int])
+        _lib.attn_fwd_f16_variant.restype = ctypes.c_int
+        _lib.attn_fwd_f16_variant.argtypes = _lib.attn_fwd_variant.argtypes
         _lib.attn_bwd_plain.restype = ctypes.c_int
         _lib.attn_bwd_plain.argtypes = [ctypes.c_void_p] * 10 + [ctypes.c_int] * 6 + [ctypes.c_float, ctypes.c_void_p]
     return _lib
 
 
 def attn_fwd_variant(q, k, v, causal, scale, variant):
-    """attn_fwd_variant on torch bf16 device tensors; returns (o, lse) or raises on a non-zero status."""
+    """attn_fwd_variant (attn_fwd_f16_variant) on torch bf16 (fp16) device tensors; returns (o, lse) or raises on a
+    non-zero status."""
     import torch
+    call = lib().attn_fwd_f16_variant if q.dtype == torch.float16 else lib().attn_fwd_variant
     B, H, S_q, D = q.shape
     S_kv = k.shape[2]
     o = torch.full(q.shape, float("nan"), dtype=q.dtype, device=q.device)
     lse = torch.full((B, H, S_q), float("nan"), dtype=torch.float32, device=q.device)
-    rc = lib().attn_fwd_variant(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), lse.data_ptr(), B, H, S_q, S_kv,
-                                D, int(bool(causal)), float(scale), torch.cuda.current_stream().cuda_stream,
-                                int(variant))
+    rc = call(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), lse.data_ptr(), B, H, S_q, S_kv, D, int(bool(causal)),
+              float(scale), torch.cuda.current_stream().cuda_stream, int(variant))
     if rc != 0:
         raise RuntimeError("attn_fwd_variant(%d): status %d" % (variant, rc))
     return o, lse

@@ -43,7 +43,6 @@ def test_key_groups_against_the_oracle(S_q, S_kv, causal):
             if dtype == "f16":
                 o, lse = binding.attn_fwd_f16(qd, kd, vd, causal=causal, scale=scale)
                 check(o, lse, want, o_tol)
-                continue
             for d, variant in TILINGS:
                 if d == D:
                     print("S_q", S_q, "S_kv", S_kv, "D", D, "causal", causal, "variant", variant, flush=True)
@@ -84,13 +83,14 @@ def test_the_128_row_tilings_give_the_bits_of_the_256_row_ones(heads, S_q, S_kv,
     g.manual_seed(heads)
     for D, wide, narrow in ((64, debug_lib.FWD_D64_8_WAVES, debug_lib.FWD_D64_4_WAVES),
                             (128, debug_lib.FWD_D128_ONE_WAVE_PER_SIMD, debug_lib.FWD_D128_2_WAVES)):
-        q, k, v = (torch.empty((1, heads, S, D), device="cuda").normal_(0, 2, generator=g).bfloat16()
-                   for S in (S_q, S_kv, S_kv))
-        print("heads", heads, "S_q", S_q, "S_kv", S_kv, "D", D, "causal", causal, flush=True)
-        want = debug_lib.attn_fwd_variant(q, k, v, causal, synth.default_scale(D), wide)
-        for variant in (narrow, debug_lib.FWD_AS_DISPATCHED):
-            got = debug_lib.attn_fwd_variant(q, k, v, causal, synth.default_scale(D), variant)
-            assert all(torch.equal(x, y) for x, y in zip(got, want)), variant
+        x = [torch.empty((1, heads, S, D), device="cuda").normal_(0, 2, generator=g) for S in (S_q, S_kv, S_kv)]
+        for dt in (torch.bfloat16, torch.float16):
+            q, k, v = (t.to(dt) for t in x)
+            print("heads", heads, "S_q", S_q, "S_kv", S_kv, "D", D, "causal", causal, dt, flush=True)
+            want = debug_lib.attn_fwd_variant(q, k, v, causal, synth.default_scale(D), wide)
+            for variant in (narrow, debug_lib.FWD_AS_DISPATCHED):
+                got = debug_lib.attn_fwd_variant(q, k, v, causal, synth.default_scale(D), variant)
+                assert all(torch.equal(a, b) for a, b in zip(got, want)), variant
 
 
 # queries, keys (with S_q >= 64 one key group works on all keys)
