@@ -176,8 +176,10 @@ def _allocate(make, device, stream, returned=True):
     returned to the caller may be used on the caller's current stream as well until it is freed."""
     import torch
 
+    if stream is None:
+        return make()
     current = torch.cuda.current_stream(device)
-    if stream is None or stream.cuda_stream == current.cuda_stream:
+    if stream.cuda_stream == current.cuda_stream:
         return make()
     if not isinstance(stream, torch.cuda.Stream):
         stream = (torch.cuda.ExternalStream(stream.cuda_stream, device=device) if stream.cuda_stream else

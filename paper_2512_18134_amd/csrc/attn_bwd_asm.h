@@ -1,4 +1,5 @@
-// attn_bwd_asm.h -- attention-backward sweeps whose main loop is hand scheduled (one wave per SIMD).
+// attn_bwd_asm.h -- attention-backward sweeps whose main loop is hand scheduled (one wave per SIMD at D = 128, two at
+// D = 64).
 //
 // Same mathematics and data layout as attn_bwd_sweep_kernel (attn_bwd_kernels.h): a workgroup of four
 // waves owns 128 keys (KEY_OWNER) or 128 queries and streams the other side; the owner index is the
@@ -14,7 +15,7 @@
 //
 // Workgroups are persistent, like the forward kernels': a launch has as many workgroups as the chip holds at
 // once and each walks the queue of owner tiles of its XCD.  One launch holds both sweeps: the queue is all key-owner
-// tiles, then all query-owner tiles (BwdQueue).
+// tiles, then all query-owner tiles (BwdQueue); or one of them, the other count being zero (sweeps_apart in attn_bwd.hip).
 #pragma once
 #include "attn_bwd_kernels.h"  // BwdParams
 #include "attn_common.h"
@@ -23,8 +24,8 @@
 
 namespace attn {
 
-// The queue of a launch: entries [0, n_kv) are key-owner tiles (heavier: four products per streamed tile against three,
-// so they go first), entries [q_first, q_first + n_q) query-owner tiles; q_first is n_kv rounded up to a multiple of the
+// The queue of a launch: entries [0, n_kv) are key-owner tiles (four products per streamed tile against three, so they go
+// first), entries [q_first, q_first + n_q) query-owner tiles; q_first is n_kv rounded up to a multiple of the
 // XCD count, so that entry e belongs to XCD e % 8 in both halves.  Entries in between stand for nothing.
 struct BwdQueue {
     int n_kv, q_first, n_entries;

@@ -89,9 +89,12 @@ int launch_asm(Params p, int BH, int causal, hipStream_t stream)
 
 // Below this many queries a launch may use the tilings whose keys are shared out between two groups of waves.  They
 // cut the serial walk over the keys in half (D = 128, one query: 8 heads of 1024 keys 22.1 -> 10.6 us, 64 heads of
-// 4096 keys 70.5 -> 27.7 us) but add up in another order.  O moves by 5e-4 of its norm with that, well inside the
-// rounding of its 16 bits; the dQ that attn_bwd computes from such an O moves by 2e-2 when the softmax is nearly
-// one-hot (dO . O cancels there).  So calls as long as a wave's rows, training calls among them, keep one order.
+// 4096 keys 70.5 -> 27.7 us) but add up in another order, and each group rounds P to 16 bits against a reference of its
+// own: O moves by up to 3e-3 of its norm in bf16 (64 heads of one query and 8191 keys), which is the rounding of its P and
+// of itself, and the dQ that attn_bwd computes from such an O by 2e-2 when the softmax is nearly one-hot (dO . O cancels
+// there).  Neither is further from the exact result than one walk's (240 forward + backward calls with 1 to 63 queries,
+// bf16, rms: O 2.1e-3, dQ of peaked rows 2.4e-2, either way).  The line is a choice: calls with fewer queries, training
+// calls among them, have this order, all others the one that they share with the wide tilings, bit for bit.
 constexpr int kKeyGroupMaxQueries = 64;
 
 // D = 64: what a launch of one tiling costs, in us, fitted to launches of one kernel on 1 to 2000 heads of 1 to 16384
@@ -331,7 +334,7 @@ static int launch_ranges(Params &p, int BH, int n_eff, hipStream_t st)
 
 // Tiling of the ranges.  Up to 64 queries (decode) a 256-row tile is mostly rows that do not exist: 64-row tiles with
 // two key groups stream the keys at the rate of a large copy (D = 128, one query, 64 heads of 8191 keys in 8 ranges:
-// 77.4 -> 51.9 us; 16 heads of 131072 keys in 64 ranges: 260 -> 187 us), at D = 64 for long ranges or few of them, the
+// 69.8 -> 51.6 us; 16 heads of 131072 keys in 64 ranges: 260 -> 187 us), at D = 64 for long ranges or few of them, the
 // 128-row workgroups (two to a CU) otherwise (512 ranges of 1024 keys: 42.6 us with 256-row tiles, 28.3 with 128, 29.8
 // with 64; 1024 ranges of 2048 keys: 151 / 113 / 96).  With more queries the small tiles win while they find idle
 // compute units (256 queries, 8 heads of 8192 keys in 8 ranges: D = 128 28.9 -> 17.5 us, D = 64 19.6 -> 11.2 us), the

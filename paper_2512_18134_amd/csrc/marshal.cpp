@@ -4,7 +4,7 @@
 // two allocations, the current stream, ctypes conversions), which is more than the kernels of a small call take.  The
 // functions here do the same for a call whose arguments are plain contiguous tensors on one GPU, and return None for
 // every other one without having done anything: the binding's Python code then handles it, errors included.  Host
-// only; the entry points' addresses come from the binding (set_entry), so nothing links to the library.
+// only; the entry points' addresses come from the binding (set_entries), so nothing links to the library.
 #include <ATen/ATen.h>
 #include <Python.h>
 #include <c10/core/DeviceGuard.h>
