@@ -44,7 +44,7 @@ def generate_sources(verbose=False, out_dir=None):
     gen = os.path.join(HERE, "csrc", "gen_attn_loop.py")
     out_dir = out_dir or os.path.join(HERE, "csrc", "generated")
     os.makedirs(out_dir, exist_ok=True)
-    for name in ("d64", "d64_w4", "d64_w2", "d128", "d128a", "d128a_w2", "d128_w2", "d256a"):
+    for name in ("d64", "d64_w4", "d64_w2", "d128", "d128a", "d128a_w2", "d128_w2", "d128_w4", "d256a"):
         for dtype in ("bf16", "f16"):
             out = os.path.join(out_dir, "attn_loop_%s%s.inc" % (name, "" if dtype == "bf16" else "_" + dtype))
             _run_generator([sys.executable, gen, name, out, dtype], verbose)

@@ -194,16 +194,61 @@ float d128_cost(int rows, int BH, const Params &p, int causal, int cus)
     return fmaxf(walk, start * r + (two ? 0.83f : 0.72f) * sum * BH / (float)slots);
 }
 
-// 64 queries and more
-int choose_d128(int BH, const Params &p, int causal)
+// 64 queries and more: the better one of the two tilings of 64-row waves
+int choose_d128(int BH, const Params &p, int causal, float *cost = nullptr)
 {
     const int cus = attn::cu_count(1) > 0 ? attn::cu_count(1) : 256;
-    return d128_cost(128, BH, p, causal, cus) < (causal ? 1.f : 0.99f) * d128_cost(256, BH, p, causal, cus) ? 3 : 1;
+    const float narrow = d128_cost(128, BH, p, causal, cus), wide = d128_cost(256, BH, p, causal, cus);
+    const bool two = narrow < (causal ? 1.f : 0.99f) * wide;
+    if (cost)
+        *cost = two ? narrow : wide;
+    return two ? 3 : 1;
+}
+
+// D = 128, 64 queries and more: the 128-row tiling of 32-row waves that move their references in pairs.  A wave has half the
+// products and half the softmax of a 64-row one, so that the walk over the keys is shorter wherever the launch does not
+// fill the chip's SIMDs twice over; it reads twice the LDS operands per product, so that full launches stay with 64-row
+// waves (two workgroups of either kind share a CU's matrix pipes: 0.84 us per 32 keys, where a 256-row one takes 0.80).
+// us, best tiling of 64-row waves / paired: 16 heads of 128 rows 9.5 / 7.4, of 777 rows, causal, 20.5 / 14.4, of 1024 23.2 /
+// 15.8; 32 of 2048, causal, 48.1 / 38.0; 4 of 6000, causal, 98.8 / 70.4; 1 of 16384, causal, 255 / 171; 16 of 2048 41.7 /
+// 34.6; 24 of 2816 122 / 115; but 6 of 5468 93 / 120, 128 of 2048 223 / 244, 32 of 4096, causal, 117 / 131.
+// Up to one tile per CU it is always ahead (by 10 to 34 % over 650 launches).  A CU's second workgroup then halves the
+// speed of both, so that the line is an estimate again, fitted over 1800 launches of 1 to 600 heads.  Not causal: rounds of
+// two tiles per CU, of which the last walks faster where most CUs have one tile or none; heads of a single query tile
+// stay out, whose keys come from memory once per workgroup (310 heads of 112 queries and 960 keys 33.8 / 39.7).  Causal: heavy
+// and light tiles share a CU and it is ahead (18 % on average, 5 % behind at worst) up to 2 1/4 tiles per CU, and up to
+// 1024 keys at any number of tiles (7 % on average, 4 % behind at worst; 213 heads of 623 rows 42.6 / 37.0); beyond that the
+// better of the others has its balance to win or lose (32 heads of 3845 rows 111 / 151).  With this rule 10 of the 2200
+// launches are more than 2 % slower than without it (5 % at worst), and the mean is 16 % faster.
+bool paired_pays(int BH, const Params &p, int causal, int cus, float others)
+{
+    const long long nt = (p.S_q + 127) / 128, tiles = BH * nt, slots = 2ll * cus;
+    const long long n = ((causal && p.S_q < p.S_kv ? p.S_q : p.S_kv) + 31) / 32;
+    if (4 * tiles <= (causal ? 9 : 4) * cus || (causal && n <= 32))
+        return true;
+    const float whole = (float)(tiles / slots), rest = (float)(tiles % slots) / (float)slots;
+    if (!causal) {
+        if (nt == 1 && n >= 16)
+            return false;
+        const float last = rest > 0.5f ? 7.8f + (0.63f + 0.43f * (rest - 0.5f)) * n : rest > 0.f ? 5.0f + (0.31f + 0.29f * rest) * n : 0.f;
+        return whole * (5.5f + 0.84f * n) + last < 0.95f * others;
+    }
+    const long long k = nt < n / 4 ? nt : n / 4;   // tiles below the last keys
+    const float sum = (float)(2 * k * (k + 1) + (nt - k) * n), r = fmaxf(1.f, whole + 0.5f * (rest + (rest > 0.f ? 1.f : 0.f)));
+    return fmaxf(5.9f + 0.39f * n, 7.0f * r + 0.873f * sum * BH / (float)slots + 0.056f * n) < 1.04f * others;
+}
+
+int choose_d128_all(int BH, const Params &p, int causal)
+{
+    const int cus = attn::cu_count(1) > 0 ? attn::cu_count(1) : 256;
+    float others;
+    const int tiling = choose_d128(BH, p, causal, &others);
+    return paired_pays(BH, p, causal, cus, others) ? 4 : tiling;
 }
 
 // D = 128.  tiling: -1 = choose, 0 = 8 waves x 32 rows (two waves per SIMD), 1 = 4 waves x 64 rows (one wave
 // per SIMD, half the LDS operand reads per MFMA), 2 = 2 x 2 waves x 32 rows (64 rows, two key groups), 3 = 2 waves x 64
-// rows (two workgroups per CU; the same results as 1).
+// rows (two workgroups per CU; the same results as 1), 4 = 4 waves x 32 rows in pairs (two per CU; the same results as 1).
 // Measured, us for tiling 1 / 3: 300 heads of 100 queries and 2048 keys 112 / 61; 100 heads of 600 rows 39.0 / 26.2; 512
 // heads of 300 rows 59.1 / 50.8; causal: 128 heads of 520 rows 32.2 / 25.0, 100 of 777 rows 37.8 / 31.6, 128 of 1100
 // rows 68.4 / 59.3.  Full rounds of full tiles stay with tiling 1: 32 heads of 4096 rows 207 / 221, causal 116 / 120.
@@ -211,7 +256,7 @@ template <bool F16>
 int launch_d128(const Params &p, int BH, int causal, hipStream_t stream, int tiling = -1)
 {
     if (tiling < 0)
-        tiling = p.S_q < kKeyGroupMaxQueries ? 2 : choose_d128(BH, p, causal);
+        tiling = p.S_q < kKeyGroupMaxQueries ? 2 : choose_d128_all(BH, p, causal);
     switch (tiling) {
     case 0:
         return launch_asm<128, 1, 2, 8, F16>(p, BH, causal, stream);
@@ -219,6 +264,8 @@ int launch_d128(const Params &p, int BH, int causal, hipStream_t stream, int til
         return launch_asm<128, 1, 1, 2, F16, 2>(p, BH, causal, stream);
     case 3:
         return launch_asm<128, 2, 1, 2, F16>(p, BH, causal, stream);
+    case 4:
+        return launch_asm<128, 1, 1, 4, F16>(p, BH, causal, stream);
     default:
         return launch_asm<128, 2, 1, 4, F16>(p, BH, causal, stream);
     }
@@ -459,8 +506,8 @@ extern "C" int attn_fwd(const void *q, const void *k, const void *v, void *o, fl
 // kernel chosen by the caller.  variant 0: as attn_fwd; 1: the generic program-order kernel;
 // 2 / 5: D = 128 on the one-wave-per-SIMD tiling (4 waves x 64 query rows) / on the two-waves-per-SIMD
 // tiling (8 waves x 32 rows); 3 / 4: D = 64 with 8-wave / 4-wave workgroups; 6: D = 64 or 128 in 64-row
-// workgroups with two key groups; 7: D = 128 in 128-row workgroups (2 waves x 64 rows).  A variant that does not
-// apply to the arguments returns ATTN_ERR_UNSUPPORTED.
+// workgroups with two key groups; 7 / 8: D = 128 in 128-row workgroups (2 waves x 64 rows / 4 waves x 32 rows in pairs).
+// A variant that does not apply to the arguments returns ATTN_ERR_UNSUPPORTED.
 template <bool F16>
 static int fwd_tiling(const Params &p, int BH, int D, int causal, hipStream_t st, int variant)
 {
@@ -475,7 +522,8 @@ static int fwd_tiling(const Params &p, int BH, int D, int causal, hipStream_t st
         return D == 128 ? launch_d128<F16>(p, BH, causal, st, 2)
                : D == 64 ? launch_d64<F16>(p, BH, causal, st, 2) : ATTN_ERR_UNSUPPORTED;
     case 7:
-        return D == 128 ? launch_d128<F16>(p, BH, causal, st, 3) : ATTN_ERR_UNSUPPORTED;
+    case 8:
+        return D == 128 ? launch_d128<F16>(p, BH, causal, st, variant - 4) : ATTN_ERR_UNSUPPORTED;
     case 3:
     case 4:
         return D == 64 ? launch_d64<F16>(p, BH, causal, st, variant - 3) : ATTN_ERR_UNSUPPORTED;
@@ -514,13 +562,23 @@ extern "C" int attn_fwd_f16_variant(const void *q, const void *k, const void *v,
 #endif
 
 #ifdef ATTN_DEBUG_ENTRY_POINTS
-// Test-only, host only: rows of the query tiles that the dispatcher takes for D = 64 or 128 and at least 64 queries.
+// Test-only, host only: rows of the query tiles that the dispatcher takes for D = 64 and at least 64 queries, and at D = 128
+// takes of the two tilings of 64-row waves (where attn_fwd_paired says no).
 extern "C" int attn_fwd_tile_rows(int D, int heads, int S_q, int S_kv, int causal)
 {
     Params p;
     p.S_q = S_q;
     p.S_kv = S_kv;
     return (D == 128 ? choose_d128(heads, p, causal) == 3 : choose_d64(heads, p, causal) == 1) ? 128 : 256;
+}
+
+// Test-only, host only: does a D = 128 launch of at least 64 queries take the tiling whose waves work in pairs?
+extern "C" int attn_fwd_paired(int heads, int S_q, int S_kv, int causal)
+{
+    Params p;
+    p.S_q = S_q;
+    p.S_kv = S_kv;
+    return choose_d128_all(heads, p, causal) == 4;
 }
 
 // Measurement entry point of the debug build: attn_fwd (hand-scheduled kernels) that also records, per

@@ -23,6 +23,9 @@
 //   <D=128,    QB=2, SB=1, NW=4>  one wave per SIMD, O and Q in AGPRs; a K / V^T fragment
 //                                  read from LDS feeds two MFMAs (half the LDS reads)
 //   <D=128,    QB=2, SB=1, NW=2>  the same with BM = 128 (two workgroups per CU; the same results)
+//   <D=128,    QB=1, SB=1, NW=4>  BM = 128 in 32-row waves (two workgroups per CU, two waves per SIMD) that move their
+//                                  references in pairs, as the 64-row waves do (the same results): half the work per
+//                                  wave and tile, for launches that a wave's walk bounds
 //   <D=256,    QB=1, SB=1, NW=4>  one wave per SIMD, O and Q in AGPRs
 // K/V tiles in two 4-stage LDS rings (8 * BN * D * 2 bytes).  The kernel starts S(0) as soon as K(0)
 // and Q have landed; the other five tiles of the ring fill behind it.
@@ -92,15 +95,19 @@ struct FwdTiling {
     // written out.  Without it Q is loaded straight into registers (32-byte pieces).  O is staged in the rings
     // once the loop has left them.
     static constexpr bool HAS_STAGE = !SPLIT && G == 1 && NW * QB == 8 && RING_BYTES + STAGE_BYTES <= 160 * 1024;
-    static constexpr int LDS_BYTES = G * RING_BYTES + (HAS_STAGE ? STAGE_BYTES : 0);
+    // 32-row waves that test their tiles' row sums in pairs (gen_attn_loop.py, PairedGen): the sums pass through LDS
+    static constexpr bool PAIRED = D == 128 && QB == 1 && SB == 1 && G == 1;
+    static constexpr int XCH_SUMS = G * RING_BYTES, XCH_SUMS_BYTES = PAIRED ? 2 * NW * 64 * 4 : 0;
+    static constexpr int LDS_BYTES = XCH_SUMS + XCH_SUMS_BYTES + (HAS_STAGE ? STAGE_BYTES : 0);
     // Persistent workgroups (see attn_fwd_asm_kernel) wherever the loop leaves the compiler registers to carry
     // a tile's state across it: the 8-wave D = 128 loop assigns all 256 VGPRs itself, and a split-KV launch
     // has a workgroup per (tile, key range)
     static constexpr bool PERSIST = !SPLIT && !(D == 128 && QB == 1 && SB == 2);
-    // the 4-wave D = 64 workgroups are meant to run two to a CU: their waves must fit half a SIMD's registers
-    static constexpr int MIN_WAVES_PER_SIMD = (D == 64 && NW == 4) ? 2 : 1;
+    // the 4-wave D = 64 and paired workgroups are meant to run two to a CU: their waves must fit half a SIMD's registers
+    static constexpr int MIN_WAVES_PER_SIMD = ((D == 64 && NW == 4) || PAIRED) ? 2 : 1;
     // ... and the 2-wave D = 128 ones, by their 64 KB of LDS
-    static constexpr bool TWO_PER_CU = (D == 64 && NW == 4) || (D == 128 && QB == 2 && NW == 2);
+    static constexpr bool TWO_PER_CU = (D == 64 && NW == 4) || (D == 128 && QB == 2 && NW == 2) || PAIRED;
+    static_assert(!(PAIRED && HAS_STAGE), "the row sums lie behind the rings");
     static_assert(SPLIT || STAGE_BYTES <= RING_BYTES, "O staging must fit the rings");
     // the two key groups exchange half of their fp32 accumulators, their row maxima and sums, then stage half rows
     static constexpr int XCH_O = 0, XCH_ML = 2 * NW * 32 * D * 2, XCH_STAGE = XCH_ML + 2 * NW * 64 * 8;
@@ -114,12 +121,12 @@ struct FwdTiling {
 // multiple of the XCD count unless every tile has a workgroup of its own), and workgroup `blockIdx.x` walks the
 // tile queue of its XCD (persistent_entry), so that no dispatch gap separates two tiles of a CU.
 template <int D, int QB, int SB, int NW, bool CAUSAL, bool F16 = false, bool SPLIT = false, int G = 1>
-__global__ __launch_bounds__(NW * G * 64, (D == 64 && NW == 4) ? 2 : 1)  // = FwdTiling::MIN_WAVES_PER_SIMD
+__global__ __launch_bounds__(NW * G * 64, (D == 64 && NW == 4) || (D == 128 && QB == 1 && SB == 1 && G == 1) ? 2 : 1)  // = FwdTiling::MIN_WAVES_PER_SIMD
     void attn_fwd_asm_kernel(const Params p)
 {
     static_assert((QB == 1 && SB == 2 && (D == 64 || D == 128) && NW == 8 && G == 1) ||
                       (QB == 1 && SB == 2 && D == 64 && ((NW == 4 && G == 1) || (NW == 2 && G == 2))) ||
-                      (QB == 1 && SB == 1 && D == 128 && NW == 2 && G == 2) ||
+                      (QB == 1 && SB == 1 && D == 128 && ((NW == 2 && G == 2) || (NW == 4 && G == 1 && !SPLIT))) ||
                       (QB == 2 && SB == 1 && D == 128 && (NW == 4 || (NW == 2 && !SPLIT)) && G == 1) ||
                       (QB == 1 && SB == 1 && D == 256 && NW == 4 && G == 1 && !SPLIT),
                   "no generated loop for this tiling");
@@ -147,13 +154,13 @@ __global__ __launch_bounds__(NW * G * 64, (D == 64 && NW == 4) ? 2 : 1)  // = Fw
     unsigned char *const o_stage = smem;                          // O is staged in the rings, after the loop
 
     const int tid = threadIdx.x;
-    const int lane = tid & 63;
+    int lane = tid & 63;
     const int wave_wg = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int grp = G == 1 ? 0 : wave_wg / NW;    // key group of this wave
     const int wave = G == 1 ? wave_wg : wave_wg % NW;   // ... and its place in the group
     const uint32_t lds0 = (uint32_t)(uintptr_t)(ATTN_LDS_PTR(unsigned char))smem + grp * T::RING_BYTES;
-    const int lq = lane & 31;
-    const int g = lane >> 5;
+    int lq = lane & 31;
+    int g = lane >> 5;
 
     // ---- this workgroup's walk through the tile queue of its XCD (persistent_entry)
     const int n_slots = T::PERSIST ? (int)gridDim.x : p.total_wg;
@@ -425,6 +432,13 @@ __global__ __launch_bounds__(NW * G * 64, (D == 64 && NW == 4) ? 2 : 1)  // = Fw
             finish_groups(t);
             return;
         }
+        if constexpr (T::PAIRED) {
+            // the paired loop leaves few registers for what lives across it: the addresses of this part are made from a
+            // lane number that the compiler cannot see is the same for every tile
+            asm volatile("" : "+v"(lane));
+            lq = lane & 31;
+            g = lane >> 5;
+        }
         float inv[QB], lse_row[QB];
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) {
@@ -545,7 +559,7 @@ __global__ __launch_bounds__(NW * G * 64, (D == 64 && NW == 4) ? 2 : 1)  // = Fw
         for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
             for (int sb = 0; sb < SB; ++sb) {
-                const ex8 a = *(ATTN_LDS_PTR(const ex8))(uintptr_t)(koff[ks] + sb * 32 * ROWB);
+                const ex8 a = *(ATTN_LDS_PTR(const ex8))(uintptr_t)((T::PAIRED ? koff_v[ks] : koff[ks]) + sb * 32 * ROWB);
 #pragma unroll
                 for (int qb = 0; qb < QB; ++qb)
                     s_init[qb * SB + sb] = E::mfma(a, bq[qb][ks], s_init[qb * SB + sb]);
@@ -583,13 +597,21 @@ __global__ __launch_bounds__(NW * G * 64, (D == 64 && NW == 4) ? 2 : 1)  // = Fw
         // tiles that hold nothing else to the waves below (it keeps their barriers and issues its loads)
         // a wave without a row below S_q writes nothing: after one tile it only keeps step (barriers, its share of the
         // loads) and leaves the LDS port and the power to the others, in launches where that pays (idle_row in attn_fwd.hip)
+        // (a pair of waves has rows or has none: either needs the other's row sums)
         const bool no_rows = G == 1 && !(CAUSAL && D == 64 && NW == 4) &&
-                             t.q0 + wave * 32 * QB >= (CAUSAL ? p.S_q : p.idle_row);
+                             t.q0 + (T::PAIRED ? wave & ~1 : wave) * 32 * QB >= (CAUSAL ? p.S_q : p.idle_row);
         const int n_tiles_wave =
             idle || no_rows ? 1 : (CAUSAL ? min(t.own_tiles, (last_row - t.kv0) / BN + 1) : t.own_tiles);
+        // this lane's place for its tile row sums and the other wave's
+        [[maybe_unused]] const uint32_t xch_own = lds0 + T::XCH_SUMS + (wave * 64 + lane) * 4;
+        [[maybe_unused]] const uint32_t xch_other = lds0 + T::XCH_SUMS + ((wave ^ 1) * 64 + lane) * 4;
         ATTN_TRACE(p, t.vb, 2);
 
-        if constexpr (D == 128 && SB == 2 && !F16) {
+        if constexpr (T::PAIRED && !F16) {
+#include "generated/attn_loop_d128_w4.inc"
+        } else if constexpr (T::PAIRED) {
+#include "generated/attn_loop_d128_w4_f16.inc"
+        } else if constexpr (D == 128 && SB == 2 && !F16) {
 #include "generated/attn_loop_d128.inc"
         } else if constexpr (D == 128 && SB == 2 && F16) {
 #include "generated/attn_loop_d128_f16.inc"

@@ -104,11 +104,20 @@ CONFIGS = {
     "d256a":  dict(D=256, QB=1, SB=1, NW=4, AG=True,  NACC=2, NF=8, PFD=7, W=4, LS=2, AT=24),
 }
 
+# tilings whose waves test their tiles' row sums in pairs (PairedGen).  AT: 4 heads of 6000 rows, causal, 70.4 us (at 8) to
+# 71.9, 16 of 777 rows 14.3 (8) to 14.5
+PAIRED = {
+    "d128_w4": dict(D=128, QB=1, SB=1, NW=4, AG=False, NACC=1, NF=8, PFD=7, W=4, AT=8),
+}
+
 
 class Gen(Emitter):
+    configs = CONFIGS
+    paired = False
+
     def __init__(self, name, dtype="bf16", NF=None, PFD=None, W=None, drop=(), DEP=None, LS=None):
         Emitter.__init__(self)
-        cfg = CONFIGS[name]
+        cfg = self.configs[name]
         # direct loads of an iteration: LS = 0: K's in slot 0, V's in slot 1; LS > 0: one load per slot, LS slots apart
         self.LS = cfg.get("LS", 0) if LS is None else LS
         NF = cfg["NF"] if NF is None else NF
@@ -173,14 +182,7 @@ class Gen(Emitter):
         self.TP = take(2 * (2 * self.DEP + 2))   # exponent / exp temporaries: 2 DEP + 1 element pairs in flight, one kept
         self.ALPHA = take(QB)
         self.THRB = take(QB, operand=True)
-        self.THR = take(QB)
-        self.T = take(QB)
-        self.TMP2 = take(QB)
-        self.DD = take(QB)
-        self.MX = take(2 * QB)
-        self.TS = take(1) if QB == 2 else None   # sum of the tile row sums of the two query blocks
-        self.NEGINF = take(1)
-        self.DT = take(2 * self.NLD)      # address temporaries of the ragged-tile loads
+        self.take_temporaries(take)
         self.AT = take(4) if self.AG else None   # temporaries of the accumulator rescale
         self.NV, self.NA = v[0], a[0]
         assert self.NV <= 256 and self.NA <= 256, (self.NV, self.NA)
@@ -202,6 +204,17 @@ class Gen(Emitter):
         self.s_nw = self.s_last + 1       # input: tiles this wave has rows for (causal: fewer than the workgroup's)
         assert self.NLD <= 4      # the immediate offset of a load ends at 4095
         assert self.s_last < 100
+
+    def take_temporaries(self, take):
+        QB = self.QB
+        self.THR = take(QB)
+        self.T = take(QB)
+        self.TMP2 = take(QB)
+        self.DD = take(QB)
+        self.MX = take(2 * QB)
+        self.TS = take(1) if QB == 2 else None   # sum of the tile row sums of the two query blocks
+        self.NEGINF = take(1)
+        self.DT = take(2 * self.NLD)      # address temporaries of the ragged-tile loads
 
     # ------------------------------------------------------------------ helpers
     def acc(self, base, n):
@@ -595,6 +608,8 @@ class Gen(Emitter):
             self.e("s_cmp_lt_i32 s%d, s%d" % (self.s_j, self.s_jmask))
             self.e("s_cbranch_scc1 %s" % L("NOMASK%s_" % tag))
             # mask pre-pass: keys past the causal diagonal / past S_kv become -inf
+            for ins in self.before_mask():
+                self.e(ins)
             self.e("s_lshl_b32 s%d, s%d, %d" % (self.s_t2, self.s_j, {32: 5, 64: 6}[self.BN]))
             self.e("v_mov_b32 v%d, 0xff800000" % self.NEGINF)
             for qb in range(QB):
@@ -613,7 +628,7 @@ class Gen(Emitter):
             self.e("s_cmp_ge_i32 s%d, s%d" % (self.s_j, self.s_tload))     # SCC: do this iteration's loads need clamping?
             self.e("s_branch %s" % L("TOP%s_" % tag))
         if kind != "first":
-            self.slow_pass(b, tag)
+            self.slow_pass(tag, S_cur, P_new)
         if kind == "last":
             self.e("%s:" % L("OWED%d_" % b))
             if "nodma" not in self.exp:
@@ -636,12 +651,15 @@ class Gen(Emitter):
             self.dma_slow("v", (b + 2) % 4, 2)
         self.e("s_branch %s" % L("VRET%s_" % tag))
 
-    def slow_pass(self, b, tag):
+    def before_mask(self):
+        """What an iteration's scores wait for before the mask (they are complete half an iteration before its top)."""
+        return []
+
+    def slow_pass(self, tag, S_cur, P_new):
         """A tile row sum failed the test: exact row maxima of the (intact) scores, move the references there (alpha =
         exp2((m_ref - m_new) c); 0 when m_ref was still -inf), redo the tile's P, and scale the accumulators (every MFMA
         that uses the old reference has been issued; wait for the last to retire)."""
         L, QB = self.lab, self.QB
-        S_cur, S_nxt, P_prev, P_new = self.bufs(b)
         self.e("%s:" % L("SLOW%s_" % tag))
         for ins in self.max_ops(S_cur) + self.pairmax_ops():
             self.e(ins)
@@ -661,6 +679,7 @@ class Gen(Emitter):
             self.e(ins)
         self.e("s_nop 7")
         self.e("s_branch %s" % L("SLOWRET%s_" % tag))
+
     def drain(self, b):
         """Loop exit at the top of iteration b (b = 1: a launch with a single tile, whose only iteration was
         the first one): O += P(0) V(0); the operands of the first PFD groups were prefetched by that iteration."""
@@ -675,6 +694,10 @@ class Gen(Emitter):
                     prefetched=lead, wait_every=self.W)
         self.e("s_branch %s" % L("STANDBY_"))
 
+    def test_done(self):
+        """Sets SCC where a wave that stands by has met every barrier of the workgroup's walk."""
+        return "s_cmp_ge_i32 s%d, s%d" % (self.s_j, self.s_ntiles)
+
     def standby(self):
         """A wave that has no rows for the workgroup's remaining tiles (causal: its rows end before the
         diagonal tile's keys do) keeps step with the others without computing: one barrier per remaining
@@ -686,7 +709,7 @@ class Gen(Emitter):
         e("%s:" % L("AFTERLAST_"))
         e("s_add_i32 s%d, s%d, 1" % (self.s_j, self.s_j))
         e("%s:" % L("STANDBY_"))
-        e("s_cmp_ge_i32 s%d, s%d" % (self.s_j, self.s_ntiles))
+        e(self.test_done())
         e("s_cbranch_scc1 %s" % L("DONE_"))
         e("s_waitcnt vmcnt(%d)" % (2 * self.NLD))
         e("s_barrier")
@@ -765,6 +788,10 @@ class Gen(Emitter):
         e("s_nop 15")
         e("s_nop 7")
 
+    def more_inputs(self):
+        """(register, C++ name) of a derived generator's operands."""
+        return []
+
     # ----------------------------------------------------------- C++ wrapper
     def emit_inc(self):
         self.generate()
@@ -788,12 +815,14 @@ class Gen(Emitter):
         outs.append('"={%s}"(l_run_v)' % self.vr(self.L, QB))
         for i in range(4 * QB * KS // 16):
             ins.append('"{%s}"(q_pack[%d])' % (self.acc(self.Q + 16 * i, 16), i))
-        ins.append('"{%s}"(koff_v)' % self.vr(self.KOFF, KS))
-        ins.append('"{%s}"(voff_v)' % self.vr(self.VOFF, 2 * DB))
+        # (paired: in and out, so that the compiler keeps these across the loop where they are and nowhere else)
+        for name, r, n in (("koff_v", self.KOFF, KS), ("voff_v", self.VOFF, 2 * DB)):
+            (outs if self.paired else ins).append('"%s{%s}"(%s)' % ("+" if self.paired else "", self.vr(r, n), name))
         ins.append('"{%s}"(dma_voff_v)' % self.vr(self.DVOFF, self.NLD))
         ins.append('"{%s}"(dma_row_v)' % self.vr(self.DROW, self.NLD))
         ins.append('"{%s}"(dma_choff_v)' % self.vr(self.DCH, self.NLD))
         ins.append('"{%s}"(thr_base_v)' % self.vr(self.THRB, QB))
+        ins += ['"{v%d}"(%s)' % x for x in self.more_inputs()]
         ins.append('"{%s}"(k_head)' % self.sr(self.s_kbase, 2))
         ins.append('"{%s}"(v_head)' % self.sr(self.s_vbase, 2))
         ins.append('"{s%d}"(c_log2e)' % self.s_c)
@@ -814,6 +843,7 @@ class Gen(Emitter):
         for base, n in ((self.MREF, QB), (self.L, QB), (self.THRB, QB), (self.KOFF, KS), (self.VOFF, 2 * DB),
                         (self.DVOFF, self.NLD), (self.DROW, self.NLD), (self.DCH, self.NLD)):
             pinned.update(range(base, base + n))
+        pinned.update(r for r, _ in self.more_inputs())
         clob = ['"memory"', '"vcc"', '"scc"']
         clob += ['"v%d"' % i for i in range(self.NV) if i not in pinned]
         clob += ['"s%d"' % i for i in range(self.s_j, self.s_last + 1)]
@@ -823,6 +853,191 @@ class Gen(Emitter):
         out.append("    : " + ", ".join(ins))
         out.append("    : " + ", ".join(clob) + ");")
         return "\n".join(out) + "\n"
+
+
+class PairedGen(Gen):
+    """32-row waves that move their references as one 64-row wave would, bit for bit.
+
+    A 64-row wave (QB = 2) leaves the fast path when, in any lane, the row sums of its two query blocks together reach the
+    bound, and then moves the references of all its rows.  Here two waves on different SIMDs hold one block each: half the
+    products and half the softmax per wave and tile, so that a walk that is bound by what one wave can issue is shorter.
+    For the same results both need the sum over the two blocks: every wave writes its tile row sums to LDS, and reads
+    the other's after the barrier at the top of the next iteration.  The test of tile j-1 (and the pass it may take) then
+    lies a few slots into iteration j.  So that the matrix pipe has work until the answer is there, the second half of
+    P V trails by one more iteration: iteration j issues
+
+        second half of P(j-2) V(j-2), [test of tile j-1], first half of P(j-1) V(j-1), K(j+1) Q^T, beside softmax(S(j))
+
+    with the trailing half's V fragments read before the barrier that frees their ring stage.  Every accumulator still
+    takes its products in the order of the tiles and of their keys.  A wave's last tile has its test behind one more
+    barrier: a workgroup of n tiles meets n + 1 of them.  (Causal: the upper wave of a pair has one tile less, whose keys
+    are all masked for its rows: its share of that tile's sums is 0.)"""
+    configs = PAIRED
+    paired = True
+
+    def take_temporaries(self, take):
+        assert (self.QB, self.NACC, self.LS, self.AG, self.NLD) == (1, 1, 0, False, 2) and self.PFD >= self.NPVG // 2
+        # those of the mask and of the exact maximum share registers with the exponents, which start after them
+        self.MX, self.T, self.TMP2, self.THR, self.NEGINF = self.TP, self.TP + 2, self.TP + 3, self.TP + 4, self.TP + 5
+        self.DD = take(1)
+        self.DT = take(4)
+        self.XOWN = take(1)      # LDS address of this lane's tile row sums, [parity of the tile][wave][lane], and of
+        self.XOTH = take(1)      # those of the other wave
+        self.PS = take(1)        # the other wave's sums
+        self.TS = take(1)
+
+    def more_inputs(self):
+        return [(self.XOWN, "xch_own"), (self.XOTH, "xch_other")]
+
+    def slot_of(self, b):
+        return " offset:%d" % (self.NW * 256) if b % 2 else ""
+
+    def groups(self):
+        pv = [("pv", kc, db) for kc in range(2 * self.SB) for db in range(self.DB)]
+        h = self.NPVG // 2
+        qk = [("qk", ks, sb) for ks in range(self.KS) for sb in range(self.SB)]
+        # (in turn: K Q^T alone is one chain of dependent products; 32 heads of 2048 rows, causal, 40.2 -> 40.0 us)
+        return [("trail",) + g[1:] for g in pv[h:]] + [g for both in zip(pv[:h], qk) for g in both] + qk[h:]
+
+    def vote(self, tag, in_flight):
+        """The test of a tile by both waves of the pair; in_flight: LDS reads issued after that of the other's sums."""
+        return ["s_waitcnt lgkmcnt(%d)" % in_flight,
+                "v_add_f32 v%d, v%d, v%d" % (self.TS, self.TLA, self.PS),
+                "v_cmp_ngt_f32 vcc, s%d, v%d" % (self.s_tau, self.TS),
+                "s_cbranch_vccnz %s" % self.lab("SLOW%s_" % tag),
+                "%s:" % self.lab("SLOWRET%s_" % tag),
+                "v_add_f32 v%d, v%d, v%d" % (self.L, self.L, self.TLA)]
+
+    def loads_of(self, b):
+        """frag_loads of an iteration in ring phase b."""
+        vst, kst = (b + 3) % 4, (b + 1) % 4
+        return lambda g, buf: (self.frag_loads(("pv",) + g[1:], buf, 0, (b + 2) % 4) if g[0] == "trail"
+                               else self.frag_loads(g, buf, kst, vst))
+
+    def body(self, b, kind="loop"):
+        tag = {"loop": "%d" % b, "first": "F", "last": "L%d" % b}[kind]
+        S_cur, S_nxt, P_prev, P_new = self.bufs(b)
+        all_groups = self.groups()
+        half = self.NPVG // 2
+        trail, pva, qk = ([g for g in all_groups if g[0] == k] for k in ("trail", "pv", "qk"))
+        pvb = [("pv",) + g[1:] for g in trail]
+        groups = {"loop": all_groups, "first": qk, "last": trail + pva + pvb}[kind]
+        tail = [("tail",) + g[1:] for g in pva + pvb] if kind == "last" else []
+        n_soft = len(groups)
+        L = self.lab
+        if kind != "last":
+            self.e("%s:" % L({"loop": "BODY%d_" % b, "first": "FIRST_"}[kind]))
+            self.e("s_cmp_ge_i32 s%d, s%d" % (self.s_j, self.s_special))
+            self.e("s_cbranch_scc1 %s" % L("SPECIAL%s_" % tag))
+        self.e("%s:" % L("TOP%s_" % tag))
+        # (lgkmcnt: this wave's row sums are in LDS, and its reads of the V stage that is free behind the barrier are done)
+        self.e("s_waitcnt vmcnt(%d) lgkmcnt(0)" % (0 if kind == "last" else 2 * self.NLD))
+        self.e("s_barrier")
+        if kind == "last":
+            self.e("s_cmp_lt_i32 s%d, s%d" % (self.s_j, self.s_wgnm1))
+            self.e("s_cbranch_scc1 %s" % L("OWED%d_" % b))
+            self.e("%s:" % L("OWEDRET%d_" % b))
+        self.outstanding = []
+        if kind != "first":
+            self.lds_issue(-2, ["ds_read_b32 v%d, v%d%s" % (self.PS, self.XOTH, self.slot_of(b + 1))])
+        extra = {}
+        if kind != "last":
+            extra[0] = ["s_cbranch_scc1 %s" % L("KSLOW%s_" % tag)] + sum(self.dma_fast("k", b), []) + ["%s:" % L("KRET%s_" % tag)]
+            extra[1] = ["s_cbranch_scc1 %s" % L("VSLOW%s_" % tag)] + sum(self.dma_fast("v", (b + 2) % 4), []) + ["%s:" % L("VRET%s_" % tag)]
+            extra[2] = [
+                "s_add_u32 s%d, s%d, %d" % (self.s_kptr, self.s_kptr, self.TB),
+                "s_addc_u32 s%d, s%d, 0" % (self.s_kptr + 1, self.s_kptr + 1),
+                "s_add_u32 s%d, s%d, %d" % (self.s_vptr, self.s_vptr, self.TB),
+                "s_addc_u32 s%d, s%d, 0" % (self.s_vptr + 1, self.s_vptr + 1),
+                "s_add_i32 s%d, s%d, 1" % (self.s_j, self.s_j)]
+        # ---- VALU program: behind the test of the tile before
+        b_ops = self.first_ops(S_cur, P_new) if kind == "first" else self.pair_ops(S_cur, P_new)
+        lead = 0 if kind == "first" else half
+        fixed = {}
+        for slot in range(lead, n_soft):
+            cost = 1.0 + (1.0 if slot % self.W == 0 else 0.0)
+            nxt_g = (groups + tail + all_groups)[slot + self.PFD]
+            cost += 1.0 if nxt_g[0] == "qk" else 2.0
+            cost += len([x for x in extra.get(slot, []) if not x.endswith(":")])
+            fixed[slot - lead] = cost
+        valu = {slot + lead: ops for slot, ops in spread(b_ops, fixed, n_soft - lead).items()}
+        # groups whose fragments the iteration before has read
+        lead_groups = next(i for i in range(self.PFD + 1) if i == self.PFD or groups[i] != all_groups[i]) if kind == "last" else self.PFD
+        if kind != "first":
+            order = groups + tail + all_groups
+            in_flight = sum(2 if g[0] != "qk" else 1 for g in order[lead_groups:self.PFD + half])
+            valu[half - 1] = self.vote("M%d" % b if kind == "last" else tag, in_flight) + valu.get(half - 1, [])
+        else:     # tile 0 has its exact maximum: its test passes, and its sums are in place
+            valu[n_soft - 1] += ["v_mov_b32 v%d, 0" % self.TLA]
+        valu[n_soft - 1] += ["ds_write_b32 v%d, v%d%s" % (self.XOWN, self.TLA, self.slot_of(b))]
+        mfma = lambda g, buf: (self.mfma_texts(("pv",) + g[1:], buf, P_new, 0) if g[0] in ("trail", "tail")
+                               else self.mfma_texts(g, buf, P_prev, S_nxt))
+        if kind == "last":
+            # the tile's own test: behind the barrier of the iteration after it, with that iteration's loads
+            valu[n_soft - 1] += [
+                "s_waitcnt vmcnt(%d) lgkmcnt(0)" % (2 * self.NLD),
+                "s_barrier",
+                "ds_read_b32 v%d, v%d%s" % (self.PS, self.XOTH, self.slot_of(b)),
+                "v_mov_b32 v%d, 0" % self.TLB,
+                "ds_write_b32 v%d, v%d%s" % (self.XOWN, self.TLB, self.slot_of(b + 1)),
+                "s_add_i32 s%d, s%d, 1" % (self.s_j, self.s_j),
+                "s_cmp_lt_i32 s%d, s%d" % (self.s_j, self.s_wgnm1),
+                "s_cbranch_scc1 %s" % L("NEXTOWED%d_" % b),
+                "%s:" % L("NEXTOWEDRET%d_" % b)] + self.vote(tag, 0)
+            loads = self.loads_of(b)
+            self.stream(groups + tail, mfma,
+                        lambda g, buf: self.frag_loads(("pv",) + g[1:], buf, 0, b) if g[0] == "tail" else loads(g, buf),
+                        self.NF, self.PFD, valu, extra, None, prefetched=lead_groups, wait_every=self.W)
+            self.e("s_branch %s" % L("AFTERLAST_"))
+            return
+        nxt = self.loads_of((b + 1) % 4)
+        if kind == "first":   # nothing trails tile 0: zeros for the products of the next iteration's first slots
+            self.stream(groups, mfma, self.loads_of(b), self.NF, self.PFD, valu, extra,
+                        lambda i, buf: [] if i < half else nxt(all_groups[i], buf), prefetched=0, wait_every=self.W)
+            for r in [P_prev + r for r in range(8 * self.SB)] + [self.FR + r for r in range(4 * half)]:
+                self.e("v_mov_b32 v%d, 0" % r)
+            self.e("s_branch %s" % L("BODY1_"))
+            return
+        self.stream(groups, mfma, self.loads_of(b), self.NF, self.PFD, valu, extra,
+                    lambda i, buf: nxt(all_groups[i], buf), wait_every=self.W)
+        if b == 3:
+            self.e("s_branch %s" % L("BODY0_"))
+
+    def before_mask(self):
+        return ["s_nop 11"]      # K Q^T ends with the iteration
+
+    def slow_pass(self, tag, S_cur, P_new):
+        if tag.startswith("L"):      # a last tile's own test
+            return Gen.slow_pass(self, tag, S_cur, P_new)
+        # the tile before that of ring phase b: its scores are intact until K(j+1) Q^T
+        b = int(tag[-1])
+        S_cur, S_nxt, P_prev, P_new = self.bufs(b)
+        Gen.slow_pass(self, tag, S_nxt, P_prev)
+
+    def out_of_line(self, b, kind="loop"):
+        Gen.out_of_line(self, b, kind)
+        if kind == "last":
+            self.slow_pass("M%d" % b, None, None)
+            self.e("%s:" % self.lab("NEXTOWED%d_" % b))
+            self.dma_slow("k", (b + 1) % 4, 4)
+            self.dma_slow("v", (b + 3) % 4, 2)
+            self.e("s_branch %s" % self.lab("NEXTOWEDRET%d_" % b))
+
+    def drain(self, b):
+        """A wave with one tile: P(0) V(0), with the other wave's test of tile 1 answered."""
+        S_cur, S_nxt, P_prev, P_new = self.bufs(b)
+        self.e("%s:" % self.lab("EXIT%d_" % b))
+        self.e("s_waitcnt lgkmcnt(0)")
+        self.e("ds_write_b32 v%d, v%d%s" % (self.XOWN, self.TLA, self.slot_of(b)))
+        self.outstanding = []
+        pv = [("pv", kc, db) for kc in range(2 * self.SB) for db in range(self.DB)]
+        self.stream(pv, lambda g, buf: self.mfma_texts(g, buf, P_prev, 0),
+                    lambda g, buf: self.frag_loads(g, buf, 0, (b + 3) % 4), self.NF, self.PFD, {}, {}, None,
+                    prefetched=0, wait_every=self.W)
+        self.e("s_branch %s" % self.lab("STANDBY_"))
+
+    def test_done(self):
+        return "s_cmp_lt_i32 s%d, s%d" % (self.s_ntiles, self.s_j)
 
 
 def main(argv):
@@ -843,7 +1058,7 @@ def main(argv):
             kw["drop"] = tuple(filter(None, args[-1].split(",")))
         args = args[:-2]
     dtype = args[2] if len(args) > 2 else "bf16"
-    text = Gen(args[0], dtype=dtype, **kw).emit_inc()
+    text = (PairedGen if args[0] in PAIRED else Gen)(args[0], dtype=dtype, **kw).emit_inc()
     with open(args[1], "w") as f:
         f.write(text)
 

@@ -9,7 +9,7 @@ PATH = os.path.join(_ROOT, "paper_2512_18134_amd", "libmi355attn_debug.so")
 
 FWD_AS_DISPATCHED, FWD_PROGRAM_ORDER, FWD_D128_ONE_WAVE_PER_SIMD, FWD_D64_8_WAVES, FWD_D64_4_WAVES = range(5)
 FWD_D128_TWO_WAVES_PER_SIMD = 5
-FWD_KEY_GROUPS, FWD_D128_2_WAVES = 6, 7
+FWD_KEY_GROUPS, FWD_D128_2_WAVES, FWD_D128_PAIRED = 6, 7, 8
 ATTN_ERR_UNSUPPORTED = -7
 
 _lib = None
