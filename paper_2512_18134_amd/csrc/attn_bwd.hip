@@ -60,7 +60,7 @@ bool sweeps_apart(const BwdParams &p, int causal, int slots)
 template <int D, bool F16>
 int launch_asm(const BwdParams &p, int causal, hipStream_t stream)
 {
-    constexpr int LDS = 2 * 6 * 32 * D * 2 + 6 * 256;
+    constexpr int LDS = attn::BwdLds<D>::BYTES;
     auto kern = causal ? attn::attn_bwd_asm_kernel<D, true, F16> : attn::attn_bwd_asm_kernel<D, false, F16>;
     if (!attn::allow_lds(reinterpret_cast<const void *>(kern), LDS))
         return ATTN_ERR_LAUNCH;

@@ -54,6 +54,14 @@ struct BwdQueue {
     }
 };
 
+// LDS of a workgroup: the two rings, the LSE' / Delta ring, and what the waves' owner rows need beyond stage 4 of the rings
+// (which no streamed tile occupies before the loop runs)
+template <int D>
+struct BwdLds {
+    static constexpr int NST = 6, TB = 32 * D * 2;
+    static constexpr int RING1 = 0, RING2 = NST * TB, AUX = 2 * NST * TB, OWN = AUX + NST * 256, BYTES = OWN + 6 * TB;
+};
+
 // One sweep's part of the workgroup's walk: takes up entries from pass `pass` on for as long as they are this sweep's.
 // F16: q, k, v, d_o and the gradients are IEEE fp16 instead of bf16 (the element type of the paper's
 // Section 6.3 figures); the pointers in BwdParams are then reinterpreted.
@@ -72,10 +80,13 @@ __device__ __forceinline__ void bwd_sweep(const BwdParams &p, const BwdQueue &qu
     constexpr int TB = BN * ROWB;
     constexpr int NLD = TB / (NW * 1024);
     constexpr int NSET = KEY_OWNER ? 2 : 1;
+    constexpr int NGRP = 2 * NLD + (KEY_OWNER ? 1 : 0);   // direct loads per wave and streamed tile
     constexpr int NBP = 4 * KS / 16;  // owner fragments packed 16 dwords at a time
 
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    constexpr uint32_t RING1 = 0, RING2 = NST * TB, AUX = 2 * NST * TB;
+    typedef BwdLds<D> Lds;
+    static_assert(Lds::NST == NST && Lds::TB == TB, "one layout");
+    constexpr uint32_t RING1 = Lds::RING1, RING2 = Lds::RING2, AUX = Lds::AUX;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(ATTN_LDS_PTR(unsigned char))smem;
 
     // (the lane number is asked from the hardware again in either sweep, at D = 64 in the epilogue too: no address made
@@ -118,6 +129,23 @@ __device__ __forceinline__ void bwd_sweep(const BwdParams &p, const BwdQueue &qu
             const int r = min(t * BN + lq, p.S_q - 1);
             dma4(lds_aux + stage * 256, aux_head, (uint32_t)r * 4 + aux_sel);
         }
+    };
+
+    // This wave's 32 owner rows of both tensors, laid out like a streamed tile.  Whole rows by direct loads: straight into MFMA
+    // operand registers they would be 32-byte pieces of 32 rows per load, four times the address unit's work
+    const uint32_t own_1 = lds0 + (wave == 0 ? RING1 + 4 * TB : (uint32_t)Lds::OWN + (wave - 1) * TB);
+    const uint32_t own_2 = lds0 + (wave == 0 ? RING2 + 4 * TB : (uint32_t)Lds::OWN + (wave + 2) * TB);
+    auto issue_own = [&](const elem_t *x1, const elem_t *x2, const float *aux_head, int row0, int last) {
+        const int ln = lane_id();
+#pragma unroll
+        for (int i = 0; i < TB / 1024; ++i) {
+            const int r = (1024 / ROWB) * i + ln / CPR;
+            const uint32_t voff = (uint32_t)min(row0 + r, last) * ROWB + (uint32_t)(((ln % CPR) ^ swz<D>(r)) * 16);
+            dma16(own_1 + i * 1024, x1, voff);
+            dma16(own_2 + i * 1024, x2, voff);
+        }
+        if (!KEY_OWNER)   // LSE' and Delta of the rows, where key owners keep those of the streamed tiles
+            dma4(lds_aux + wave * 256, aux_head, (uint32_t)min(row0 + (ln & 31), last) * 4 + (ln >> 5 ? (uint32_t)(p.n_rows * 4) : 0u));
     };
 
     // ---- operand addressing inside a tile
@@ -167,8 +195,8 @@ __device__ __forceinline__ void bwd_sweep(const BwdParams &p, const BwdQueue &qu
         const int S_str = KEY_OWNER ? p.S_q : p.S_kv;
         const int o0 = ot * BO;
         const int o0w = o0 + wave * 32;
-        const int own = o0w + lq;
-        const int own_c = min(own, S_own - 1);
+        const int p_lane = lane_id();   // (no lane number is kept in registers across a loop)
+        const int own = o0w + (p_lane & 31);
 
         const size_t q_head = (size_t)bh * p.S_q * D, k_head = (size_t)bh * p.S_kv * D;
         auto el = [](const bf16_t *ptr) { return reinterpret_cast<const elem_t *>(ptr); };
@@ -200,21 +228,35 @@ __device__ __forceinline__ void bwd_sweep(const BwdParams &p, const BwdQueue &qu
         if (!KEY_OWNER && CAUSAL)
             j_hi = min(j_hi, o0w / BN);
 
-        // ---- prologue: tiles 0..3, and tile 0 once more as a stand-in for "tile -1" (multiplied by zeros)
+        // ---- prologue: the owner rows and tile 0, which S(0) and dP(0) wait for, then tiles 1..3; zeros for "tile -1",
+        // which the first iteration's contraction reads (and multiplies by zeros).  (Owner rows straight into registers, a
+        // copy of tile 0 for the zeros and a wait for everything before S(0): 16 heads of 515 rows, D = 64, causal 16.6 -> 15.5
+        // us, 200 of 300 rows 32.4 -> 30.0, 16 of 128 rows, D = 128, 13.1 -> 12.4, 128 of 4096 rows 3131 -> 3113; the same bits.)
+        issue_own(x1, x2, aux_head, o0w, S_own - 1);
     #pragma unroll
         for (int t = 0; t < 4; ++t)
             issue_tile(t1_head, t2_head, aux_head, S_str, t, t_begin + t);
-        issue_tile(t1_head, t2_head, aux_head, S_str, NST - 1, t_begin);
-
-        ex8 b1[KS], b2[KS];
-        {
-            const elem_t *s1 = x1 + (size_t)own_c * D + 8 * g;
-            const elem_t *s2 = x2 + (size_t)own_c * D + 8 * g;
     #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                b1[ks] = *reinterpret_cast<const ex8 *>(s1 + 16 * ks);
-                b2[ks] = *reinterpret_cast<const ex8 *>(s2 + 16 * ks);
-            }
+        for (int i = 0; i < NLD; ++i) {
+            const u32x4 zero = {0u, 0u, 0u, 0u};
+            const uint32_t at = (NST - 1) * TB + (i * NW + wave) * 1024 + p_lane * 16;
+            *(ATTN_LDS_PTR(u32x4))(uintptr_t)(lds0 + RING1 + at) = zero;
+            if (KEY_OWNER)
+                *(ATTN_LDS_PTR(u32x4))(uintptr_t)(lds0 + RING2 + at) = zero;
+        }
+        wait_vmcnt<3 * NGRP>();
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();   // every wave's part of tile 0 and of the zeros is in LDS
+        asm volatile("" ::: "memory");
+
+        // (sums that the compiler cannot take out of the tile loop, where they would cost registers)
+        uint32_t from_1 = own_1 - (lds0 + RING1), from_2 = own_2 - (lds0 + RING1);
+        asm volatile("" : "+s"(from_1), "+s"(from_2));
+        ex8 b1[KS], b2[KS];
+    #pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            b1[ks] = *(ATTN_LDS_PTR(const ex8))(uintptr_t)(roff[ks] + from_1);
+            b2[ks] = *(ATTN_LDS_PTR(const ex8))(uintptr_t)(roff[ks] + from_2);
         }
         // the second operand is negated and dP starts from Delta: the MFMAs deliver t = Delta - dP (gen_attn_bwd_loop.py)
     #pragma unroll
@@ -226,9 +268,6 @@ __device__ __forceinline__ void bwd_sweep(const BwdParams &p, const BwdQueue &qu
     #pragma unroll
             for (int r = 0; r < 16; ++r)
                 acc[i][r] = 0.f;
-
-        wait_vmcnt<0>();
-        __syncthreads();
 
         // LSE' and Delta of tile 0 (key-owner: 16 rows per lane; query-owner: this lane's query)
         typename std::conditional<KEY_OWNER, f32x16, float>::type aux_l;
@@ -245,8 +284,9 @@ __device__ __forceinline__ void bwd_sweep(const BwdParams &p, const BwdQueue &qu
                 }
             }
         } else {
-            aux_l = aux_head[own_c];
-            const float delta = aux_head[p.n_rows + own_c];
+            const uint32_t at = lds_aux + wave * 256 + (p_lane & 31) * 4;
+            aux_l = *(ATTN_LDS_PTR(const float))(uintptr_t)at;
+            const float delta = *(ATTN_LDS_PTR(const float))(uintptr_t)(at + 128);
     #pragma unroll
             for (int r = 0; r < 16; ++r)
                 aux_d[r] = delta;
@@ -277,9 +317,9 @@ __device__ __forceinline__ void bwd_sweep(const BwdParams &p, const BwdQueue &qu
             b2_pack[i] = __builtin_bit_cast(u32x16, f2);
         }
         // mask thresholds of this lane, minus the lane-group part of the accumulator row and the first tile
-        const uint32_t thr_lo_base = (uint32_t)(own - 4 * g - BN * t_begin);
+        const uint32_t thr_lo_base = (uint32_t)(own - 4 * (p_lane >> 5) - BN * t_begin);
         const uint32_t thr_hi_base =
-            (uint32_t)((KEY_OWNER ? str_m1 : (CAUSAL ? min(own, str_m1) : str_m1)) - 4 * g - BN * t_begin);
+            (uint32_t)((KEY_OWNER ? str_m1 : (CAUSAL ? min(own, str_m1) : str_m1)) - 4 * (p_lane >> 5) - BN * t_begin);
         const float c_log2e = p.c;
 
         if constexpr (D == 64 && KEY_OWNER && !F16) {
