@@ -177,6 +177,19 @@ __device__ __forceinline__ void bwd_sweep(const BwdParams &p, const BwdQueue &qu
     const uint32_t aux_off = lds_aux + 16 * g;
 
     const int n_t = KEY_OWNER ? p.n_t : p.n_tq, total = KEY_OWNER ? p.total_wg : p.total_q;
+    auto el = [](const bf16_t *ptr) { return reinterpret_cast<const elem_t *>(ptr); };
+    auto locate = [&](int entry, int &bh, int &ot) {
+        // a head's sweeps stream Q, dO, K and V between them
+        wg_to_tile_n<CAUSAL>(KEY_OWNER ? entry : entry - queue.q_first, total, n_t, 4ll * (p.S_q + p.S_kv) * D, bh, ot);
+        if (CAUSAL && KEY_OWNER)
+            ot = n_t - 1 - ot;  // early key tiles stream the most queries: heaviest first
+    };
+    auto issue_own_of = [&](int bh, int ot) {
+        const size_t q_head = (size_t)bh * p.S_q * D, k_head = (size_t)bh * p.S_kv * D;
+        issue_own(KEY_OWNER ? el(p.k) + k_head : el(p.q) + q_head, KEY_OWNER ? el(p.v) + k_head : el(p.d_o) + q_head,
+                  p.lse2 + (size_t)bh * p.S_q, ot * BO + wave * 32, (KEY_OWNER ? p.S_kv : p.S_q) - 1);
+    };
+    bool own_on_its_way = false;
 #pragma clang loop unroll(disable)
     for (;; ++pass) {
         const int entry = queue.entry(blockIdx.x, (int)gridDim.x, p.cus_per_xcd, pass);
@@ -187,10 +200,7 @@ __device__ __forceinline__ void bwd_sweep(const BwdParams &p, const BwdQueue &qu
         if (pass > 0)
             __syncthreads();  // every wave has read the previous tile's staged gradients back: the rings are free
         int bh, ot;
-        // a head's sweeps stream Q, dO, K and V between them
-        wg_to_tile_n<CAUSAL>(KEY_OWNER ? entry : entry - queue.q_first, total, n_t, 4ll * (p.S_q + p.S_kv) * D, bh, ot);
-        if (CAUSAL && KEY_OWNER)
-            ot = n_t - 1 - ot;  // early key tiles stream the most queries: heaviest first
+        locate(entry, bh, ot);
         const int S_own = KEY_OWNER ? p.S_kv : p.S_q;
         const int S_str = KEY_OWNER ? p.S_q : p.S_kv;
         const int o0 = ot * BO;
@@ -199,9 +209,6 @@ __device__ __forceinline__ void bwd_sweep(const BwdParams &p, const BwdQueue &qu
         const int own = o0w + (p_lane & 31);
 
         const size_t q_head = (size_t)bh * p.S_q * D, k_head = (size_t)bh * p.S_kv * D;
-        auto el = [](const bf16_t *ptr) { return reinterpret_cast<const elem_t *>(ptr); };
-        const elem_t *x1 = KEY_OWNER ? el(p.k) + k_head : el(p.q) + q_head;
-        const elem_t *x2 = KEY_OWNER ? el(p.v) + k_head : el(p.d_o) + q_head;
         const elem_t *t1_head = KEY_OWNER ? el(p.q) + q_head : el(p.k) + k_head;
         const elem_t *t2_head = KEY_OWNER ? el(p.d_o) + q_head : el(p.v) + k_head;
         const float *aux_head = p.lse2 + (size_t)bh * p.S_q;  // LSE' rows of this head; Delta is n_rows floats further
@@ -232,7 +239,8 @@ __device__ __forceinline__ void bwd_sweep(const BwdParams &p, const BwdQueue &qu
         // which the first iteration's contraction reads (and multiplies by zeros).  (Owner rows straight into registers, a
         // copy of tile 0 for the zeros and a wait for everything before S(0): 16 heads of 515 rows, D = 64, causal 16.6 -> 15.5
         // us, 200 of 300 rows 32.4 -> 30.0, 16 of 128 rows, D = 128, 13.1 -> 12.4, 128 of 4096 rows 3131 -> 3113; the same bits.)
-        issue_own(x1, x2, aux_head, o0w, S_own - 1);
+        if (!own_on_its_way)
+            issue_own_of(bh, ot);
     #pragma unroll
         for (int t = 0; t < 4; ++t)
             issue_tile(t1_head, t2_head, aux_head, S_str, t, t_begin + t);
@@ -346,6 +354,17 @@ __device__ __forceinline__ void bwd_sweep(const BwdParams &p, const BwdQueue &qu
         // 32 x ROWB bytes of a ring (dK / dQ in the first, dV in the second) and reads back only what it wrote;
         // rows are XOR-swizzled by 16-byte chunk.
         __syncthreads();  // every wave has left the loop (its loads have landed): the rings are free
+        if constexpr (D == 128) {
+            // the next tile's owner rows travel while this one is written out.  (At D = 64 a second workgroup on the CU
+            // does as much, and there are no registers for it)
+            const int next = queue.entry(blockIdx.x, (int)gridDim.x, p.cus_per_xcd, pass + 1);
+            own_on_its_way = next >= 0 && (KEY_OWNER ? next < queue.n_kv : true);
+            if (own_on_its_way) {
+                int next_bh, next_ot;
+                locate(next, next_bh, next_ot);
+                issue_own_of(next_bh, next_ot);
+            }
+        }
         const int e_lane = D == 64 ? lane_id() : lane;
         const int e_lq = e_lane & 31, e_g = e_lane >> 5;
         auto write_out = [&](const f32x16 *a, auto value, elem_t *out_head, uint32_t ring) {
