@@ -106,9 +106,9 @@ class Gen(Emitter):
         self.DPA = take(16)
         self.SB = take(16)
         self.DPB = take(16)
-        self.PA = take(8)
+        self.PA = take(8) if key_owner else None
         self.DSA = take(8)
-        self.PB = take(8)
+        self.PB = take(8) if key_owner else None
         self.DSB = take(8)
         self.NAUX = 16 if key_owner else 1
         self.AUXL = take(self.NAUX)
@@ -216,9 +216,12 @@ class Gen(Emitter):
         def M(k):
             return ["v_mul_f32 v%d, v%d, v%d" % (DP_cur + 2 * k + i, S_cur + 2 * k + i, DP_cur + 2 * k + i)
                     for i in range(2)]
+        # (only dV takes P itself: 56 instructions per tile in the query-owner sweep.  With the packs that nothing read and the
+        # test for a diagonal that this sweep does not have, 16 heads of 4096 rows, D = 64, 217.2 -> 214.2 us, D = 128, 128
+        # heads 3104 -> 3079)
         def C(k):
-            return ["%s v%d, v%d, v%d" % (self.cvt, P_new + k, S_cur + 2 * k, S_cur + 2 * k + 1),
-                    "%s v%d, v%d, v%d" % (self.cvt, DS_new + k, DP_cur + 2 * k, DP_cur + 2 * k + 1)]
+            p = ["%s v%d, v%d, v%d" % (self.cvt, P_new + k, S_cur + 2 * k, S_cur + 2 * k + 1)] if self.KO else []
+            return p + ["%s v%d, v%d, v%d" % (self.cvt, DS_new + k, DP_cur + 2 * k, DP_cur + 2 * k + 1)]
         ops = []
         for t in range(8 + 2):
             if t < 8:
@@ -305,9 +308,10 @@ class Gen(Emitter):
         self.e("%s:" % L("BODY%d_" % b))
         self.e("s_cmp_ge_i32 s%d, s%d" % (self.s_j, self.s_ntiles))
         self.e("s_cbranch_scc1 %s" % L("EXIT%d_" % b))
-        self.e("s_cmp_lt_i32 s%d, s%d" % (self.s_j, self.s_jlo))
-        self.e("s_cbranch_scc1 %s" % L("MASKLO%d_" % b))
-        self.e("%s:" % L("MASKLORET%d_" % b))
+        if self.KO:
+            self.e("s_cmp_lt_i32 s%d, s%d" % (self.s_j, self.s_jlo))
+            self.e("s_cbranch_scc1 %s" % L("MASKLO%d_" % b))
+            self.e("%s:" % L("MASKLORET%d_" % b))
         self.e("s_cmp_ge_i32 s%d, s%d" % (self.s_j, self.s_jhi))
         self.e("s_cbranch_scc1 %s" % L("MASKHI%d_" % b))
         self.e("%s:" % L("MASKHIRET%d_" % b))
@@ -375,7 +379,7 @@ class Gen(Emitter):
         S_cur = self.bufs(b)[0]
         # ---- mask pre-passes on S(j): invalid elements become -inf, so p = 0 and ds = 0.
         # Element r of a lane is streamed row 32*(t_begin + j) + 8*(r/4) + 4*g + r%4.
-        for kind, base, cmp in (("LO", self.THRLOB, "v_cmp_lt_i32"), ("HI", self.THRHIB, "v_cmp_gt_i32")):
+        for kind, base, cmp in (("LO", self.THRLOB, "v_cmp_lt_i32"), ("HI", self.THRHIB, "v_cmp_gt_i32"))[0 if self.KO else 1:]:
             self.e("%s:" % L("MASK%s%d_" % (kind, b)))
             self.e("s_lshl_b32 s%d, s%d, 5" % (self.s_t2, self.s_j))
             self.e("v_mov_b32 v%d, 0xff800000" % self.NEGINF)
@@ -420,7 +424,8 @@ class Gen(Emitter):
         e("s_add_u32 s%d, s%d, s%d" % (self.s_ptr2, self.s_t2base, self.s_t2))
         e("s_addc_u32 s%d, s%d, 0" % (self.s_ptr2 + 1, self.s_t2base + 1))
         for i in range(8):
-            e("v_mov_b32 v%d, 0" % (self.PA + i))                # P(-1) = dS(-1) = 0
+            if self.KO:
+                e("v_mov_b32 v%d, 0" % (self.PA + i))            # P(-1) = dS(-1) = 0
             e("v_mov_b32 v%d, 0" % (self.DSA + i))
         self.outstanding = []
         g0 = self.groups()
