@@ -80,6 +80,10 @@ __device__ __forceinline__ void bwd_sweep(const BwdParams &p, const BwdQueue &qu
     constexpr int TB = BN * ROWB;
     constexpr int NLD = TB / (NW * 1024);
     constexpr int NSET = KEY_OWNER ? 2 : 1;
+    // Streamed tiles that go out ahead of S(0).  D = 128: two, the next two behind its products: the address unit takes 64
+    // bytes a cycle, 0.25 us for those two (16 heads of 128 rows 12.2 -> 12.0 us, of 512 19.9 -> 19.7, of 1024 37.0 -> 36.7);
+    // D = 64, half as many bytes: all four (two: 200 heads of 300 rows, causal, 30.1 -> 30.6)
+    constexpr int FIRST = D == 128 ? 2 : 4;
     constexpr int NGRP = 2 * NLD + (KEY_OWNER ? 1 : 0);   // direct loads per wave and streamed tile
     constexpr int NBP = 4 * KS / 16;  // owner fragments packed 16 dwords at a time
 
@@ -235,14 +239,14 @@ __device__ __forceinline__ void bwd_sweep(const BwdParams &p, const BwdQueue &qu
         if (!KEY_OWNER && CAUSAL)
             j_hi = min(j_hi, o0w / BN);
 
-        // ---- prologue: the owner rows and tile 0, which S(0) and dP(0) wait for, then tiles 1..3; zeros for "tile -1",
+        // ---- prologue: the owner rows and tile 0, which S(0) and dP(0) wait for, then the other tiles; zeros for "tile -1",
         // which the first iteration's contraction reads (and multiplies by zeros).  (Owner rows straight into registers, a
         // copy of tile 0 for the zeros and a wait for everything before S(0): 16 heads of 515 rows, D = 64, causal 16.6 -> 15.5
         // us, 200 of 300 rows 32.4 -> 30.0, 16 of 128 rows, D = 128, 13.1 -> 12.4, 128 of 4096 rows 3131 -> 3113; the same bits.)
         if (!own_on_its_way)
             issue_own_of(bh, ot);
     #pragma unroll
-        for (int t = 0; t < 4; ++t)
+        for (int t = 0; t < FIRST; ++t)
             issue_tile(t1_head, t2_head, aux_head, S_str, t, t_begin + t);
     #pragma unroll
         for (int i = 0; i < NLD; ++i) {
@@ -252,7 +256,7 @@ __device__ __forceinline__ void bwd_sweep(const BwdParams &p, const BwdQueue &qu
             if (KEY_OWNER)
                 *(ATTN_LDS_PTR(u32x4))(uintptr_t)(lds0 + RING2 + at) = zero;
         }
-        wait_vmcnt<3 * NGRP>();
+        wait_vmcnt<(FIRST - 1) * NGRP>();
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();   // every wave's part of tile 0 and of the zeros is in LDS
         asm volatile("" ::: "memory");
@@ -313,6 +317,9 @@ __device__ __forceinline__ void bwd_sweep(const BwdParams &p, const BwdQueue &qu
             dp_init = E::mfma(a2, b2[ks], dp_init);
         }
 
+    #pragma unroll
+        for (int t = FIRST; t < 4; ++t)
+            issue_tile(t1_head, t2_head, aux_head, S_str, t, t_begin + t);
         typedef uint32_t u32x16 __attribute__((ext_vector_type(16)));
         u32x16 b1_pack[NBP], b2_pack[NBP];
     #pragma unroll
