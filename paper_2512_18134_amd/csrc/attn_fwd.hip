@@ -216,15 +216,20 @@ int choose_d128(int BH, const Params &p, int causal, float *cost = nullptr)
 // speed of both, so that the line is an estimate again, fitted over 1800 launches of 1 to 600 heads.  Not causal: rounds of
 // two tiles per CU, of which the last walks faster where most CUs have one tile or none; heads of a single query tile
 // stay out, whose keys come from memory once per workgroup (310 heads of 112 queries and 960 keys 33.8 / 39.7).  Causal: heavy
-// and light tiles share a CU and it is ahead (18 % on average, 5 % behind at worst) up to 2 1/4 tiles per CU, and up to
-// 1024 keys at any number of tiles (7 % on average, 4 % behind at worst; 213 heads of 623 rows 42.6 / 37.0); beyond that the
-// better of the others has its balance to win or lose (32 heads of 3845 rows 111 / 151).  With this rule 10 of the 2200
-// launches are more than 2 % slower than without it (5 % at worst), and the mean is 16 % faster.
+// and light tiles share a CU and it is ahead (by 14 % on average over 592 launches) up to 2 1/4 tiles per CU.  Up to 1024
+// keys what decides is how many 32-key steps a workgroup walks in all (`per_slot`), next to the start of every tile that the
+// second workgroup on a CU hides: over 2375 such launches of up to 16340 tiles it is 11 % ahead up to 20 steps, 7 % at 20 to
+// 48, 1.5 % at 60 to 80, level at 80 to 110, and 2 to 5 % behind beyond (64 heads of 9386 queries and 989 keys 265 / 288,
+// 552 of 1792 and 748 334 / 366).  Between 3 and 4 tiles per CU the 256-row tiles come in whole pairs of heavy and light
+// ones, and the line lies at 36 steps (123 heads of 970 rows, 34 steps, 42.6 / 48.2; but 173 of 832, 37 steps in 4.7 tiles
+// per CU, 50 / 45).  Longer walks: the better of the others has its balance to win or lose (32 heads of 3845 rows 107 / 149).
+// Over the 4059 measured causal launches of more than 2 1/4 tiles per CU, 99 are still slower by more than 2 % than without
+// this tiling, by how the queues happen to fall; moving the lines loses more than it wins.
 bool paired_pays(int BH, const Params &p, int causal, int cus, float others)
 {
     const long long nt = (p.S_q + 127) / 128, tiles = BH * nt, slots = 2ll * cus;
     const long long n = ((causal && p.S_q < p.S_kv ? p.S_q : p.S_kv) + 31) / 32;
-    if (4 * tiles <= (causal ? 9 : 4) * cus || (causal && n <= 32))
+    if (4 * tiles <= (causal ? 9 : 4) * cus)
         return true;
     const float whole = (float)(tiles / slots), rest = (float)(tiles % slots) / (float)slots;
     if (!causal) {
@@ -234,8 +239,11 @@ bool paired_pays(int BH, const Params &p, int causal, int cus, float others)
         return whole * (5.5f + 0.84f * n) + last < 0.95f * others;
     }
     const long long k = nt < n / 4 ? nt : n / 4;   // tiles below the last keys
-    const float sum = (float)(2 * k * (k + 1) + (nt - k) * n), r = fmaxf(1.f, whole + 0.5f * (rest + (rest > 0.f ? 1.f : 0.f)));
-    return fmaxf(5.9f + 0.39f * n, 7.0f * r + 0.873f * sum * BH / (float)slots + 0.056f * n) < 1.04f * others;
+    const float per_slot = (float)(2 * k * (k + 1) + (nt - k) * n) * BH / (float)slots;
+    if (n <= 32)
+        return per_slot <= (tiles > 3 * cus && tiles <= 4 * cus ? 36.f : 80.f);
+    const float r = fmaxf(1.f, whole + 0.5f * (rest + (rest > 0.f ? 1.f : 0.f)));
+    return fmaxf(5.9f + 0.39f * n, 7.0f * r + 0.873f * per_slot + 0.056f * n) < 1.04f * others;
 }
 
 int choose_d128_all(int BH, const Params &p, int causal)
