@@ -212,7 +212,10 @@ int choose_d128(int BH, const Params &p, int causal, float *cost = nullptr)
 // us, best tiling of 64-row waves / paired: 16 heads of 128 rows 9.5 / 7.4, of 777 rows, causal, 20.5 / 14.4, of 1024 23.2 /
 // 15.8; 32 of 2048, causal, 48.1 / 38.0; 4 of 6000, causal, 98.8 / 70.4; 1 of 16384, causal, 255 / 171; 16 of 2048 41.7 /
 // 34.6; 24 of 2816 122 / 115; but 6 of 5468 93 / 120, 128 of 2048 223 / 244, 32 of 4096, causal, 117 / 131.
-// Up to one tile per CU it is always ahead (by 10 to 34 % over 650 launches).  A CU's second workgroup then halves the
+// Up to one tile per CU it is always ahead (by 10 to 34 % over 950 launches).  Where the 256-row tiling needs one round and
+// more 128-row tiles than CUs walk all keys (no mask, or more queries than keys), it is behind from some 500 keys on, by 5
+// to 28 %: 87 heads of 344 queries and 2557 keys 47.9 / 59.3, 96 of 320 and 4494 82.5 / 101, causal 6 of 8256 and 2233 50.3 /
+// 58.2, 8 of 6643 and 1856 45.5 / 51.1; with fewer keys up to 5 % either way.  Otherwise a CU's second workgroup halves the
 // speed of both, so that the line is an estimate again, fitted over 1800 launches of 1 to 600 heads.  Not causal: rounds of
 // two tiles per CU, of which the last walks faster where most CUs have one tile or none; heads of a single query tile
 // stay out, whose keys come from memory once per workgroup (310 heads of 112 queries and 960 keys 33.8 / 39.7).  Causal: heavy
@@ -229,6 +232,9 @@ bool paired_pays(int BH, const Params &p, int causal, int cus, float others)
 {
     const long long nt = (p.S_q + 127) / 128, tiles = BH * nt, slots = 2ll * cus;
     const long long n = ((causal && p.S_q < p.S_kv ? p.S_q : p.S_kv) + 31) / 32;
+    const long long k = causal ? (nt < n / 4 ? nt : n / 4) : 0;   // tiles below the last keys
+    if (n > 16 && BH * (nt - k) > cus && (long long)BH * ((p.S_q + 255) / 256) <= cus)
+        return false;
     if (4 * tiles <= (causal ? 9 : 4) * cus)
         return true;
     const float whole = (float)(tiles / slots), rest = (float)(tiles % slots) / (float)slots;
@@ -238,7 +244,6 @@ bool paired_pays(int BH, const Params &p, int causal, int cus, float others)
         const float last = rest > 0.5f ? 7.8f + (0.63f + 0.43f * (rest - 0.5f)) * n : rest > 0.f ? 5.0f + (0.31f + 0.29f * rest) * n : 0.f;
         return whole * (5.5f + 0.84f * n) + last < 0.95f * others;
     }
-    const long long k = nt < n / 4 ? nt : n / 4;   // tiles below the last keys
     const float per_slot = (float)(2 * k * (k + 1) + (nt - k) * n) * BH / (float)slots;
     if (n <= 32)
         return per_slot <= (tiles > 3 * cus && tiles <= 4 * cus ? 36.f : 80.f);

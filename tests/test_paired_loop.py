@@ -145,6 +145,10 @@ MEASURED = [(16, 128, 128, 1, 1), (16, 777, 777, 1, 1), (16, 1024, 1024, 0, 1), 
 MEASURED += [(64, 9386, 989, 1, 0), (372, 2742, 832, 1, 0), (128, 10048, 704, 1, 0), (552, 1792, 748, 1, 0), (64, 8192, 512, 1, 0),
              (410, 1024, 1024, 1, 0), (420, 148, 148, 1, 1), (224, 384, 384, 1, 1), (173, 832, 832, 1, 1),
              (16, 4000, 300, 1, 1)]
+# ... one round of the 256-row tiling against two 128-row tiles on some compute units
+MEASURED += [(87, 344, 2557, 0, 0), (96, 320, 4494, 0, 0), (56, 557, 3839, 0, 0), (3, 13632, 2779, 1, 0), (6, 8256, 2233, 1, 0),
+             (8, 6643, 1856, 1, 0), (32, 2158, 642, 1, 1), (80, 567, 567, 1, 1), (5, 8780, 4736, 1, 1), (4, 9152, 1984, 1, 1),
+             (4, 7514, 1353, 0, 1)]
 
 
 @pytest.mark.parametrize("heads,s_q,s_kv,causal,taken", MEASURED)
