@@ -167,15 +167,9 @@ int launch_d64(const Params &p, int BH, int causal, hipStream_t stream, int tili
 }
 
 // D = 128: the same estimate for the 256-row tiling (one workgroup per CU) and the 128-row one (two).  A CU with a single
-// 128-row workgroup walks a tile's keys at 0.6 us per 32 of them.  Causal: the sum of the tiles' keys, ragged last
+// 128-row workgroup walks a tile's keys at 0.6 us per 32 of them, 0.64 without a mask.  Causal: the sum of the tiles' keys, ragged last
 // tiles included, or the walk of the tile with the most of them in an otherwise idle chip, whichever is longer.
-// With at most one 128-row tile per CU there is only that walk: the 128-row tiling starts 0.7 us sooner (not on a head of
-// at most 128 rows, where only two waves share its loads) and is 1 % slower at it, so that the line lies at some 3700
-// keys.  Measured, 1 to 64 heads, us for 256 / 128 rows: 16 heads of 128 rows 10.2 / 10.4, of 200 12.5 / 11.6, of 512
-// 17.4 / 16.7, of 777 21.5 / 20.8, of 1100 26.3 / 26.2, of 2048 41.6 / 41.1; 8 of 3000 55.7 / 54.9, of 4096 72.8 / 72.9;
-// 4 of 6000 101.3 / 102.6, of 8192 135.9 / 136.7; 1 of 16384 259.9 / 262.2.  Not causal, such tiles walk at 0.64 us: 16
-// heads of 2048 rows 40.6 / 41.6, 8 of 4096 79.9 / 81.1; 500 of 270 rows and 100 keys 32.4 / 30.9.  (Over 848 launches the
-// choice costs more than 1 % against the better tiling at 384 rows only: 600 heads 65.2 / 66.8, 1024 heads 115 / 120.)
+// (Launches with at most one 128-row tile per CU take neither: paired_pays.)
 float d128_cost(int rows, int BH, const Params &p, int causal, int cus)
 {
     const bool two = rows == 128;
@@ -190,8 +184,7 @@ float d128_cost(int rows, int BH, const Params &p, int causal, int cus)
     const long long step = rows / 32, k = nt < n / step ? nt : n / step;   // tiles below the last keys
     const float sum = (float)(step * k * (k + 1) / 2 + (nt - k) * n);
     const float start = two ? 7.0f : 6.0f, r = fmaxf(1.f, whole + 0.5f * (rest + (rest > 0.f ? 1.f : 0.f)));
-    const float walk = two && tiles <= cus && nt > 1 ? 5.3f + 0.606f * n : start + 0.60f * n;
-    return fmaxf(walk, start * r + (two ? 0.83f : 0.72f) * sum * BH / (float)slots);
+    return fmaxf(start + 0.60f * n, start * r + (two ? 0.83f : 0.72f) * sum * BH / (float)slots);
 }
 
 // 64 queries and more: the better one of the two tilings of 64-row waves
@@ -262,9 +255,9 @@ int choose_d128_all(int BH, const Params &p, int causal)
 // D = 128.  tiling: -1 = choose, 0 = 8 waves x 32 rows (two waves per SIMD), 1 = 4 waves x 64 rows (one wave
 // per SIMD, half the LDS operand reads per MFMA), 2 = 2 x 2 waves x 32 rows (64 rows, two key groups), 3 = 2 waves x 64
 // rows (two workgroups per CU; the same results as 1), 4 = 4 waves x 32 rows in pairs (two per CU; the same results as 1).
-// Measured, us for tiling 1 / 3: 300 heads of 100 queries and 2048 keys 112 / 61; 100 heads of 600 rows 39.0 / 26.2; 512
-// heads of 300 rows 59.1 / 50.8; causal: 128 heads of 520 rows 32.2 / 25.0, 100 of 777 rows 37.8 / 31.6, 128 of 1100
-// rows 68.4 / 59.3.  Full rounds of full tiles stay with tiling 1: 32 heads of 4096 rows 207 / 221, causal 116 / 120.
+// Measured, us for tiling 1 / 3 / 4: 96 heads of 640 queries and 2578 keys 112 / 74 / 80; 160 of 320 queries and 7680 keys 280 /
+// 198 / 215; causal: 244 of 1088 rows 124 / 109 / 114, 202 of 1871 245 / 206 / 220.  Full rounds of full tiles stay with
+// tiling 1: 32 heads of 4096 rows 209 / 222 / 233, causal 116 / 121 / 126.
 template <bool F16>
 int launch_d128(const Params &p, int BH, int causal, hipStream_t stream, int tiling = -1)
 {
@@ -575,23 +568,14 @@ extern "C" int attn_fwd_f16_variant(const void *q, const void *k, const void *v,
 #endif
 
 #ifdef ATTN_DEBUG_ENTRY_POINTS
-// Test-only, host only: rows of the query tiles that the dispatcher takes for D = 64 and at least 64 queries, and at D = 128
-// takes of the two tilings of 64-row waves (where attn_fwd_paired says no).
-extern "C" int attn_fwd_tile_rows(int D, int heads, int S_q, int S_kv, int causal)
+// Test-only, host only: the tiling that the dispatcher takes for D = 64 or 128 and at least 64 queries (numbers as in
+// launch_d64 and launch_d128).
+extern "C" int attn_fwd_tiling(int D, int heads, int S_q, int S_kv, int causal)
 {
     Params p;
     p.S_q = S_q;
     p.S_kv = S_kv;
-    return (D == 128 ? choose_d128(heads, p, causal) == 3 : choose_d64(heads, p, causal) == 1) ? 128 : 256;
-}
-
-// Test-only, host only: does a D = 128 launch of at least 64 queries take the tiling whose waves work in pairs?
-extern "C" int attn_fwd_paired(int heads, int S_q, int S_kv, int causal)
-{
-    Params p;
-    p.S_q = S_q;
-    p.S_kv = S_kv;
-    return choose_d128_all(heads, p, causal) == 4;
+    return D == 128 ? choose_d128_all(heads, p, causal) : choose_d64(heads, p, causal);
 }
 
 // Measurement entry point of the debug build: attn_fwd (hand-scheduled kernels) that also records, per

@@ -153,9 +153,9 @@ MEASURED += [(87, 344, 2557, 0, 0), (96, 320, 4494, 0, 0), (56, 557, 3839, 0, 0)
 
 @pytest.mark.parametrize("heads,s_q,s_kv,causal,taken", MEASURED)
 def test_taken_where_it_is_the_faster_tiling(heads, s_q, s_kv, causal, taken):
-    rule = ctypes.CDLL(debug_lib.PATH).attn_fwd_paired
-    rule.restype, rule.argtypes = ctypes.c_int, [ctypes.c_int] * 4
-    assert rule(heads, s_q, s_kv, causal) == taken
+    rule = ctypes.CDLL(debug_lib.PATH).attn_fwd_tiling
+    rule.restype, rule.argtypes = ctypes.c_int, [ctypes.c_int] * 5
+    assert (rule(128, heads, s_q, s_kv, causal) == 4) == bool(taken)
 
 
 # edges of the 32-row waves and their pairs, of the tiles and of the mask; waves and pairs without rows; one tile, several
