@@ -234,7 +234,7 @@ __device__ __forceinline__ void bwd_sweep(const BwdParams &p, const BwdQueue &qu
         const int str_m1 = S_str - 1;
         // tiles j < j_lo touch the causal diagonal from below (key-owner), tiles j >= j_hi touch the ragged
         // end of the streamed tensor or the diagonal from above (query-owner)
-        const int j_lo = (KEY_OWNER && CAUSAL) ? o0w / BN - t_begin + 1 : 0;
+        [[maybe_unused]] const int j_lo = CAUSAL ? o0w / BN - t_begin + 1 : 0;
         int j_hi = t_full - t_begin;
         if (!KEY_OWNER && CAUSAL)
             j_hi = min(j_hi, o0w / BN);
@@ -332,7 +332,8 @@ __device__ __forceinline__ void bwd_sweep(const BwdParams &p, const BwdQueue &qu
             b2_pack[i] = __builtin_bit_cast(u32x16, f2);
         }
         // mask thresholds of this lane, minus the lane-group part of the accumulator row and the first tile
-        const uint32_t thr_lo_base = (uint32_t)(own - 4 * (p_lane >> 5) - BN * t_begin);
+        [[maybe_unused]] const uint32_t thr_lo_base =   // (the key owners' mask from below)
+            (uint32_t)(own - 4 * (p_lane >> 5) - BN * t_begin);
         const uint32_t thr_hi_base =
             (uint32_t)((KEY_OWNER ? str_m1 : (CAUSAL ? min(own, str_m1) : str_m1)) - 4 * (p_lane >> 5) - BN * t_begin);
         const float c_log2e = p.c;

@@ -131,7 +131,7 @@ class Gen(Emitter):
             self.AOFF = take(1)
             self.AUXROW = take(1)
             self.AUXSEL = take(1)
-        self.THRLOB = take(1)
+            self.THRLOB = take(1)
         self.THRHIB = take(1)
         # temporaries of the clamped loads, of the mask pre-passes and of the LSE' / Delta load: never live together.
         # D = 64: the mask limits go through a scalar register, one instruction more per element, for want of a register
@@ -379,7 +379,7 @@ class Gen(Emitter):
         S_cur = self.bufs(b)[0]
         # ---- mask pre-passes on S(j): invalid elements become -inf, so p = 0 and ds = 0.
         # Element r of a lane is streamed row 32*(t_begin + j) + 8*(r/4) + 4*g + r%4.
-        for kind, base, cmp in (("LO", self.THRLOB, "v_cmp_lt_i32"), ("HI", self.THRHIB, "v_cmp_gt_i32"))[0 if self.KO else 1:]:
+        for kind, base, cmp in ((("LO", self.THRLOB, "v_cmp_lt_i32"),) if self.KO else ()) + (("HI", self.THRHIB, "v_cmp_gt_i32"),):
             self.e("%s:" % L("MASK%s%d_" % (kind, b)))
             self.e("s_lshl_b32 s%d, s%d, 5" % (self.s_t2, self.s_j))
             self.e("v_mov_b32 v%d, 0xff800000" % self.NEGINF)
@@ -480,14 +480,14 @@ class Gen(Emitter):
             ins.append('"{v%d}"(aux_off)' % self.AOFF)
             ins.append('"{v%d}"(aux_row)' % self.AUXROW)
             ins.append('"{v%d}"(aux_sel)' % self.AUXSEL)
-        ins.append('"{v%d}"(thr_lo_base)' % self.THRLOB)
+            ins.append('"{v%d}"(thr_lo_base)' % self.THRLOB)
+            ins.append('"{s%d}"(j_lo)' % self.s_jlo)
         ins.append('"{v%d}"(thr_hi_base)' % self.THRHIB)
         ins.append('"{%s}"(t1_head)' % self.sr(self.s_t1base, 2))
         ins.append('"{%s}"(t2_head)' % self.sr(self.s_t2base, 2))
         ins.append('"{%s}"(aux_head)' % self.sr(self.s_auxbase, 2))
         ins.append('"{s%d}"(c_log2e)' % self.s_c)
         ins.append('"{s%d}"(n_tiles)' % self.s_ntiles)
-        ins.append('"{s%d}"(j_lo)' % self.s_jlo)
         ins.append('"{s%d}"(j_hi)' % self.s_jhi)
         ins.append('"{s%d}"(t_full)' % self.s_tfull)
         ins.append('"{s%d}"(str_m1)' % self.s_strm1)
@@ -498,8 +498,8 @@ class Gen(Emitter):
         pinned = set()
         for base, n in ((self.SA, 16), (self.DPA, 16), (self.AUXL, self.NAUX),
                         (self.ROFF1, KS), (self.ROFF2, KS), (self.TOFF1, 2 * DB), (self.TOFF2, 2 * DB),
-                        (self.DVOFF, self.NLD), (self.DROW, self.NLD), (self.THRLOB, 1), (self.THRHIB, 1)) + (
-                        ((self.AOFF, 1), (self.AUXROW, 1), (self.AUXSEL, 1)) if self.KO else ()):
+                        (self.DVOFF, self.NLD), (self.DROW, self.NLD), (self.THRHIB, 1)) + (
+                        ((self.AOFF, 1), (self.AUXROW, 1), (self.AUXSEL, 1), (self.THRLOB, 1)) if self.KO else ()):
             pinned.update(range(base, base + n))
         if not self.KO:
             pinned.update(range(self.AUXD, self.AUXD + 16))
