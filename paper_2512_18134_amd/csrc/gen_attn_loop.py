@@ -128,8 +128,8 @@ class Gen(Emitter):
         self.at = cfg.get("AT")
         # A key group starts in the middle of the keys, where all of a row's scores may be -inf (finite inputs whose
         # products overflow): against a reference of -inf they would give NaN, and the whole row with them.  Against the
-        # lowest finite number they give exactly 0 and pass the row-sum test; a finite score fails it, as in a first tile.
-        # Sums and accumulators are the same bits as with -inf otherwise (0 until the first move of the reference)
+        # lowest finite number they give exactly 0 and pass the row-sum test; a finite score fails it and
+        # moves the reference.  Sums and accumulators are the same bits as with -inf otherwise (0 until the reference moves)
         self.ref0 = 0xff7fffff if cfg.get("LOW") else 0xff800000
         # the two element types differ only in the MFMA and in the pack instruction (both round to nearest even)
         self.mfma = "v_mfma_f32_32x32x16_" + dtype
@@ -760,9 +760,8 @@ class Gen(Emitter):
             e("s_add_u32 s%d, s%d, %d" % (self.s_lk + st, self.s_ldsk, st * self.TB))
             e("s_add_u32 s%d, s%d, %d" % (self.s_lv + st, self.s_ldsv, st * self.TB))
         for qb in range(QB):
-            e("v_mov_b32 v%d, 0x%08x" % (self.MREF + qb, self.ref0))  # no reference yet: the first tile's test fails
-            e("v_mov_b32 v%d, 0x%08x" % (self.MRC + qb, self.ref0))
-            e("v_mov_b32 v%d, 0" % (self.L + qb))
+            # no reference yet: the first tile's maxima become it (first_ops, which also sets MRC and the running sum)
+            e("v_mov_b32 v%d, 0x%08x" % (self.MREF + qb, self.ref0))
         if "nolds" in self.exp:      # timing experiment: the fragments are never read; keep them finite
             for r in range(4 * self.NF):
                 e("v_mov_b32 v%d, 0" % (self.FR + r))
