@@ -270,7 +270,8 @@ def walk(lines, take=(), loop_label=None, loop_visits=2, limit=200000):
     """One execution path through `lines` as a flat instruction list: conditional branches are taken the
     first time their target is in `take` (each entry of `take` is used once) and fall through otherwise;
     unconditional branches are followed, except that the path ends when `loop_label` would be entered for
-    the (loop_visits+1)-th time.  Labels are dropped."""
+    the (loop_visits+1)-th time.  Labels are dropped.  Every entry of `take` has to be met: a detour through
+    a section that the text does not have is an error, not the plain path."""
     where = {}
     for i, l in enumerate(lines):
         l = l.strip()
@@ -305,6 +306,7 @@ def walk(lines, take=(), loop_label=None, loop_visits=2, limit=200000):
             continue
         out.append(l)
         pc += 1
+    assert not take, "never branched to: %s" % take
     return out
 
 

@@ -128,10 +128,10 @@ def test_no_scratch_around_the_hand_scheduled_loops(compiled):
         d, qb, sb, nw = (int(x) for x in m.groups())
         scratch = int(re.search(r"\.private_segment_fixed_size:\s+(\d+)", block).group(1))
         spills = int(re.search(r"\.vgpr_spill_count:\s+(\d+)", block).group(1))
-        if d == 64 and nw == 4:
+        if (d, nw) == (64, 4) or (d, qb, sb, nw) == (128, 1, 1, 4):
             # two of these workgroups share a CU: a wave may use half a SIMD's registers (VGPRs + AGPRs)
             assert int(re.search(r"\.vgpr_count:\s+(\d+)", block).group(1)) <= 256, name
-        if d == 128 and qb == 1:
+        if (d, qb, sb, nw) == (128, 1, 2, 8):
             assert scratch <= 64, (name, scratch)      # the loop that leaves the compiler no VGPR
         else:
             assert scratch == 0 and spills == 0, (name, scratch, spills)
@@ -153,18 +153,21 @@ def test_no_use_of_q_registers_before_the_wait(compiled):
 def test_where_the_loops_start(compiled):
     from test_generated_loops import gen_attn_loop
     # tiling as in the kernel's name: bytes behind a multiple of 32
-    at = {(c["D"], c["QB"], c["SB"], c["NW"]): c["AT"] for c in gen_attn_loop.CONFIGS.values() if "AT" in c}
-    assert len(at) == 6
-    seen = 0
+    at = {(c["D"], c["QB"], c["SB"], c["NW"]): c["AT"] for c in
+          list(gen_attn_loop.CONFIGS.values()) + list(gen_attn_loop.PAIRED.values()) if "AT" in c}
+    assert len(at) == 7
+    seen = set()
     for m in re.finditer(r"^_ZN4attn19attn_fwd_asm_kernelILi(\d+)ELi(\d)ELi(\d)ELi(\d)E\S+:(.*?)^\s*BODY0_\d+:",
                          compiled, re.M | re.S):
-        want = at.get(tuple(int(x) for x in m.groups()[:4]))
+        tiling = tuple(int(x) for x in m.groups()[:4])
+        want = at.get(tiling)
         if want is None:
             continue
         lines = [l.strip() for l in m.group(5).split("\n") if l.strip()]
         n = want // 4
         assert lines[-n - 2].startswith("s_branch BODY1_") and lines[-n - 1:] == [".p2align 5"] + n * ["s_nop 0"], lines[-n - 2:]
-        seen += 1
-    assert seen >= 20                              # causal or not, both element types
+        seen.add((m.group(0).split(":")[0], tiling))
+    assert len(seen) >= 24                         # causal or not, both element types
+    assert {t for _, t in seen} == set(at)
     # ... which is an address: the kernels themselves start at multiples of 256
     assert re.search(r"\.p2align\s+8.*\n(.*\n){0,3}_ZN4attn19attn_fwd_asm_kernelILi128ELi2ELi1ELi4E", compiled)

@@ -77,11 +77,13 @@ def test_forward_out_of_line_sections(name, b):
 def test_forward_first_iteration_and_single_tile(name):
     lines = fwd_lines(name)
     g = gen_attn_loop.Gen(name)
-    for detour in (["SLOWF_"], ["SPECIALF_"] + clamped_loads(g, "F"), ["SPECIALF_", "NOMASKF_"] + clamped_loads(g, "F")):
+    # (the first tile takes its exact maximum: it has no row-sum test and no pass out of line)
+    assert "SLOWF_:" not in (l.strip() for l in lines)
+    for detour in (["SPECIALF_"] + clamped_loads(g, "F"), ["SPECIALF_", "NOMASKF_"] + clamped_loads(g, "F")):
         path = asm_emit.walk(lines, take=detour, loop_label="BODY0_", loop_visits=1)
         assert asm_emit.check_stream(path) == len(path)
     # a launch with one tile: the first iteration (its loads clamped), then straight to P(0) V(0)
-    path = asm_emit.walk(lines, take=["SPECIALF_", "SLOWF_"] + clamped_loads(g, "F") + ["SPECIAL1_", "EXIT1_", "DONE_"])
+    path = asm_emit.walk(lines, take=["SPECIALF_"] + clamped_loads(g, "F") + ["SPECIAL1_", "EXIT1_", "DONE_"])
     assert asm_emit.check_stream(path) == len(path)
     assert sum(1 for l in path if l.startswith("v_mfma")) == (g.NQKG + g.NPVG) * g.QB
     assert path[-1].startswith("s_nop") and any(l.startswith("s_mov_b32 m0, s") for l in path[-4:])
@@ -188,10 +190,18 @@ def test_backward_sweeps(key_owner, d, dtype):
     assert sum(1 for l in path if l.startswith("v_mfma")) == 2 * g.NST * g.NM
     assert asm_emit.check_stream(path) == len(path)
     for b in range(g.NST):
-        for detour in (["MASKLO%d_" % b], ["MASKHI%d_" % b], ["SLOW%d_" % b], ["MASKLO%d_" % b, "MASKHI%d_" % b, "SLOW%d_" % b],
-                       ["EXIT%d_" % b]):
+        masks = ["MASKLO%d_" % b, "MASKHI%d_" % b] if key_owner else ["MASKHI%d_" % b]   # (query owners: one diagonal)
+        for detour in [[m] for m in masks] + [["SLOW%d_" % b], masks + ["SLOW%d_" % b], ["EXIT%d_" % b]]:
             path = asm_emit.walk(lines, take=detour, loop_label="BODY0_", loop_visits=2)
             assert asm_emit.check_stream(path) == len(path)
+
+
+def test_a_detour_that_the_text_does_not_have_is_an_error():
+    lines = fwd_lines("d128")
+    assert asm_emit.walk(lines, take=["SLOW1_"], loop_label="BODY0_", loop_visits=1)
+    for missing in ("SLOWF_", "NOWHERE_"):
+        with pytest.raises(AssertionError):
+            asm_emit.walk(lines, take=[missing], loop_label="BODY0_", loop_visits=1)
 
 
 def test_checker_catches_planted_mistakes():
