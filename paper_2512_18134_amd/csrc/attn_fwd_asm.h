@@ -24,7 +24,7 @@
 //                                  read from LDS feeds two MFMAs (half the LDS reads)
 //   <D=128,    QB=2, SB=1, NW=2>  the same with BM = 128 (two workgroups per CU; the same results)
 //   <D=128,    QB=1, SB=1, NW=4>  BM = 128 in 32-row waves (two workgroups per CU, two waves per SIMD) that move their
-//                                  references in pairs, as the 64-row waves do (the same results): half the work per
+//                                  references in pairs, as the 64-row waves do (the same results: PairedGen): half the work per
 //                                  wave and tile, for launches that a wave's walk bounds
 //   <D=256,    QB=1, SB=1, NW=4>  one wave per SIMD, O and Q in AGPRs
 // K/V tiles in two 4-stage LDS rings (8 * BN * D * 2 bytes).  The kernel starts S(0) as soon as K(0)

@@ -870,7 +870,9 @@ class PairedGen(Gen):
     with the trailing half's V fragments read before the barrier that frees their ring stage.  Every accumulator still
     takes its products in the order of the tiles and of their keys.  A wave's last tile has its test behind one more
     barrier: a workgroup of n tiles meets n + 1 of them.  (Causal: the upper wave of a pair has one tile less, whose keys
-    are all masked for its rows: its share of that tile's sums is 0.)"""
+    are all masked for its rows: its share of that tile's sums is 0.  A 64-row wave's is 0 as well, but for a row whose scores
+    have all been -inf: that one makes the sums NaN there and moves the references of the other rows, which is the only
+    case where the bits differ.)"""
     configs = PAIRED
     paired = True
 

@@ -182,3 +182,48 @@ def test_same_bits_as_64_row_waves(h, s_q, s_kv, causal, dtype):
         o2, lse2 = debug_lib.attn_fwd_variant(q, k, v, causal, 128 ** -0.5, debug_lib.FWD_D128_PAIRED)
         assert torch.equal(o.view(torch.int16), o2.view(torch.int16)) and torch.equal(lse, lse2)
         assert not torch.isnan(lse).any()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("what", ["keys", "first keys", "rows", "plus", "nan"])
+@pytest.mark.parametrize("h,s_q,s_kv", [(2, 64, 64), (3, 130, 200), (2, 333, 333), (1, 515, 129)])
+def test_infinite_and_nan_scores(h, s_q, s_kv, what, causal, dtype):
+    """Scores of -inf in the middle and at the start of a walk, for all rows or for some, +inf and NaN.  The same rows are NaN as
+    with 64-row waves, and the others the same bits, but for one case: with a causal mask, a row whose scores have all been -inf
+    makes the row sums of a 64-row wave NaN also in the tile that its block does not have, and moves the references of
+    the rows beside it there, which 32-row waves leave.  Either reference is right: P is rounded to 16 bits (relative error up
+    to eps / 2) against either, and O again."""
+    import torch
+    t = torch.bfloat16 if dtype == "bf16" else torch.float16
+    gen = torch.Generator(device="cuda").manual_seed(s_q + 3 * s_kv)
+    q, k, v = (torch.randn((1, h, s, 128), generator=gen, device="cuda") for s in (s_q, s_kv, s_kv))
+    q[..., 0], k[..., 0] = q[..., 0].abs() + 0.1, k[..., 0].abs() + 0.1   # (a factor of inf in place 0 has a known sign)
+    inf = float("inf")
+    bad = torch.zeros((1, h, s_q), dtype=torch.bool, device="cuda")
+    if what == "keys":
+        k[:, :, 32:min(70, s_kv - 1), 0] = -inf
+        k[:, :, s_kv - 1, 0] = -inf
+    elif what == "first keys":      # a walk that starts with a whole tile of them has no reference that gives numbers
+        k[:, :, :7, 0] = -inf
+        bad[:, :, :7] = causal      # (rows that see no other key)
+    else:
+        rows = torch.tensor([3, 31, 32, 40, 63], device="cuda")
+        q[:, :, rows, 0] = {"rows": -inf, "plus": inf, "nan": float("nan")}[what]
+        bad[:, :, rows] = True
+    q, k, v = q.to(t), k.to(t), v.to(t)
+    o, lse = debug_lib.attn_fwd_variant(q, k, v, causal, 128 ** -0.5, debug_lib.FWD_D128_2_WAVES)
+    o2, lse2 = debug_lib.attn_fwd_variant(q, k, v, causal, 128 ** -0.5, debug_lib.FWD_D128_PAIRED)
+    assert torch.equal(torch.isnan(o).all(-1), bad) and torch.equal(torch.isnan(o2).all(-1), bad)
+    assert torch.equal(torch.isnan(o).any(-1), bad) and torch.equal(torch.isnan(o2).any(-1), bad)
+    assert torch.equal(torch.isnan(lse), torch.isnan(lse2))
+    o, o2, v = o.float().nan_to_num(0.0), o2.float().nan_to_num(0.0), v.float()
+    lse, lse2 = lse.masked_fill(bad, 0.0), lse2.masked_fill(bad, 0.0)
+    assert torch.isfinite(lse).all()
+    if causal and what in ("rows", "first keys"):      # rows without a finite score, all in the first 64-row block
+        eps = torch.finfo(t).eps
+        assert (o - o2).abs().max() <= 2 * eps * v.abs().max()     # (P twice, O twice, half an ulp each)
+        assert (lse - lse2).abs().max() <= 1e-5
+        o, o2, lse, lse2 = o[:, :, 64:], o2[:, :, 64:], lse[:, :, 64:], lse2[:, :, 64:]
+    assert torch.equal(o, o2) and torch.equal(lse, lse2)
