@@ -20,18 +20,19 @@ using attn::Params;
 
 using attn::allow_lds;
 
-// Params::idle_row of a launch.  A wave without a row below S_q that stops after its first K/V tile leaves the LDS port and
-// the power to the others (128 heads of 520 rows, D = 128 35.0 -> 33.5 us, 512 of 300 rows, D = 64 36.0 -> 32.1, D = 256
-// 119 -> 113), but it leaves the loop by code that the others do not run: 0.1 to 0.3 us of instruction fetches, which a
-// short walk does not win back.  Measured without / with, us: 200 heads of 70 rows, D = 128, 64 keys 7.7 / 7.9, 256 keys
-// 11.2 / 11.2, 700 keys 20.4 / 19.0; 4 such heads, 64 keys 7.1 / 7.3, 256 keys 10.5 / 10.7, 1000 keys 22.3 / 22.5; D = 256,
-// where all waves but one have no row, 64 heads of 5 rows, 64 keys 7.6 / 7.7, 135 keys 10.1 / 9.9, 700 keys 18.7 / 18.1;
-// 600 heads of 300 rows, D = 128, 128 keys 39.1 / 38.9; D = 256, 128 keys 75.4 / 76.0, 256 keys 116 / 111; D = 64, where it is
-// never slower, 96 keys 27.9 / 26.2.  Causal: the last query tile of a head, which has these waves, walks the most keys (128
-// heads of 520 rows, D = 128 25.6 / 25.2, 96 of 2100 rows 124.4 / 121.5; 4 of 70 rows 8.57 / 8.63), so that these launches
-// always do it (one more argument costs their crowded scalar registers as much as it brings), but for the 4-wave D = 64
-// ones, which never do: 1 head of 192 rows 5.6 / 5.8, 32 of 600 rows 9.9 / 10.1, 100 of 256 rows 7.3 / 7.4, 400 of 777 rows
-// 76.7 / 75.5.
+// Params::idle_row of a launch.  A wave without a row below S_q (at D = 128 in pairs: a pair without one) that stops after its
+// first K/V tile leaves the LDS port and the power to the others, but it leaves the loop by code that the others do not
+// run: 0.1 to 0.3 us of instruction fetches, which a short walk does not win back.  Measured without / with, us: D = 64,
+// where it is never slower, 512 heads of 300 rows 36.0 / 32.1, 600 heads against 96 keys 27.9 / 26.2; D = 256, 512 of 300 119
+// / 113, 600 of 300 rows and 128 keys 75.4 / 76.0, 256 keys 116 / 111, and where all waves but one have no row, 64 heads of 5
+// rows, 64 keys 7.6 / 7.7, 135 keys 10.1 / 9.9, 700 keys 18.7 / 18.1.  D = 128, in pairs, 200 heads of 70 rows, 64 keys 5.66 / 5.68, 256
+// keys 8.85 / 8.85, 600 of 300 rows and 128 keys 32.5 / 32.2; over 260 launches it is level up to 256 keys and 0.3 to 1.1 %
+// ahead beyond with up to 256 tiles, 0.6 to 2.5 % ahead at any length with more than 512.  (The 64-row waves of that size, 200
+// heads of 70 rows, 64 keys 7.7 / 7.9, 700 keys 20.4 / 19.0; 128 of 520 rows 35.0 / 33.5.)  Causal: the last query tile
+// of a head, which has these waves, walks the most keys (D = 128, in pairs, 128 heads of 520 rows 23.2 / 22.4; 4 of 70 rows 5.64 /
+// 5.65; over 300 launches it is level to 2 % ahead), so that these launches always do it (one more argument costs their
+// crowded scalar registers as much as it brings), but for the 4-wave D = 64 ones, which never do: 1 head of 192 rows 5.6 /
+// 5.8, 32 of 600 rows 9.9 / 10.1, 100 of 256 rows 7.3 / 7.4, 400 of 777 rows 76.7 / 75.5.
 int idle_row(const Params &p, int D, long long tiles)
 {
     const bool soon = D == 64 || (D == 128 && tiles > 512) || (D == 256 && p.S_q <= 64);
