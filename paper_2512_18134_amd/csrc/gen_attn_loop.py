@@ -392,8 +392,8 @@ class Gen(Emitter):
         """Softmax of tile 0.  There is no reference to take it against: a pass against -inf would fail the row-sum test
         whatever the scores are, so the exact row maxima come first (as in the out-of-line pass, and with its results:
         the running sum and the accumulators that pass would scale are zero).  One softmax per tile walk less and one trip
-        out of line less, the same bits: one head of 128 rows, D = 64, 4.25 -> 3.94 us, 64 heads of 1024 rows 20.2 -> 19.3,
-        100 heads of 600 rows, D = 128, 24.2 -> 23.8, 16 heads of 777 rows, causal, 19.8 -> 19.5."""
+        out of line less, the same bits: one head of 128 rows, D = 64, 4.58 -> 4.31 us, 64 heads of 1024 rows 20.1 -> 19.6,
+        100 heads of 600 rows, D = 128, 23.3 -> 23.0, 16 heads of 777 rows, causal, in 64-row waves 20.4 -> 20.1."""
         if "novalu" in self.exp:
             return []
         return self.max_ops(S_cur) + self.pairmax_ops() + self.move_reference_ops() + self.pair_ops(S_cur, P_new, self.L)
