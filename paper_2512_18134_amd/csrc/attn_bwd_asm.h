@@ -204,7 +204,7 @@ __device__ __forceinline__ void bwd_sweep(const BwdParams &p, const BwdQueue &qu
             continue;
         if (pass > 0)
             __syncthreads();  // every wave has read the previous tile's staged gradients back: the rings are free
-        if (!own_on_its_way)
+        if (__builtin_expect(!own_on_its_way, 1))
             locate(entry, bh, ot);
         const int S_own = KEY_OWNER ? p.S_kv : p.S_q;
         const int S_str = KEY_OWNER ? p.S_q : p.S_kv;
@@ -244,7 +244,7 @@ __device__ __forceinline__ void bwd_sweep(const BwdParams &p, const BwdQueue &qu
         // which the first iteration's contraction reads (and multiplies by zeros).  (Owner rows straight into registers, a
         // copy of tile 0 for the zeros and a wait for everything before S(0): 16 heads of 515 rows, D = 64, causal 16.6 -> 15.5
         // us, 200 of 300 rows 32.4 -> 30.0, 16 of 128 rows, D = 128, 13.1 -> 12.4, 128 of 4096 rows 3131 -> 3113; the same bits.)
-        if (!own_on_its_way)
+        if (__builtin_expect(!own_on_its_way, 1))
             issue_own_of(bh, ot);
     #pragma unroll
         for (int t = 0; t < FIRST; ++t)
@@ -367,10 +367,12 @@ __device__ __forceinline__ void bwd_sweep(const BwdParams &p, const BwdQueue &qu
             // the next tile's owner rows travel while this one is written out.  (At D = 64 a second workgroup on the CU
             // does as much, and there are no registers for it.  The tile is located once, here: with a causal mask that is
             // six divisions, and doing it again at the head cost what the early loads win: 373 heads of 33 queries and 940
-            // keys 103.6 -> 99.3 us, 451 of 576 rows 269 -> 260, mean over 132 causal calls of several passes -1.3 %)
+            // keys 103.6 -> 99.3 us, 451 of 576 rows 269 -> 260, mean over 132 causal calls of several passes -1.3 %.  A tile
+            // with none behind it runs straight on, past no code that is not its own: a jump is a fetch more in a short
+            // launch.  82 heads of 187 rows 20.0 -> 19.7 us, 134 of 70 rows, causal, 17.0 -> 16.8)
             const int next = queue.entry(blockIdx.x, (int)gridDim.x, p.cus_per_xcd, pass + 1);
             own_on_its_way = next >= 0 && (KEY_OWNER ? next < queue.n_kv : true);
-            if (own_on_its_way) {
+            if (__builtin_expect(own_on_its_way, 0)) {
                 locate(next, bh, ot);
                 issue_own_of(bh, ot);
             }
