@@ -214,14 +214,16 @@ int choose_d128(int BH, const Params &p, int causal, float *cost = nullptr)
 // two tiles per CU, of which the last walks faster where most CUs have one tile or none; heads of a single query tile
 // stay out, whose keys come from memory once per workgroup (310 heads of 112 queries and 960 keys 33.8 / 39.7).  Causal: heavy
 // and light tiles share a CU and it is ahead (by 14 % on average over 592 launches) up to 2 1/4 tiles per CU.  Up to 1024
-// keys what decides is how many 32-key steps a workgroup walks in all (`per_slot`), next to the start of every tile that the
-// second workgroup on a CU hides: over 2375 such launches of up to 16340 tiles it is 11 % ahead up to 20 steps, 7 % at 20 to
-// 48, 1.5 % at 60 to 80, level at 80 to 110, and 2 to 5 % behind beyond (64 heads of 9386 queries and 989 keys 265 / 288,
-// 552 of 1792 and 748 334 / 366).  Between 3 and 4 tiles per CU the 256-row tiles come in whole pairs of heavy and light
-// ones, and the line lies at 36 steps (123 heads of 970 rows, 34 steps, 42.6 / 48.2; but 173 of 832, 37 steps in 4.7 tiles
-// per CU, 50 / 45).  Longer walks: the better of the others has its balance to win or lose (32 heads of 3845 rows 107 / 149).
-// Over the 4059 measured causal launches of more than 2 1/4 tiles per CU, 99 are still slower by more than 2 % than without
-// this tiling, by how the queues happen to fall; moving the lines loses more than it wins.
+// keys the second workgroup on a CU hides the start of every tile, which counts the less the more 32-key steps a workgroup
+// walks in all (`per_slot`).  Over 8000 such launches of up to 16000 tiles it is 11 to 13 % ahead up to 20 steps and 7 % at 20
+// to 36.  With more than twice as many queries as keys: 4 % ahead at 36 to 60, 2 % at 60 to 110, level at 110 to 160 (146 heads
+// of 5519 queries and 361 keys 216 / 212), and 2 to 3 % behind beyond (71 of 7215 and 844 221 / 236, 155 of 10560 and 951
+// 782 / 849), which is where the line lies.  With fewer queries it is 1.5 % ahead at 36 to 60 steps and 2 % behind to 2 %
+// ahead beyond, but one launch 7 % ahead and the next 8 % behind, by how the queues happen to fall (757 heads of 655 queries and
+// 1307 keys 173 / 171, 601 of 755 rows 159 / 145, 495 of 939 and 1790 180 / 215): a line at 80 steps makes 520
+// of the 8000 more than 2 % faster and 303 slower, and sizes, remainders and the queues' longest walk tell them apart no
+// better than that, so that there is none.  Longer walks: the better of the others has its balance to
+// win or lose (32 heads of 3845 rows 107 / 149).
 bool paired_pays(int BH, const Params &p, int causal, int cus, float others)
 {
     const long long nt = (p.S_q + 127) / 128, tiles = BH * nt, slots = 2ll * cus;
@@ -240,7 +242,7 @@ bool paired_pays(int BH, const Params &p, int causal, int cus, float others)
     }
     const float per_slot = (float)(2 * k * (k + 1) + (nt - k) * n) * BH / (float)slots;
     if (n <= 32)
-        return per_slot <= (tiles > 3 * cus && tiles <= 4 * cus ? 36.f : 80.f);
+        return p.S_q <= 2ll * p.S_kv || per_slot <= 160.f;
     const float r = fmaxf(1.f, whole + 0.5f * (rest + (rest > 0.f ? 1.f : 0.f)));
     return fmaxf(5.9f + 0.39f * n, 7.0f * r + 0.873f * per_slot + 0.056f * n) < 1.04f * others;
 }

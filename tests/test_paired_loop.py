@@ -141,9 +141,10 @@ MEASURED = [(16, 128, 128, 1, 1), (16, 777, 777, 1, 1), (16, 1024, 1024, 0, 1), 
             (1, 16384, 16384, 1, 1), (16, 2048, 2048, 0, 1), (24, 2816, 2816, 0, 1), (1, 64, 64, 0, 1), (213, 623, 623, 1, 1),
             (6, 5468, 5468, 0, 0), (128, 2048, 2048, 0, 0), (32, 4096, 4096, 1, 0), (32, 3845, 3845, 1, 0), (16, 16384, 16384, 0, 0),
             (310, 112, 960, 0, 0)]
-# ... causal, up to 1024 keys: more queries than keys, many tiles, tiles that come in whole pairs
-MEASURED += [(64, 9386, 989, 1, 0), (372, 2742, 832, 1, 0), (128, 10048, 704, 1, 0), (552, 1792, 748, 1, 0), (64, 8192, 512, 1, 0),
-             (410, 1024, 1024, 1, 0), (420, 148, 148, 1, 1), (224, 384, 384, 1, 1), (173, 832, 832, 1, 1),
+# ... causal, up to 1024 keys: more than twice as many queries, beyond 160 32-key steps per workgroup and up to that (level), and
+# fewer queries, where many tiles and long walks are as often ahead as behind
+MEASURED += [(64, 9386, 989, 1, 0), (372, 2742, 832, 1, 0), (128, 10048, 704, 1, 0), (552, 1792, 748, 1, 0), (64, 8192, 512, 1, 1),
+             (410, 1024, 1024, 1, 1), (757, 655, 1307, 1, 1), (420, 148, 148, 1, 1), (224, 384, 384, 1, 1), (173, 832, 832, 1, 1),
              (16, 4000, 300, 1, 1)]
 # ... one round of the 256-row tiling against two 128-row tiles on some compute units
 MEASURED += [(87, 344, 2557, 0, 0), (96, 320, 4494, 0, 0), (56, 557, 3839, 0, 0), (3, 13632, 2779, 1, 0), (6, 8256, 2233, 1, 0),
