@@ -53,6 +53,11 @@ def generate_sources(verbose=False, out_dir=None):
                            ("kv", 64, "bf16"), ("q", 64, "bf16"), ("kv", 64, "f16"), ("q", 64, "f16")):
         out = os.path.join(out_dir, "attn_bwd_loop_%s_d%d%s.inc" % (kind, d, "" if dtype == "bf16" else "_" + dtype))
         _run_generator([sys.executable, gen3, kind, str(d), out, dtype], verbose)
+    gen4 = os.path.join(HERE, "csrc", "gen_attn_bwd_wide_loop.py")
+    for kind in ("kv", "q"):
+        for dtype in ("bf16", "f16"):
+            out = os.path.join(out_dir, "attn_bwd_wide_loop_%s%s.inc" % (kind, "" if dtype == "bf16" else "_" + dtype))
+            _run_generator([sys.executable, gen4, kind, out, dtype], verbose)
 
 
 def _hipcc():

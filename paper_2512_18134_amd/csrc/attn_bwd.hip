@@ -9,6 +9,7 @@
 #include "attn_bwd.h"  // the C declaration (include/)
 #include "attn_bwd_asm.h"
 #include "attn_bwd_kernels.h"
+#include "attn_bwd_wide.h"
 #include "attn_fwd.h"  // attn_status
 #include "attn_launch.h"
 
@@ -57,11 +58,8 @@ bool sweeps_apart(const BwdParams &p, int causal, int slots)
 
 // both hand-scheduled sweeps: as many workgroups as the chip holds at once, each walking the queue of owner tiles of its
 // XCD
-template <int D, bool F16>
-int launch_asm(const BwdParams &p, int causal, hipStream_t stream)
+int launch_sweeps(void (*kern)(const BwdParams), int LDS, const BwdParams &p, int causal, hipStream_t stream)
 {
-    constexpr int LDS = attn::BwdLds<D>::BYTES;
-    auto kern = causal ? attn::attn_bwd_asm_kernel<D, true, F16> : attn::attn_bwd_asm_kernel<D, false, F16>;
     if (!attn::allow_lds(reinterpret_cast<const void *>(kern), LDS))
         return ATTN_ERR_LAUNCH;
     // (a runtime that cannot tell the occupancy gets one workgroup per entry: the kernel takes either)
@@ -82,6 +80,117 @@ int launch_asm(const BwdParams &p, int causal, hipStream_t stream)
     return rc == ATTN_OK ? run(0, p.total_q) : rc;
 }
 
+enum BwdTiling { kAsDispatched, kRows128, kRows256 };
+
+// What a workgroup's walk costs, in us: per owner tile and per streamed tile of either sweep; `launch` + `mean` times the mean
+// walk of all compute units is added to the longest one (full compute units take each other's power).  Fitted to 8300
+// launches of 1 to 256 heads and 64 to 16384 rows, D = 128, causal or not (root mean square of the error 5 and 6 %).
+struct WalkCost {
+    float key_tile, key_step, query_tile, query_step, launch, mean;
+};
+constexpr WalkCost kWalk128 = {4.10f, 0.521f, 3.37f, 0.366f, 5.8f, 0.58f}, kWalk256 = {7.38f, 0.932f, 5.50f, 0.656f, 4.6f, 0.52f};
+
+// Streamed tiles of owner tile t (`rows` rows) of a key-owner or query-owner sweep
+int walk_steps(const BwdParams &p, int causal, int rows, bool keys, int t)
+{
+    if (keys) {
+        const int n = (p.S_q + 31) / 32, first = t * (rows / 32);
+        return !causal ? n : (first < n ? n - first : 0);
+    }
+    int end = p.S_kv;
+    if (causal) {
+        const int last = p.S_q / rows > t ? (t + 1) * rows : p.S_q;
+        end = last < end ? last : end;
+    }
+    return (end + 31) / 32;
+}
+
+// Estimated time of a D = 128 launch with owner tiles of `rows` rows: the longest walk among workgroups of one XCD, of which a
+// few are followed through the queue, those around the ends of the sweeps among them.
+float launch_estimate(const BwdParams &p, int BH, int causal, int rows, const WalkCost &c, int slots)
+{
+    const int n_t = (p.S_kv + rows - 1) / rows, n_tq = (p.S_q + rows - 1) / rows;
+    const attn::BwdQueue queue(BH * n_t, BH * n_tq);
+    const int per_pass = slots / attn::kNumXcd;
+    // steps of a head's tiles: they fall (key owners) or rise (query owners) by rows / 32 from tile to tile while a mask cuts them
+    const auto steps = [&](bool keys, int n) {
+        double sum = 0;
+        if (!causal)
+            return (double)n * walk_steps(p, 0, rows, keys, 0);
+        const int cut = (p.S_q < p.S_kv ? p.S_q : p.S_kv) / rows, m = cut < n ? cut : n;    // tiles the mask's edge runs through
+        const int d = rows / 32;
+        if (keys) {
+            const int first = (p.S_q + 31) / 32, all = (first + d - 1) / d < n ? (first + d - 1) / d : n;
+            sum = (double)all * first - 0.5 * d * all * (all - 1.0);
+        } else {
+            sum = 0.5 * d * m * (m + 1.0) + (double)(n - m) * walk_steps(p, causal, rows, keys, n - 1);
+        }
+        return sum;
+    };
+    const double all = BH * (n_t * (double)c.key_tile + steps(true, n_t) * c.key_step + n_tq * (double)c.query_tile +
+                             steps(false, n_tq) * c.query_step);
+    const float mean = (float)(all / slots);
+    const float keys = c.key_tile + c.key_step * walk_steps(p, causal, rows, true, 0);
+    const float queries = c.query_tile + c.query_step * walk_steps(p, causal, rows, false, n_tq - 1);
+    const float heaviest = keys > queries ? keys : queries;
+    if (queue.n_entries <= slots)
+        return c.launch + heaviest + c.mean * mean;
+    if (queue.n_entries > 12 * slots)
+        return c.launch + mean + heaviest * (causal ? 0.25f : 0.5f) + c.mean * mean;
+    float longest = 0.f;
+    const auto follow = [&](int m) {
+        float sum = 0.f;
+        for (int k = 0;; ++k) {
+            const int entry = queue.entry(m * attn::kNumXcd, slots, per_pass, k);
+            if (entry < 0)
+                break;
+            const bool own_keys = entry < queue.n_kv;
+            if (!own_keys && entry < queue.q_first)
+                continue;
+            int bh = 0, t = 0;
+            if (causal)
+                attn::wg_to_tile_n<true>(own_keys ? entry : entry - queue.q_first, BH * (own_keys ? n_t : n_tq),
+                                         own_keys ? n_t : n_tq, 4ll * (p.S_q + p.S_kv) * 128, bh, t);
+            if (causal && own_keys)
+                t = n_t - 1 - t;
+            const int n = walk_steps(p, causal, rows, own_keys, t);
+            sum += own_keys ? c.key_tile + c.key_step * n : c.query_tile + c.query_step * n;
+        }
+        longest = sum > longest ? sum : longest;
+    };
+    for (int m = 0; m < per_pass; m += (per_pass + 7) / 8)
+        follow(m);
+    follow(per_pass - 1);
+    const int ends[3] = {(queue.n_kv + 7) / 8, queue.q_first / 8 + 1, (queue.n_entries + 7) / 8 - 1};
+    for (const int end : ends)
+        for (int i = end - 1; i <= end + 1; ++i)
+            if (i >= 0 && i < (queue.n_entries + 7) / 8) {
+                const int at = i / per_pass & 1 ? per_pass - 1 - i % per_pass : i % per_pass;
+                follow(per_pass - 1 - at);
+            }
+    return c.launch + longest + c.mean * mean;
+}
+
+// D = 128: whether owner tiles of 256 rows (64-row waves) are ahead of tiles of 128.  Half the LDS operand reads and half
+// the stream per product: long walks on a full chip are 8 to 11 % faster (32 heads of 2048 rows 209 -> 190 us, 128 of 4096
+// 3085 -> 2768, causal 1701 -> 1561).  Half the tiles, each with twice as much around its loop and more rows that do not exist:
+// launches that do not fill the chip are up to 1.7 times slower (16 heads of 1024 rows 35 -> 44).  Launches that the smaller
+// tiles run one sweep after the other stay with them.
+bool wide_pays(const BwdParams &p, int BH, int causal, int slots)
+{
+    if (slots < attn::kNumXcd || 2ll * BH * ((p.S_kv + 255) / 256 + (p.S_q + 255) / 256) < slots)
+        return false;   // (no launch of fewer tiles gained)
+    BwdParams small = p;
+    small.total_wg = BH * ((p.S_kv + 127) / 128);
+    small.total_q = BH * ((p.S_q + 127) / 128);
+    if (sweeps_apart(small, causal, slots))
+        return false;
+    // (of 8300 launches 20 % take them, 7 % faster in the mean; 42 of those are more than 2 % slower, 1.16 times at worst: 14 causal
+    // heads of 5182 queries and 11160 keys.  A margin of 0.98 with a mask would gain a tenth more and lose in twice as many)
+    return launch_estimate(p, BH, causal, 256, kWalk256, slots) <
+           (causal ? 0.96f : 0.98f) * launch_estimate(p, BH, causal, 128, kWalk128, slots);
+}
+
 template <int D, typename ELEM>
 int launch_delta(const BwdParams &p, hipStream_t stream)
 {
@@ -96,21 +205,28 @@ int launch_delta(const BwdParams &p, hipStream_t stream)
 // sweep -> one for both), D = 128: 16 heads of 128 rows 20.2 -> 13.2 us, of 1024 rows 54.4 -> 38.2, causal 53.5 -> 34.4;
 // of 4096 rows 408.8 -> 404.7; 128 heads of 2048 rows 860 -> 850.
 template <int D, bool F16>
-int launch_hand(BwdParams p, int BH, int causal, hipStream_t stream)
+int launch_hand(BwdParams p, int BH, int causal, hipStream_t stream, BwdTiling tiling = kAsDispatched)
 {
-    p.n_t = (p.S_kv + 127) / 128;
-    p.n_tq = (p.S_q + 127) / 128;
-    const long long total_kv = (long long)BH * p.n_t, total_q = (long long)BH * p.n_tq;
-    if (total_kv + total_q > 0x7fffffffLL - attn::kNumXcd)
+    if ((long long)BH * ((p.S_kv + 127) / 128 + (p.S_q + 127) / 128) > 0x7fffffffLL - attn::kNumXcd)
         return ATTN_ERR_SHAPE;
-    p.total_wg = (int)total_kv;
-    p.total_q = (int)total_q;
+    const bool wide = D == 128 && (tiling == kAsDispatched ? wide_pays(p, BH, causal, attn::cu_count(attn::kNumXcd)) : tiling == kRows256);
+    const int rows = wide ? 256 : 128;
+    p.n_t = (p.S_kv + rows - 1) / rows;
+    p.n_tq = (p.S_q + rows - 1) / rows;
+    p.total_wg = BH * p.n_t;
+    p.total_q = BH * p.n_tq;
     const int cus = attn::cu_count(attn::kNumXcd);
     p.cus_per_xcd = cus > 0 ? cus / attn::kNumXcd : 32;
     const int rc = launch_delta<D, typename std::conditional<F16, _Float16, attn::bf16_t>::type>(p, stream);
     if (rc != ATTN_OK)
         return rc;
-    return launch_asm<D, F16>(p, causal, stream);
+    if constexpr (D == 128) {
+        if (wide)
+            return launch_sweeps(causal ? attn::attn_bwd_wide_kernel<true, F16> : attn::attn_bwd_wide_kernel<false, F16>,
+                                 attn::BwdWideLds::BYTES, p, causal, stream);
+    }
+    return launch_sweeps(causal ? attn::attn_bwd_asm_kernel<D, true, F16> : attn::attn_bwd_asm_kernel<D, false, F16>,
+                         attn::BwdLds<D>::BYTES, p, causal, stream);
 }
 
 // plain: run the compiler-scheduled sweeps (always when scale == 0, which the hand-scheduled loops exclude)
@@ -259,6 +375,33 @@ extern "C" int attn_bwd_sweeps_apart(int heads, int S_q, int S_kv, int causal, i
     p.total_wg = heads * ((S_kv + 127) / 128);
     p.total_q = heads * ((S_q + 127) / 128);
     return sweeps_apart(p, causal, slots);
+}
+
+// Test-only, host only: whether a D = 128 launch takes owner tiles of 256 rows; est: the two estimates in us.
+extern "C" int attn_bwd_wide_pays(int heads, int S_q, int S_kv, int causal, int slots, float *est)
+{
+    BwdParams p;
+    p.S_q = S_q;
+    p.S_kv = S_kv;
+    est[0] = launch_estimate(p, heads, causal, 128, kWalk128, slots);
+    est[1] = launch_estimate(p, heads, causal, 256, kWalk256, slots);
+    return wide_pays(p, heads, causal, slots);
+}
+
+// Test-only: attn_bwd / attn_bwd_f16 (D = 128, scale > 0) on owner tiles of 128 (tiling 1) or 256 rows (2).
+extern "C" int attn_bwd_tiling(const void *q, const void *k, const void *v, const void *o, const void *d_o,
+                               const float *lse, void *dq, void *dk, void *dv, float *delta_ws, int B, int H, int S_q,
+                               int S_kv, int f16, int causal, float scale, void *stream, int tiling)
+{
+    BwdParams p;
+    const int rc = validate_bwd(q, k, v, o, d_o, lse, dq, dk, dv, delta_ws, B, H, S_q, S_kv, 128, scale, p);
+    if (rc != ATTN_OK)
+        return rc;
+    if (!(scale > 0.f))
+        return ATTN_ERR_SCALE;
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    return f16 ? launch_hand<128, true>(p, B * H, causal, st, (BwdTiling)tiling)
+               : launch_hand<128, false>(p, B * H, causal, st, (BwdTiling)tiling);
 }
 
 // Test-only entry point of the debug build of the library: attn_bwd on the compiler-scheduled sweeps
