@@ -10,6 +10,7 @@ And _marshal.so, the host-only extension module that takes torch tensors to the 
 points (csrc/marshal.cpp); it is left out where torch or the headers of Python are not
 installed (the C ABI needs neither).
 """
+import itertools
 import os
 import subprocess
 import sys
@@ -54,10 +55,9 @@ def generate_sources(verbose=False, out_dir=None):
         out = os.path.join(out_dir, "attn_bwd_loop_%s_d%d%s.inc" % (kind, d, "" if dtype == "bf16" else "_" + dtype))
         _run_generator([sys.executable, gen3, kind, str(d), out, dtype], verbose)
     gen4 = os.path.join(HERE, "csrc", "gen_attn_bwd_wide_loop.py")
-    for kind in ("kv", "q"):
-        for dtype in ("bf16", "f16"):
-            out = os.path.join(out_dir, "attn_bwd_wide_loop_%s%s.inc" % (kind, "" if dtype == "bf16" else "_" + dtype))
-            _run_generator([sys.executable, gen4, kind, out, dtype], verbose)
+    for kind, waves, dtype in itertools.product(("kv", "q"), (2, 4), ("bf16", "f16")):
+        out = os.path.join(out_dir, "attn_bwd_wide_loop_%s_w%d%s.inc" % (kind, waves, "" if dtype == "bf16" else "_" + dtype))
+        _run_generator([sys.executable, gen4, kind, str(waves), out, dtype], verbose)
 
 
 def _hipcc():

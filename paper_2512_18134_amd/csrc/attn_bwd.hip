@@ -58,12 +58,12 @@ bool sweeps_apart(const BwdParams &p, int causal, int slots)
 
 // both hand-scheduled sweeps: as many workgroups as the chip holds at once, each walking the queue of owner tiles of its
 // XCD
-int launch_sweeps(void (*kern)(const BwdParams), int LDS, const BwdParams &p, int causal, hipStream_t stream)
+int launch_sweeps(void (*kern)(const BwdParams), int threads, int LDS, const BwdParams &p, int causal, hipStream_t stream)
 {
     if (!attn::allow_lds(reinterpret_cast<const void *>(kern), LDS))
         return ATTN_ERR_LAUNCH;
     // (a runtime that cannot tell the occupancy gets one workgroup per entry: the kernel takes either)
-    int slots = attn::persistent_slots(reinterpret_cast<const void *>(kern), 256, LDS, attn::kNumXcd);
+    int slots = attn::persistent_slots(reinterpret_cast<const void *>(kern), threads, LDS, attn::kNumXcd);
     if (slots < attn::kNumXcd)
         slots = 0x7fffffff;
     const auto run = [&](int n_kv, int n_q) {
@@ -71,7 +71,7 @@ int launch_sweeps(void (*kern)(const BwdParams), int LDS, const BwdParams &p, in
         r.total_wg = n_kv;
         r.total_q = n_q;
         const int entries = attn::BwdQueue(n_kv, n_q).n_entries;
-        hipLaunchKernelGGL(kern, dim3((unsigned)(slots < entries ? slots : entries)), dim3(256), LDS, stream, r);
+        hipLaunchKernelGGL(kern, dim3((unsigned)(slots < entries ? slots : entries)), dim3(threads), LDS, stream, r);
         return hipGetLastError() == hipSuccess ? ATTN_OK : ATTN_ERR_LAUNCH;
     };
     if (!sweeps_apart(p, causal, slots))
@@ -80,15 +80,18 @@ int launch_sweeps(void (*kern)(const BwdParams), int LDS, const BwdParams &p, in
     return rc == ATTN_OK ? run(0, p.total_q) : rc;
 }
 
-enum BwdTiling { kAsDispatched, kRows128, kRows256 };
+enum BwdTiling { kAsDispatched, kRows128, kRows256, kRows128TwoWaves };
 
 // What a workgroup's walk costs, in us: per owner tile and per streamed tile of either sweep; `launch` + `mean` times the mean
-// walk of all compute units is added to the longest one (full compute units take each other's power).  Fitted to 8300
-// launches of 1 to 256 heads and 64 to 16384 rows, D = 128, causal or not (root mean square of the error 5 and 6 %).
+// walk of all workgroups is added to the longest one (full compute units take each other's power).  Fitted to 7200 launches
+// of 1 to 256 heads and 64 to 16384 rows, D = 128, causal or not (root mean square of the error 5, 6 and 5 %).
 struct WalkCost {
+    int rows, per_cu;   // of an owner tile; workgroups that a compute unit holds
     float key_tile, key_step, query_tile, query_step, launch, mean;
 };
-constexpr WalkCost kWalk128 = {4.10f, 0.521f, 3.37f, 0.366f, 5.8f, 0.58f}, kWalk256 = {7.38f, 0.932f, 5.50f, 0.656f, 4.6f, 0.52f};
+constexpr WalkCost kWalk128 = {128, 1, 4.18f, 0.522f, 3.55f, 0.367f, 5.76f, 0.535f},
+                   kWalk256 = {256, 1, 7.26f, 0.924f, 5.56f, 0.644f, 4.83f, 0.503f},
+                   kWalk128TwoWaves = {128, 2, 7.27f, 0.920f, 6.32f, 0.654f, 4.72f, 0.551f};
 
 // Streamed tiles of owner tile t (`rows` rows) of a key-owner or query-owner sweep
 int walk_steps(const BwdParams &p, int causal, int rows, bool keys, int t)
@@ -105,27 +108,48 @@ int walk_steps(const BwdParams &p, int causal, int rows, bool keys, int t)
     return (end + 31) / 32;
 }
 
-// Estimated time of a D = 128 launch with owner tiles of `rows` rows: the longest walk among workgroups of one XCD, of which a
-// few are followed through the queue, those around the ends of the sweeps among them.
-float launch_estimate(const BwdParams &p, int BH, int causal, int rows, const WalkCost &c, int slots)
+// The tiles of one sweep that XCD 0 takes up, in its queue's order: what wg_to_tile_n gives for entries 0, 8, 16, ..., without its
+// divisions.  each(t) per tile.
+template <typename F>
+void xcd_tiles(int heads, int n_t, int causal, long long head_bytes, F &&each)
 {
+    using attn::kNumXcd;
+    const int a = heads / kNumXcd, r = heads % kNumXcd, n_left = r * n_t;
+    if (!causal) {
+        for (long long i = 0; i < (long long)heads * n_t; i += kNumXcd)
+            each(0);   // (all alike)
+        return;
+    }
+    for (int i = 0; kNumXcd * i < n_left; ++i)
+        each(n_t - 1 - (kNumXcd * i + ((i & 1) && kNumXcd * (i + 1) <= n_left ? kNumXcd - 1 : 0)) / r);
+    if (a == 0)
+        return;
+    const int want = attn::causal_group_heads(n_t, head_bytes), ng = a > want ? a / want : 1;
+    for (int g = 0; g < ng; ++g)
+        for (int t = n_t - 1; t >= 0; --t)
+            for (int h = 0; h < a / ng + (g < a % ng); ++h)
+                each(t);
+}
+
+// Estimated time of a D = 128 launch on `cus` compute units: the longest walk among XCD 0's workgroups
+float launch_estimate(const BwdParams &p, int BH, int causal, const WalkCost &c, int cus)
+{
+    constexpr int kMaxPasses = 12, kMaxSlots = 128;      // per XCD
+    const int rows = c.rows, slots = cus * c.per_cu;
     const int n_t = (p.S_kv + rows - 1) / rows, n_tq = (p.S_q + rows - 1) / rows;
     const attn::BwdQueue queue(BH * n_t, BH * n_tq);
-    const int per_pass = slots / attn::kNumXcd;
+    const int per_pass = slots / attn::kNumXcd, first = cus / attn::kNumXcd < per_pass ? cus / attn::kNumXcd : per_pass;
     // steps of a head's tiles: they fall (key owners) or rise (query owners) by rows / 32 from tile to tile while a mask cuts them
     const auto steps = [&](bool keys, int n) {
-        double sum = 0;
         if (!causal)
             return (double)n * walk_steps(p, 0, rows, keys, 0);
-        const int cut = (p.S_q < p.S_kv ? p.S_q : p.S_kv) / rows, m = cut < n ? cut : n;    // tiles the mask's edge runs through
-        const int d = rows / 32;
+        const int d = rows / 32, top = (p.S_q + 31) / 32;
         if (keys) {
-            const int first = (p.S_q + 31) / 32, all = (first + d - 1) / d < n ? (first + d - 1) / d : n;
-            sum = (double)all * first - 0.5 * d * all * (all - 1.0);
-        } else {
-            sum = 0.5 * d * m * (m + 1.0) + (double)(n - m) * walk_steps(p, causal, rows, keys, n - 1);
+            const int all = (top + d - 1) / d < n ? (top + d - 1) / d : n;
+            return (double)all * top - 0.5 * d * all * (all - 1.0);
         }
-        return sum;
+        const int cut = (p.S_q < p.S_kv ? p.S_q : p.S_kv) / rows, m = cut < n ? cut : n;    // tiles the mask's edge runs through
+        return 0.5 * d * m * (m + 1.0) + (double)(n - m) * walk_steps(p, causal, rows, keys, n - 1);
     };
     const double all = BH * (n_t * (double)c.key_tile + steps(true, n_t) * c.key_step + n_tq * (double)c.query_tile +
                              steps(false, n_tq) * c.query_step);
@@ -135,60 +159,47 @@ float launch_estimate(const BwdParams &p, int BH, int causal, int rows, const Wa
     const float heaviest = keys > queries ? keys : queries;
     if (queue.n_entries <= slots)
         return c.launch + heaviest + c.mean * mean;
-    if (queue.n_entries > 12 * slots)
+    if (queue.n_entries > kMaxPasses * slots || per_pass > kMaxSlots)
         return c.launch + mean + heaviest * (causal ? 0.25f : 0.5f) + c.mean * mean;
-    float longest = 0.f;
-    const auto follow = [&](int m) {
-        float sum = 0.f;
-        for (int k = 0;; ++k) {
-            const int entry = queue.entry(m * attn::kNumXcd, slots, per_pass, k);
-            if (entry < 0)
-                break;
-            const bool own_keys = entry < queue.n_kv;
-            if (!own_keys && entry < queue.q_first)
-                continue;
-            int bh = 0, t = 0;
-            if (causal)
-                attn::wg_to_tile_n<true>(own_keys ? entry : entry - queue.q_first, BH * (own_keys ? n_t : n_tq),
-                                         own_keys ? n_t : n_tq, 4ll * (p.S_q + p.S_kv) * 128, bh, t);
-            if (causal && own_keys)
-                t = n_t - 1 - t;
-            const int n = walk_steps(p, causal, rows, own_keys, t);
-            sum += own_keys ? c.key_tile + c.key_step * n : c.query_tile + c.query_step * n;
-        }
-        longest = sum > longest ? sum : longest;
-    };
-    for (int m = 0; m < per_pass; m += (per_pass + 7) / 8)
-        follow(m);
-    follow(per_pass - 1);
-    const int ends[3] = {(queue.n_kv + 7) / 8, queue.q_first / 8 + 1, (queue.n_entries + 7) / 8 - 1};
-    for (const int end : ends)
-        for (int i = end - 1; i <= end + 1; ++i)
-            if (i >= 0 && i < (queue.n_entries + 7) / 8) {
-                const int at = i / per_pass & 1 ? per_pass - 1 - i % per_pass : i % per_pass;
-                follow(per_pass - 1 - at);
+    float walk[kMaxSlots] = {};
+    int k = 0, at = 0;      // pass, place in it (BwdQueue::entry)
+    const long long head_bytes = 4ll * (p.S_q + p.S_kv) * 128;
+    for (const bool own_keys : {true, false})
+        xcd_tiles(BH, own_keys ? n_t : n_tq, causal, head_bytes, [&](int t) {
+            const int n = walk_steps(p, causal, rows, own_keys, causal && own_keys ? n_t - 1 - t : t);
+            const int m = k & 1 ? per_pass - 1 - at : at;
+            walk[m < first ? first - 1 - m : m] += own_keys ? c.key_tile + c.key_step * n : c.query_tile + c.query_step * n;
+            if (++at == per_pass) {
+                at = 0;
+                ++k;
             }
+        });
+    float longest = 0.f;
+    for (int m = 0; m < per_pass; ++m)
+        longest = walk[m] > longest ? walk[m] : longest;
     return c.launch + longest + c.mean * mean;
 }
 
-// D = 128: whether owner tiles of 256 rows (64-row waves) are ahead of tiles of 128.  Half the LDS operand reads and half
-// the stream per product: long walks on a full chip are 8 to 11 % faster (32 heads of 2048 rows 209 -> 190 us, 128 of 4096
-// 3085 -> 2768, causal 1701 -> 1561).  Half the tiles, each with twice as much around its loop and more rows that do not exist:
-// launches that do not fill the chip are up to 1.7 times slower (16 heads of 1024 rows 35 -> 44).  Launches that the smaller
-// tiles run one sweep after the other stay with them.
-bool wide_pays(const BwdParams &p, int BH, int causal, int slots)
+// D = 128: which owner tiles a launch takes.  64-row waves read half the LDS operands per product: in tiles of 256 rows (four
+// waves, half the stream as well) long walks on a full chip are 8 to 11 % faster than in tiles of 128 rows and 32-row waves (32
+// heads of 2048 rows 206 -> 187 us, 128 of 4096 3026 -> 2691); in tiles of 128 rows (two waves, two workgroups to a CU that
+// fill each other's gaps) causal and ragged launches (128 causal heads of 4096 rows 1673 -> 1516, of 1024 147 -> 140, 300 of
+// 300 rows 91 -> 84).  A 64-row wave takes 1.6 times as long for a tile as a 32-row one: launches that do not fill the chip are
+// up to 1.7 times slower (16 heads of 1024 rows 35 -> 44).  Of 7200 launches 24 % take 64-row waves, 8 % faster in the mean; one in
+// a hundred of those is more than 2 % slower, 1.2 times at worst.  Launches that the 32-row waves run one sweep after the
+// other stay with them.
+BwdTiling pick_tiling(const BwdParams &p, int BH, int causal, int cus)
 {
-    if (slots < attn::kNumXcd || 2ll * BH * ((p.S_kv + 255) / 256 + (p.S_q + 255) / 256) < slots)
-        return false;   // (no launch of fewer tiles gained)
+    if (cus < attn::kNumXcd || 2ll * BH * ((p.S_kv + 255) / 256 + (p.S_q + 255) / 256) < cus)
+        return kRows128;   // (no launch of fewer tiles gained)
     BwdParams small = p;
     small.total_wg = BH * ((p.S_kv + 127) / 128);
     small.total_q = BH * ((p.S_q + 127) / 128);
-    if (sweeps_apart(small, causal, slots))
-        return false;
-    // (of 8300 launches 20 % take them, 7 % faster in the mean; 42 of those are more than 2 % slower, 1.16 times at worst: 14 causal
-    // heads of 5182 queries and 11160 keys.  A margin of 0.98 with a mask would gain a tenth more and lose in twice as many)
-    return launch_estimate(p, BH, causal, 256, kWalk256, slots) <
-           (causal ? 0.96f : 0.98f) * launch_estimate(p, BH, causal, 128, kWalk128, slots);
+    if (sweeps_apart(small, causal, cus))
+        return kRows128;
+    const float t32 = 0.975f * launch_estimate(p, BH, causal, kWalk128, cus);
+    const float t256 = launch_estimate(p, BH, causal, kWalk256, cus), t2 = launch_estimate(p, BH, causal, kWalk128TwoWaves, cus);
+    return t32 <= t256 && t32 <= t2 ? kRows128 : t256 <= t2 ? kRows256 : kRows128TwoWaves;
 }
 
 template <int D, typename ELEM>
@@ -209,23 +220,27 @@ int launch_hand(BwdParams p, int BH, int causal, hipStream_t stream, BwdTiling t
 {
     if ((long long)BH * ((p.S_kv + 127) / 128 + (p.S_q + 127) / 128) > 0x7fffffffLL - attn::kNumXcd)
         return ATTN_ERR_SHAPE;
-    const bool wide = D == 128 && (tiling == kAsDispatched ? wide_pays(p, BH, causal, attn::cu_count(attn::kNumXcd)) : tiling == kRows256);
-    const int rows = wide ? 256 : 128;
-    p.n_t = (p.S_kv + rows - 1) / rows;
-    p.n_tq = (p.S_q + rows - 1) / rows;
-    p.total_wg = BH * p.n_t;
-    p.total_q = BH * p.n_tq;
     const int cus = attn::cu_count(attn::kNumXcd);
     p.cus_per_xcd = cus > 0 ? cus / attn::kNumXcd : 32;
     const int rc = launch_delta<D, typename std::conditional<F16, _Float16, attn::bf16_t>::type>(p, stream);
     if (rc != ATTN_OK)
         return rc;
+    if (tiling == kAsDispatched)   // (while the Delta kernel runs)
+        tiling = D == 128 ? pick_tiling(p, BH, causal, cus) : kRows128;
+    const int rows = tiling == kRows256 ? 256 : 128;
+    p.n_t = (p.S_kv + rows - 1) / rows;
+    p.n_tq = (p.S_q + rows - 1) / rows;
+    p.total_wg = BH * p.n_t;
+    p.total_q = BH * p.n_tq;
     if constexpr (D == 128) {
-        if (wide)
-            return launch_sweeps(causal ? attn::attn_bwd_wide_kernel<true, F16> : attn::attn_bwd_wide_kernel<false, F16>,
-                                 attn::BwdWideLds::BYTES, p, causal, stream);
+        if (tiling == kRows256)
+            return launch_sweeps(causal ? attn::attn_bwd_wide_kernel<4, true, F16> : attn::attn_bwd_wide_kernel<4, false, F16>, 256,
+                                 attn::BwdWideLds<4>::BYTES, p, causal, stream);
+        if (tiling == kRows128TwoWaves)
+            return launch_sweeps(causal ? attn::attn_bwd_wide_kernel<2, true, F16> : attn::attn_bwd_wide_kernel<2, false, F16>, 128,
+                                 attn::BwdWideLds<2>::BYTES, p, causal, stream);
     }
-    return launch_sweeps(causal ? attn::attn_bwd_asm_kernel<D, true, F16> : attn::attn_bwd_asm_kernel<D, false, F16>,
+    return launch_sweeps(causal ? attn::attn_bwd_asm_kernel<D, true, F16> : attn::attn_bwd_asm_kernel<D, false, F16>, 256,
                          attn::BwdLds<D>::BYTES, p, causal, stream);
 }
 
@@ -377,18 +392,32 @@ extern "C" int attn_bwd_sweeps_apart(int heads, int S_q, int S_kv, int causal, i
     return sweeps_apart(p, causal, slots);
 }
 
-// Test-only, host only: whether a D = 128 launch takes owner tiles of 256 rows; est: the two estimates in us.
-extern "C" int attn_bwd_wide_pays(int heads, int S_q, int S_kv, int causal, int slots, float *est)
+// Test-only, host only: the i-th tile that XCD 0 takes up of a sweep (xcd_tiles), -1 behind the last, and the same from
+// wg_to_tile_n in *want.
+extern "C" int attn_bwd_xcd_tile(int heads, int n_t, int causal, long long head_bytes, int i, int *want)
+{
+    int at = 0, got = -1, bh = 0, t = -1;
+    xcd_tiles(heads, n_t, causal, head_bytes, [&](int x) { got = at++ == i ? x : got; });
+    if (causal && (long long)attn::kNumXcd * i < (long long)heads * n_t)
+        attn::wg_to_tile_n<true>(attn::kNumXcd * i, heads * n_t, n_t, head_bytes, bh, t);
+    *want = causal ? t : (long long)attn::kNumXcd * i < (long long)heads * n_t ? 0 : -1;
+    return got;
+}
+
+// Test-only, host only: the tiling that a D = 128 launch on `cus` compute units takes (1: tiles of 128 rows and 32-row waves, 2: of
+// 256 rows, 3: of 128 rows and 64-row waves); est: the three estimates in us.
+extern "C" int attn_bwd_pick_tiling(int heads, int S_q, int S_kv, int causal, int cus, float *est)
 {
     BwdParams p;
     p.S_q = S_q;
     p.S_kv = S_kv;
-    est[0] = launch_estimate(p, heads, causal, 128, kWalk128, slots);
-    est[1] = launch_estimate(p, heads, causal, 256, kWalk256, slots);
-    return wide_pays(p, heads, causal, slots);
+    est[0] = cus ? launch_estimate(p, heads, causal, kWalk128, cus) : 0.f;
+    est[1] = cus ? launch_estimate(p, heads, causal, kWalk256, cus) : 0.f;
+    est[2] = cus ? launch_estimate(p, heads, causal, kWalk128TwoWaves, cus) : 0.f;
+    return pick_tiling(p, heads, causal, cus);
 }
 
-// Test-only: attn_bwd / attn_bwd_f16 (D = 128, scale > 0) on owner tiles of 128 (tiling 1) or 256 rows (2).
+// Test-only: attn_bwd / attn_bwd_f16 (D = 128, scale > 0) in the tiling that is asked for (BwdTiling).
 extern "C" int attn_bwd_tiling(const void *q, const void *k, const void *v, const void *o, const void *d_o,
                                const float *lse, void *dq, void *dk, void *dv, float *delta_ws, int B, int H, int S_q,
                                int S_kv, int f16, int causal, float scale, void *stream, int tiling)

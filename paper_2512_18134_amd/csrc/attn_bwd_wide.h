@@ -1,9 +1,9 @@
 // attn_bwd_wide.h -- attention-backward sweeps whose waves own 64 rows (D = 128, one wave per SIMD).
 //
-// The sweeps of attn_bwd_asm.h with owner tiles of 256 rows: the same mathematics, the same order of sums, the same bits.
-// Every operand that a wave reads from LDS feeds two MFMAs, and a streamed tile serves twice as many rows, which is what
-// the sweeps of 32-row waves are bound by (gen_attn_bwd_wide_loop.py has the schedule).  Where owner tiles are few, or short
-// walks make what stands around the loop count, the smaller tiles keep more of the chip busy: wide_pays in attn_bwd.hip.
+// The sweeps of attn_bwd_asm.h with owner tiles of 256 rows (four waves) or of 128 (two waves, two workgroups to a CU): the same
+// mathematics, the same order of sums, the same bits.  Every operand that a wave reads from LDS feeds two MFMAs, which is
+// what the sweeps of 32-row waves are bound by (gen_attn_bwd_wide_loop.py has the schedule; with four waves a streamed tile
+// also serves twice as many rows).  Whether and which: pick_tiling in attn_bwd.hip.
 //
 // Streamed tiles of 32 rows in one 4-stage LDS ring; the owner's rows arrive in LDS as whole rows behind stage 0 and are in
 // registers before tiles 1 and 2 go out.  The loop's asm statement takes over once those loads are on their way.
@@ -12,13 +12,20 @@
 
 namespace attn {
 
-// LDS of a workgroup: the ring (stage: tile of the first tensor, tile of the second), the owner rows over stages 1-3 and
-// behind them [wave][tensor][64 rows], the LSE' / Delta ring (query owners: those of the owner's rows).  Gradients leave
-// through what lies around the owner rows, 32 rows of a wave at a time: waves 0 and 1 in stage 0, waves 2 and 3 at the end.
+// LDS of a workgroup of NW waves: the ring (stage: tile of the first tensor, tile of the second), the owner rows over it from
+// OWN on [wave][tensor][64 rows], the LSE' / Delta ring (query owners: those of the owner's rows).  Gradients leave through what
+// lies around the owner rows, 32 rows of a wave at a time.  Four waves: the owner rows lie behind stage 0.  Two waves, which
+// share the CU's 160 KB with two others: behind the first half of stage 0 (tile 0 of the second tensor goes out later).
+template <int NW>
 struct BwdWideLds {
-    static constexpr int NST = 4, TB = 32 * 128 * 2, STAGE = 2 * TB, OWN = STAGE, OWN_TENSOR = 64 * 128 * 2;
-    static constexpr int AUX = OWN + 4 * 2 * OWN_TENSOR, OUT_2 = AUX, BYTES = OUT_2 + 2 * TB;
-    static_assert(BYTES <= 160 * 1024 && AUX + 4 * 512 <= BYTES, "one workgroup per CU");
+    static constexpr int TB = 32 * 128 * 2, STAGE = 2 * TB, OWN = NW == 4 ? STAGE : TB, OWN_TENSOR = 64 * 128 * 2;
+    static constexpr int AUX = OWN + NW * 2 * OWN_TENSOR, OUT_1 = NW == 4 ? TB : AUX, OUT_2 = AUX + (NW == 4 ? 0 : TB);
+    static constexpr int BYTES = NW * 40 * 1024;
+    static __device__ __forceinline__ int out(int wave)   // 8 KB
+    {
+        return wave == 0 ? 0 : wave == 1 ? OUT_1 : OUT_2 + (wave - 2) * TB;
+    }
+    static_assert((NW == 4 ? OUT_2 + 2 * TB : OUT_1 + TB) <= BYTES && AUX + NW * 512 <= BYTES && 4 * STAGE <= AUX, "160 KB per CU");
 };
 
 // The tile that a workgroup has taken up, and whether its owner rows are on their way to LDS
@@ -27,15 +34,15 @@ struct BwdWideTile {
     bool on_its_way;
 };
 
-template <bool CAUSAL, bool KEY_OWNER, bool F16>
+template <int NW, bool CAUSAL, bool KEY_OWNER, bool F16>
 __device__ __forceinline__ void bwd_wide_sweep(const BwdParams &p, const BwdQueue &queue, const int wave, int &pass,
                                                BwdWideTile &tile)
 {
     typedef typename std::conditional<F16, ElemF16, ElemBF16>::type E;
     typedef typename E::t elem_t;
-    typedef BwdWideLds Lds;
-    constexpr int D = 128, BN = 32, NW = 4, BO = NW * 64, CPR = D / 8, KS = D / 16, DB = D / 32, ROWB = D * 2, TB = Lds::TB;
-    constexpr int NLD = TB / (NW * 1024), NSET = KEY_OWNER ? 2 : 1;
+    typedef BwdWideLds<NW> Lds;
+    constexpr int D = 128, BN = 32, BO = NW * 64, CPR = D / 8, KS = D / 16, DB = D / 32, ROWB = D * 2, TB = Lds::TB;
+    constexpr int NLD = TB / (NW * 1024), NVOFF = 2, NSET = KEY_OWNER ? 2 : 1;
 
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const uint32_t lds0 = (uint32_t)(uintptr_t)(ATTN_LDS_PTR(unsigned char))smem;
@@ -128,11 +135,11 @@ __device__ __forceinline__ void bwd_wide_sweep(const BwdParams &p, const BwdQueu
         // ---- addresses inside a tile (the loop keeps them in the registers they come in)
         const int lane = lane_id();
         const int lq = lane & 31, g = lane >> 5;
-        typename U32Vec<NLD>::type dma_voff_v;
+        typename U32Vec<NVOFF>::type dma_voff_v;
 #pragma unroll
-        for (int i = 0; i < NLD; ++i) {
+        for (int i = 0; i < NVOFF; ++i) {
             const int row = 4 * (i * NW + wave) + lane / CPR;
-            U32Vec<NLD>::set(dma_voff_v, i, row * ROWB + (uint32_t)(((lane % CPR) ^ swz<D>(row)) * 16));
+            U32Vec<NVOFF>::set(dma_voff_v, i, row * ROWB + (uint32_t)(((lane % CPR) ^ swz<D>(row)) * 16));
         }
         const uint32_t lds_wave = lds0 + wave * 1024, lds_aux = lds0 + Lds::AUX;
         const uint32_t aux_sel = g ? (uint32_t)(p.n_rows * 4) : 0u;
@@ -144,9 +151,11 @@ __device__ __forceinline__ void bwd_wide_sweep(const BwdParams &p, const BwdQueu
                 dma4(lds_aux + wave * 512 + k * 256, aux_head, (uint32_t)min(o0w + 32 * k + lq, S_own - 1) * 4 + aux_sel);
 #pragma unroll
         for (int i = 0; i < NLD; ++i) {
-            const uint32_t voff = (uint32_t)min(t_begin * BN + (int)(dma_voff_v[i] / ROWB), str_m1) * ROWB + dma_voff_v[i] % ROWB;
+            const uint32_t row = dma_voff_v[i % NVOFF] / ROWB + 4 * NW * NVOFF * (i / NVOFF);
+            const uint32_t voff = (uint32_t)min(t_begin * BN + (int)row, str_m1) * ROWB + dma_voff_v[i % NVOFF] % ROWB;
             dma16(lds_wave + i * NW * 1024, t1_head, voff);
-            dma16(lds_wave + TB + i * NW * 1024, t2_head, voff);
+            if (NW == 4)
+                dma16(lds_wave + TB + i * NW * 1024, t2_head, voff);
         }
         if (KEY_OWNER)
             dma4(lds_aux, aux_head, (uint32_t)min(t_begin * BN + lq, str_m1) * 4 + aux_sel);
@@ -182,14 +191,22 @@ __device__ __forceinline__ void bwd_wide_sweep(const BwdParams &p, const BwdQueu
         const float c_log2e = p.c;
         f32x16 acc[NSET * 2 * DB];
 
-        if constexpr (KEY_OWNER && !F16) {
-#include "generated/attn_bwd_wide_loop_kv.inc"
-        } else if constexpr (!F16) {
-#include "generated/attn_bwd_wide_loop_q.inc"
-        } else if constexpr (KEY_OWNER) {
-#include "generated/attn_bwd_wide_loop_kv_f16.inc"
-        } else {
-#include "generated/attn_bwd_wide_loop_q_f16.inc"
+        if constexpr (NW == 4 && KEY_OWNER && !F16) {
+#include "generated/attn_bwd_wide_loop_kv_w4.inc"
+        } else if constexpr (NW == 4 && !KEY_OWNER && !F16) {
+#include "generated/attn_bwd_wide_loop_q_w4.inc"
+        } else if constexpr (NW == 4 && KEY_OWNER && F16) {
+#include "generated/attn_bwd_wide_loop_kv_w4_f16.inc"
+        } else if constexpr (NW == 4 && !KEY_OWNER && F16) {
+#include "generated/attn_bwd_wide_loop_q_w4_f16.inc"
+        } else if constexpr (NW == 2 && KEY_OWNER && !F16) {
+#include "generated/attn_bwd_wide_loop_kv_w2.inc"
+        } else if constexpr (NW == 2 && !KEY_OWNER && !F16) {
+#include "generated/attn_bwd_wide_loop_q_w2.inc"
+        } else if constexpr (NW == 2 && KEY_OWNER && F16) {
+#include "generated/attn_bwd_wide_loop_kv_w2_f16.inc"
+        } else if constexpr (NW == 2 && !KEY_OWNER && F16) {
+#include "generated/attn_bwd_wide_loop_q_w2_f16.inc"
         }
 
         // ---- epilogue: dK = -scale * acc[0..], dV = acc[2 DB..] (or dQ = -scale * acc), 16-bit, row = owner, through LDS in whole
@@ -202,7 +219,7 @@ __device__ __forceinline__ void bwd_wide_sweep(const BwdParams &p, const BwdQueu
             locate(next);
         const int e_lane = lane_id();
         const int e_lq = e_lane & 31, e_g = e_lane >> 5;
-        unsigned char *const stage = smem + (wave < 2 ? wave * TB : Lds::OUT_2 + (wave - 2) * TB);
+        unsigned char *const stage = smem + Lds::out(wave);
         auto write_out = [&](const f32x16 *a, auto value, elem_t *out_head, int k) {
             typedef typename E::x2 ex2;
             typedef typename E::x4 ex4;
@@ -246,15 +263,15 @@ __device__ __forceinline__ void bwd_wide_sweep(const BwdParams &p, const BwdQueu
     }
 }
 
-template <bool CAUSAL, bool F16>
-__global__ __launch_bounds__(256) void attn_bwd_wide_kernel(const BwdParams p)
+template <int NW, bool CAUSAL, bool F16>
+__global__ __launch_bounds__(NW * 64) void attn_bwd_wide_kernel(const BwdParams p)
 {
     const BwdQueue queue(p.total_wg, p.total_q);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int pass = 0;
     BwdWideTile tile = {0, 0, false};
-    bwd_wide_sweep<CAUSAL, true, F16>(p, queue, wave, pass, tile);
-    bwd_wide_sweep<CAUSAL, false, F16>(p, queue, wave, pass, tile);
+    bwd_wide_sweep<NW, CAUSAL, true, F16>(p, queue, wave, pass, tile);
+    bwd_wide_sweep<NW, CAUSAL, false, F16>(p, queue, wave, pass, tile);
 }
 
 }  // namespace attn

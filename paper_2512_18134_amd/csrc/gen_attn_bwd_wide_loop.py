@@ -31,7 +31,7 @@ queries all lie before its keys, waves without rows) stand by: the barrier and t
 
 Hazards as in gen_attn_bwd_loop.py; the tests check them on the emitted text (asm_emit.check_stream).
 
-usage: gen_attn_bwd_wide_loop.py <kv|q> <out.inc> [bf16|f16]
+usage: gen_attn_bwd_wide_loop.py <kv|q> <waves: 2|4> <out.inc> [bf16|f16]
 """
 import os
 import sys
@@ -69,15 +69,16 @@ def deal(ops, fixed_cost, first, n, cost=lambda ins: 2.5 if ins.startswith("v_ex
 
 
 class WideGen(Emitter):
-    D, NW, BN, NST = 128, 4, 32, 4
+    D, BN, NST = 128, 32, 4
     KS, DB, ROWB = 8, 4, 256
     TB = BN * ROWB                  # one tensor's tile
     SB = 2 * TB                     # a stage: tile of the first tensor, tile of the second
-    NLD = TB // (NW * 1024)
     AHEAD = 3                       # tile j + AHEAD is loaded in iteration j
 
-    def __init__(self, key_owner, dtype="bf16", NF=None, PFD=None, W=None):
+    def __init__(self, key_owner, dtype="bf16", NW=4, NF=None, PFD=None, W=None):
         Emitter.__init__(self)
+        self.NW = NW                # waves of a workgroup
+        self.NLD = self.TB // (NW * 1024)
         assert dtype in ("bf16", "f16")
         self.KO, self.dtype = bool(key_owner), dtype
         self.mfma = "v_mfma_f32_32x32x16_" + dtype
@@ -108,7 +109,10 @@ class WideGen(Emitter):
         self.AUXL = take(8 if self.KO else 2)
         r += r & 1
         self.ROFF, self.TOFF = take(8), take(8)
-        self.DVOFF = take(self.NLD)
+        # a wave's direct loads of a tile bring rows 4 NW apart; from 16 rows on the swizzle repeats, and the rest is 4 KB
+        # more for every 16 rows
+        self.NVOFF = 2
+        self.DVOFF = take(self.NVOFF)
         self.AOFF = take(1)
         if self.KO:
             self.AUXV, self.THRLO = take(1), take(1)
@@ -125,7 +129,8 @@ class WideGen(Emitter):
         self.s_own, self.s_j, self.s_tk = 48, 49, 50
         self.s_ptr1, self.s_ptr2, self.s_ptra = 52, 54, 56
         self.s_row, self.s_255, self.s_dyn, self.s_dyna = 58, 59, 60, 61
-        self.s_m0 = 62
+        self.s_far = 62             # (a pair) streamed tile plus 4 KB
+        self.s_m0 = 64
         self.plan()
 
     # ------------------------------------------------------------ MFMA program
@@ -295,35 +300,45 @@ class WideGen(Emitter):
     # ------------------------------------------------------------------- DMA
     def dma_fast(self, stage):
         out = []
-        for i in range(self.NLD):
+        for far in range(self.NLD // self.NVOFF):
             for t, ptr in ((0, self.s_ptr1), (1, self.s_ptr2)):
-                out += ["s_add_u32 m0, s%d, %d" % (self.s_lds, stage * self.SB + t * self.TB + i * self.NW * 1024),
-                        "s_nop 0",
-                        "global_load_lds_dwordx4 v%d, %s" % (self.DVOFF + i, self.sr(ptr, 2))]
+                if far:
+                    out += ["s_add_u32 s%d, s%d, 4096" % (self.s_far, ptr), "s_addc_u32 s%d, s%d, 0" % (self.s_far + 1, ptr + 1)]
+                    ptr = self.s_far
+                for k in range(self.NVOFF):
+                    i = far * self.NVOFF + k
+                    out += ["s_add_u32 m0, s%d, %d" % (self.s_lds, stage * self.SB + t * self.TB + i * self.NW * 1024),
+                            "s_nop 0",
+                            "global_load_lds_dwordx4 v%d, %s" % (self.DVOFF + k, self.sr(ptr, 2))]
         if self.KO:                 # 32 LSE' (lanes 0-31) and 32 Delta (lanes 32-63) values
             out += ["s_add_u32 m0, s%d, %d" % (self.s_ldsaux, stage * 256),
                     "s_nop 0",
                     "global_load_lds_dword v%d, %s" % (self.AUXV, self.sr(self.s_ptra, 2))]
         return out
 
-    def dma_clamped(self, stage):
-        """Tile s_tk with its rows clamped to the last one; stage None: its ring place is in s_dyn / s_dyna."""
+    def dma_clamped(self, stage, second=False):
+        """Tile s_tk with its rows clamped to the last one; stage None: its ring place is in s_dyn / s_dyna.  second: of the
+        second tensor only."""
         e, T = self.e, self.T
         lds = (self.s_lds, self.s_ldsaux) if stage is not None else (self.s_dyn, self.s_dyna)
         at = stage or 0
         e("s_lshl_b32 s%d, s%d, 5" % (self.s_row, self.s_tk))
         e("s_mov_b32 s%d, 255" % self.s_255)
         for i in range(self.NLD):
-            e("v_lshrrev_b32 v%d, 8, v%d" % (T, self.DVOFF + i))          # an offset is 256 row + chunk
+            if i == self.NVOFF:
+                e("s_add_i32 s%d, s%d, 16" % (self.s_row, self.s_row))
+            e("v_lshrrev_b32 v%d, 8, v%d" % (T, self.DVOFF + i % self.NVOFF))      # an offset is 256 row + chunk
             e("v_add_u32 v%d, s%d, v%d" % (T, self.s_row, T))
             e("v_min_i32 v%d, s%d, v%d" % (T, self.s_strm1, T))
             e("v_lshlrev_b32 v%d, 8, v%d" % (T, T))
-            e("v_and_or_b32 v%d, v%d, s%d, v%d" % (T, self.DVOFF + i, self.s_255, T))
-            for t, base in ((0, self.s_t1base), (1, self.s_t2base)):
+            e("v_and_or_b32 v%d, v%d, s%d, v%d" % (T, self.DVOFF + i % self.NVOFF, self.s_255, T))
+            for t, base in ((0, self.s_t1base), (1, self.s_t2base))[1 if second else 0:]:
                 e("s_add_u32 m0, s%d, %d" % (lds[0], at * self.SB + t * self.TB + i * self.NW * 1024))
                 e("s_nop 0")
                 e("global_load_lds_dwordx4 v%d, %s" % (T, self.sr(base, 2)))
-        if self.KO:
+        if self.KO and not second:
+            if self.NLD > self.NVOFF:
+                e("s_sub_i32 s%d, s%d, 16" % (self.s_row, self.s_row))
             e("v_mbcnt_lo_u32_b32 v%d, -1, 0" % self.T2)
             e("v_mbcnt_hi_u32_b32 v%d, -1, v%d" % (self.T2, self.T2))
             e("v_and_b32 v%d, 31, v%d" % (self.T2, self.T2))              # the row that this lane brings
@@ -454,7 +469,7 @@ class WideGen(Emitter):
             e("v_accvgpr_write_b32 a%d, 0" % (self.ACC + i))
         e("s_waitcnt vmcnt(0)")
         e("s_barrier")                       # every wave's part of tile 0 is in LDS
-        e("s_mov_b32 s%d, 0x80008000" % self.s_row)
+        e("s_mov_b32 s%d, 0x80008000" % self.s_dyn)
         own = self.vr if self.KO else self.ar
         raw = self.B2 if self.KO else self.S[0][0]      # (query owners: 64 registers that nothing lives in yet)
         raw = [raw[0], raw[1]] if self.KO else [raw, raw + 32]
@@ -470,10 +485,13 @@ class WideGen(Emitter):
                 e("ds_read_b32 v%d, v%d offset:%d" % (self.AUXD[k], self.AOFF, 256 * k + 128))
         e("s_waitcnt lgkmcnt(0)")
         e("s_barrier")                       # every wave has its rows in registers: stages 1 to 3 are free
+        if self.NW < 4:                      # ... and the second half of stage 0, which 160 KB have no room for besides
+            e("s_mov_b32 s%d, s%d" % (self.s_tk, self.s_tbeg))
+            self.dma_clamped(0, second=True)
         e("s_add_i32 s%d, s%d, 1" % (self.s_tk, self.s_tbeg))
         for k in range(2):
             for i in range(32):
-                e("v_xor_b32 v%d, s%d, v%d" % (raw[k] + i, self.s_row, raw[k] + i))
+                e("v_xor_b32 v%d, s%d, v%d" % (raw[k] + i, self.s_dyn, raw[k] + i))
         if not self.KO:
             for k in range(2):
                 for i in range(32):
@@ -483,6 +501,9 @@ class WideGen(Emitter):
         for stage in range(1, self.AHEAD):
             self.dma_clamped(stage)
             e("s_add_i32 s%d, s%d, 1" % (self.s_tk, self.s_tk))
+        if self.NW < 4:
+            e("s_waitcnt vmcnt(%d)" % (2 * self.NGRP))
+            e("s_barrier")                   # all of tile 0 is in LDS
 
     def generate(self):
         L, e = self.lab, self.e
@@ -528,8 +549,8 @@ class WideGen(Emitter):
     # ----------------------------------------------------------- C++ wrapper
     def emit_inc(self):
         self.generate()
-        out = ["// Generated by gen_attn_bwd_wide_loop.py %s %s -- do not edit.  Main loop of bwd_wide_sweep<*, %s, %s>."
-               % ("kv" if self.KO else "q", self.dtype, "true" if self.KO else "false", "true" if self.dtype == "f16" else "false"),
+        out = ["// Generated by gen_attn_bwd_wide_loop.py %s %d %s -- do not edit.  Main loop of bwd_wide_sweep<%d, *, %s, %s>."
+               % ("kv" if self.KO else "q", self.NW, self.dtype, self.NW, "true" if self.KO else "false", "true" if self.dtype == "f16" else "false"),
                "// VGPRs used: %d, AGPRs used: %d.  MFMA slots per iteration: %d." % (self.NV, self.NA, self.NM),
                "asm volatile("]
         out += ['    "%s\\n\\t"' % ln for ln in self.lines]
@@ -541,7 +562,7 @@ class WideGen(Emitter):
             pinned.update(range(base, base + n))
         vin(self.ROFF, 8, "roff_v")
         vin(self.TOFF, 8, "toff_v")
-        vin(self.DVOFF, self.NLD, "dma_voff_v")
+        vin(self.DVOFF, self.NVOFF, "dma_voff_v")
         vin(self.AOFF, 1, "aux_off")
         if self.KO:
             vin(self.AUXV, 1, "aux_voff")
@@ -564,10 +585,10 @@ class WideGen(Emitter):
 if __name__ == "__main__":
     # --nf / --pfd / --w: fragment buffers, groups read ahead, groups per wait; a library build passes none of them
     args, opts = sys.argv[1:], {}
-    while len(args) > 2 and args[-2] in ("--nf", "--pfd", "--w"):
+    while len(args) > 3 and args[-2] in ("--nf", "--pfd", "--w"):
         opts[args[-2]] = int(args[-1])
         args = args[:-2]
-    text = WideGen(args[0] == "kv", dtype=args[2] if len(args) > 2 else "bf16", NF=opts.get("--nf"), PFD=opts.get("--pfd"),
+    text = WideGen(args[0] == "kv", dtype=args[3] if len(args) > 3 else "bf16", NW=int(args[1]), NF=opts.get("--nf"), PFD=opts.get("--pfd"),
                    W=opts.get("--w")).emit_inc()
-    with open(args[1], "w") as f:
+    with open(args[2], "w") as f:
         f.write(text)

@@ -15,11 +15,11 @@ import debug_lib  # noqa: E402
 from test_generated_loops import ROOT, asm_emit  # noqa: E402
 import gen_attn_bwd_wide_loop  # noqa: E402
 
-SWEEPS = [(True, "bf16"), (True, "f16"), (False, "bf16"), (False, "f16")]
+SWEEPS = [(ko, nw, dt) for ko in (True, False) for nw in (2, 4) for dt in ("bf16", "f16")]
 
 
-def make(key_owner, dtype="bf16"):
-    g = gen_attn_bwd_wide_loop.WideGen(key_owner, dtype=dtype)
+def make(key_owner, waves, dtype="bf16"):
+    g = gen_attn_bwd_wide_loop.WideGen(key_owner, dtype=dtype, NW=waves)
     g.generate()
     return g, [l.replace("%=", "") for l in g.lines]
 
@@ -29,9 +29,9 @@ def entry(key_owner):
     return ["STANDBYEND_"] if key_owner else []
 
 
-@pytest.mark.parametrize("key_owner,dtype", SWEEPS)
-def test_main_path_and_detours(key_owner, dtype):
-    g, lines = make(key_owner, dtype)
+@pytest.mark.parametrize("key_owner,waves,dtype", SWEEPS)
+def test_main_path_and_detours(key_owner, waves, dtype):
+    g, lines = make(key_owner, waves, dtype)
     path = asm_emit.walk(lines, take=entry(key_owner), loop_label="BODY0_", loop_visits=2)
     assert sum(l.startswith("v_mfma") for l in path) == 16 + 2 * g.NST * g.NM
     assert asm_emit.check_stream(path) == len(path)
@@ -54,12 +54,14 @@ def test_main_path_and_detours(key_owner, dtype):
 
 
 def intervals(g, lines, n, n_wave, t_full, t_begin=0):
-    """Per barrier interval the loads (tensor, tile, ring place) of a wave's run, behind the two barriers of the set-up."""
+    """Per barrier interval the loads (tensor, tile, ring place) of a wave's run, from the second barrier of the set-up on (two
+    waves: the third follows its loads; the intervals on both sides of it are one here)."""
     sg = {g.s_ntiles: n, g.s_nw: n_wave, g.s_tfull: t_full, g.s_tbeg: t_begin, g.s_jlo: 0, g.s_jhi: n, g.s_strm1: 10 ** 6,
           g.s_lds: 1 << 20, g.s_ldsaux: 1 << 24}
-    for base, at in ((g.s_t1base, 0), (g.s_t2base, 0), (g.s_auxbase, 0)):
+    for base, at in ((g.s_t1base, 0), (g.s_t2base, 1 << 28), (g.s_auxbase, 0)):
         sg[base] = at
-    bases = {"1": (g.s_t1base, g.s_ptr1), "2": (g.s_t2base, g.s_ptr2), "aux": (g.s_auxbase, g.s_ptra)}
+    # (the far half of a tile goes through one pair for both tensors: told apart by the address)
+    bases = {"1": (g.s_t1base, g.s_ptr1), "2": (g.s_t2base, g.s_ptr2), "aux": (g.s_auxbase, g.s_ptra), "far": (200, g.s_far)}
     out = [[]]
     for e in asm_emit.run_scalar(lines, sg, g.BN, g.TB, bases):
         if e[0] == "barrier":
@@ -67,16 +69,18 @@ def intervals(g, lines, n, n_wave, t_full, t_begin=0):
         elif e[1] == "aux":
             out[-1].append(("aux", (e[3] - (1 << 24)) // 256))
         else:
-            out[-1].append((e[1], e[2], (e[3] - (1 << 20))))
-    return out
+            which, tile = ("12"[e[2] >= (1 << 28) // g.TB], e[2] % ((1 << 28) // g.TB)) if e[1] == "far" else e[1:3]
+            out[-1].append((which, tile, (e[3] - (1 << 20))))
+    return out if g.NW == 4 else out[:2] + [out[2] + out[3]] + out[4:]
 
 
+@pytest.mark.parametrize("waves", [2, 4])
 @pytest.mark.parametrize("key_owner", [True, False])
-def test_waves_keep_step(key_owner):
-    """n tiles: two barriers of the set-up and one per tile for every wave, and between them the same loads, whichever tiles
+def test_waves_keep_step(key_owner, waves):
+    """n tiles: the barriers of the set-up and one per tile for every wave, and between them the same loads, whichever tiles
     the wave computes; iteration j brings tile j + 3 into stage (j + 3) % 4."""
-    g, lines = make(key_owner)
-    own = [0, 2, 4, 6]
+    g, lines = make(key_owner, waves)
+    own = [0, 2, 4, 6][:waves]
     for n in (0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 13) if key_owner else (1, 2, 3, 4, 5, 6, 7, 8, 9, 13):
         for t_begin in (0, 3):
             for t_full in sorted({0, t_begin, t_begin + max(n - 1, 0), t_begin + n}):
@@ -84,8 +88,10 @@ def test_waves_keep_step(key_owner):
                 assert len(whole) == n + 3
                 for j, loads in enumerate(whole[2:], -1):     # (the set-up's tiles 1 and 2 stand in the interval of "j = -1")
                     tiles = (1, 2) if j == -1 else (j + 3,)
-                    want = [(t, t_begin + k, k % 4 * g.SB + (t == "2") * g.TB + i * 4096)
+                    want = [(t, t_begin + k, k % 4 * g.SB + (t == "2") * g.TB + i * 1024 * waves)
                             for k in tiles for t in ("1", "2") for i in range(g.NLD)]
+                    if j == -1 and waves == 2:
+                        want += [("2", t_begin, g.TB + i * 2048) for i in range(g.NLD)]
                     assert sorted(l for l in loads if l[0] != "aux") == sorted(want), (n, t_begin, t_full, j)
                     assert [l[1] for l in loads if l[0] == "aux"] == ([k % 4 for k in tiles] if key_owner else [])
                 parts = [x for x in own if x < n] + [n] if key_owner else range(0, n)
@@ -94,16 +100,32 @@ def test_waves_keep_step(key_owner):
                     assert [sorted(x) for x in part] == [sorted(x) for x in whole], (n, n_wave, t_full)
 
 
-def test_the_rule_between_owner_tiles_of_128_and_256_rows():
-    pays = ctypes.CDLL(debug_lib.PATH).attn_bwd_wide_pays
-    pays.restype, pays.argtypes = ctypes.c_int, [ctypes.c_int] * 5 + [ctypes.POINTER(ctypes.c_float)]
-    est = (ctypes.c_float * 2)()
-    for heads, s_q, s_kv, causal, slots, want in [
-            (128, 4096, 4096, 0, 256, 1), (128, 4096, 4096, 1, 256, 1), (32, 2048, 2048, 0, 256, 1), (16, 16384, 16384, 0, 256, 1),
-            (16, 1024, 1024, 0, 256, 0), (1, 1, 1, 0, 256, 0), (1, 1, 1, 1, 256, 0), (123, 72, 5938, 0, 256, 0),
-            (500, 300, 300, 0, 256, 0), (32768, 1, 1, 1, 256, 0), (128, 4096, 4096, 0, 0, 0), (1 << 20, 64, 64, 0, 256, 0)]:
-        assert pays(heads, s_q, s_kv, causal, slots, est) == want, (heads, s_q, s_kv, causal, slots)
-        assert slots == 0 or (0 < est[0] < 1e9 and 0 < est[1] < 1e9)
+def test_the_rule_between_the_tilings():
+    pick = ctypes.CDLL(debug_lib.PATH).attn_bwd_pick_tiling
+    pick.restype, pick.argtypes = ctypes.c_int, [ctypes.c_int] * 5 + [ctypes.POINTER(ctypes.c_float)]
+    est = (ctypes.c_float * 3)()
+    for heads, s_q, s_kv, causal, cus, want in [
+            (128, 4096, 4096, 0, 256, 2), (32, 2048, 2048, 0, 256, 2), (16, 16384, 16384, 0, 256, 2), (128, 1024, 1024, 1, 256, 3),
+            (300, 300, 300, 0, 256, 3), (16, 1024, 1024, 0, 256, 1), (1, 1, 1, 0, 256, 1), (1, 1, 1, 1, 256, 1),
+            (123, 72, 5938, 0, 256, 1), (128, 4096, 4096, 0, 0, 1)]:
+        assert pick(heads, s_q, s_kv, causal, cus, est) == want, (heads, s_q, s_kv, causal, cus, list(est))
+    for heads, s_q, s_kv in [(1, 1, 1), (32768, 1, 1), (1 << 20, 64, 64), (3, 8000000, 1), (1, 1, 8000000)]:
+        for causal in (0, 1):
+            assert pick(heads, s_q, s_kv, causal, 256, est) in (1, 2, 3) and all(0 < x < 1e9 for x in est)
+
+
+def test_tiles_of_an_xcd_in_its_queues_order():
+    tile = ctypes.CDLL(debug_lib.PATH).attn_bwd_xcd_tile
+    tile.restype, tile.argtypes = ctypes.c_int, [ctypes.c_int] * 3 + [ctypes.c_longlong, ctypes.c_int, ctypes.POINTER(ctypes.c_int)]
+    want = ctypes.c_int()
+    for heads in (1, 3, 7, 8, 9, 16, 21, 40, 130):
+        for n_t in (1, 2, 5, 9, 33):
+            for head_bytes in (4 * 256 * 128, 4 * 3000 * 128, 4 * 20000 * 128):
+                for causal in (0, 1):
+                    n = (heads * n_t + 7) // 8
+                    for i in range(n + 1):
+                        assert tile(heads, n_t, causal, head_bytes, i, want) == want.value, (heads, n_t, head_bytes, causal, i)
+                    assert want.value == -1
 
 
 def test_registers_of_the_compiled_kernels(tmp_path):
@@ -125,4 +147,4 @@ def test_registers_of_the_compiled_kernels(tmp_path):
         value = lambda key: int(re.search(r"\.%s:\s+(\d+)" % key, block).group(1))
         assert value("private_segment_fixed_size") == 0 and value("vgpr_spill_count") == 0 and value("vgpr_count") <= 512
         seen += 1
-    assert seen == 4          # causal, element type
+    assert seen == 8          # waves, causal, element type
