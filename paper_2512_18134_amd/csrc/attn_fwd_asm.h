@@ -98,6 +98,10 @@ struct FwdTiling {
     // 32-row waves that test their tiles' row sums in pairs (gen_attn_loop.py, PairedGen): the sums pass through LDS
     static constexpr bool PAIRED = D == 128 && QB == 1 && SB == 1 && G == 1;
     static constexpr int XCH_SUMS = G * RING_BYTES, XCH_SUMS_BYTES = PAIRED ? 2 * NW * 64 * 4 : 0;
+    // fp32 partial rows of a split-KV range leave in whole rows where launches with many queries come (stored by the lanes
+    // that hold them, a wave-wide store touches 32 rows with 16 bytes each): 16 heads of 400 queries and 20000 keys, D = 64, 53.2
+    // -> 51.3 us; one query: 28.8 -> 29.1, which the 4-wave tiling is for
+    static constexpr bool WHOLE_PARTS = SPLIT && (QB == 2 || (D == 64 && NW == 8));
     static constexpr int LDS_BYTES = XCH_SUMS + XCH_SUMS_BYTES + (HAS_STAGE ? STAGE_BYTES : 0);
     // Persistent workgroups (see attn_fwd_asm_kernel) wherever the loop leaves the compiler registers to carry
     // a tile's state across it: the 8-wave D = 128 loop assigns all 256 VGPRs itself, and a split-KV launch
@@ -449,6 +453,40 @@ __global__ __launch_bounds__(NW * G * 64, (D == 64 && NW == 4) || (D == 128 && Q
         }
         if constexpr (SPLIT) {
             const size_t n_rows = (size_t)(p.total_wg / (p.n_qt * p.n_split)) * p.S_q;
+            if constexpr (T::WHOLE_PARTS) {
+                // whole rows through LDS, as below: 32 fp32 rows of a wave at a time, in the rings
+                constexpr int FCPR = D / 4, FROWB = D * 4;   // 16-byte chunks, bytes of a row
+                static_assert(NW * 32 * FROWB <= T::RING_BYTES, "the partial rows are staged in the rings");
+                unsigned char *stage = o_stage + wave * 32 * FROWB;
+#pragma unroll
+                for (int qb = 0; qb < QB; ++qb) {
+#pragma unroll
+                    for (int db = 0; db < DB; ++db)
+#pragma unroll
+                        for (int rb = 0; rb < 4; ++rb) {
+                            const f32x16 &oa = o_acc[qb * DB + db];
+                            const f32x4 w = {oa[4 * rb + 0] * inv[qb], oa[4 * rb + 1] * inv[qb], oa[4 * rb + 2] * inv[qb],
+                                             oa[4 * rb + 3] * inv[qb]};
+                            const int chunk = (8 * db + 2 * rb + g) ^ (lq & (FCPR - 1));
+                            *reinterpret_cast<f32x4 *>(stage + lq * FROWB + chunk * 16) = w;
+                        }
+                    const int row0 = t.q0 + (wave * QB + qb) * 32;
+                    const int rows_left = p.S_q - row0;
+                    const size_t first = (size_t)t.split * n_rows + (size_t)t.bh * p.S_q + row0;
+                    float *blk = p.o_part + first * D;
+#pragma unroll
+                    for (int i = 0; i < 32 * FCPR / 64; ++i) {
+                        const int idx = i * 64 + lane;
+                        const int r = idx / FCPR, c = idx % FCPR;
+                        const f32x4 w = *reinterpret_cast<const f32x4 *>(stage + r * FROWB + ((c ^ (r & (FCPR - 1))) * 16));
+                        if (r < rows_left)
+                            *reinterpret_cast<f32x4 *>(blk + (size_t)r * D + c * 4) = w;
+                    }
+                    if (lq < rows_left && g == 0)
+                        p.lse_part[first + lq] = lse_row[qb];
+                }
+                return;
+            }
 #pragma unroll
             for (int qb = 0; qb < QB; ++qb) {
                 const int qrow = qcol(t, qb);
