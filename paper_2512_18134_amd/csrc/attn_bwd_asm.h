@@ -5,7 +5,7 @@
 // waves owns 128 keys (KEY_OWNER) or 128 queries and streams the other side; the owner index is the
 // MFMA column = the lane.  The steady-state loop -- the three-stage modulo schedule described in
 // gen_attn_bwd_loop.py -- is one inline-asm statement generated by that script, with the accumulators
-// and the owner's rows in AGPRs.  This file does what surrounds the loop: work decomposition,
+// and the owner's rows in AGPRs at D = 128.  This file does what surrounds the loop: work decomposition,
 // addressing, the start of the stream, S(0)/dP(0), and the epilogue.
 //
 // Streamed tiles of 32 rows in two 6-stage LDS rings (2 * 6 * 32 * D * 2 bytes) plus a ring of
@@ -413,13 +413,13 @@ __device__ __forceinline__ void bwd_sweep(const BwdParams &p, const BwdQueue &qu
     }
 }
 
-// At D = 64 two workgroups share a CU: 256 registers a wave (VGPRs and AGPRs together) must hold either sweep, which a
+// At D = 64 two workgroups share a CU: 256 registers a wave (all of them VGPRs) must hold either sweep, which a
 // test of the compiled kernel checks.  A lone wave per SIMD is bound by the instructions it can issue (matrix pipe 43 %
 // busy); two of them fill each other's gaps.  Whole call against one workgroup per CU: 16 heads of 4096 rows 236 -> 223
 // us, causal 139 -> 125; 128 heads of 512 rows 46.6 -> 39.9; 512 heads of 300 rows, causal 84 -> 71.  Where one
 // workgroup per CU is all there is, the half as many operand buffers cost 2-4 % (16 heads of 1024 rows 22.6 -> 23.1).
 template <int D, bool CAUSAL, bool F16>
-__global__ __launch_bounds__(256) void attn_bwd_asm_kernel(const BwdParams p)
+__global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_bwd_asm_kernel(const BwdParams p)
 {
     const BwdQueue queue(p.total_wg, p.total_q);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);

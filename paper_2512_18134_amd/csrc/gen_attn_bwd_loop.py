@@ -24,7 +24,7 @@ instructions it issues, at long D = 128 launches by the power they take): 16 hea
 D = 64 242 -> 230 us; the results' distance from exact ones does not change (2.4e-3 bf16, 3.0e-4 fp16).
 
 Registers are assigned here: the accumulators and the owner's K/V (or Q/dO) rows, which only the
-matrix pipe touches, live in AGPRs; S, dP, P, dS and all addresses in VGPRs.  Streamed tiles
+matrix pipe touches, live in AGPRs at D = 128; S, dP, P, dS and all addresses in VGPRs.  Streamed tiles
 arrive by direct global->LDS loads into two 6-stage rings, four tiles ahead, one barrier per tile;
 the key-owner sweep also streams 32 LSE' and 32 Delta values per tile into a small ring.
 
@@ -54,7 +54,7 @@ DEFAULTS = {
     (True, 128):  dict(NF=8, PFD=6, W=2),
     (False, 128): dict(NF=8, PFD=4, W=2),
     (True, 64):   dict(NF=4, PFD=3, W=1),      # (what 256 registers a wave leave room for)
-    (False, 64):  dict(NF=4, PFD=2, W=1),
+    (False, 64):  dict(NF=6, PFD=4, W=2),
 }
 
 
@@ -89,19 +89,23 @@ class Gen(Emitter):
         self.NM = 2 * self.NC + 2 * self.KS          # MFMA slots per iteration
         self.NGRP = 2 * self.NLD + (1 if key_owner else 0)  # direct loads per wave and tile
         assert self.NM % NF == 0 and PFD < NF
-        # ---- AGPR map
-        self.ACC = 0
-        self.B1 = 16 * self.NSET * self.DB
-        self.B2 = self.B1 + 4 * self.KS
-        self.NA = self.B2 + 4 * self.KS
-        assert self.NA <= 256
-        # ---- VGPR map
+        # ---- AGPR map.  D = 64: VGPRs instead, which a wave's 256 may all be: the set-up and the epilogue then move nothing
+        # from one kind to the other (16 heads of 515 rows 15.1 -> 14.4 us, causal 15.4 -> 15.0, of 1024 24.4 -> 24.0, 64 of 2048,
+        # causal, 143.8 -> 142.7; the same bits)
+        n_acc, n_own = 16 * self.NSET * self.DB, 4 * self.KS
+        self.AG = D == 128
         r = 0
         def take(n):
             nonlocal r
             b = r
             r += n
             return b
+        self.ACC, self.B1, self.B2 = take(n_acc), take(n_own), take(n_own)
+        self.NA = r if self.AG else 0
+        assert self.NA <= 256
+        # ---- VGPR map
+        if self.AG:
+            r = 0
         self.SA = take(16)
         self.DPA = take(16)
         self.SB = take(16)
@@ -152,6 +156,9 @@ class Gen(Emitter):
         self.exp = set(drop)
 
     # ------------------------------------------------------------------ helpers
+    def acc(self, base, n):
+        return self.ar(base, n) if self.AG else self.vr(base, n)
+
     def bufs(self, b):
         """(S_cur, dP_cur, S_nxt, dP_nxt, P_prev, dS_prev, P_new, dS_new) of body b."""
         if b % 2 == 0:
@@ -189,12 +196,12 @@ class Gen(Emitter):
         kind, a, b, c = grp
         if kind == "c":
             ch, db, st = a, b, c
-            acc = self.ar(self.ACC + 16 * (st * self.DB + db), 16)
+            acc = self.acc(self.ACC + 16 * (st * self.DB + db), 16)
             src = DS_prev if st == 0 else P_prev      # set 0: dK^T (or dQ^T) from dS; set 1: dV^T from P
             return "%s %s, %s, %s, %s" % (self.mfma, acc, f, self.vr(src + 4 * ch, 4), acc)
         ks, t = a, b
         dst = self.vr(S_nxt if t == 0 else DP_nxt, 16)
-        own = self.ar((self.B1 if t == 0 else self.B2) + 4 * ks, 4)
+        own = self.acc((self.B1 if t == 0 else self.B2) + 4 * ks, 4)
         start = "0" if t == 0 else dst if self.KO else self.vr(self.AUXD, 16)
         return "%s %s, %s, %s, %s" % (self.mfma, dst, f, own, start if ks == 0 else dst)
 
@@ -459,14 +466,14 @@ class Gen(Emitter):
             out.append('    "%s\\n\\t"' % ln)
         outs, ins = [], []
         for i in range(self.NSET * DB):
-            outs.append('"+{%s}"(acc[%d])' % (self.ar(self.ACC + 16 * i, 16), i))
+            outs.append('"+{%s}"(acc[%d])' % (self.acc(self.ACC + 16 * i, 16), i))
         outs.append('"+{%s}"(s_init)' % self.vr(self.SA, 16))
         outs.append('"+{%s}"(dp_init)' % self.vr(self.DPA, 16))
         outs.append('"+{%s}"(aux_l)' % self.vr(self.AUXL, self.NAUX))
         for i in range(4 * KS // 16):
-            ins.append('"{%s}"(b1_pack[%d])' % (self.ar(self.B1 + 16 * i, 16), i))
+            ins.append('"{%s}"(b1_pack[%d])' % (self.acc(self.B1 + 16 * i, 16), i))
         for i in range(4 * KS // 16):
-            ins.append('"{%s}"(b2_pack[%d])' % (self.ar(self.B2 + 16 * i, 16), i))
+            ins.append('"{%s}"(b2_pack[%d])' % (self.acc(self.B2 + 16 * i, 16), i))
         if not self.KO:
             ins.append('"{%s}"(aux_d)' % self.vr(self.AUXD, 16))
         ins.append('"{%s}"(roff1_v)' % self.vr(self.ROFF1, KS))
@@ -503,6 +510,8 @@ class Gen(Emitter):
             pinned.update(range(base, base + n))
         if not self.KO:
             pinned.update(range(self.AUXD, self.AUXD + 16))
+        if not self.AG:
+            pinned.update(range(self.ACC, self.B2 + 4 * KS))
         clob = ['"memory"', '"vcc"', '"scc"']
         clob += ['"v%d"' % i for i in range(self.NV) if i not in pinned]
         clob += ['"s%d"' % i for i in range(self.s_j, self.s_m0 + 1)]
