@@ -44,7 +44,8 @@ int launch_sweep(K kern, BwdParams p, int BH, int S_own, int NW, int lds_bytes, 
 // keys 102 -> 90 (D = 64 60 -> 50); 16 heads of 1000 queries and 8000 keys 332 -> 258, causal 80 -> 72 (D = 64 208 -> 155,
 // 52 -> 45).  Where the tiles end in the pass they began in, are short, or enough for the workgroups (causal: for half of
 // them, as half of the tiles are short), one launch is ahead or level (48 heads of 72 x 1500 49 / 61, 123 of 64 x 512,
-// causal, 29 / 33; 48 of 1000 x 8000, causal, D = 64 83 / 92; 400 of 72 x 5938 983 / 1004).
+// causal, 29 / 33; 48 of 1000 x 8000, causal, D = 64 83 / 92; 400 of 72 x 5938 983 / 1004).  Most of them now take a plan
+// (plan_walks), which is asked first; these are left where it does not pay or has too many entries.
 bool sweeps_apart(const BwdParams &p, int causal, int slots)
 {
     const attn::BwdQueue queue(p.total_wg, p.total_q);
@@ -56,30 +57,6 @@ bool sweeps_apart(const BwdParams &p, int causal, int slots)
     return first % per_pass != 0 && first / per_pass != last / per_pass;
 }
 
-// both hand-scheduled sweeps: as many workgroups as the chip holds at once, each walking the queue of owner tiles of its
-// XCD
-int launch_sweeps(void (*kern)(const BwdParams), int threads, int LDS, const BwdParams &p, int causal, hipStream_t stream)
-{
-    if (!attn::allow_lds(reinterpret_cast<const void *>(kern), LDS))
-        return ATTN_ERR_LAUNCH;
-    // (a runtime that cannot tell the occupancy gets one workgroup per entry: the kernel takes either)
-    int slots = attn::persistent_slots(reinterpret_cast<const void *>(kern), threads, LDS, attn::kNumXcd);
-    if (slots < attn::kNumXcd)
-        slots = 0x7fffffff;
-    const auto run = [&](int n_kv, int n_q) {
-        BwdParams r = p;
-        r.total_wg = n_kv;
-        r.total_q = n_q;
-        const int entries = attn::BwdQueue(n_kv, n_q).n_entries;
-        hipLaunchKernelGGL(kern, dim3((unsigned)(slots < entries ? slots : entries)), dim3(threads), LDS, stream, r);
-        return hipGetLastError() == hipSuccess ? ATTN_OK : ATTN_ERR_LAUNCH;
-    };
-    if (!sweeps_apart(p, causal, slots))
-        return run(p.total_wg, p.total_q);
-    const int rc = run(p.total_wg, 0);
-    return rc == ATTN_OK ? run(0, p.total_q) : rc;
-}
-
 enum BwdTiling { kAsDispatched, kRows128, kRows256, kRows128TwoWaves };
 
 // What a workgroup's walk costs, in us: per owner tile and per streamed tile of either sweep; `launch` + `mean` times the mean
@@ -87,11 +64,14 @@ enum BwdTiling { kAsDispatched, kRows128, kRows256, kRows128TwoWaves };
 // of 1 to 256 heads and 64 to 16384 rows, D = 128, causal or not (root mean square of the error 5, 6 and 5 %).
 struct WalkCost {
     int rows, per_cu;   // of an owner tile; workgroups that a compute unit holds
-    float key_tile, key_step, query_tile, query_step, launch, mean;
+    float key_tile, key_step, query_tile, query_step, launch, mean, plan_pays;
 };
-constexpr WalkCost kWalk128 = {128, 1, 4.18f, 0.522f, 3.55f, 0.367f, 5.76f, 0.535f},
-                   kWalk256 = {256, 1, 7.26f, 0.924f, 5.56f, 0.644f, 4.83f, 0.503f},
-                   kWalk128TwoWaves = {128, 2, 7.27f, 0.920f, 6.32f, 0.654f, 4.72f, 0.551f};
+constexpr WalkCost kWalk128 = {128, 1, 4.18f, 0.522f, 3.55f, 0.367f, 5.76f, 0.535f, 0.95f},
+                   kWalk256 = {256, 1, 7.26f, 0.924f, 5.56f, 0.644f, 4.83f, 0.503f, 0.95f},
+                   kWalk128TwoWaves = {128, 2, 7.27f, 0.920f, 6.32f, 0.654f, 4.72f, 0.551f, 0.95f};
+constexpr float kPlanTail = 0.5f;   // (the mean tile's share that a planned launch's longest walk lies above the mean one)
+// D = 64 (two workgroups to a CU): what the tiles' walks cost beside each other is all that is asked of it
+constexpr WalkCost kWalkD64 = {128, 2, 4.0f, 0.60f, 3.5f, 0.45f, 0.f, 0.f, 0.93f};
 
 // Streamed tiles of owner tile t (`rows` rows) of a key-owner or query-owner sweep
 int walk_steps(const BwdParams &p, int causal, int rows, bool keys, int t)
@@ -108,20 +88,20 @@ int walk_steps(const BwdParams &p, int causal, int rows, bool keys, int t)
     return (end + 31) / 32;
 }
 
-// The tiles of one sweep that XCD 0 takes up, in its queue's order: what wg_to_tile_n gives for entries 0, 8, 16, ..., without its
-// divisions.  each(t) per tile.
+// The tiles of one sweep that an XCD takes up, in its queue's order: what wg_to_tile_n gives for entries xcd, xcd + 8, xcd + 16,
+// ..., without its divisions.  each(t) per tile.
 template <typename F>
-void xcd_tiles(int heads, int n_t, int causal, long long head_bytes, F &&each)
+void xcd_tiles(int heads, int n_t, int causal, long long head_bytes, int xcd, F &&each)
 {
     using attn::kNumXcd;
     const int a = heads / kNumXcd, r = heads % kNumXcd, n_left = r * n_t;
     if (!causal) {
-        for (long long i = 0; i < (long long)heads * n_t; i += kNumXcd)
+        for (long long i = xcd; i < (long long)heads * n_t; i += kNumXcd)
             each(0);   // (all alike)
         return;
     }
-    for (int i = 0; kNumXcd * i < n_left; ++i)
-        each(n_t - 1 - (kNumXcd * i + ((i & 1) && kNumXcd * (i + 1) <= n_left ? kNumXcd - 1 : 0)) / r);
+    for (int i = 0; kNumXcd * i + xcd < n_left; ++i)
+        each(n_t - 1 - (kNumXcd * i + ((i & 1) && kNumXcd * (i + 1) <= n_left ? kNumXcd - 1 - xcd : xcd)) / r);
     if (a == 0)
         return;
     const int want = attn::causal_group_heads(n_t, head_bytes), ng = a > want ? a / want : 1;
@@ -129,6 +109,140 @@ void xcd_tiles(int heads, int n_t, int causal, long long head_bytes, F &&each)
         for (int t = n_t - 1; t >= 0; --t)
             for (int h = 0; h < a / ng + (g < a % ng); ++h)
                 each(t);
+}
+
+// The plan of a launch's walks (BwdPlan): the sweep with the longer tiles first, every entry of an XCD's queue to the workgroup that
+// is free first.  Taking one pass through the queue after the other, odd ones backwards, leaves walks up to a third apart where
+// tiles differ, by the mask or by the sweep they belong to.  By passes -> by plan, in us: D = 128, 40 causal heads of 1500 rows
+// 106.7 -> 95, 12 of 6000 1.17 times as fast, 123 heads of 72 x 5938 1.12 (against one sweep after the other), 16 causal of
+// 1000 x 8000 1.36; D = 64, 123 of 72 x 5938 1.36, 16 of 1000 x 8000 1.28.  The host takes 3 to 38 us for it, behind the Delta
+// kernel's launch.  Returns the longest walk over that of the passes (of any XCD); 1 and no plan: one pass, or too many entries.
+float plan_walks(attn::BwdPlan &plan, const BwdParams &p, int BH, int causal, const WalkCost &c, int slots)
+{
+    using attn::BwdPlan;
+    using attn::kNumXcd;
+    const attn::BwdQueue queue(p.total_wg, p.total_q);
+    const int per_xcd = slots / kNumXcd, cus = p.cus_per_xcd, n = (queue.n_entries + kNumXcd - 1) / kNumXcd;
+    if (queue.n_entries <= slots || slots % kNumXcd || per_xcd > BwdPlan::kMaxSlots || n > BwdPlan::kMaxEntries ||
+        !p.total_wg || !p.total_q)
+        return 1.f;
+    const long long head_bytes = 4ll * (p.S_q + p.S_kv) * p.D;
+    const auto cost = [&](bool keys, int t) {
+        const int steps = walk_steps(p, causal, c.rows, keys, causal && keys ? p.n_t - 1 - t : t);
+        return keys ? c.key_tile + c.key_step * steps : c.query_tile + c.query_step * steps;
+    };
+    // go(place in the queue, cost) for an XCD's entries of both sweeps
+    const auto each_entry = [&](int xcd, auto &&go) {
+        for (const bool keys : {true, false}) {
+            int at = keys ? 0 : queue.q_first / kNumXcd;
+            xcd_tiles(BH, keys ? p.n_t : p.n_tq, causal, head_bytes, xcd, [&](int t) { go(at++, cost(keys, t)); });
+        }
+    };
+    // heads that are dealt out tile by tile give the XCDs different tiles: the plan is made for the longest in each place
+    const int xcds = causal && BH % kNumXcd ? kNumXcd : 1;
+    float longest_of[BwdPlan::kMaxEntries] = {};
+    for (int x = 0; x < xcds; ++x)
+        each_entry(x, [&](int at, float l) { longest_of[at] = l > longest_of[at] ? l : longest_of[at]; });
+    // binary heap of (load, workgroup), the least load on top
+    struct Free {
+        float load;
+        int m;
+    } heap[BwdPlan::kMaxSlots];
+    for (int m = 0; m < per_xcd; ++m)
+        heap[m] = {0.f, m};
+    const auto less = [](const Free &x, const Free &y) { return x.load < y.load || (x.load == y.load && x.m < y.m); };
+    uint8_t owner[BwdPlan::kMaxEntries];
+    int of_slot[BwdPlan::kMaxSlots] = {};
+    const int first_q = queue.q_first / kNumXcd;
+    const bool keys_first = cost(true, causal ? p.n_t - 1 : 0) >= cost(false, p.n_tq - 1);
+    for (const bool keys : {keys_first, !keys_first})
+        for (int at = keys ? 0 : first_q; at < (keys ? first_q : n); ++at) {
+            Free top = heap[0];
+            owner[at] = (uint8_t)top.m;
+            ++of_slot[top.m];
+            top.load += longest_of[at];
+            int i = 0;
+            for (;;) {
+                int child = 2 * i + 1;
+                if (child >= per_xcd)
+                    break;
+                if (child + 1 < per_xcd && less(heap[child + 1], heap[child]))
+                    ++child;
+                if (!less(heap[child], top))
+                    break;
+                heap[i] = heap[child];
+                i = child;
+            }
+            heap[i] = top;
+        }
+    // the workgroups that begin with the heaviest tiles share their compute units with those that begin with the lightest
+    // (BwdQueue::entry)
+    const auto place = [&](int m) { return m < cus ? m : per_xcd - 1 - (m - cus); };
+    int first[BwdPlan::kMaxSlots + 1] = {};
+    for (int m = 0; m < per_xcd; ++m)
+        first[place(m) + 1] = of_slot[m];
+    for (int m = 0; m < per_xcd; ++m)
+        first[m + 1] += first[m];
+    for (int m = 0; m <= per_xcd; ++m)
+        BwdPlan::set(plan.first, m, first[m]);
+    for (int i = 0; i < n; ++i)
+        BwdPlan::set(plan.idx, first[place(owner[i])]++, i);
+    float planned = 0.f, passes = 0.f;
+    for (int x = 0; x < xcds; ++x) {
+        float by_plan[BwdPlan::kMaxSlots] = {}, by_pass[BwdPlan::kMaxSlots] = {};
+        each_entry(x, [&](int at, float l) {
+            const int m = at % per_xcd;
+            by_plan[owner[at]] += l;
+            by_pass[at / per_xcd & 1 ? per_xcd - 1 - m : m] += l;
+        });
+        for (int m = 0; m < per_xcd; ++m) {
+            planned = by_plan[m] > planned ? by_plan[m] : planned;
+            passes = by_pass[m] > passes ? by_pass[m] : passes;
+        }
+    }
+    return planned / passes;
+}
+
+// both hand-scheduled sweeps: as many workgroups as the chip holds at once, each walking the queue of owner tiles of its
+// XCD, or what a plan gives it
+struct BwdKernels {
+    void (*plain)(const BwdParams);
+    void (*planned)(const BwdParams, const attn::BwdPlan);
+};
+int launch_sweeps(const BwdKernels &kern, int threads, int LDS, const BwdParams &p, int BH, int causal, const WalkCost &cost,
+                  hipStream_t stream)
+{
+    // (a runtime that cannot tell the occupancy gets one workgroup per entry: the kernel takes either)
+    int slots = attn::persistent_slots(reinterpret_cast<const void *>(kern.plain), threads, LDS, attn::kNumXcd);
+    if (slots < attn::kNumXcd)
+        slots = 0x7fffffff;
+    attn::BwdPlan plan;
+    const auto run = [&](int n_kv, int n_q, bool planned) {
+        BwdParams r = p;
+        r.total_wg = n_kv;
+        r.total_q = n_q;
+        const int entries = attn::BwdQueue(n_kv, n_q).n_entries;
+        if (!attn::allow_lds(planned ? (const void *)kern.planned : (const void *)kern.plain, LDS))
+            return (int)ATTN_ERR_LAUNCH;
+        const dim3 grid((unsigned)(slots < entries ? slots : entries));
+        if (planned)
+            hipLaunchKernelGGL(kern.planned, grid, dim3(threads), LDS, stream, r, plan);
+        else
+            hipLaunchKernelGGL(kern.plain, grid, dim3(threads), LDS, stream, r);
+        return (int)(hipGetLastError() == hipSuccess ? ATTN_OK : ATTN_ERR_LAUNCH);
+    };
+    // Time by plan over time by passes, over 190 launches: D = 128, 0.73 to 0.98 where the longest walk is under 0.95 of the passes'
+    // (one of 97 1.02), 0.96 to 1.05 above.  D = 64, 0.81 to 1.02 under 0.93 (0.94 in the mean), 0.96 to 1.07 above; but the costs of
+    // short causal walks are less sure there: of 28 launches under 1024 rows and between 0.8 and 0.93, seven gained more than 3 % and
+    // the rest took up to 1.09 times as long (116 heads of 607 rows 38.1 -> 41.3).
+    const int walk = causal && p.S_q < p.S_kv ? p.S_q : p.S_kv;
+    const float pays = p.D == 64 && causal && walk < 1024 ? 0.8f : cost.plan_pays;
+    if (plan_walks(plan, p, BH, causal, cost, slots) < pays)
+        return run(p.total_wg, p.total_q, true);
+    if (!sweeps_apart(p, causal, slots))
+        return run(p.total_wg, p.total_q, false);
+    const int rc = run(p.total_wg, 0, false);
+    return rc == ATTN_OK ? run(0, p.total_q, false) : rc;
 }
 
 // Estimated time of a D = 128 launch on `cus` compute units: the longest walk among XCD 0's workgroups
@@ -165,7 +279,7 @@ float launch_estimate(const BwdParams &p, int BH, int causal, const WalkCost &c,
     int k = 0, at = 0;      // pass, place in it (BwdQueue::entry)
     const long long head_bytes = 4ll * (p.S_q + p.S_kv) * 128;
     for (const bool own_keys : {true, false})
-        xcd_tiles(BH, own_keys ? n_t : n_tq, causal, head_bytes, [&](int t) {
+        xcd_tiles(BH, own_keys ? n_t : n_tq, causal, head_bytes, 0, [&](int t) {
             const int n = walk_steps(p, causal, rows, own_keys, causal && own_keys ? n_t - 1 - t : t);
             const int m = k & 1 ? per_pass - 1 - at : at;
             walk[m < first ? first - 1 - m : m] += own_keys ? c.key_tile + c.key_step * n : c.query_tile + c.query_step * n;
@@ -177,6 +291,10 @@ float launch_estimate(const BwdParams &p, int BH, int causal, const WalkCost &c,
     float longest = 0.f;
     for (int m = 0; m < per_pass; ++m)
         longest = walk[m] > longest ? walk[m] : longest;
+    // what a plan makes of it (plan_walks): the heaviest tile, or little more than the mean
+    const float by_plan = mean + kPlanTail * (float)(all / queue.n_entries);
+    const float planned = by_plan > heaviest ? by_plan : heaviest;
+    longest = planned < c.plan_pays * longest ? planned : longest;
     return c.launch + longest + c.mean * mean;
 }
 
@@ -185,18 +303,12 @@ float launch_estimate(const BwdParams &p, int BH, int causal, const WalkCost &c,
 // heads of 2048 rows 206 -> 187 us, 128 of 4096 3026 -> 2691); in tiles of 128 rows (two waves, two workgroups to a CU that
 // fill each other's gaps) causal and ragged launches (128 causal heads of 4096 rows 1673 -> 1516, of 1024 147 -> 140, 300 of
 // 300 rows 91 -> 84).  A 64-row wave takes 1.6 times as long for a tile as a 32-row one: launches that do not fill the chip are
-// up to 1.7 times slower (16 heads of 1024 rows 35 -> 44).  Of 7200 launches 24 % take 64-row waves, 8 % faster in the mean; one in
-// a hundred of those is more than 2 % slower, 1.2 times at worst.  Launches that the 32-row waves run one sweep after the
-// other stay with them.
+// up to 1.7 times slower (16 heads of 1024 rows 35 -> 44).  Of 6200 launches 29 % take 64-row waves, 7 % faster in the mean; one in
+// thirty of those is more than 2 % slower, 1.12 times at worst.
 BwdTiling pick_tiling(const BwdParams &p, int BH, int causal, int cus)
 {
     if (cus < attn::kNumXcd || 2ll * BH * ((p.S_kv + 255) / 256 + (p.S_q + 255) / 256) < cus)
         return kRows128;   // (no launch of fewer tiles gained)
-    BwdParams small = p;
-    small.total_wg = BH * ((p.S_kv + 127) / 128);
-    small.total_q = BH * ((p.S_q + 127) / 128);
-    if (sweeps_apart(small, causal, cus))
-        return kRows128;
     const float t32 = 0.975f * launch_estimate(p, BH, causal, kWalk128, cus);
     const float t256 = launch_estimate(p, BH, causal, kWalk256, cus), t2 = launch_estimate(p, BH, causal, kWalk128TwoWaves, cus);
     return t32 <= t256 && t32 <= t2 ? kRows128 : t256 <= t2 ? kRows256 : kRows128TwoWaves;
@@ -232,16 +344,25 @@ int launch_hand(BwdParams p, int BH, int causal, hipStream_t stream, BwdTiling t
     p.n_tq = (p.S_q + rows - 1) / rows;
     p.total_wg = BH * p.n_t;
     p.total_q = BH * p.n_tq;
+    const auto run = [&](const BwdKernels &kern, int threads, int lds, const WalkCost &cost) {
+        return launch_sweeps(kern, threads, lds, p, BH, causal, cost, stream);
+    };
+    using namespace attn;
     if constexpr (D == 128) {
         if (tiling == kRows256)
-            return launch_sweeps(causal ? attn::attn_bwd_wide_kernel<4, true, F16> : attn::attn_bwd_wide_kernel<4, false, F16>, 256,
-                                 attn::BwdWideLds<4>::BYTES, p, causal, stream);
+            return causal ? run({attn_bwd_wide_kernel<4, true, F16>, attn_bwd_wide_planned_kernel<4, true, F16>}, 256,
+                                BwdWideLds<4>::BYTES, kWalk256)
+                          : run({attn_bwd_wide_kernel<4, false, F16>, attn_bwd_wide_planned_kernel<4, false, F16>}, 256,
+                                BwdWideLds<4>::BYTES, kWalk256);
         if (tiling == kRows128TwoWaves)
-            return launch_sweeps(causal ? attn::attn_bwd_wide_kernel<2, true, F16> : attn::attn_bwd_wide_kernel<2, false, F16>, 128,
-                                 attn::BwdWideLds<2>::BYTES, p, causal, stream);
+            return causal ? run({attn_bwd_wide_kernel<2, true, F16>, attn_bwd_wide_planned_kernel<2, true, F16>}, 128,
+                                BwdWideLds<2>::BYTES, kWalk128TwoWaves)
+                          : run({attn_bwd_wide_kernel<2, false, F16>, attn_bwd_wide_planned_kernel<2, false, F16>}, 128,
+                                BwdWideLds<2>::BYTES, kWalk128TwoWaves);
     }
-    return launch_sweeps(causal ? attn::attn_bwd_asm_kernel<D, true, F16> : attn::attn_bwd_asm_kernel<D, false, F16>, 256,
-                         attn::BwdLds<D>::BYTES, p, causal, stream);
+    const WalkCost &cost = D == 64 ? kWalkD64 : kWalk128;
+    return causal ? run({attn_bwd_asm_kernel<D, true, F16>, attn_bwd_asm_planned_kernel<D, true, F16>}, 256, BwdLds<D>::BYTES, cost)
+                  : run({attn_bwd_asm_kernel<D, false, F16>, attn_bwd_asm_planned_kernel<D, false, F16>}, 256, BwdLds<D>::BYTES, cost);
 }
 
 // plain: run the compiler-scheduled sweeps (always when scale == 0, which the hand-scheduled loops exclude)
@@ -308,6 +429,7 @@ static int validate_bwd(const void *q, const void *k, const void *v, const void 
     p.n_tq = 0;
     p.total_q = 0;
     p.n_rows = BH * S_q;
+    p.D = D;
     p.c = scale * 1.44269504088896340736f;
     p.scale = scale;
     return ATTN_OK;
@@ -392,15 +514,38 @@ extern "C" int attn_bwd_sweeps_apart(int heads, int S_q, int S_kv, int causal, i
     return sweeps_apart(p, causal, slots);
 }
 
-// Test-only, host only: the i-th tile that XCD 0 takes up of a sweep (xcd_tiles), -1 behind the last, and the same from
+// Test-only, host only: what plan_walks says of a launch.
+extern "C" float attn_bwd_plan(int heads, int S_q, int S_kv, int D, int causal, int tiling, int cus, uint32_t *first, uint32_t *idx)
+{
+    const WalkCost &c = D == 64 ? kWalkD64 : tiling == kRows256 ? kWalk256 : tiling == kRows128 ? kWalk128 : kWalk128TwoWaves;
+    BwdParams p;
+    p.S_q = S_q;
+    p.S_kv = S_kv;
+    p.D = D;
+    p.n_t = (S_kv + c.rows - 1) / c.rows;
+    p.n_tq = (S_q + c.rows - 1) / c.rows;
+    p.total_wg = heads * p.n_t;
+    p.total_q = heads * p.n_tq;
+    p.cus_per_xcd = cus / attn::kNumXcd;
+    attn::BwdPlan plan = {};
+    const float ratio = plan_walks(plan, p, heads, causal, c, cus * c.per_cu);
+    for (int i = 0; i < (int)(sizeof plan.first / 4); ++i)
+        first[i] = plan.first[i];
+    for (int i = 0; i < (int)(sizeof plan.idx / 4); ++i)
+        idx[i] = plan.idx[i];
+    return ratio;
+}
+
+// Test-only, host only: the i-th tile that an XCD takes up of a sweep (xcd_tiles), -1 behind the last, and the same from
 // wg_to_tile_n in *want.
-extern "C" int attn_bwd_xcd_tile(int heads, int n_t, int causal, long long head_bytes, int i, int *want)
+extern "C" int attn_bwd_xcd_tile(int heads, int n_t, int causal, long long head_bytes, int xcd, int i, int *want)
 {
     int at = 0, got = -1, bh = 0, t = -1;
-    xcd_tiles(heads, n_t, causal, head_bytes, [&](int x) { got = at++ == i ? x : got; });
-    if (causal && (long long)attn::kNumXcd * i < (long long)heads * n_t)
-        attn::wg_to_tile_n<true>(attn::kNumXcd * i, heads * n_t, n_t, head_bytes, bh, t);
-    *want = causal ? t : (long long)attn::kNumXcd * i < (long long)heads * n_t ? 0 : -1;
+    const long long entry = (long long)attn::kNumXcd * i + xcd;
+    xcd_tiles(heads, n_t, causal, head_bytes, xcd, [&](int x) { got = at++ == i ? x : got; });
+    if (causal && entry < (long long)heads * n_t)
+        attn::wg_to_tile_n<true>((int)entry, heads * n_t, n_t, head_bytes, bh, t);
+    *want = causal ? t : entry < (long long)heads * n_t ? 0 : -1;
     return got;
 }
 

@@ -54,6 +54,34 @@ struct BwdQueue {
     }
 };
 
+// Which workgroup of an XCD takes up which entries of its queue, for launches of several passes: the host deals the tiles out
+// so that the workgroups' walks end together (plan_walks in attn_bwd.hip).  Workgroup m takes up entries idx(first(m)) to
+// idx(first(m + 1) - 1) of its XCD's queue, in rising order.  The plan is XCD 0's, whose queue is the longest.
+struct BwdPlan {
+    static constexpr int kMaxSlots = 64, kMaxEntries = 768;   // per XCD
+    // (two 16-bit numbers to a word, which a scalar load can bring)
+    uint32_t first[(kMaxSlots + 2) / 2], idx[kMaxEntries / 2];
+    static __host__ __device__ int get(const uint32_t *words, int i) { return (int)(words[i >> 1] >> (i & 1) * 16 & 0xffffu); }
+    static void set(uint32_t *words, int i, int x)
+    {
+        words[i >> 1] = (words[i >> 1] & ~(0xffffu << (i & 1) * 16)) | (uint32_t)x << (i & 1) * 16;
+    }
+};
+
+// The entry that workgroup `wg` takes up in pass k, or -1.  (Kernels of their own for launches with a plan: asking which it is cost
+// launches of 10 to 20 us 0.2 to 0.5 us, code that is fetched for the first time)
+template <bool PLANNED>
+__device__ __forceinline__ int queue_entry(const BwdQueue &queue, const BwdParams &p, const BwdPlan &plan, int wg, int n_slots, int k)
+{
+    if constexpr (!PLANNED)
+        return queue.entry(wg, n_slots, p.cus_per_xcd, k);
+    const int m = wg / kNumXcd, at = BwdPlan::get(plan.first, m) + k;
+    if (at >= BwdPlan::get(plan.first, m + 1))
+        return -1;
+    const int entry = BwdPlan::get(plan.idx, at) * kNumXcd + wg % kNumXcd;
+    return entry < queue.n_entries ? entry : -1;   // (only the last entry of XCD 0's queue has no counterpart)
+}
+
 // LDS of a workgroup: the two rings, the LSE' / Delta ring, and what the waves' owner rows need beyond stage 4 of the rings
 // (which no streamed tile occupies before the loop runs)
 template <int D>
@@ -65,8 +93,8 @@ struct BwdLds {
 // One sweep's part of the workgroup's walk: takes up entries from pass `pass` on for as long as they are this sweep's.
 // F16: q, k, v, d_o and the gradients are IEEE fp16 instead of bf16 (the element type of the paper's
 // Section 6.3 figures); the pointers in BwdParams are then reinterpreted.
-template <int D, bool CAUSAL, bool KEY_OWNER, bool F16>
-__device__ __forceinline__ void bwd_sweep(const BwdParams &p, const BwdQueue &queue, const int wave, int &pass)
+template <int D, bool CAUSAL, bool KEY_OWNER, bool F16, bool PLANNED>
+__device__ __forceinline__ void bwd_sweep(const BwdParams &p, const BwdPlan &plan, const BwdQueue &queue, const int wave, int &pass)
 {
     static_assert(D == 128 || D == 64, "hand-scheduled backward sweeps: D = 64 or 128");
     typedef typename std::conditional<F16, ElemF16, ElemBF16>::type E;
@@ -197,7 +225,7 @@ __device__ __forceinline__ void bwd_sweep(const BwdParams &p, const BwdQueue &qu
     bool own_on_its_way = false;   // the tile's owner rows, and `bh`, `ot` are this tile's
 #pragma clang loop unroll(disable)
     for (;; ++pass) {
-        const int entry = queue.entry(blockIdx.x, (int)gridDim.x, p.cus_per_xcd, pass);
+        const int entry = queue_entry<PLANNED>(queue, p, plan, blockIdx.x, (int)gridDim.x, pass);
         if (entry < 0 || (KEY_OWNER && entry >= queue.n_kv))
             break;   // (entries rise from pass to pass; only the last pass can be short)
         if (!KEY_OWNER && entry < queue.q_first)
@@ -370,7 +398,7 @@ __device__ __forceinline__ void bwd_sweep(const BwdParams &p, const BwdQueue &qu
             // keys 103.6 -> 99.3 us, 451 of 576 rows 269 -> 260, mean over 132 causal calls of several passes -1.3 %.  A tile
             // with none behind it runs straight on, past no code that is not its own: a jump is a fetch more in a short
             // launch.  82 heads of 187 rows 20.0 -> 19.7 us, 134 of 70 rows, causal, 17.0 -> 16.8)
-            const int next = queue.entry(blockIdx.x, (int)gridDim.x, p.cus_per_xcd, pass + 1);
+            const int next = queue_entry<PLANNED>(queue, p, plan, blockIdx.x, (int)gridDim.x, pass + 1);
             own_on_its_way = next >= 0 && (KEY_OWNER ? next < queue.n_kv : true);
             if (__builtin_expect(own_on_its_way, 0)) {
                 locate(next, bh, ot);
@@ -418,14 +446,27 @@ __device__ __forceinline__ void bwd_sweep(const BwdParams &p, const BwdQueue &qu
 // busy); two of them fill each other's gaps.  Whole call against one workgroup per CU: 16 heads of 4096 rows 236 -> 223
 // us, causal 139 -> 125; 128 heads of 512 rows 46.6 -> 39.9; 512 heads of 300 rows, causal 84 -> 71.  Where one
 // workgroup per CU is all there is, the half as many operand buffers cost 2-4 % (16 heads of 1024 rows 22.6 -> 23.1).
-template <int D, bool CAUSAL, bool F16>
-__global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_bwd_asm_kernel(const BwdParams p)
+template <int D, bool CAUSAL, bool F16, bool PLANNED>
+__device__ __forceinline__ void bwd_both_sweeps(const BwdParams &p, const BwdPlan &plan)
 {
     const BwdQueue queue(p.total_wg, p.total_q);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int pass = 0;
-    bwd_sweep<D, CAUSAL, true, F16>(p, queue, wave, pass);
-    bwd_sweep<D, CAUSAL, false, F16>(p, queue, wave, pass);
+    bwd_sweep<D, CAUSAL, true, F16, PLANNED>(p, plan, queue, wave, pass);
+    bwd_sweep<D, CAUSAL, false, F16, PLANNED>(p, plan, queue, wave, pass);
+}
+
+template <int D, bool CAUSAL, bool F16>
+__global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_bwd_asm_kernel(const BwdParams p)
+{
+    const BwdPlan none = {};   // (never read)
+    bwd_both_sweeps<D, CAUSAL, F16, false>(p, none);
+}
+
+template <int D, bool CAUSAL, bool F16>
+__global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_bwd_asm_planned_kernel(const BwdParams p, const BwdPlan plan)
+{
+    bwd_both_sweeps<D, CAUSAL, F16, true>(p, plan);
 }
 
 }  // namespace attn

@@ -44,6 +44,7 @@ struct BwdParams {
     long long n_rows;  // B*H*S_q (delta kernel)
     float c;       // scale * log2(e)
     float scale;
+    int D;         // (host code)
 };
 
 // Delta[r] = sum_d dO[r][d] * O[r][d] (fp32) and LSE'[r] = LSE[r] * log2(e).  D/8 lanes per row, 16 bytes per lane.

@@ -34,9 +34,9 @@ struct BwdWideTile {
     bool on_its_way;
 };
 
-template <int NW, bool CAUSAL, bool KEY_OWNER, bool F16>
-__device__ __forceinline__ void bwd_wide_sweep(const BwdParams &p, const BwdQueue &queue, const int wave, int &pass,
-                                               BwdWideTile &tile)
+template <int NW, bool CAUSAL, bool KEY_OWNER, bool F16, bool PLANNED>
+__device__ __forceinline__ void bwd_wide_sweep(const BwdParams &p, const BwdPlan &plan, const BwdQueue &queue, const int wave,
+                                               int &pass, BwdWideTile &tile)
 {
     typedef typename std::conditional<F16, ElemF16, ElemBF16>::type E;
     typedef typename E::t elem_t;
@@ -82,7 +82,7 @@ __device__ __forceinline__ void bwd_wide_sweep(const BwdParams &p, const BwdQueu
     };
 #pragma clang loop unroll(disable)
     for (;; ++pass) {
-        const int entry = queue.entry(blockIdx.x, (int)gridDim.x, p.cus_per_xcd, pass);
+        const int entry = queue_entry<PLANNED>(queue, p, plan, blockIdx.x, (int)gridDim.x, pass);
         if (entry < 0 || (KEY_OWNER && entry >= queue.n_kv))
             break;   // (entries rise from pass to pass; only the last pass can be short)
         if (!KEY_OWNER && entry < queue.q_first)
@@ -213,7 +213,7 @@ __device__ __forceinline__ void bwd_wide_sweep(const BwdParams &p, const BwdQueu
         // rows: every wave has room for 32 rows and reads back only what it wrote.  Between the steps the owner rows of the
         // workgroup's next tile go out, whichever sweep it belongs to.
         __syncthreads();  // every wave has left the loop (its loads have landed): the LDS is free
-        const int next = queue.entry(blockIdx.x, (int)gridDim.x, p.cus_per_xcd, pass + 1);
+        const int next = queue_entry<PLANNED>(queue, p, plan, blockIdx.x, (int)gridDim.x, pass + 1);
         tile.on_its_way = next >= 0 && (next < queue.n_kv || next >= queue.q_first);
         if (tile.on_its_way)
             locate(next);
@@ -263,15 +263,28 @@ __device__ __forceinline__ void bwd_wide_sweep(const BwdParams &p, const BwdQueu
     }
 }
 
-template <int NW, bool CAUSAL, bool F16>
-__global__ __launch_bounds__(NW * 64) void attn_bwd_wide_kernel(const BwdParams p)
+template <int NW, bool CAUSAL, bool F16, bool PLANNED>
+__device__ __forceinline__ void bwd_wide_both_sweeps(const BwdParams &p, const BwdPlan &plan)
 {
     const BwdQueue queue(p.total_wg, p.total_q);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int pass = 0;
     BwdWideTile tile = {0, 0, false};
-    bwd_wide_sweep<NW, CAUSAL, true, F16>(p, queue, wave, pass, tile);
-    bwd_wide_sweep<NW, CAUSAL, false, F16>(p, queue, wave, pass, tile);
+    bwd_wide_sweep<NW, CAUSAL, true, F16, PLANNED>(p, plan, queue, wave, pass, tile);
+    bwd_wide_sweep<NW, CAUSAL, false, F16, PLANNED>(p, plan, queue, wave, pass, tile);
+}
+
+template <int NW, bool CAUSAL, bool F16>
+__global__ __launch_bounds__(NW * 64) void attn_bwd_wide_kernel(const BwdParams p)
+{
+    const BwdPlan none = {};   // (never read)
+    bwd_wide_both_sweeps<NW, CAUSAL, F16, false>(p, none);
+}
+
+template <int NW, bool CAUSAL, bool F16>
+__global__ __launch_bounds__(NW * 64) void attn_bwd_wide_planned_kernel(const BwdParams p, const BwdPlan plan)
+{
+    bwd_wide_both_sweeps<NW, CAUSAL, F16, true>(p, plan);
 }
 
 }  // namespace attn

@@ -13,7 +13,8 @@ pytestmark = pytest.mark.gpu
 
 # heads, S_q, S_kv
 SIZES = [(1, 1, 1), (1, 31, 33), (2, 64, 65), (1, 255, 257), (3, 256, 256), (2, 300, 97), (1, 97, 300), (5, 513, 700), (9, 1000, 33),
-         (17, 777, 1300), (3, 100, 1100), (33, 1025, 1024), (40, 1500, 1900), (130, 260, 260)]
+         (17, 777, 1300), (3, 100, 1100), (33, 1025, 1024), (40, 1500, 1900), (130, 260, 260),
+         (12, 900, 5000), (100, 128, 1500), (9, 4000, 4000)]    # (these with a plan of the workgroups' walks)
 
 
 def run(tiling, q, k, v, o, d_o, lse, causal, scale):
@@ -69,3 +70,19 @@ def test_infinite_and_nan_inputs(causal):
         fine = torch.isfinite(y.float())
         assert torch.equal(bits(x)[fine], bits(y)[fine])
         assert not fine.all()
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("heads,S_q,S_kv", [(60, 100, 2500), (24, 2500, 300), (30, 2900, 2900)])
+def test_planned_walks_at_d64(heads, S_q, S_kv, causal):
+    """Every tile written once, against the compiler-scheduled sweeps (the bar of the schedule-equivalence test)."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(heads + S_q)
+    mk = lambda S: torch.empty((1, heads, S, 64), device="cuda").normal_(generator=g).bfloat16()
+    q, k, v, d_o = mk(S_q), mk(S_kv), mk(S_kv), mk(S_q)
+    scale = synth.default_scale(64)
+    print("heads", heads, "S_q", S_q, "S_kv", S_kv, "causal", causal, flush=True)
+    o, lse = binding.attn_fwd(q, k, v, causal=causal, scale=scale)
+    got = binding.attn_bwd(q, k, v, o, d_o, lse, *[torch.full_like(t, float("nan")) for t in (q, k, v)], causal=causal, scale=scale)
+    for x, y in zip(got, debug_lib.attn_bwd_plain(q, k, v, o, d_o, lse, causal, scale)):
+        assert torch.isfinite(x.float()).all() and float((x.float() - y.float()).norm()) <= 1e-2 * float(y.float().norm())

@@ -107,7 +107,7 @@ def test_the_rule_between_the_tilings():
     for heads, s_q, s_kv, causal, cus, want in [
             (128, 4096, 4096, 0, 256, 2), (32, 2048, 2048, 0, 256, 2), (16, 16384, 16384, 0, 256, 2), (128, 1024, 1024, 1, 256, 3),
             (300, 300, 300, 0, 256, 3), (16, 1024, 1024, 0, 256, 1), (1, 1, 1, 0, 256, 1), (1, 1, 1, 1, 256, 1),
-            (123, 72, 5938, 0, 256, 1), (128, 4096, 4096, 0, 0, 1)]:
+            (123, 72, 5938, 0, 256, 3), (128, 4096, 4096, 0, 0, 1)]:
         assert pick(heads, s_q, s_kv, causal, cus, est) == want, (heads, s_q, s_kv, causal, cus, list(est))
     for heads, s_q, s_kv in [(1, 1, 1), (32768, 1, 1), (1 << 20, 64, 64), (3, 8000000, 1), (1, 1, 8000000)]:
         for causal in (0, 1):
@@ -116,16 +116,16 @@ def test_the_rule_between_the_tilings():
 
 def test_tiles_of_an_xcd_in_its_queues_order():
     tile = ctypes.CDLL(debug_lib.PATH).attn_bwd_xcd_tile
-    tile.restype, tile.argtypes = ctypes.c_int, [ctypes.c_int] * 3 + [ctypes.c_longlong, ctypes.c_int, ctypes.POINTER(ctypes.c_int)]
+    tile.restype, tile.argtypes = ctypes.c_int, [ctypes.c_int] * 3 + [ctypes.c_longlong] + [ctypes.c_int] * 2 + [ctypes.POINTER(ctypes.c_int)]
     want = ctypes.c_int()
     for heads in (1, 3, 7, 8, 9, 16, 21, 40, 130):
         for n_t in (1, 2, 5, 9, 33):
             for head_bytes in (4 * 256 * 128, 4 * 3000 * 128, 4 * 20000 * 128):
                 for causal in (0, 1):
-                    n = (heads * n_t + 7) // 8
-                    for i in range(n + 1):
-                        assert tile(heads, n_t, causal, head_bytes, i, want) == want.value, (heads, n_t, head_bytes, causal, i)
-                    assert want.value == -1
+                    for xcd in (0, 3, 7):
+                        for i in range((heads * n_t + 7) // 8 + 1):
+                            assert tile(heads, n_t, causal, head_bytes, xcd, i, want) == want.value, (heads, n_t, causal, xcd, i)
+                        assert want.value == -1
 
 
 def test_registers_of_the_compiled_kernels(tmp_path):
@@ -142,9 +142,9 @@ def test_registers_of_the_compiled_kernels(tmp_path):
     text = open(out).read()
     seen = 0
     for block in text[text.index("amdhsa.kernels:"):].split("  - .agpr_count:")[1:]:
-        if not re.search(r"\.name:\s+\S*attn_bwd_wide_kernel", block):
+        if not re.search(r"\.name:\s+\S*attn_bwd_wide_(planned_)?kernel", block):
             continue
         value = lambda key: int(re.search(r"\.%s:\s+(\d+)" % key, block).group(1))
         assert value("private_segment_fixed_size") == 0 and value("vgpr_spill_count") == 0 and value("vgpr_count") <= 512
         seen += 1
-    assert seen == 8          # waves, causal, element type
+    assert seen == 16         # waves, causal, element type, with a plan or without
