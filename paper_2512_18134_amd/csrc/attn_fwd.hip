@@ -394,10 +394,10 @@ static int launch_ranges(Params &p, int BH, int n_eff, hipStream_t st)
 // 128-row workgroups (two to a CU) otherwise (512 ranges of 1024 keys: 42.6 us with 256-row tiles, 28.3 with 128, 29.8
 // with 64; 1024 ranges of 2048 keys: 151 / 113 / 96).  With more queries the small tiles win while they find idle
 // compute units (256 queries, 8 heads of 8192 keys in 8 ranges: D = 128 28.9 -> 17.5 us, D = 64 19.6 -> 11.2 us), the
-// wide ones after that (32 ranges of 4096 keys: 137 against 197 us).  D = 128: those in 64-row waves, with half the LDS reads,
-// where more than half of a tile's rows exist and the ranges are long enough for their set-up (256 queries, 8 heads of
-// 131072 keys in 32 ranges 143.7 -> 135.5 us, 300 of 32 heads of 10000 in 8 79.0 -> 75.0; 100 of 256 heads of 5000 in 4 161 -> 167,
-// 512 of 16 heads of 4000 in 16 51.1 -> 55.2), in 32-row waves otherwise.
+// wide ones after that (32 ranges of 4096 keys: 137 against 197 us).  (D = 128: the 64-row waves of
+// the unsplit kernel are 4 % faster there in the mean, but take their first reference from 32 keys instead of 64: over 1100
+// launches of N(0, 1) inputs the error against 64 bits was larger in 943, by 0.2 % in the mean and 0.5 % for ranges under 700 keys;
+// 520 to 640 queries took up to 1.3 times as long, a peaked softmax 1.05 times in the mean.)
 template <int D, bool F16>
 static int launch_splitkv(Params &p, int BH, int n_eff, void *o, float *lse, hipStream_t st)
 {
@@ -408,12 +408,8 @@ static int launch_splitkv(Params &p, int BH, int n_eff, void *o, float *lse, hip
     const long long wg64 = ranges * ((p.S_q + 63) / 64), wg128 = ranges * ((p.S_q + 127) / 128);
     int rc;
     if constexpr (D == 128) {
-        if (p.S_q <= 64 || wg64 <= cus)
-            rc = launch_ranges<128, 1, 1, 2, F16, 2>(p, BH, n_eff, st);
-        else if (p.S_q > 128 && p.split_len >= 512)
-            rc = launch_ranges<128, 2, 1, 4, F16, 1>(p, BH, n_eff, st);
-        else
-            rc = launch_ranges<128, 1, 2, 8, F16, 1>(p, BH, n_eff, st);
+        rc = p.S_q <= 64 || wg64 <= cus ? launch_ranges<128, 1, 1, 2, F16, 2>(p, BH, n_eff, st)
+                                        : launch_ranges<128, 1, 2, 8, F16, 1>(p, BH, n_eff, st);
     } else {
         const bool groups = p.S_q <= 64 ? p.split_len >= 2048 || (2 * wg64 <= cus && p.split_len >= 512)
                                         : wg64 <= cus && p.split_len >= 512;

@@ -101,7 +101,7 @@ struct FwdTiling {
     // fp32 partial rows of a split-KV range leave in whole rows where launches with many queries come (stored by the lanes
     // that hold them, a wave-wide store touches 32 rows with 16 bytes each): 16 heads of 400 queries and 20000 keys, D = 64, 53.2
     // -> 51.3 us; one query: 28.8 -> 29.1, which the 4-wave tiling is for
-    static constexpr bool WHOLE_PARTS = SPLIT && (QB == 2 || (D == 64 && NW == 8));
+    static constexpr bool WHOLE_PARTS = SPLIT && D == 64 && NW == 8;
     static constexpr int LDS_BYTES = XCH_SUMS + XCH_SUMS_BYTES + (HAS_STAGE ? STAGE_BYTES : 0);
     // Persistent workgroups (see attn_fwd_asm_kernel) wherever the loop leaves the compiler registers to carry
     // a tile's state across it: the 8-wave D = 128 loop assigns all 256 VGPRs itself, and a split-KV launch

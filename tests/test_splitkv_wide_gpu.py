@@ -1,5 +1,4 @@
-"""Split-KV ranges in 64-row waves (D = 128, more than 128 queries, long ranges) and partial rows that leave whole (also D = 64 in 8
-waves): sizes at the edges of tiles, waves and ranges, each head against the fp64 oracle on the first and last rows and in every
+"""Split-KV ranges of many queries (8 waves, 256-row tiles) and partial rows that leave whole (D = 64): sizes at the edges of tiles, waves and ranges, each head against the fp64 oracle on the first and last rows and in every
 element against the unsplit call; the bars are test_splitkv_gpu.py's (fp16: a quarter, as its significand has three bits more)."""
 import numpy as np
 import pytest
@@ -39,3 +38,21 @@ def test_wide_ranges(case, dtype):
         got = o[:, h:h + 1].double().cpu().numpy()
         assert np.max(np.abs(got - want)) <= bar
         assert np.max(np.abs(lse[:, h:h + 1].double().cpu().numpy() - want_lse)) <= 1e-3
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("sharp", [False, True])
+def test_a_row_keeps_its_bits_beside_more_queries(dtype, sharp):
+    """Up to 128 queries and above, D = 128 ranges run in the same 32-row waves, whose references come from their own rows: 128
+    queries of a call give what they give in a call of their own."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(7)
+    rnd = lambda *s: torch.empty(s, device="cuda").normal_(generator=g)
+    mk = lambda S, off: (rnd(1, 40, S, 128) + (2 * rnd(1, 40, S, 1) if off else 0)).to(dtype)
+    q, k, v = mk(300, sharp), mk(2100, sharp), mk(2100, False)
+    split = binding.attn_fwd_splitkv if dtype == torch.bfloat16 else binding.attn_fwd_splitkv_f16
+    print("rows", dtype, "sharp", sharp, flush=True)
+    o, lse = split(q, k, v, 4)          # (160 ranges: more than 256 workgroups of 64 rows in either call)
+    few, few_lse = split(q[:, :, :128].contiguous(), k, v, 4)
+    assert torch.equal(o[:, :, :128].contiguous().view(torch.int16), few.view(torch.int16))
+    assert torch.equal(lse[:, :, :128], few_lse)
