@@ -212,6 +212,8 @@ struct BwdKernels {
 int launch_sweeps(const BwdKernels &kern, int threads, int LDS, const BwdParams &p, int BH, int causal, const WalkCost &cost,
                   hipStream_t stream)
 {
+    if (!attn::allow_lds(reinterpret_cast<const void *>(kern.plain), LDS))   // (ahead of the occupancy, which it is part of)
+        return ATTN_ERR_LAUNCH;
     // (a runtime that cannot tell the occupancy gets one workgroup per entry: the kernel takes either)
     int slots = attn::persistent_slots(reinterpret_cast<const void *>(kern.plain), threads, LDS, attn::kNumXcd);
     if (slots < attn::kNumXcd)
@@ -222,7 +224,7 @@ int launch_sweeps(const BwdKernels &kern, int threads, int LDS, const BwdParams 
         r.total_wg = n_kv;
         r.total_q = n_q;
         const int entries = attn::BwdQueue(n_kv, n_q).n_entries;
-        if (!attn::allow_lds(planned ? (const void *)kern.planned : (const void *)kern.plain, LDS))
+        if (planned && !attn::allow_lds(reinterpret_cast<const void *>(kern.planned), LDS))
             return (int)ATTN_ERR_LAUNCH;
         const dim3 grid((unsigned)(slots < entries ? slots : entries));
         if (planned)

@@ -1,0 +1,13 @@
+"""What a backward call asks of the HIP runtime and launches, on a stand-in for it (fake_hip.py)."""
+import fake_hip
+
+# heads, S_q, S_kv, D, causal, f16, tiling (0: as dispatched)
+CALLS = [(16, 515, 515, 64, 0, 1, 0), (16, 1024, 1024, 128, 0, 0, 0), (128, 4096, 4096, 128, 0, 0, 0), (40, 1500, 1500, 128, 1, 0, 0),
+         (123, 72, 5938, 64, 0, 0, 0), (12, 6000, 6000, 128, 1, 1, 2), (300, 300, 300, 128, 0, 0, 3)]
+
+
+def test_a_kernel_may_use_its_lds_before_it_is_asked_about_or_launched(tmp_path):
+    for call, (rc, lines) in zip(CALLS, fake_hip.backward_calls(tmp_path, CALLS)):
+        assert rc == 0 and lines[-1]["what"] == "launch", call
+        for line in lines:
+            assert line["allowed"], (call, line)
