@@ -126,6 +126,7 @@ float plan_walks(attn::BwdPlan &plan, const BwdParams &p, int BH, int causal, co
     if (queue.n_entries <= slots || slots % kNumXcd || per_xcd > BwdPlan::kMaxSlots || n > BwdPlan::kMaxEntries ||
         !p.total_wg || !p.total_q)
         return 1.f;
+    plan = {};   // (all of it goes to the device, and set() keeps the other half of a word)
     const long long head_bytes = 4ll * (p.S_q + p.S_kv) * p.D;
     const auto cost = [&](bool keys, int t) {
         const int steps = walk_steps(p, causal, c.rows, keys, causal && keys ? p.n_t - 1 - t : t);

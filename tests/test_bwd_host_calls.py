@@ -11,3 +11,16 @@ def test_a_kernel_may_use_its_lds_before_it_is_asked_about_or_launched(tmp_path)
         assert rc == 0 and lines[-1]["what"] == "launch", call
         for line in lines:
             assert line["allowed"], (call, line)
+
+
+def test_a_plan_holds_nothing_but_itself(tmp_path):
+    """Its words behind the last entry are zero, whatever stood on the stack."""
+    calls = [(123, 72, 5938, 64, 0, 0, 0), (40, 1500, 1500, 128, 1, 0, 0)] * 2 + [(16, 1000, 8000, 64, 1, 0, 0)]
+    plans = [line["plan"] for _, lines in fake_hip.backward_calls(tmp_path, calls) for line in lines if "plan" in line]
+    assert len(plans) >= 4
+    for words in plans:
+        first = [w >> s & 0xffff for w in words[:33] for s in (0, 16)]
+        slots = first.index(max(first))
+        entries = [w >> s & 0xffff for w in words[33:] for s in (0, 16)]
+        assert sorted(entries[:first[slots]]) == list(range(first[slots])) and slots in (32, 64)
+        assert not any(first[slots + 1:]) and not any(entries[first[slots]:])
