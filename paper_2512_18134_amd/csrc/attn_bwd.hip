@@ -213,25 +213,27 @@ struct BwdKernels {
 int launch_sweeps(const BwdKernels &kern, int threads, int LDS, const BwdParams &p, int BH, int causal, const WalkCost &cost,
                   hipStream_t stream)
 {
-    if (!attn::allow_lds(reinterpret_cast<const void *>(kern.plain), LDS))   // (ahead of the occupancy, which it is part of)
+    // Workgroups of a kernel that the chip holds, 0 if its LDS is refused.  (A runtime that cannot tell the occupancy gets one
+    // workgroup per entry: the kernel takes either)
+    const auto slots_of = [&](const void *k) {
+        if (!attn::allow_lds(k, LDS))   // (ahead of the occupancy, which it is part of)
+            return 0;
+        const int n = attn::persistent_slots(k, threads, LDS, attn::kNumXcd);
+        return n < attn::kNumXcd ? 0x7fffffff : n;
+    };
+    const int slots = slots_of(reinterpret_cast<const void *>(kern.plain));
+    if (slots == 0)
         return ATTN_ERR_LAUNCH;
-    // (a runtime that cannot tell the occupancy gets one workgroup per entry: the kernel takes either)
-    int slots = attn::persistent_slots(reinterpret_cast<const void *>(kern.plain), threads, LDS, attn::kNumXcd);
-    if (slots < attn::kNumXcd)
-        slots = 0x7fffffff;
     attn::BwdPlan plan;
-    const auto run = [&](int n_kv, int n_q, bool planned) {
+    const auto run = [&](int n_kv, int n_q, int planned) {
         BwdParams r = p;
         r.total_wg = n_kv;
         r.total_q = n_q;
         const int entries = attn::BwdQueue(n_kv, n_q).n_entries;
-        if (planned && !attn::allow_lds(reinterpret_cast<const void *>(kern.planned), LDS))
-            return (int)ATTN_ERR_LAUNCH;
-        const dim3 grid((unsigned)(slots < entries ? slots : entries));
         if (planned)
-            hipLaunchKernelGGL(kern.planned, grid, dim3(threads), LDS, stream, r, plan);
+            hipLaunchKernelGGL(kern.planned, dim3((unsigned)planned), dim3(threads), LDS, stream, r, plan);
         else
-            hipLaunchKernelGGL(kern.plain, grid, dim3(threads), LDS, stream, r);
+            hipLaunchKernelGGL(kern.plain, dim3((unsigned)(slots < entries ? slots : entries)), dim3(threads), LDS, stream, r);
         return (int)(hipGetLastError() == hipSuccess ? ATTN_OK : ATTN_ERR_LAUNCH);
     };
     // Time by plan over time by passes, over 190 launches: D = 128, 0.73 to 0.98 where the longest walk is under 0.95 of the passes'
@@ -240,12 +242,16 @@ int launch_sweeps(const BwdKernels &kern, int threads, int LDS, const BwdParams 
     // the rest took up to 1.09 times as long (116 heads of 607 rows 38.1 -> 41.3).
     const int walk = causal && p.S_q < p.S_kv ? p.S_q : p.S_kv;
     const float pays = p.D == 64 && causal && walk < 1024 ? 0.8f : cost.plan_pays;
-    if (plan_walks(plan, p, BH, causal, cost, slots) < pays)
-        return run(p.total_wg, p.total_q, true);
+    if (attn::BwdQueue(p.total_wg, p.total_q).n_entries > slots) {
+        // (as many workgroups as the planned kernel fits: all of a plan's run at once)
+        const int planned = slots_of(reinterpret_cast<const void *>(kern.planned));
+        if (planned && plan_walks(plan, p, BH, causal, cost, planned) < pays)
+            return run(p.total_wg, p.total_q, planned);
+    }
     if (!sweeps_apart(p, causal, slots))
-        return run(p.total_wg, p.total_q, false);
-    const int rc = run(p.total_wg, 0, false);
-    return rc == ATTN_OK ? run(0, p.total_q, false) : rc;
+        return run(p.total_wg, p.total_q, 0);
+    const int rc = run(p.total_wg, 0, 0);
+    return rc == ATTN_OK ? run(0, p.total_q, 0) : rc;
 }
 
 // Estimated time of a D = 128 launch on `cus` compute units: the longest walk among XCD 0's workgroups

@@ -61,7 +61,7 @@ int hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *fn, int thr
 {
     const int k = kernel(fn), ok = lds <= 65536 || (int)lds <= kernels[k].lds;
     *n = ok ? 163840 / (int)lds : 0;
-    fprintf(out, "{\"what\": \"occupancy\", \"kernel\": \"%s\", \"allowed\": %d}\n", kernels[k].name, ok);
+    fprintf(out, "{\"what\": \"occupancy\", \"kernel\": \"%s\", \"allowed\": %d, \"fits\": %d}\n", kernels[k].name, ok, *n);
     return ok ? 0 : 1;
 }
 int hipLaunchKernel(const void *fn, dim3 grid, dim3 block, void **args, size_t lds, void *stream)

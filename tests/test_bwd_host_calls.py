@@ -24,3 +24,17 @@ def test_a_plan_holds_nothing_but_itself(tmp_path):
         entries = [w >> s & 0xffff for w in words[33:] for s in (0, 16)]
         assert sorted(entries[:first[slots]]) == list(range(first[slots])) and slots in (32, 64)
         assert not any(first[slots + 1:]) and not any(entries[first[slots]:])
+
+
+def test_a_planned_launch_has_the_workgroups_that_its_kernel_fits(tmp_path):
+    """A plan is made for so many workgroups; all of them have to run at once."""
+    calls = [(123, 72, 5938, 64, 0, 0, 0), (40, 1500, 1500, 128, 1, 0, 0), (12, 6000, 6000, 128, 1, 1, 2), (40, 1500, 1500, 128, 1, 0, 1)]
+    fits, planned = {}, 0
+    for call, (rc, lines) in zip(calls, fake_hip.backward_calls(tmp_path, calls)):
+        for line in lines:
+            if line["what"] == "occupancy":
+                fits[line["kernel"]] = line["fits"]
+            elif "plan" in line:
+                planned += 1
+                assert line["grid"] == 256 * fits.get(line["kernel"], 0), (call, line["kernel"], line["grid"])
+    assert planned == len(calls)
