@@ -2,7 +2,9 @@
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
+#include <string.h>
 
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 
@@ -82,8 +84,8 @@ int walk_steps(const BwdParams &p, int causal, int rows, bool keys, int t)
     }
     int end = p.S_kv;
     if (causal) {
-        const int last = p.S_q / rows > t ? (t + 1) * rows : p.S_q;
-        end = last < end ? last : end;
+        const long long last = (t + 1ll) * rows < p.S_q ? (t + 1ll) * rows : p.S_q;
+        end = last < end ? (int)last : end;
     }
     return (end + 31) / 32;
 }
@@ -111,70 +113,125 @@ void xcd_tiles(int heads, int n_t, int causal, long long head_bytes, int xcd, F 
                 each(t);
 }
 
-// The plan of a launch's walks (BwdPlan): the sweep with the longer tiles first, every entry of an XCD's queue to the workgroup that
-// is free first.  Taking one pass through the queue after the other, odd ones backwards, leaves walks up to a third apart where
-// tiles differ, by the mask or by the sweep they belong to.  By passes -> by plan, in us: D = 128, 40 causal heads of 1500 rows
-// 106.7 -> 95, 12 of 6000 1.17 times as fast, 123 heads of 72 x 5938 1.12 (against one sweep after the other), 16 causal of
-// 1000 x 8000 1.36; D = 64, 123 of 72 x 5938 1.36, 16 of 1000 x 8000 1.28.  The host takes 3 to 38 us for it, behind the Delta
-// kernel's launch.  Returns the longest walk over that of the passes (of any XCD); 1 and no plan: one pass, or too many entries.
-float plan_walks(attn::BwdPlan &plan, const BwdParams &p, int BH, int causal, const WalkCost &c, int slots)
+// The walks of a launch's workgroups in one tiling, from what every entry of an XCD's queue costs
+struct BwdWalks {
+    static constexpr int kMax = attn::BwdPlan::kMaxEntries;
+    int n, first_q, per_xcd;   // entries of XCD 0, the first of a query owner, workgroups of an XCD
+    int xcds;                  // 2: heads are dealt out tile by tile and give the XCDs different tiles
+    // by place in the queue: XCD 0's entries and XCD 7's, which have the heaviest tile of each place between them (heaviest first,
+    // every other row of eight in reverse); 0 where XCD 7 has none
+    float cost[2][kMax];
+    float passes;   // the longest walk where the queue is taken pass by pass (BwdQueue::entry)
+    float least;    // no plan's longest walk is shorter
+    bool keys_first;   // the key owners' tiles are the longer ones
+
+    // false: a single pass, or too many entries
+    bool fill(const BwdParams &p, int BH, int causal, const WalkCost &c, int slots)
+    {
+        using attn::kNumXcd;
+        const attn::BwdQueue queue(p.total_wg, p.total_q);
+        if (queue.n_entries <= slots || slots % kNumXcd || slots / kNumXcd > attn::BwdPlan::kMaxSlots ||
+            queue.n_entries > kMax * kNumXcd || !p.total_wg || !p.total_q)
+            return false;
+        n = (queue.n_entries + kNumXcd - 1) / kNumXcd;
+        first_q = queue.q_first / kNumXcd;
+        per_xcd = slots / kNumXcd;
+        xcds = causal && BH % kNumXcd ? 2 : 1;
+        const long long head_bytes = 4ll * (p.S_q + p.S_kv) * p.D;
+        const auto tile = [&](bool keys, int t) {
+            const int steps = walk_steps(p, causal, c.rows, keys, causal && keys ? p.n_t - 1 - t : t);
+            return keys ? c.key_tile + c.key_step * steps : c.query_tile + c.query_step * steps;
+        };
+        keys_first = tile(true, causal ? p.n_t - 1 : 0) >= tile(false, p.n_tq - 1);
+        passes = least = 0.f;
+        for (int x = 0; x < xcds; ++x) {
+            float *const of = cost[x], *at = of;
+            if (causal) {
+                xcd_tiles(BH, p.n_t, causal, head_bytes, x * (kNumXcd - 1), [&](int t) { *at++ = tile(true, t); });
+                std::fill(at, of + first_q, 0.f);
+                at = of + first_q;
+                xcd_tiles(BH, p.n_tq, causal, head_bytes, x * (kNumXcd - 1), [&](int t) { *at++ = tile(false, t); });
+                std::fill(at, of + n, 0.f);
+            } else {
+                std::fill(of, of + first_q, tile(true, 0));
+                std::fill(of + first_q, of + n, tile(false, 0));
+            }
+            float walk[attn::BwdPlan::kMaxSlots] = {}, sum = 0.f, heaviest = 0.f;
+            for (int k = 0, first = 0; first < n; ++k, first += per_xcd)
+                for (int i = 0; i < per_xcd && first + i < n; ++i) {
+                    const float l = of[first + i];
+                    walk[k & 1 ? per_xcd - 1 - i : i] += l;
+                    sum += l;
+                    heaviest = l > heaviest ? l : heaviest;
+                }
+            for (int m = 0; m < per_xcd; ++m)
+                passes = walk[m] > passes ? walk[m] : passes;
+            least = std::max({least, sum / per_xcd, heaviest});
+        }
+        if (!causal)
+            least = two_costs(keys_first ? first_q : n - first_q, std::max(cost[0][0], cost[0][n - 1]),
+                              keys_first ? n - first_q : first_q, std::min(cost[0][0], cost[0][n - 1]));
+        return true;
+    }
+
+    // plan_walks's longest walk where there are only two costs: n1 tiles of l1, then n2 of l2.  Workgroups in two classes, one
+    // l1 apart; the one that is free first takes a tile each
+    float two_costs(int n1, float l1, int n2, float l2) const
+    {
+        const int more = n1 % per_xcd;
+        float load[2] = {(float)(n1 / per_xcd) * l1, (float)(n1 / per_xcd + 1) * l1};
+        const int of[2] = {per_xcd - more, more};
+        float longest = load[more > 0];
+        while (n2 > 0) {
+            const int i = more > 0 && load[1] < load[0];
+            load[i] += l2;
+            longest = std::max(longest, load[i]);
+            n2 -= of[i];
+        }
+        return longest;
+    }
+};
+
+// The plan of a launch's walks (BwdPlan): list scheduling.  The sweep with the longer tiles first, every entry of an XCD's queue, in the
+// queue's order, to the workgroup that is free first.  Taking one pass through the queue after the other, odd ones backwards, leaves walks up to
+// a third apart where tiles differ, by the mask or by the sweep they belong to.  By passes -> by plan, in us: D = 128, 40 causal heads
+// of 1500 rows 106.7 -> 95, 12 of 6000 1.17 times as fast, 123 heads of 72 x 5938 1.12 (against one sweep after the other), 16 causal of
+// 1000 x 8000 1.36; D = 64, 123 of 72 x 5938 1.36, 16 of 1000 x 8000 1.28.  The queue is sorted within a group of heads only: where
+// many groups follow each other a plan can be longer than the passes (and is not taken).  Returns the longest walk.
+float plan_walks(attn::BwdPlan &plan, const BwdWalks &w, int cus)
 {
     using attn::BwdPlan;
-    using attn::kNumXcd;
-    const attn::BwdQueue queue(p.total_wg, p.total_q);
-    const int per_xcd = slots / kNumXcd, cus = p.cus_per_xcd, n = (queue.n_entries + kNumXcd - 1) / kNumXcd;
-    if (queue.n_entries <= slots || slots % kNumXcd || per_xcd > BwdPlan::kMaxSlots || n > BwdPlan::kMaxEntries ||
-        !p.total_wg || !p.total_q)
-        return 1.f;
     plan = {};   // (all of it goes to the device, and set() keeps the other half of a word)
-    const long long head_bytes = 4ll * (p.S_q + p.S_kv) * p.D;
-    const auto cost = [&](bool keys, int t) {
-        const int steps = walk_steps(p, causal, c.rows, keys, causal && keys ? p.n_t - 1 - t : t);
-        return keys ? c.key_tile + c.key_step * steps : c.query_tile + c.query_step * steps;
-    };
-    // go(place in the queue, cost) for an XCD's entries of both sweeps
-    const auto each_entry = [&](int xcd, auto &&go) {
-        for (const bool keys : {true, false}) {
-            int at = keys ? 0 : queue.q_first / kNumXcd;
-            xcd_tiles(BH, keys ? p.n_t : p.n_tq, causal, head_bytes, xcd, [&](int t) { go(at++, cost(keys, t)); });
-        }
-    };
-    // heads that are dealt out tile by tile give the XCDs different tiles: the plan is made for the longest in each place
-    const int xcds = causal && BH % kNumXcd ? kNumXcd : 1;
-    float longest_of[BwdPlan::kMaxEntries] = {};
-    for (int x = 0; x < xcds; ++x)
-        each_entry(x, [&](int at, float l) { longest_of[at] = l > longest_of[at] ? l : longest_of[at]; });
-    // binary heap of (load, workgroup), the least load on top
-    struct Free {
-        float load;
-        int m;
-    } heap[BwdPlan::kMaxSlots];
-    for (int m = 0; m < per_xcd; ++m)
-        heap[m] = {0.f, m};
-    const auto less = [](const Free &x, const Free &y) { return x.load < y.load || (x.load == y.load && x.m < y.m); };
+    const int per_xcd = w.per_xcd;
+    // (load, workgroup) at the leaves of a tree whose nodes hold the lesser of their two: its root is free first, and one path to it is
+    // renewed per entry, without branches to guess (10 ns; a binary heap takes 30).  (The bits of floats that are not negative have the
+    // floats' order)
+    int leaves = 1;
+    while (leaves < per_xcd)
+        leaves *= 2;
+    uint64_t tree[2 * BwdPlan::kMaxSlots];
+    for (int m = 0; m < leaves; ++m)
+        tree[leaves + m] = m < per_xcd ? (uint64_t)m : ~0ull;
+    for (int i = leaves - 1; i > 0; --i)
+        tree[i] = std::min(tree[2 * i], tree[2 * i + 1]);
     uint8_t owner[BwdPlan::kMaxEntries];
     int of_slot[BwdPlan::kMaxSlots] = {};
-    const int first_q = queue.q_first / kNumXcd;
-    const bool keys_first = cost(true, causal ? p.n_t - 1 : 0) >= cost(false, p.n_tq - 1);
-    for (const bool keys : {keys_first, !keys_first})
-        for (int at = keys ? 0 : first_q; at < (keys ? first_q : n); ++at) {
-            Free top = heap[0];
-            owner[at] = (uint8_t)top.m;
-            ++of_slot[top.m];
-            top.load += longest_of[at];
-            int i = 0;
-            for (;;) {
-                int child = 2 * i + 1;
-                if (child >= per_xcd)
-                    break;
-                if (child + 1 < per_xcd && less(heap[child + 1], heap[child]))
-                    ++child;
-                if (!less(heap[child], top))
-                    break;
-                heap[i] = heap[child];
-                i = child;
+    for (const bool keys : {w.keys_first, !w.keys_first})
+        for (int at = keys ? 0 : w.first_q; at < (keys ? w.first_q : w.n); ++at) {
+            const int m = (int)(uint32_t)tree[1];
+            owner[at] = (uint8_t)m;
+            ++of_slot[m];
+            uint32_t bits = (uint32_t)(tree[1] >> 32);
+            float load;
+            memcpy(&load, &bits, sizeof load);
+            load += w.xcds > 1 ? std::max(w.cost[0][at], w.cost[1][at]) : w.cost[0][at];
+            memcpy(&bits, &load, sizeof load);
+            uint64_t least = (uint64_t)bits << 32 | (uint32_t)m;
+            for (int i = leaves + m; i > 1; i /= 2) {
+                tree[i] = least;
+                least = std::min(least, tree[i ^ 1]);
             }
-            heap[i] = top;
+            tree[1] = least;
         }
     // the workgroups that begin with the heaviest tiles share their compute units with those that begin with the lightest
     // (BwdQueue::entry)
@@ -186,22 +243,17 @@ float plan_walks(attn::BwdPlan &plan, const BwdParams &p, int BH, int causal, co
         first[m + 1] += first[m];
     for (int m = 0; m <= per_xcd; ++m)
         BwdPlan::set(plan.first, m, first[m]);
-    for (int i = 0; i < n; ++i)
-        BwdPlan::set(plan.idx, first[place(owner[i])]++, i);
-    float planned = 0.f, passes = 0.f;
-    for (int x = 0; x < xcds; ++x) {
-        float by_plan[BwdPlan::kMaxSlots] = {}, by_pass[BwdPlan::kMaxSlots] = {};
-        each_entry(x, [&](int at, float l) {
-            const int m = at % per_xcd;
-            by_plan[owner[at]] += l;
-            by_pass[at / per_xcd & 1 ? per_xcd - 1 - m : m] += l;
-        });
-        for (int m = 0; m < per_xcd; ++m) {
-            planned = by_plan[m] > planned ? by_plan[m] : planned;
-            passes = by_pass[m] > passes ? by_pass[m] : passes;
-        }
+    float longest = 0.f;
+    for (int x = 0; x < w.xcds; ++x) {
+        float walk[BwdPlan::kMaxSlots] = {};
+        for (int at = 0; at < w.n; ++at)
+            walk[owner[at]] += w.cost[x][at];
+        for (int m = 0; m < per_xcd; ++m)
+            longest = walk[m] > longest ? walk[m] : longest;
     }
-    return planned / passes;
+    for (int at = 0; at < w.n; ++at)
+        BwdPlan::set(plan.idx, first[place(owner[at])]++, at);
+    return longest;
 }
 
 // both hand-scheduled sweeps: as many workgroups as the chip holds at once, each walking the queue of owner tiles of its
@@ -245,7 +297,11 @@ int launch_sweeps(const BwdKernels &kern, int threads, int LDS, const BwdParams 
     if (attn::BwdQueue(p.total_wg, p.total_q).n_entries > slots) {
         // (as many workgroups as the planned kernel fits: all of a plan's run at once)
         const int planned = slots_of(reinterpret_cast<const void *>(kern.planned));
-        if (planned && plan_walks(plan, p, BH, causal, cost, planned) < pays)
+        // The host works behind the Delta kernel's launch; a call that is waited for pays what that leaves.  0.4 to 5 us for the walks and
+        // to see that no plan pays, 1 to 10 more for a plan that is made.
+        BwdWalks w;
+        if (planned && w.fill(p, BH, causal, cost, planned) && w.least < pays * w.passes &&
+            plan_walks(plan, w, p.cus_per_xcd) < pays * w.passes)
             return run(p.total_wg, p.total_q, planned);
     }
     if (!sweeps_apart(p, causal, slots))
@@ -523,8 +579,10 @@ extern "C" int attn_bwd_sweeps_apart(int heads, int S_q, int S_kv, int causal, i
     return sweeps_apart(p, causal, slots);
 }
 
-// Test-only, host only: what plan_walks says of a launch.
-extern "C" float attn_bwd_plan(int heads, int S_q, int S_kv, int D, int causal, int tiling, int cus, uint32_t *first, uint32_t *idx)
+// Test-only, host only: a launch's plan; the longest walk over that of the passes, 1 without walks (BwdWalks::fill).  walks, in us: the longest
+// by plan and by passes, what no order goes below, then XCD 0's entries.
+extern "C" float attn_bwd_plan(int heads, int S_q, int S_kv, int D, int causal, int tiling, int cus, uint32_t *first, uint32_t *idx,
+                               float *walks)
 {
     const WalkCost &c = D == 64 ? kWalkD64 : tiling == kRows256 ? kWalk256 : tiling == kRows128 ? kWalk128 : kWalk128TwoWaves;
     BwdParams p;
@@ -535,14 +593,19 @@ extern "C" float attn_bwd_plan(int heads, int S_q, int S_kv, int D, int causal, 
     p.n_tq = (S_q + c.rows - 1) / c.rows;
     p.total_wg = heads * p.n_t;
     p.total_q = heads * p.n_tq;
-    p.cus_per_xcd = cus / attn::kNumXcd;
-    attn::BwdPlan plan = {};
-    const float ratio = plan_walks(plan, p, heads, causal, c, cus * c.per_cu);
+    attn::BwdPlan plan;
+    BwdWalks w;
+    if (!w.fill(p, heads, causal, c, cus * c.per_cu))
+        return 1.f;
+    walks[0] = plan_walks(plan, w, cus / attn::kNumXcd);
+    walks[1] = w.passes;
+    walks[2] = w.least;
+    std::copy(w.cost[0], w.cost[0] + w.n, walks + 3);
     for (int i = 0; i < (int)(sizeof plan.first / 4); ++i)
         first[i] = plan.first[i];
     for (int i = 0; i < (int)(sizeof plan.idx / 4); ++i)
         idx[i] = plan.idx[i];
-    return ratio;
+    return walks[0] / walks[1];
 }
 
 // Test-only, host only: the i-th tile that an XCD takes up of a sweep (xcd_tiles), -1 behind the last, and the same from
