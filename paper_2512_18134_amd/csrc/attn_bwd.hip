@@ -67,11 +67,12 @@ enum BwdTiling { kAsDispatched, kRows128, kRows256, kRows128TwoWaves };
 struct WalkCost {
     int rows, per_cu;   // of an owner tile; workgroups that a compute unit holds
     float key_tile, key_step, query_tile, query_step, launch, mean, plan_pays;
+    float key(int steps) const { return key_tile + key_step * steps; }
+    float query(int steps) const { return query_tile + query_step * steps; }
 };
 constexpr WalkCost kWalk128 = {128, 1, 4.18f, 0.522f, 3.55f, 0.367f, 5.76f, 0.535f, 0.95f},
                    kWalk256 = {256, 1, 7.26f, 0.924f, 5.56f, 0.644f, 4.83f, 0.503f, 0.95f},
                    kWalk128TwoWaves = {128, 2, 7.27f, 0.920f, 6.32f, 0.654f, 4.72f, 0.551f, 0.95f};
-constexpr float kPlanTail = 0.5f;   // (the mean tile's share that a planned launch's longest walk lies above the mean one)
 // D = 64 (two workgroups to a CU): what the tiles' walks cost beside each other is all that is asked of it
 constexpr WalkCost kWalkD64 = {128, 2, 4.0f, 0.60f, 3.5f, 0.45f, 0.f, 0.f, 0.93f};
 
@@ -91,26 +92,24 @@ int walk_steps(const BwdParams &p, int causal, int rows, bool keys, int t)
 }
 
 // The tiles of one sweep that an XCD takes up, in its queue's order: what wg_to_tile_n gives for entries xcd, xcd + 8, xcd + 16,
-// ..., without its divisions.  each(t) per tile.
+// ..., without its divisions.  each(t, n) per n tiles t.
 template <typename F>
 void xcd_tiles(int heads, int n_t, int causal, long long head_bytes, int xcd, F &&each)
 {
     using attn::kNumXcd;
     const int a = heads / kNumXcd, r = heads % kNumXcd, n_left = r * n_t;
     if (!causal) {
-        for (long long i = xcd; i < (long long)heads * n_t; i += kNumXcd)
-            each(0);   // (all alike)
+        each(0, (int)(((long long)heads * n_t - xcd + kNumXcd - 1) / kNumXcd));   // (all alike)
         return;
     }
     for (int i = 0; kNumXcd * i + xcd < n_left; ++i)
-        each(n_t - 1 - (kNumXcd * i + ((i & 1) && kNumXcd * (i + 1) <= n_left ? kNumXcd - 1 - xcd : xcd)) / r);
+        each(n_t - 1 - (kNumXcd * i + ((i & 1) && kNumXcd * (i + 1) <= n_left ? kNumXcd - 1 - xcd : xcd)) / r, 1);
     if (a == 0)
         return;
     const int want = attn::causal_group_heads(n_t, head_bytes), ng = a > want ? a / want : 1;
     for (int g = 0; g < ng; ++g)
         for (int t = n_t - 1; t >= 0; --t)
-            for (int h = 0; h < a / ng + (g < a % ng); ++h)
-                each(t);
+            each(t, a / ng + (g < a % ng));
 }
 
 // The walks of a launch's workgroups in one tiling, from what every entry of an XCD's queue costs
@@ -138,35 +137,40 @@ struct BwdWalks {
         per_xcd = slots / kNumXcd;
         xcds = causal && BH % kNumXcd ? 2 : 1;
         const long long head_bytes = 4ll * (p.S_q + p.S_kv) * p.D;
-        const auto tile = [&](bool keys, int t) {
-            const int steps = walk_steps(p, causal, c.rows, keys, causal && keys ? p.n_t - 1 - t : t);
-            return keys ? c.key_tile + c.key_step * steps : c.query_tile + c.query_step * steps;
-        };
-        keys_first = tile(true, causal ? p.n_t - 1 : 0) >= tile(false, p.n_tq - 1);
-        passes = least = 0.f;
+        const float first_key = c.key(walk_steps(p, causal, c.rows, true, 0)),
+                    last_query = c.query(walk_steps(p, causal, c.rows, false, p.n_tq - 1));   // the heaviest of either sweep
+        keys_first = first_key >= last_query;
+        passes = 0.f;
+        least = std::max(first_key, last_query);
         for (int x = 0; x < xcds; ++x) {
             float *const of = cost[x], *at = of;
             if (causal) {
-                xcd_tiles(BH, p.n_t, causal, head_bytes, x * (kNumXcd - 1), [&](int t) { *at++ = tile(true, t); });
+                xcd_tiles(BH, p.n_t, causal, head_bytes, x * (kNumXcd - 1),
+                          [&](int t, int m) { at = std::fill_n(at, m, c.key(walk_steps(p, causal, c.rows, true, p.n_t - 1 - t))); });
                 std::fill(at, of + first_q, 0.f);
                 at = of + first_q;
-                xcd_tiles(BH, p.n_tq, causal, head_bytes, x * (kNumXcd - 1), [&](int t) { *at++ = tile(false, t); });
+                xcd_tiles(BH, p.n_tq, causal, head_bytes, x * (kNumXcd - 1),
+                          [&](int t, int m) { at = std::fill_n(at, m, c.query(walk_steps(p, causal, c.rows, false, t))); });
                 std::fill(at, of + n, 0.f);
             } else {
-                std::fill(of, of + first_q, tile(true, 0));
-                std::fill(of + first_q, of + n, tile(false, 0));
+                std::fill(of, of + first_q, first_key);
+                std::fill(of + first_q, of + n, last_query);
             }
-            float walk[attn::BwdPlan::kMaxSlots] = {}, sum = 0.f, heaviest = 0.f;
-            for (int k = 0, first = 0; first < n; ++k, first += per_xcd)
-                for (int i = 0; i < per_xcd && first + i < n; ++i) {
-                    const float l = of[first + i];
-                    walk[k & 1 ? per_xcd - 1 - i : i] += l;
-                    sum += l;
-                    heaviest = l > heaviest ? l : heaviest;
-                }
-            for (int m = 0; m < per_xcd; ++m)
-                passes = walk[m] > passes ? walk[m] : passes;
-            least = std::max({least, sum / per_xcd, heaviest});
+            float walk[attn::BwdPlan::kMaxSlots] = {}, sum = 0.f;
+            for (int k = 0, first = 0; first < n; ++k, first += per_xcd) {
+                const int m = std::min(per_xcd, n - first);
+                if (k & 1)
+                    for (int i = 0; i < m; ++i)
+                        walk[per_xcd - 1 - i] += of[first + i];
+                else
+                    for (int i = 0; i < m; ++i)
+                        walk[i] += of[first + i];
+            }
+            for (int m = 0; m < per_xcd; ++m) {
+                passes = std::max(passes, walk[m]);
+                sum += walk[m];
+            }
+            least = std::max(least, sum / per_xcd);
         }
         if (!causal)
             least = two_costs(keys_first ? first_q : n - first_q, std::max(cost[0][0], cost[0][n - 1]),
@@ -256,14 +260,99 @@ float plan_walks(attn::BwdPlan &plan, const BwdWalks &w, int cus)
     return longest;
 }
 
+// A launch in one tiling: its walks, the plan of them if it has one, and (D = 128) what it is estimated to take.  In three steps, as
+// the host's time counts: set() asks no walks, walk() makes no plan, and `us` is the least that the next step could leave.
+struct BwdLaunch {
+    BwdParams p;
+    const WalkCost *c;
+    BwdWalks walks;
+    attn::BwdPlan plan;
+    float pays;       // the walk that a plan has to stay below
+    float rest, us;   // what is added to the longest walk; the sum
+    enum { kSet, kWalked, kDone } step;
+    bool planned;
+
+    void set(const BwdParams &of, int BH, int causal, const WalkCost &cost, int cus)
+    {
+        p = of;
+        c = &cost;
+        p.n_t = (p.S_kv + cost.rows - 1) / cost.rows;
+        p.n_tq = (p.S_q + cost.rows - 1) / cost.rows;
+        p.total_wg = BH * p.n_t;
+        p.total_q = BH * p.n_tq;
+        planned = false;
+        rest = us = 0.f;
+        step = cus > 0 ? kSet : kDone;
+        if (p.D != 128 || cus <= 0)
+            return;
+        const int slots = cus * cost.per_cu, entries = attn::BwdQueue(p.total_wg, p.total_q).n_entries;
+        // steps of a head's tiles: they fall (key owners) or rise (query owners) by rows / 32 from tile to tile while a mask cuts them
+        const auto steps = [&](bool keys, int n) {
+            if (!causal)
+                return (double)n * walk_steps(p, 0, cost.rows, keys, 0);
+            const int d = cost.rows / 32, top = (p.S_q + 31) / 32;
+            if (keys) {
+                const int all = (top + d - 1) / d < n ? (top + d - 1) / d : n;
+                return (double)all * top - 0.5 * d * all * (all - 1.0);
+            }
+            const int cut = (p.S_q < p.S_kv ? p.S_q : p.S_kv) / cost.rows, m = cut < n ? cut : n;   // tiles the mask's edge runs through
+            return 0.5 * d * m * (m + 1.0) + (double)(n - m) * walk_steps(p, causal, cost.rows, keys, n - 1);
+        };
+        const double all = BH * (p.n_t * (double)cost.key_tile + steps(true, p.n_t) * cost.key_step + p.n_tq * (double)cost.query_tile +
+                                 steps(false, p.n_tq) * cost.query_step);
+        const float mean = (float)(all / slots);
+        const float heaviest = std::max(cost.key(walk_steps(p, causal, cost.rows, true, 0)),
+                                        cost.query(walk_steps(p, causal, cost.rows, false, p.n_tq - 1)));
+        rest = cost.launch + cost.mean * mean;
+        us = rest + std::max(mean, heaviest);
+        if (entries <= slots || entries > BwdWalks::kMax * attn::kNumXcd) {
+            us = rest + (entries <= slots ? heaviest : mean + heaviest * (causal ? 0.25f : 0.5f));
+            step = kDone;
+        }
+    }
+    void walk(int BH, int causal, int cus)
+    {
+        step = kDone;
+        if (!walks.fill(p, BH, causal, *c, cus * c->per_cu))
+            return;
+        // Time by plan over time by passes, over 190 launches: D = 128, 0.73 to 0.98 where the longest walk is under 0.95 of the
+        // passes' (one of 97 1.02), 0.96 to 1.05 above.  D = 64, 0.81 to 1.02 under 0.93 (0.94 in the mean), 0.96 to 1.07 above; but
+        // the costs of short causal walks are less sure there: of 28 launches under 1024 rows and between 0.8 and 0.93, seven
+        // gained more than 3 % and the rest took up to 1.09 times as long (116 heads of 607 rows 38.1 -> 41.3).
+        const int keys = causal && p.S_q < p.S_kv ? p.S_q : p.S_kv;
+        pays = (p.D == 64 && causal && keys < 1024 ? 0.8f : c->plan_pays) * walks.passes;
+        if (walks.least < pays)
+            step = kWalked;
+        us = rest + (step == kWalked ? walks.least : walks.passes);
+    }
+    // makes the plan, and takes it if it pays
+    void close()
+    {
+        const float longest = plan_walks(plan, walks, p.cus_per_xcd);
+        planned = longest < pays;
+        us = rest + (planned ? longest : walks.passes);
+        step = kDone;
+    }
+    // the next step; false: there is none
+    bool go_on(int BH, int causal, int cus)
+    {
+        if (step == kDone)
+            return false;
+        if (step == kSet)
+            walk(BH, causal, cus);
+        else
+            close();
+        return true;
+    }
+};
+
 // both hand-scheduled sweeps: as many workgroups as the chip holds at once, each walking the queue of owner tiles of its
 // XCD, or what a plan gives it
 struct BwdKernels {
     void (*plain)(const BwdParams);
     void (*planned)(const BwdParams, const attn::BwdPlan);
 };
-int launch_sweeps(const BwdKernels &kern, int threads, int LDS, const BwdParams &p, int BH, int causal, const WalkCost &cost,
-                  hipStream_t stream)
+int launch_sweeps(const BwdKernels &kern, int threads, int LDS, const BwdLaunch &l, int causal, hipStream_t stream)
 {
     // Workgroups of a kernel that the chip holds, 0 if its LDS is refused.  (A runtime that cannot tell the occupancy gets one
     // workgroup per entry: the kernel takes either)
@@ -273,94 +362,26 @@ int launch_sweeps(const BwdKernels &kern, int threads, int LDS, const BwdParams 
         const int n = attn::persistent_slots(k, threads, LDS, attn::kNumXcd);
         return n < attn::kNumXcd ? 0x7fffffff : n;
     };
+    // (all of a plan's workgroups have to run at once: as many as the planned kernel fits)
+    if (l.planned && slots_of(reinterpret_cast<const void *>(kern.planned)) == l.walks.per_xcd * attn::kNumXcd) {
+        hipLaunchKernelGGL(kern.planned, dim3((unsigned)(l.walks.per_xcd * attn::kNumXcd)), dim3(threads), LDS, stream, l.p, l.plan);
+        return hipGetLastError() == hipSuccess ? ATTN_OK : ATTN_ERR_LAUNCH;
+    }
     const int slots = slots_of(reinterpret_cast<const void *>(kern.plain));
     if (slots == 0)
         return ATTN_ERR_LAUNCH;
-    attn::BwdPlan plan;
-    const auto run = [&](int n_kv, int n_q, int planned) {
-        BwdParams r = p;
+    const auto run = [&](int n_kv, int n_q) {
+        BwdParams r = l.p;
         r.total_wg = n_kv;
         r.total_q = n_q;
         const int entries = attn::BwdQueue(n_kv, n_q).n_entries;
-        if (planned)
-            hipLaunchKernelGGL(kern.planned, dim3((unsigned)planned), dim3(threads), LDS, stream, r, plan);
-        else
-            hipLaunchKernelGGL(kern.plain, dim3((unsigned)(slots < entries ? slots : entries)), dim3(threads), LDS, stream, r);
+        hipLaunchKernelGGL(kern.plain, dim3((unsigned)(slots < entries ? slots : entries)), dim3(threads), LDS, stream, r);
         return (int)(hipGetLastError() == hipSuccess ? ATTN_OK : ATTN_ERR_LAUNCH);
     };
-    // Time by plan over time by passes, over 190 launches: D = 128, 0.73 to 0.98 where the longest walk is under 0.95 of the passes'
-    // (one of 97 1.02), 0.96 to 1.05 above.  D = 64, 0.81 to 1.02 under 0.93 (0.94 in the mean), 0.96 to 1.07 above; but the costs of
-    // short causal walks are less sure there: of 28 launches under 1024 rows and between 0.8 and 0.93, seven gained more than 3 % and
-    // the rest took up to 1.09 times as long (116 heads of 607 rows 38.1 -> 41.3).
-    const int walk = causal && p.S_q < p.S_kv ? p.S_q : p.S_kv;
-    const float pays = p.D == 64 && causal && walk < 1024 ? 0.8f : cost.plan_pays;
-    if (attn::BwdQueue(p.total_wg, p.total_q).n_entries > slots) {
-        // (as many workgroups as the planned kernel fits: all of a plan's run at once)
-        const int planned = slots_of(reinterpret_cast<const void *>(kern.planned));
-        // The host works behind the Delta kernel's launch; a call that is waited for pays what that leaves.  0.4 to 5 us for the walks and
-        // to see that no plan pays, 1 to 10 more for a plan that is made.
-        BwdWalks w;
-        if (planned && w.fill(p, BH, causal, cost, planned) && w.least < pays * w.passes &&
-            plan_walks(plan, w, p.cus_per_xcd) < pays * w.passes)
-            return run(p.total_wg, p.total_q, planned);
-    }
-    if (!sweeps_apart(p, causal, slots))
-        return run(p.total_wg, p.total_q, 0);
-    const int rc = run(p.total_wg, 0, 0);
-    return rc == ATTN_OK ? run(0, p.total_q, 0) : rc;
-}
-
-// Estimated time of a D = 128 launch on `cus` compute units: the longest walk among XCD 0's workgroups
-float launch_estimate(const BwdParams &p, int BH, int causal, const WalkCost &c, int cus)
-{
-    constexpr int kMaxPasses = 12, kMaxSlots = 128;      // per XCD
-    const int rows = c.rows, slots = cus * c.per_cu;
-    const int n_t = (p.S_kv + rows - 1) / rows, n_tq = (p.S_q + rows - 1) / rows;
-    const attn::BwdQueue queue(BH * n_t, BH * n_tq);
-    const int per_pass = slots / attn::kNumXcd, first = cus / attn::kNumXcd < per_pass ? cus / attn::kNumXcd : per_pass;
-    // steps of a head's tiles: they fall (key owners) or rise (query owners) by rows / 32 from tile to tile while a mask cuts them
-    const auto steps = [&](bool keys, int n) {
-        if (!causal)
-            return (double)n * walk_steps(p, 0, rows, keys, 0);
-        const int d = rows / 32, top = (p.S_q + 31) / 32;
-        if (keys) {
-            const int all = (top + d - 1) / d < n ? (top + d - 1) / d : n;
-            return (double)all * top - 0.5 * d * all * (all - 1.0);
-        }
-        const int cut = (p.S_q < p.S_kv ? p.S_q : p.S_kv) / rows, m = cut < n ? cut : n;    // tiles the mask's edge runs through
-        return 0.5 * d * m * (m + 1.0) + (double)(n - m) * walk_steps(p, causal, rows, keys, n - 1);
-    };
-    const double all = BH * (n_t * (double)c.key_tile + steps(true, n_t) * c.key_step + n_tq * (double)c.query_tile +
-                             steps(false, n_tq) * c.query_step);
-    const float mean = (float)(all / slots);
-    const float keys = c.key_tile + c.key_step * walk_steps(p, causal, rows, true, 0);
-    const float queries = c.query_tile + c.query_step * walk_steps(p, causal, rows, false, n_tq - 1);
-    const float heaviest = keys > queries ? keys : queries;
-    if (queue.n_entries <= slots)
-        return c.launch + heaviest + c.mean * mean;
-    if (queue.n_entries > kMaxPasses * slots || per_pass > kMaxSlots)
-        return c.launch + mean + heaviest * (causal ? 0.25f : 0.5f) + c.mean * mean;
-    float walk[kMaxSlots] = {};
-    int k = 0, at = 0;      // pass, place in it (BwdQueue::entry)
-    const long long head_bytes = 4ll * (p.S_q + p.S_kv) * 128;
-    for (const bool own_keys : {true, false})
-        xcd_tiles(BH, own_keys ? n_t : n_tq, causal, head_bytes, 0, [&](int t) {
-            const int n = walk_steps(p, causal, rows, own_keys, causal && own_keys ? n_t - 1 - t : t);
-            const int m = k & 1 ? per_pass - 1 - at : at;
-            walk[m < first ? first - 1 - m : m] += own_keys ? c.key_tile + c.key_step * n : c.query_tile + c.query_step * n;
-            if (++at == per_pass) {
-                at = 0;
-                ++k;
-            }
-        });
-    float longest = 0.f;
-    for (int m = 0; m < per_pass; ++m)
-        longest = walk[m] > longest ? walk[m] : longest;
-    // what a plan makes of it (plan_walks): the heaviest tile, or little more than the mean
-    const float by_plan = mean + kPlanTail * (float)(all / queue.n_entries);
-    const float planned = by_plan > heaviest ? by_plan : heaviest;
-    longest = planned < c.plan_pays * longest ? planned : longest;
-    return c.launch + longest + c.mean * mean;
+    if (!sweeps_apart(l.p, causal, slots))
+        return run(l.p.total_wg, l.p.total_q);
+    const int rc = run(l.p.total_wg, 0);
+    return rc == ATTN_OK ? run(0, l.p.total_q) : rc;
 }
 
 // D = 128: which owner tiles a launch takes.  64-row waves read half the LDS operands per product: in tiles of 256 rows (four
@@ -368,15 +389,25 @@ float launch_estimate(const BwdParams &p, int BH, int causal, const WalkCost &c,
 // heads of 2048 rows 206 -> 187 us, 128 of 4096 3026 -> 2691); in tiles of 128 rows (two waves, two workgroups to a CU that
 // fill each other's gaps) causal and ragged launches (128 causal heads of 4096 rows 1673 -> 1516, of 1024 147 -> 140, 300 of
 // 300 rows 91 -> 84).  A 64-row wave takes 1.6 times as long for a tile as a 32-row one: launches that do not fill the chip are
-// up to 1.7 times slower (16 heads of 1024 rows 35 -> 44).  Of 6200 launches 29 % take 64-row waves, 7 % faster in the mean; one in
-// thirty of those is more than 2 % slower, 1.12 times at worst.
-BwdTiling pick_tiling(const BwdParams &p, int BH, int causal, int cus)
+// up to 1.7 times slower (16 heads of 1024 rows 35 -> 44).  The estimate rests on the
+// walk that the launch then has, by plan or by passes.  Of 6170 launches (1 to 256 heads, 64 to 16384 rows) 29 % take 64-row waves, 8 % faster in the
+// mean; 12 of those 1795 are more than 2 % slower, 1.08 times at worst.  (Where any of them was taken to have a plan little above its mean
+// walk, 62 were, 1.12 times at worst.)
+BwdTiling pick_tiling(const BwdParams &p, int BH, int causal, int cus, BwdLaunch (&l)[3])
 {
-    if (cus < attn::kNumXcd || 2ll * BH * ((p.S_kv + 255) / 256 + (p.S_q + 255) / 256) < cus)
-        return kRows128;   // (no launch of fewer tiles gained)
-    const float t32 = 0.975f * launch_estimate(p, BH, causal, kWalk128, cus);
-    const float t256 = launch_estimate(p, BH, causal, kWalk256, cus), t2 = launch_estimate(p, BH, causal, kWalk128TwoWaves, cus);
-    return t32 <= t256 && t32 <= t2 ? kRows128 : t256 <= t2 ? kRows256 : kRows128TwoWaves;
+    l[0].set(p, BH, causal, kWalk128, cus);
+    const bool all = cus >= attn::kNumXcd && 2ll * BH * ((p.S_kv + 255) / 256 + (p.S_q + 255) / 256) >= cus;   // (no launch of fewer tiles gained)
+    if (all) {
+        l[1].set(p, BH, causal, kWalk256, cus);
+        l[2].set(p, BH, causal, kWalk128TwoWaves, cus);
+    }
+    for (;;) {   // the least estimate, worked out only where it could be that
+        // (the two factors by the same launches: 1.3 % of them are left more than 3 % behind their best tiling, 1.8 % at 0.975 and 1)
+        const float t32 = 0.98f * l[0].us, t256 = (l[1].planned ? 1.01f : 1.f) * l[1].us;
+        const int i = !all || (t32 <= t256 && t32 <= l[2].us) ? 0 : t256 <= l[2].us ? 1 : 2;
+        if (!l[i].go_on(BH, causal, cus))
+            return i == 0 ? kRows128 : i == 1 ? kRows256 : kRows128TwoWaves;
+    }
 }
 
 template <int D, typename ELEM>
@@ -402,32 +433,30 @@ int launch_hand(BwdParams p, int BH, int causal, hipStream_t stream, BwdTiling t
     const int rc = launch_delta<D, typename std::conditional<F16, _Float16, attn::bf16_t>::type>(p, stream);
     if (rc != ATTN_OK)
         return rc;
-    if (tiling == kAsDispatched)   // (while the Delta kernel runs)
-        tiling = D == 128 ? pick_tiling(p, BH, causal, cus) : kRows128;
-    const int rows = tiling == kRows256 ? 256 : 128;
-    p.n_t = (p.S_kv + rows - 1) / rows;
-    p.n_tq = (p.S_q + rows - 1) / rows;
-    p.total_wg = BH * p.n_t;
-    p.total_q = BH * p.n_tq;
-    const auto run = [&](const BwdKernels &kern, int threads, int lds, const WalkCost &cost) {
-        return launch_sweeps(kern, threads, lds, p, BH, causal, cost, stream);
-    };
+    // (while the Delta kernel runs)
+    BwdLaunch launch[3];
+    if (D == 128 && tiling == kAsDispatched) {
+        tiling = pick_tiling(p, BH, causal, cus, launch);
+    } else {
+        tiling = D == 128 ? tiling : kRows128;
+        BwdLaunch &l = launch[tiling - kRows128];
+        l.set(p, BH, causal, D == 64 ? kWalkD64 : tiling == kRows128 ? kWalk128 : tiling == kRows256 ? kWalk256 : kWalk128TwoWaves, cus);
+        while (l.go_on(BH, causal, cus)) {
+        }
+    }
+    const BwdLaunch &l = launch[tiling - kRows128];
+    const auto run = [&](const BwdKernels &kern, int threads, int lds) { return launch_sweeps(kern, threads, lds, l, causal, stream); };
     using namespace attn;
     if constexpr (D == 128) {
         if (tiling == kRows256)
-            return causal ? run({attn_bwd_wide_kernel<4, true, F16>, attn_bwd_wide_planned_kernel<4, true, F16>}, 256,
-                                BwdWideLds<4>::BYTES, kWalk256)
-                          : run({attn_bwd_wide_kernel<4, false, F16>, attn_bwd_wide_planned_kernel<4, false, F16>}, 256,
-                                BwdWideLds<4>::BYTES, kWalk256);
+            return causal ? run({attn_bwd_wide_kernel<4, true, F16>, attn_bwd_wide_planned_kernel<4, true, F16>}, 256, BwdWideLds<4>::BYTES)
+                          : run({attn_bwd_wide_kernel<4, false, F16>, attn_bwd_wide_planned_kernel<4, false, F16>}, 256, BwdWideLds<4>::BYTES);
         if (tiling == kRows128TwoWaves)
-            return causal ? run({attn_bwd_wide_kernel<2, true, F16>, attn_bwd_wide_planned_kernel<2, true, F16>}, 128,
-                                BwdWideLds<2>::BYTES, kWalk128TwoWaves)
-                          : run({attn_bwd_wide_kernel<2, false, F16>, attn_bwd_wide_planned_kernel<2, false, F16>}, 128,
-                                BwdWideLds<2>::BYTES, kWalk128TwoWaves);
+            return causal ? run({attn_bwd_wide_kernel<2, true, F16>, attn_bwd_wide_planned_kernel<2, true, F16>}, 128, BwdWideLds<2>::BYTES)
+                          : run({attn_bwd_wide_kernel<2, false, F16>, attn_bwd_wide_planned_kernel<2, false, F16>}, 128, BwdWideLds<2>::BYTES);
     }
-    const WalkCost &cost = D == 64 ? kWalkD64 : kWalk128;
-    return causal ? run({attn_bwd_asm_kernel<D, true, F16>, attn_bwd_asm_planned_kernel<D, true, F16>}, 256, BwdLds<D>::BYTES, cost)
-                  : run({attn_bwd_asm_kernel<D, false, F16>, attn_bwd_asm_planned_kernel<D, false, F16>}, 256, BwdLds<D>::BYTES, cost);
+    return causal ? run({attn_bwd_asm_kernel<D, true, F16>, attn_bwd_asm_planned_kernel<D, true, F16>}, 256, BwdLds<D>::BYTES)
+                  : run({attn_bwd_asm_kernel<D, false, F16>, attn_bwd_asm_planned_kernel<D, false, F16>}, 256, BwdLds<D>::BYTES);
 }
 
 // plain: run the compiler-scheduled sweeps (always when scale == 0, which the hand-scheduled loops exclude)
@@ -614,7 +643,10 @@ extern "C" int attn_bwd_xcd_tile(int heads, int n_t, int causal, long long head_
 {
     int at = 0, got = -1, bh = 0, t = -1;
     const long long entry = (long long)attn::kNumXcd * i + xcd;
-    xcd_tiles(heads, n_t, causal, head_bytes, xcd, [&](int x) { got = at++ == i ? x : got; });
+    xcd_tiles(heads, n_t, causal, head_bytes, xcd, [&](int x, int n) {
+        got = at <= i && i < at + n ? x : got;
+        at += n;
+    });
     if (causal && entry < (long long)heads * n_t)
         attn::wg_to_tile_n<true>((int)entry, heads * n_t, n_t, head_bytes, bh, t);
     *want = causal ? t : entry < (long long)heads * n_t ? 0 : -1;
@@ -622,16 +654,33 @@ extern "C" int attn_bwd_xcd_tile(int heads, int n_t, int causal, long long head_
 }
 
 // Test-only, host only: the tiling that a D = 128 launch on `cus` compute units takes (1: tiles of 128 rows and 32-row waves, 2: of
-// 256 rows, 3: of 128 rows and 64-row waves); est: the three estimates in us.
-extern "C" int attn_bwd_pick_tiling(int heads, int S_q, int S_kv, int causal, int cus, float *est)
+// 256 rows, 3: of 128 rows and 64-row waves) and the three estimates in us, of the others the least that they could come to.
+// walk: the longest walk that the taken tiling's estimate rests on, and whether it has a plan.
+extern "C" int attn_bwd_picked_walk(int heads, int S_q, int S_kv, int causal, int cus, float *est, float *walk)
 {
     BwdParams p;
     p.S_q = S_q;
     p.S_kv = S_kv;
-    est[0] = cus ? launch_estimate(p, heads, causal, kWalk128, cus) : 0.f;
-    est[1] = cus ? launch_estimate(p, heads, causal, kWalk256, cus) : 0.f;
-    est[2] = cus ? launch_estimate(p, heads, causal, kWalk128TwoWaves, cus) : 0.f;
-    return pick_tiling(p, heads, causal, cus);
+    p.D = 128;
+    p.cus_per_xcd = cus / attn::kNumXcd;
+    BwdLaunch l[3];
+    l[1].us = l[2].us = -1.f;
+    const BwdTiling t = pick_tiling(p, heads, causal, cus, l);
+    if (l[1].us < 0.f) {
+        l[1].set(p, heads, causal, kWalk256, cus);
+        l[2].set(p, heads, causal, kWalk128TwoWaves, cus);
+    }
+    for (int i = 0; i < 3; ++i)
+        est[i] = l[i].us;
+    walk[0] = l[t - kRows128].us - l[t - kRows128].rest;
+    walk[1] = l[t - kRows128].planned;
+    return t;
+}
+
+extern "C" int attn_bwd_pick_tiling(int heads, int S_q, int S_kv, int causal, int cus, float *est)
+{
+    float walk[2];
+    return attn_bwd_picked_walk(heads, S_q, S_kv, causal, cus, est, walk);
 }
 
 // Test-only: attn_bwd / attn_bwd_f16 (D = 128, scale > 0) in the tiling that is asked for (BwdTiling).

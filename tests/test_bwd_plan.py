@@ -79,3 +79,26 @@ def test_hopeless_plans_are_refused_before_they_are_made():
                   (159, 1185, 1185, 128, 0, 2), (213, 1352, 1352, 128, 0, 3), (199, 338, 338, 64, 0, 1)]:
         _, _, _, (by_plan, by_passes, least), _ = plan(*shape)
         assert least >= (0.93 if shape[3] == 64 else 0.95) * by_passes, (shape, by_plan, by_passes, least)
+
+
+def test_the_tiling_is_chosen_by_the_walk_that_it_gets():
+    """A D = 128 launch's estimate rests on its plan's longest walk where the plan is taken, and on the passes' where it is not."""
+    call = ctypes.CDLL(debug_lib.PATH).attn_bwd_picked_walk
+    call.restype, call.argtypes = ctypes.c_int, [ctypes.c_int] * 5 + [ctypes.POINTER(ctypes.c_float)] * 2
+    est, walk = (ctypes.c_float * 3)(), (ctypes.c_float * 2)()
+    rng = random.Random(4)
+    shapes = [(65, 484, 484, 0), (140, 194, 194, 0), (40, 1500, 1500, 1), (123, 72, 5938, 0), (159, 1185, 1185, 0)]
+    for _ in range(400):
+        s = rng.randint(64, 5000)
+        shapes.append((rng.randint(8, 200), s, s if rng.random() < 0.6 else rng.randint(64, 5000), rng.randint(0, 1)))
+    taken = {}
+    for heads, s_q, s_kv, causal in shapes:
+        t = call(heads, s_q, s_kv, causal, 256, est, walk)
+        ratio, _, _, (by_plan, by_passes, _), _ = plan(heads, s_q, s_kv, 128, causal, t)
+        planned = ratio < 0.95
+        taken[t, planned] = taken.get((t, planned), 0) + 1
+        if ratio == 1 and by_passes == 0:       # (a single pass, or too many entries)
+            assert not walk[1]
+            continue
+        assert walk[1] == planned and abs(walk[0] - (by_plan if planned else by_passes)) < 1e-3 * by_passes, (heads, s_q, s_kv, causal, t)
+    assert all(taken.get((t, planned), 0) >= 5 for t in (1, 2, 3) for planned in (False, True)), taken
