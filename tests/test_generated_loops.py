@@ -196,6 +196,13 @@ def test_backward_sweeps(key_owner, d, dtype):
             assert asm_emit.check_stream(path) == len(path)
 
 
+def test_backward_waits_leave_operands_in_flight():
+    """The reading distances are the ones that the table names (the first chunk caps them), and no wait takes all that is ahead."""
+    for (key_owner, d), want in gen_attn_bwd_loop.DEFAULTS.items():
+        g = gen_attn_bwd_loop.Gen(key_owner, d)
+        assert (g.NF, g.PFD, g.W) == (want["NF"], want["PFD"], want["W"]) and g.W < g.PFD, (key_owner, d)
+
+
 def test_a_detour_that_the_text_does_not_have_is_an_error():
     lines = fwd_lines("d128")
     assert asm_emit.walk(lines, take=["SLOW1_"], loop_label="BODY0_", loop_visits=1)
