@@ -47,7 +47,9 @@ int launch_sweep(K kern, BwdParams p, int BH, int S_own, int NW, int lds_bytes, 
 // 52 -> 45).  Where the tiles end in the pass they began in, are short, or enough for the workgroups (causal: for half of
 // them, as half of the tiles are short), one launch is ahead or level (48 heads of 72 x 1500 49 / 61, 123 of 64 x 512,
 // causal, 29 / 33; 48 of 1000 x 8000, causal, D = 64 83 / 92; 400 of 72 x 5938 983 / 1004).  Most of them now take a plan
-// (plan_walks), which is asked first; these are left where it does not pay or has too many entries.
+// (plan_walks), which is asked first; these are left where it does not pay or has too many entries.  64-row waves (one after the
+// other / one launch): no mask 257 heads of 90 x 3413 337 / 387, 201 of 121 x 5021 404 / 497, 75 of 459 x 13920 911 / 1148; causal
+// 6 of 1443 x 10145 101 / 66, 7 of 1103 x 7699 84 / 53: those run in one launch.
 bool sweeps_apart(const BwdParams &p, int causal, int slots)
 {
     const attn::BwdQueue queue(p.total_wg, p.total_q);
@@ -378,7 +380,8 @@ int launch_sweeps(const BwdKernels &kern, int threads, int LDS, const BwdLaunch 
         hipLaunchKernelGGL(kern.plain, dim3((unsigned)(slots < entries ? slots : entries)), dim3(threads), LDS, stream, r);
         return (int)(hipGetLastError() == hipSuccess ? ATTN_OK : ATTN_ERR_LAUNCH);
     };
-    if (!sweeps_apart(l.p, causal, slots))
+    const bool rows64 = l.c == &kWalk256 || l.c == &kWalk128TwoWaves;
+    if ((rows64 && causal) || !sweeps_apart(l.p, causal, slots))
         return run(l.p.total_wg, l.p.total_q);
     const int rc = run(l.p.total_wg, 0);
     return rc == ATTN_OK ? run(0, l.p.total_q) : rc;

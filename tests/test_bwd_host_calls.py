@@ -38,3 +38,12 @@ def test_a_planned_launch_has_the_workgroups_that_its_kernel_fits(tmp_path):
                 planned += 1
                 assert line["grid"] == 256 * fits.get(line["kernel"], 0), (call, line["kernel"], line["grid"])
     assert planned == len(calls)
+
+
+def test_which_launches_run_one_sweep_after_the_other(tmp_path):
+    """Without a plan: few queries against many keys, but not causal launches in 64-row waves."""
+    calls = [(257, 90, 3413, 128, 0, 0, 3), (104, 88, 8595, 128, 0, 1, 3), (6, 1443, 10145, 128, 1, 0, 3), (7, 1103, 7699, 128, 1, 0, 2),
+             (24, 1223, 17813, 128, 1, 0, 2), (16, 1024, 1024, 128, 0, 0, 3)]
+    for call, want, (rc, lines) in zip(calls, (2, 2, 1, 1, 1, 1), fake_hip.backward_calls(tmp_path, calls)):
+        sweeps = [line for line in lines if line["what"] == "launch" and "delta" not in line["kernel"]]
+        assert rc == 0 and len(sweeps) == want and not any("plan" in line for line in sweeps), (call, sweeps)
