@@ -274,7 +274,8 @@ struct BwdLaunch {
     enum { kSet, kWalked, kDone } step;
     bool planned;
 
-    void set(const BwdParams &of, int BH, int causal, const WalkCost &cost, int cus)
+    // estimate: between tilings (D = 128); a launch that has no choice takes its walks only
+    void set(const BwdParams &of, int BH, int causal, const WalkCost &cost, int cus, bool estimate)
     {
         p = of;
         c = &cost;
@@ -284,10 +285,10 @@ struct BwdLaunch {
         p.total_q = BH * p.n_tq;
         planned = false;
         rest = us = 0.f;
-        step = cus > 0 ? kSet : kDone;
-        if (p.D != 128 || cus <= 0)
-            return;
         const int slots = cus * cost.per_cu, entries = attn::BwdQueue(p.total_wg, p.total_q).n_entries;
+        step = cus <= 0 || entries <= slots || entries > BwdWalks::kMax * attn::kNumXcd ? kDone : kSet;
+        if (!estimate || cus <= 0)
+            return;
         // steps of a head's tiles: they fall (key owners) or rise (query owners) by rows / 32 from tile to tile while a mask cuts them
         const auto steps = [&](bool keys, int n) {
             if (!causal)
@@ -307,10 +308,8 @@ struct BwdLaunch {
                                         cost.query(walk_steps(p, causal, cost.rows, false, p.n_tq - 1)));
         rest = cost.launch + cost.mean * mean;
         us = rest + std::max(mean, heaviest);
-        if (entries <= slots || entries > BwdWalks::kMax * attn::kNumXcd) {
+        if (step == kDone)
             us = rest + (entries <= slots ? heaviest : mean + heaviest * (causal ? 0.25f : 0.5f));
-            step = kDone;
-        }
     }
     void walk(int BH, int causal, int cus)
     {
@@ -398,11 +397,11 @@ int launch_sweeps(const BwdKernels &kern, int threads, int LDS, const BwdLaunch 
 // walk, 62 were, 1.12 times at worst.)
 BwdTiling pick_tiling(const BwdParams &p, int BH, int causal, int cus, BwdLaunch (&l)[3])
 {
-    l[0].set(p, BH, causal, kWalk128, cus);
     const bool all = cus >= attn::kNumXcd && 2ll * BH * ((p.S_kv + 255) / 256 + (p.S_q + 255) / 256) >= cus;   // (no launch of fewer tiles gained)
+    l[0].set(p, BH, causal, kWalk128, cus, all);
     if (all) {
-        l[1].set(p, BH, causal, kWalk256, cus);
-        l[2].set(p, BH, causal, kWalk128TwoWaves, cus);
+        l[1].set(p, BH, causal, kWalk256, cus, true);
+        l[2].set(p, BH, causal, kWalk128TwoWaves, cus, true);
     }
     for (;;) {   // the least estimate, worked out only where it could be that
         // (the two factors by the same launches: 1.3 % of them are left more than 3 % behind their best tiling, 1.8 % at 0.975 and 1)
@@ -443,7 +442,7 @@ int launch_hand(BwdParams p, int BH, int causal, hipStream_t stream, BwdTiling t
     } else {
         tiling = D == 128 ? tiling : kRows128;
         BwdLaunch &l = launch[tiling - kRows128];
-        l.set(p, BH, causal, D == 64 ? kWalkD64 : tiling == kRows128 ? kWalk128 : tiling == kRows256 ? kWalk256 : kWalk128TwoWaves, cus);
+        l.set(p, BH, causal, D == 64 ? kWalkD64 : tiling == kRows128 ? kWalk128 : tiling == kRows256 ? kWalk256 : kWalk128TwoWaves, cus, false);
         while (l.go_on(BH, causal, cus)) {
         }
     }
@@ -670,8 +669,9 @@ extern "C" int attn_bwd_picked_walk(int heads, int S_q, int S_kv, int causal, in
     l[1].us = l[2].us = -1.f;
     const BwdTiling t = pick_tiling(p, heads, causal, cus, l);
     if (l[1].us < 0.f) {
-        l[1].set(p, heads, causal, kWalk256, cus);
-        l[2].set(p, heads, causal, kWalk128TwoWaves, cus);
+        l[0].set(p, heads, causal, kWalk128, cus, true);
+        l[1].set(p, heads, causal, kWalk256, cus, true);
+        l[2].set(p, heads, causal, kWalk128TwoWaves, cus, true);
     }
     for (int i = 0; i < 3; ++i)
         est[i] = l[i].us;
