@@ -10,7 +10,7 @@ from paper_2512_18134_amd import binding, synth
 pytestmark = pytest.mark.gpu
 
 # heads, S_q, S_kv, D, ranges: more than 256 workgroups, the last range short, waves without rows (129, 200, 300)
-CASES = [(24, 129, 2100, 128, 4), (12, 256, 4097, 128, 8), (24, 193, 1100, 128, 2), (9, 300, 6000, 128, 7), (40, 200, 2100, 64, 4),
+CASES = [(24, 129, 2100, 128, 4), (12, 256, 4097, 128, 8), (40, 193, 1100, 128, 2), (9, 300, 6000, 128, 7), (40, 200, 2100, 64, 4),
          (24, 300, 3333, 64, 5)]
 
 
@@ -18,6 +18,10 @@ CASES = [(24, 129, 2100, 128, 4), (12, 256, 4097, 128, 8), (24, 193, 1100, 128, 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 def test_wide_ranges(case, dtype):
     H, S_q, S_kv, D, n_split = case
+    split_len = -(-(-(-S_kv // n_split)) // 64) * 64
+    tiles = H * -(-S_kv // split_len) * -(-S_q // (64 if D == 128 else 128))
+    # (what launch_splitkv gives to the 8-wave tiling)
+    assert S_q > (64 if D == 128 else 128) and tiles > torch.cuda.get_device_properties(0).multi_processor_count
     print("case", case, dtype, flush=True)
     q, k, v = synth.make_qkv(1, H, S_q, S_kv, D, seed=S_q + S_kv)
     scale = synth.default_scale(D)
