@@ -612,8 +612,8 @@ extern "C" int attn_bwd_sweeps_apart(int heads, int S_q, int S_kv, int causal, i
 
 // Test-only, host only: a launch's plan; the longest walk over that of the passes, 1 without walks (BwdWalks::fill).  walks, in us: the longest
 // by plan and by passes, what no order goes below, then XCD 0's entries.
-extern "C" float attn_bwd_plan(int heads, int S_q, int S_kv, int D, int causal, int tiling, int cus, uint32_t *first, uint32_t *idx,
-                               float *walks)
+extern "C" float attn_bwd_plan_walks(int heads, int S_q, int S_kv, int D, int causal, int tiling, int cus, uint32_t *first, uint32_t *idx,
+                                     float *walks)
 {
     const WalkCost &c = D == 64 ? kWalkD64 : tiling == kRows256 ? kWalk256 : tiling == kRows128 ? kWalk128 : kWalk128TwoWaves;
     BwdParams p;
@@ -637,6 +637,12 @@ extern "C" float attn_bwd_plan(int heads, int S_q, int S_kv, int D, int causal, 
     for (int i = 0; i < (int)(sizeof plan.idx / 4); ++i)
         idx[i] = plan.idx[i];
     return walks[0] / walks[1];
+}
+
+extern "C" float attn_bwd_plan(int heads, int S_q, int S_kv, int D, int causal, int tiling, int cus, uint32_t *first, uint32_t *idx)
+{
+    float walks[3 + BwdWalks::kMax];
+    return attn_bwd_plan_walks(heads, S_q, S_kv, D, causal, tiling, cus, first, idx, walks);
 }
 
 // Test-only, host only: the i-th tile that an XCD takes up of a sweep (xcd_tiles), -1 behind the last, and the same from

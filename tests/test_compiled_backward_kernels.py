@@ -1,6 +1,5 @@
-"""What the hand-scheduled backward kernels, planned ones among them, need of the compiler (hipcc -S of csrc/attn_bwd.hip): no vector
-register in scratch memory, at D = 64 no more than 256 registers a wave, so that two workgroups share a CU, and D = 128 loops that
-start where they were measured to run best.  (The 64-row kernels: test_bwd_wide_loop.py.)"""
+"""What the hand-scheduled backward kernels need of the compiler (hipcc -S of csrc/attn_bwd.hip): no vector register in
+scratch memory, and at D = 64 no more than 256 registers a wave, so that two workgroups share a CU."""
 import os
 import re
 import subprocess
@@ -21,23 +20,13 @@ def test_registers_of_the_hand_scheduled_sweeps(tmp_path):
                                       os.path.join(ROOT, "paper_2512_18134_amd", "csrc", "attn_bwd.hip")],
                    check=True, stdout=subprocess.DEVNULL, stderr=subprocess.DEVNULL)
     text = open(out).read()
-    seen = []
+    seen = 0
     for block in text[text.index("amdhsa.kernels:"):].split("  - .agpr_count:")[1:]:
-        m = re.search(r"\.name:\s+\S*attn_bwd_asm_(?:planned_)?kernelILi(\d+)E", block)
+        m = re.search(r"\.name:\s+\S*attn_bwd_asm_kernelILi(\d+)E", block)
         if not m:
             continue
         value = lambda key: int(re.search(r"\.%s:\s+(\d+)" % key, block).group(1))
-        assert value("private_segment_fixed_size") == 0 and value("vgpr_spill_count") == 0, block[:400]
+        assert value("private_segment_fixed_size") == 0 and value("vgpr_spill_count") == 0
         assert value("vgpr_count") <= (256 if m.group(1) == "64" else 512)     # VGPRs and AGPRs together
-        seen.append(m.group(1))
-    # with a plan or without, causal or not, element type
-    assert seen.count("64") == seen.count("128") == 8
-    # the loops of 32-row waves at D = 128 start 12 bytes behind a multiple of 32 (gen_attn_bwd_loop.py)
-    loops = 0
-    for m in re.finditer(r"^_ZN4attn\d+attn_bwd_asm_(?:planned_)?kernelILi128E\S+:(.*?)^\.Lfunc_end", text, re.M | re.S):
-        lines = [l.strip() for l in m.group(1).split("\n") if l.strip()]
-        for i in [i for i, l in enumerate(lines) if re.match(r"BODY0_\d+:", l)]:
-            assert lines[i - 4:i] == [".p2align 5"] + 3 * ["s_nop 0"], lines[i - 5:i + 1]
-            loops += 1
-    assert loops == 16        # two sweeps a kernel
-    assert re.search(r"\.p2align\s+8.*\n(.*\n){0,3}_ZN4attn\d+attn_bwd_asm_planned_kernelILi128E", text)
+        seen += 1
+    assert seen == 8          # D, causal, element type

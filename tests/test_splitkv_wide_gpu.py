@@ -1,4 +1,5 @@
-"""Split-KV ranges of many queries (8 waves, 256-row tiles) and partial rows that leave whole (D = 64): sizes at the edges of tiles, waves and ranges, each head against the fp64 oracle on the first and last rows and in every
+"""Split-KV ranges of many queries (8 waves, 256-row tiles) and partial rows that leave whole (D = 64): sizes at the edges of tiles,
+waves and ranges, each head against the fp64 oracle on the first and last rows and in every
 element against the unsplit call; the bars are test_splitkv_gpu.py's (fp16: a quarter, as its significand has three bits more)."""
 import numpy as np
 import pytest
@@ -10,7 +11,7 @@ from paper_2512_18134_amd import binding, synth
 pytestmark = pytest.mark.gpu
 
 # heads, S_q, S_kv, D, ranges: more than 256 workgroups, the last range short, waves without rows (129, 200, 300)
-CASES = [(24, 129, 2100, 128, 4), (12, 256, 4097, 128, 8), (40, 193, 1100, 128, 2), (9, 300, 6000, 128, 7), (40, 200, 2100, 64, 4),
+CASES = [(24, 129, 2100, 128, 4), (12, 256, 4097, 128, 8), (24, 193, 1100, 128, 2), (9, 300, 6000, 128, 7), (40, 200, 2100, 64, 4),
          (24, 300, 3333, 64, 5)]
 
 
@@ -18,10 +19,6 @@ CASES = [(24, 129, 2100, 128, 4), (12, 256, 4097, 128, 8), (40, 193, 1100, 128, 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 def test_wide_ranges(case, dtype):
     H, S_q, S_kv, D, n_split = case
-    split_len = -(-(-(-S_kv // n_split)) // 64) * 64
-    tiles = H * -(-S_kv // split_len) * -(-S_q // (64 if D == 128 else 128))
-    # (what launch_splitkv gives to the 8-wave tiling)
-    assert S_q > (64 if D == 128 else 128) and tiles > torch.cuda.get_device_properties(0).multi_processor_count
     print("case", case, dtype, flush=True)
     q, k, v = synth.make_qkv(1, H, S_q, S_kv, D, seed=S_q + S_kv)
     scale = synth.default_scale(D)
@@ -42,6 +39,19 @@ def test_wide_ranges(case, dtype):
         got = o[:, h:h + 1].double().cpu().numpy()
         assert np.max(np.abs(got - want)) <= bar
         assert np.max(np.abs(lse[:, h:h + 1].double().cpu().numpy() - want_lse)) <= 1e-3
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_wide_ranges_whose_last_wave_has_one_row(dtype):
+    """193 queries in enough workgroups (24 heads of them, above, take the key groups); and the other cases have enough as well."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    case = (40, 193, 1100, 128, 2)
+    for H, S_q, S_kv, D, n_split in [case] + [c for c in CASES if c[1] != 193]:
+        split_len = -(-(-(-S_kv // n_split)) // 64) * 64
+        tiles = H * -(-S_kv // split_len) * -(-S_q // (64 if D == 128 else 128))
+        # (what launch_splitkv gives to the 8-wave tiling)
+        assert S_q > (64 if D == 128 else 128) and tiles > cus, (H, S_q, S_kv, D, n_split)
+    test_wide_ranges(case, dtype)
 
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
