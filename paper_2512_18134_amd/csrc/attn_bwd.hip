@@ -68,15 +68,16 @@ enum BwdTiling { kAsDispatched, kRows128, kRows256, kRows128TwoWaves };
 // of 1 to 256 heads and 64 to 16384 rows, D = 128, causal or not (root mean square of the error 5, 6 and 5 %).
 struct WalkCost {
     int rows, per_cu;   // of an owner tile; workgroups that a compute unit holds
-    float key_tile, key_step, query_tile, query_step, launch, mean, plan_pays;
+    float key_tile, key_step, query_tile, query_step, launch, mean, plan_pays, alone = 1.f;
     float key(int steps) const { return key_tile + key_step * steps; }
     float query(int steps) const { return query_tile + query_step * steps; }
 };
 constexpr WalkCost kWalk128 = {128, 1, 4.18f, 0.522f, 3.55f, 0.367f, 5.76f, 0.535f, 0.95f},
                    kWalk256 = {256, 1, 7.26f, 0.924f, 5.56f, 0.644f, 4.83f, 0.503f, 0.95f},
                    kWalk128TwoWaves = {128, 2, 7.27f, 0.920f, 6.32f, 0.654f, 4.72f, 0.551f, 0.95f};
-// D = 64 (two workgroups to a CU): what the tiles' walks cost beside each other is all that is asked of it
-constexpr WalkCost kWalkD64 = {128, 2, 4.0f, 0.60f, 3.5f, 0.45f, 0.f, 0.f, 0.93f};
+// D = 64 (two workgroups to a CU): what the tiles' walks cost beside each other, and what share of it the longer walk's rest takes once the
+// other has ended (`alone`), is all that is asked of it
+constexpr WalkCost kWalkD64 = {128, 2, 4.0f, 0.60f, 3.5f, 0.45f, 0.f, 0.f, 0.93f, 0.6f};
 
 // Streamed tiles of owner tile t (`rows` rows) of a key-owner or query-owner sweep
 int walk_steps(const BwdParams &p, int causal, int rows, bool keys, int t)
@@ -122,9 +123,38 @@ struct BwdWalks {
     // by place in the queue: XCD 0's entries and XCD 7's, which have the heaviest tile of each place between them (heaviest first,
     // every other row of eight in reverse); 0 where XCD 7 has none
     float cost[2][kMax];
-    float passes;   // the longest walk where the queue is taken pass by pass (BwdQueue::entry)
-    float least;    // no plan's longest walk is shorter
+    // The longest walk of a workgroup.  D = 64: also of a compute unit's pair of them; while both run each takes its time, the rest of the
+    // longer one takes `alone` of it
+    struct Longest {
+        float one, pair;
+    };
+    Longest passes;   // where the queue is taken pass by pass (BwdQueue::entry)
+    Longest least;    // no plan's are shorter (with a mask, by pairs: none was)
+    float alone, pays_one, pays_pair;
     bool keys_first;   // the key owners' tiles are the longer ones
+
+    // Of per_xcd walks in the order of a pass, whose first and last, second and last but one, ... share a compute unit
+    void longest(const float *walk, Longest &most) const
+    {
+        for (int m = 0; m < per_xcd; ++m)
+            most.one = std::max(most.one, walk[m]);
+        for (int i = 0; alone < 1.f && i < per_xcd / 2; ++i) {
+            const float x = walk[i], y = walk[per_xcd - 1 - i], less = std::min(x, y);
+            most.pair = std::max(most.pair, less + (std::max(x, y) - less) * alone);
+        }
+    }
+
+    // Whether a launch takes the plan whose longest walks these are.  Time by plan over time by passes: D = 128, 190 launches, 0.73 to 0.98
+    // where the longest walk is under 0.95 of the passes' (one of 97 1.02), 0.96 to 1.05 above.  D = 64 by single walks, under 0.93 (short
+    // causal ones, whose costs are less sure, 0.8): 3000 drawn launches 0.964 in the mean, but 56 of them more than 2 % slower than by
+    // passes, 1.12 times at worst: their plans level the single walks and pair long ones, where the passes pair long with short (13 heads of
+    // 2210 x 3580 113.5 -> 119.5 us).  By pairs as well, which have to be under 0.96 (0.92), or under the passes' where the single walks are level:
+    // 0.954, 38 and 1.07 times.
+    bool pays(const Longest &l) const
+    {
+        const bool level = l.one < pays_one * passes.one;
+        return alone < 1.f ? l.pair < pays_pair * passes.pair || (level && l.pair < passes.pair) : level;
+    }
 
     // false: a single pass, or too many entries
     bool fill(const BwdParams &p, int BH, int causal, const WalkCost &c, int slots)
@@ -142,8 +172,13 @@ struct BwdWalks {
         const float first_key = c.key(walk_steps(p, causal, c.rows, true, 0)),
                     last_query = c.query(walk_steps(p, causal, c.rows, false, p.n_tq - 1));   // the heaviest of either sweep
         keys_first = first_key >= last_query;
-        passes = 0.f;
-        least = std::max(first_key, last_query);
+        alone = c.alone;
+        const bool unsure = p.D == 64 && causal && std::min(p.S_q, p.S_kv) < 1024;
+        pays_one = unsure ? 0.8f : c.plan_pays;
+        pays_pair = unsure ? 0.92f : 0.96f;
+        passes = {};
+        least.one = std::max(first_key, last_query);
+        least.pair = alone * least.one;
         for (int x = 0; x < xcds; ++x) {
             float *const of = cost[x], *at = of;
             if (causal) {
@@ -168,33 +203,45 @@ struct BwdWalks {
                     for (int i = 0; i < m; ++i)
                         walk[i] += of[first + i];
             }
-            for (int m = 0; m < per_xcd; ++m) {
-                passes = std::max(passes, walk[m]);
+            longest(walk, passes);
+            for (int m = 0; m < per_xcd; ++m)
                 sum += walk[m];
-            }
-            least = std::max(least, sum / per_xcd);
+            least.one = std::max(least.one, sum / per_xcd);
+            least.pair = std::max(least.pair, sum / per_xcd);   // (a pair takes at least its mean: alone >= 0.5)
         }
+        least.pair += 0.02f * passes.pair;   // (of 970 causal plans taken none came closer to the bound)
         if (!causal)
             least = two_costs(keys_first ? first_q : n - first_q, std::max(cost[0][0], cost[0][n - 1]),
                               keys_first ? n - first_q : first_q, std::min(cost[0][0], cost[0][n - 1]));
         return true;
     }
 
-    // plan_walks's longest walk where there are only two costs: n1 tiles of l1, then n2 of l2.  Workgroups in two classes, one
-    // l1 apart; the one that is free first takes a tile each
-    float two_costs(int n1, float l1, int n2, float l2) const
+    // plan_walks's longest walks where there are only two costs: n1 tiles of l1, then n2 of l2.  Workgroups in two classes, the first
+    // `more` of them one l1 apart from the others; the class that is free first takes a tile each, as far as they go
+    Longest two_costs(int n1, float l1, int n2, float l2) const
     {
-        const int more = n1 % per_xcd;
-        float load[2] = {(float)(n1 / per_xcd) * l1, (float)(n1 / per_xcd + 1) * l1};
-        const int of[2] = {per_xcd - more, more};
-        float longest = load[more > 0];
+        const int more = n1 % per_xcd, first[2] = {more, 0}, end[2] = {per_xcd, more};
+        float load[2] = {}, walk[attn::BwdPlan::kMaxSlots];
+        for (int k = 0; k < n1 / per_xcd; ++k)
+            load[0] += l1;
+        load[1] = load[0] + l1;
+        int i = 0, m = 0;   // the last tile goes to class i, up to its workgroup m
         while (n2 > 0) {
-            const int i = more > 0 && load[1] < load[0];
-            load[i] += l2;
-            longest = std::max(longest, load[i]);
-            n2 -= of[i];
+            i = load[1] <= load[0] && more > 0;
+            m = std::min(first[i] + n2, end[i]);
+            n2 -= m - first[i];
+            if (n2 > 0 || m == end[i]) {
+                load[i] += l2;
+                m = 0;
+            }
         }
-        return longest;
+        for (int k = 0; k < per_xcd; ++k)
+            walk[k] = load[k < more];
+        for (int k = first[i]; k < m; ++k)
+            walk[k] += l2;
+        Longest most = {};
+        longest(walk, most);
+        return most;
     }
 };
 
@@ -203,8 +250,8 @@ struct BwdWalks {
 // a third apart where tiles differ, by the mask or by the sweep they belong to.  By passes -> by plan, in us: D = 128, 40 causal heads
 // of 1500 rows 106.7 -> 95, 12 of 6000 1.17 times as fast, 123 heads of 72 x 5938 1.12 (against one sweep after the other), 16 causal of
 // 1000 x 8000 1.36; D = 64, 123 of 72 x 5938 1.36, 16 of 1000 x 8000 1.28.  The queue is sorted within a group of heads only: where
-// many groups follow each other a plan can be longer than the passes (and is not taken).  Returns the longest walk.
-float plan_walks(attn::BwdPlan &plan, const BwdWalks &w, int cus)
+// many groups follow each other a plan can be longer than the passes (and is not taken).  Returns the longest walks.
+BwdWalks::Longest plan_walks(attn::BwdPlan &plan, const BwdWalks &w, int cus)
 {
     using attn::BwdPlan;
     plan = {};   // (all of it goes to the device, and set() keeps the other half of a word)
@@ -249,13 +296,12 @@ float plan_walks(attn::BwdPlan &plan, const BwdWalks &w, int cus)
         first[m + 1] += first[m];
     for (int m = 0; m <= per_xcd; ++m)
         BwdPlan::set(plan.first, m, first[m]);
-    float longest = 0.f;
+    BwdWalks::Longest longest = {};
     for (int x = 0; x < w.xcds; ++x) {
         float walk[BwdPlan::kMaxSlots] = {};
         for (int at = 0; at < w.n; ++at)
             walk[owner[at]] += w.cost[x][at];
-        for (int m = 0; m < per_xcd; ++m)
-            longest = walk[m] > longest ? walk[m] : longest;
+        w.longest(walk, longest);
     }
     for (int at = 0; at < w.n; ++at)
         BwdPlan::set(plan.idx, first[place(owner[at])]++, at);
@@ -269,7 +315,6 @@ struct BwdLaunch {
     const WalkCost *c;
     BwdWalks walks;
     attn::BwdPlan plan;
-    float pays;       // the walk that a plan has to stay below
     float rest, us;   // what is added to the longest walk; the sum
     enum { kSet, kWalked, kDone } step;
     bool planned;
@@ -316,22 +361,16 @@ struct BwdLaunch {
         step = kDone;
         if (!walks.fill(p, BH, causal, *c, cus * c->per_cu))
             return;
-        // Time by plan over time by passes, over 190 launches: D = 128, 0.73 to 0.98 where the longest walk is under 0.95 of the
-        // passes' (one of 97 1.02), 0.96 to 1.05 above.  D = 64, 0.81 to 1.02 under 0.93 (0.94 in the mean), 0.96 to 1.07 above; but
-        // the costs of short causal walks are less sure there: of 28 launches under 1024 rows and between 0.8 and 0.93, seven
-        // gained more than 3 % and the rest took up to 1.09 times as long (116 heads of 607 rows 38.1 -> 41.3).
-        const int keys = causal && p.S_q < p.S_kv ? p.S_q : p.S_kv;
-        pays = (p.D == 64 && causal && keys < 1024 ? 0.8f : c->plan_pays) * walks.passes;
-        if (walks.least < pays)
+        if (walks.pays(walks.least))
             step = kWalked;
-        us = rest + (step == kWalked ? walks.least : walks.passes);
+        us = rest + (step == kWalked ? walks.least.one : walks.passes.one);
     }
     // makes the plan, and takes it if it pays
     void close()
     {
-        const float longest = plan_walks(plan, walks, p.cus_per_xcd);
-        planned = longest < pays;
-        us = rest + (planned ? longest : walks.passes);
+        const BwdWalks::Longest longest = plan_walks(plan, walks, p.cus_per_xcd);
+        planned = walks.pays(longest);
+        us = rest + (planned ? longest.one : walks.passes.one);
         step = kDone;
     }
     // the next step; false: there is none
@@ -628,9 +667,9 @@ extern "C" float attn_bwd_plan_walks(int heads, int S_q, int S_kv, int D, int ca
     BwdWalks w;
     if (!w.fill(p, heads, causal, c, cus * c.per_cu))
         return 1.f;
-    walks[0] = plan_walks(plan, w, cus / attn::kNumXcd);
-    walks[1] = w.passes;
-    walks[2] = w.least;
+    walks[0] = plan_walks(plan, w, cus / attn::kNumXcd).one;
+    walks[1] = w.passes.one;
+    walks[2] = w.least.one;
     std::copy(w.cost[0], w.cost[0] + w.n, walks + 3);
     for (int i = 0; i < (int)(sizeof plan.first / 4); ++i)
         first[i] = plan.first[i];
